@@ -336,6 +336,7 @@ int forward_common(slide_ctx* ctx, const slide_batch* b, bool with_labels, hipSt
   SpmmArgs sp{};
   if (lo.D > 0) {
     sp = make_spmm(ctx, b);
+    if (!with_labels) sp.xse = nullptr;                  // (the feature segments are only read by a training step)
     h = sp.h;
     // One lookup workgroup per sample holds a compute unit (its bitmap fills the LDS): while the batch
     // fits the machine in one round the hidden layer rides in it; a larger batch would pay the hidden
@@ -685,9 +686,9 @@ int slide_predict(slide_ctx* ctx, const slide_batch* b, int mode, int topk, int3
     const Layout& lo = ctx->lo;
     const float* h = b->hidden;
     if (lo.D > 0) {
-      const SpmmArgs sp = make_spmm(ctx, b);
+      SpmmArgs sp = make_spmm(ctx, b);
+      sp.xse = nullptr;                                  // (no training step follows on these activations)
       HIPCHK(ctx, stage(ctx, SLIDE_STAGE_HIDDEN, s, [&] { return launch_spmm_relu(b->batch, sp, ctx->ctrl(), s); }));
-      HIPCHK(ctx, launch_fill_u32(ctx->at<uint32_t>(lo.xse), (size_t)b->batch * lo.NT1 * 2, 0u, s));
       h = sp.h;
     }
     ctx->last_h = h;
@@ -701,8 +702,6 @@ int slide_predict(slide_ctx* ctx, const slide_batch* b, int mode, int topk, int3
   }
   ActiveDev ad;
   if ((rc = forward_common(ctx, b, false, s, &ad, TransposeArgs{}, TransposeArgs{}, false)) != SLIDE_OK) return rc;
-  if (ctx->lo.D > 0)   // the feature segments are only consumed by training: clear them again
-    HIPCHK(ctx, launch_fill_u32(ctx->at<uint32_t>(ctx->lo.xse), (size_t)b->batch * ctx->lo.NT1 * 2, 0u, s));
   HIPCHK(ctx, launch_topk(ad, ctx->at<float>(ctx->lo.z), topk, d_out_ids, d_out_scores, s));
   ctx->last_dh = nullptr;
   return SLIDE_OK;

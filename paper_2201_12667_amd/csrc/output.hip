@@ -4,6 +4,7 @@
 // first layer is fed by index/value arrays, the second by the first layer's activations).
 #include "slide_internal.h"
 #include "spmm.h"
+#include "topk.h"
 #include "transpose.h"
 
 #include <algorithm>
@@ -442,48 +443,44 @@ hipError_t launch_combine(const ActiveDev& ad, int H, const float* h, const floa
 }
 
 // ---------------------------------------------------------------------------------------------
-// Top-k of the logits of each sample's active set: k rounds of "largest score strictly after the
-// previous pick" in the order (score descending, id ascending).
+// Top-k of the logits of each sample's active set, in the order (score descending, id ascending); NaN scores
+// are left out.  A workgroup per sample, two sweeps over its list (see topk.h).  Bound by latency: a handful
+// of workgroups and a few thousand cached words each.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void topk_kernel(ActiveDev ad, const float* __restrict__ z, int topk,
-                                                   int32_t* __restrict__ out_ids, float* __restrict__ out_scores) {
-  __shared__ float rz[4];
-  __shared__ int rj[4];
+__global__ __launch_bounds__(kSelectThreads) void topk_kernel(ActiveDev ad, const float* __restrict__ z, int topk,
+                                                              int32_t* __restrict__ out_ids,
+                                                              float* __restrict__ out_scores) {
+  __shared__ SelectLds lds;
   const int i = blockIdx.x, tid = threadIdx.x;
   const int first = ad.as_base[i], n = ad.cnt[i];
-  float pz = INFINITY;
-  int pj = -1;
-  for (int k = 0; k < topk; ++k) {
-    float bz = -INFINITY;
-    int bj = -1;
-    for (int q = tid; q < n; q += 256) {
-      const float zz = z[first + q];
-      const int j = ad.as_ids[first + q];
-      const bool after = zz < pz || (zz == pz && j > pj);
-      if (after && (bj < 0 || zz > bz || (zz == bz && j < bj))) { bz = zz; bj = j; }
+  constexpr int UN = 8;                                  // entries per thread in flight
+  const int found = select_topk(lds, topk, [&](auto&& f) {
+    for (int q0 = tid; q0 < n; q0 += UN * kSelectThreads) {
+      float zz[UN];
+      int j[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int q = q0 + u * kSelectThreads, p = first + (q < n ? q : 0);
+        zz[u] = z[p];
+        j[u] = ad.as_ids[p];
+      }
+#pragma unroll
+      for (int u = 0; u < UN; ++u)                       // (x + 0: the two zeros tie)
+        if (q0 + u * kSelectThreads < n && zz[u] == zz[u]) f(topk_key(zz[u] + 0.0f, (uint32_t)j[u]));
     }
-    for (int d = 32; d > 0; d >>= 1) {
-      const float oz = __shfl_xor(bz, d);
-      const int oj = __shfl_xor(bj, d);
-      if (oj >= 0 && (bj < 0 || oz > bz || (oz == bz && oj < bj))) { bz = oz; bj = oj; }
-    }
-    __syncthreads();
-    if ((tid & 63) == 0) { rz[tid >> 6] = bz; rj[tid >> 6] = bj; }
-    __syncthreads();
-    bz = rz[0]; bj = rj[0];
-    for (int w = 1; w < 4; ++w)
-      if (rj[w] >= 0 && (bj < 0 || rz[w] > bz || (rz[w] == bz && rj[w] < bj))) { bz = rz[w]; bj = rj[w]; }
-    if (tid == 0) {
-      out_ids[(size_t)i * topk + k] = bj;
-      out_scores[(size_t)i * topk + k] = bj >= 0 ? bz : -INFINITY;
-    }
-    if (bj < 0) { pz = -INFINITY; pj = 0x7fffffff; } else { pz = bz; pj = bj; }
+  }, [&](int place, uint64_t key) {
+    out_ids[(size_t)i * topk + place] = (int32_t)(uint32_t)key;
+    out_scores[(size_t)i * topk + place] = topk_score(key);
+  });
+  for (int k = found + tid; k < topk; k += kSelectThreads) {
+    out_ids[(size_t)i * topk + k] = -1;
+    out_scores[(size_t)i * topk + k] = -INFINITY;
   }
 }
 
 hipError_t launch_topk(const ActiveDev& ad, const float* z, int topk, int32_t* out_ids, float* out_scores,
                        hipStream_t s) {
-  hipLaunchKernelGGL(topk_kernel, dim3(ad.B), dim3(256), 0, s, ad, z, topk, out_ids, out_scores);
+  hipLaunchKernelGGL(topk_kernel, dim3(ad.B), dim3(kSelectThreads), 0, s, ad, z, topk, out_ids, out_scores);
   return hipGetLastError();
 }
 

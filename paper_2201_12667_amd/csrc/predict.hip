@@ -10,24 +10,13 @@
 // also go to a scratch buffer, which the merge reads only for the first chunk or when a sample's
 // candidate buffer overflowed.
 #include "slide_internal.h"
+#include "topk.h"
 
 namespace slide {
 
 constexpr int kBN = 128;   // neurons per workgroup tile of the scoring kernel (chunks are multiples of it)
 constexpr int kTopkBuf = 2048;     // keys held in LDS by the top-k merge
 constexpr int kCand = kTopkBuf - 64; // candidate keys per sample and chunk handed over by the scoring kernel
-
-// Sort key of (score, id): ascending keys = descending scores, ties to the lower id.
-__device__ __forceinline__ uint64_t topk_key(float score, uint32_t id) {
-  const uint32_t u = __float_as_uint(score);
-  const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);   // orders like the float
-  return ((uint64_t)(~asc) << 32) | id;
-}
-__device__ __forceinline__ float topk_score(uint64_t key) {
-  const uint32_t asc = ~(uint32_t)(key >> 32);
-  return __uint_as_float((asc & 0x80000000u) ? (asc & 0x7fffffffu) : ~asc);
-}
-
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 

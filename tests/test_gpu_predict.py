@@ -101,6 +101,47 @@ def test_predict_when_every_or_no_later_neuron_beats_the_list(slope):
     model.destroy()
 
 
+@pytest.mark.parametrize("topk", [1, 33, 64])
+@pytest.mark.parametrize("layout", ["spread", "few-threads", "ties", "nan"])
+def test_predict_retrieved_selection_edges(layout, topk):
+    """The selection among thousands of retrieved neurons: best entries spread over the list; all of them in the
+    shares of 63 of the 256 selecting threads (more than one gather holds reach the bar); every score the
+    same (ties to the lower id); fewer comparable scores than topk.  The scores are the biases (W2 = 0), so the
+    expected lists are exact."""
+    _say("selection", layout, topk)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=32, K=1, L=16, num_classes=20011, batch=3,
+                     bucket_cap=1024, lab_mean=1.0)
+    gen, model, _ = make_pair(wl)
+    model.build_tables()
+    db = model.to_device(gen.batch(0))
+    model.predict(db, topk, mode=0)
+    as_ptr, ids, _, _, _ = model.debug_active()
+    rng = np.random.default_rng(3)
+    bias = rng.standard_normal(wl.num_classes).astype(np.float32)
+    mine = ids[as_ptr[0]:as_ptr[1]]
+    assert mine.size > 5000
+    if layout == "few-threads":
+        bias[mine[np.arange(mine.size) % 256 < 63]] += 100
+    elif layout == "ties":
+        bias[:] = 0
+        bias[::2] = -0.0
+    elif layout == "nan":
+        bias[:] = np.nan
+        bias[mine[::mine.size // 20]] = 1.5
+        bias[mine[7]] = -np.inf
+    model.p["W2"].zero_()
+    model.p["b2"].copy_(torch.from_numpy(bias))
+    got, sc = (x.cpu().numpy() for x in model.predict(db, topk, mode=0))
+    for i in range(wl.batch):
+        own = ids[as_ptr[i]:as_ptr[i + 1]]
+        own = own[~np.isnan(bias[own])]
+        own = own[np.lexsort((own, -bias[own]))][:topk]
+        assert np.array_equal(got[i, :own.size], own)
+        assert np.array_equal(sc[i, :own.size], bias[own])
+        assert np.all(got[i, own.size:] == -1) and np.all(np.isneginf(sc[i, own.size:]))
+    model.destroy()
+
+
 def test_prediction_quality_on_a_planted_task():
     """300 training steps on the GPU, then top-1 over the retrieved set (mode 0) and over all neurons
     (mode 1): both find the planted class, and they agree."""
