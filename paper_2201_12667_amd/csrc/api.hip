@@ -58,12 +58,12 @@ static size_t hash_offset_count(const slide_config* c) {
 struct Layout {
   // derived sizes
   int Bmax, Bpad, H, L, K, C, TW, TWF, NWpad, NT, NT2, NT1, DWpad, bits, PS;
-  int64_t dense_chunk;   // neurons per chunk of the dense prediction pass
+  DenseLayout dense;     // scratch of the prediction over all neurons
   int64_t N, D, Amax, max_chunks, U2max, U1max, P1max, long2, long1;
   uint32_t nb, wl_cap;
   size_t hash_words;
   // workspace offsets
-  size_t ctrl, hashw, hashoff, xse, zc, best, cand, ccnt, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
+  size_t ctrl, hashw, hashoff, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
       ylist, z, delta, partials, msum, loss_i, umeta2, pairs2, umeta1, pairs1, codes_t, entries, bh, pbase, worklist, touched, touched_rows, ws_total;
   // tables offsets
   size_t t_off, t_ids, tables_total;
@@ -161,10 +161,8 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   lo->hashw = take(lo->hash_words * 4);
   lo->hashoff = take(hash_offset_count(c) * 4);
   lo->xse = take(lo->D ? B * lo->NT1 * 8 : 0);
-  lo->dense_chunk = dense_chunk_neurons(lo->N, lo->Bmax);
-  lo->zc = take(B * (size_t)lo->dense_chunk * 4);
-  lo->best = take(B * 64 * 8);
-  lo->cand = take(B * dense_cand_keys() * 8); lo->ccnt = take(B * dense_counter_words() * 4);
+  lo->dense = dense_layout(lo->Bmax, lo->N, lo->H);
+  lo->dense_at = take(lo->dense.total);
   lo->h = take(lo->D ? B * H * 4 : 0);
   lo->dh = take(B * H * 4);
   lo->codes = take(B * lo->L * 4);
@@ -507,6 +505,7 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
   if (e == hipSuccess) { what = "hipFuncSetAttribute(table kernels)"; e = tables_setup_attributes(); }
   if (e == hipSuccess) { what = "hipFuncSetAttribute(forward kernels)"; e = forward_setup_attributes(ctx->lds_limit); }
   if (e == hipSuccess) { what = "hipFuncSetAttribute(update kernels)"; e = update_setup_attributes(ctx->lds_limit); }
+  if (e == hipSuccess) { what = "hipFuncSetAttribute(prediction kernels)"; e = predict_setup_attributes(); }
   if (e == hipSuccess) {
     what = "hipDeviceGetAttribute(compute units)";
     int dev = 0, cus = 0;
@@ -685,19 +684,20 @@ int slide_predict(slide_ctx* ctx, const slide_batch* b, int mode, int topk, int3
   if (mode == 1) {
     const Layout& lo = ctx->lo;
     const float* h = b->hidden;
+    SpmmArgs sp{};
     if (lo.D > 0) {
-      SpmmArgs sp = make_spmm(ctx, b);
+      sp = make_spmm(ctx, b);
       sp.xse = nullptr;                                  // (no training step follows on these activations)
-      HIPCHK(ctx, stage(ctx, SLIDE_STAGE_HIDDEN, s, [&] { return launch_spmm_relu(b->batch, sp, ctx->ctrl(), s); }));
       h = sp.h;
     }
+    char* scratch = ctx->ws() + lo.dense_at;
+    HIPCHK(ctx, stage(ctx, SLIDE_STAGE_HIDDEN, s, [&] { return launch_dense_prepare(b->batch, lo.H, h, sp, scratch, lo.dense, ctx->ctrl(), s); }));
     ctx->last_h = h;
     ctx->last_B = b->batch;
     ctx->last_labels = 0;
     ctx->last_dh = nullptr;
-    HIPCHK(ctx, launch_dense_topk(b->batch, lo.N, lo.H, h, ctx->buf.W2, ctx->buf.b2, topk, ctx->at<float>(lo.zc),
-                                  lo.dense_chunk, ctx->at<uint64_t>(lo.best), ctx->at<uint64_t>(lo.cand),
-                                  ctx->at<uint32_t>(lo.ccnt), d_out_ids, d_out_scores, s));
+    HIPCHK(ctx, launch_dense_topk(b->batch, lo.N, lo.H, h, ctx->buf.W2, ctx->buf.b2, topk, scratch, lo.dense, ctx->num_cus,
+                                  d_out_ids, d_out_scores, s));
     return SLIDE_OK;
   }
   ActiveDev ad;
@@ -721,33 +721,27 @@ int slide_predict_static(slide_ctx* ctx, const slide_batch* b, int topk, int32_t
     return set_err(ctx, SLIDE_ESTATE, "the current device (%d) is not the one this context was created on (%d)", dev, ctx->device);
   hipStream_t s = (hipStream_t)hip_stream;
   const Layout& lo = ctx->lo;
-  // the scratch array, carved up for the largest case (SLIDE_STATIC_MAX_BATCH samples, hidden_dim 2048);
-  // what is left holds the scores of one chunk of neurons
-  const size_t B = (size_t)b->batch, Bmax = SLIDE_STATIC_MAX_BATCH;
-  size_t o = 0;
-  auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return ctx->static_scratch + at; };
-  float* hbuf = (float*)take(Bmax * 2048 * 4);
-  uint64_t* best = (uint64_t*)take(Bmax * 64 * 8);
-  uint64_t* cand = (uint64_t*)take(Bmax * dense_cand_keys() * 8);
-  uint32_t* ccnt = (uint32_t*)take(Bmax * dense_counter_words() * 4);
-  float* zc = (float*)take(0);
-  if (o + B * 128 * 4 > kStaticScratchBytes) return set_err(ctx, SLIDE_ENOMEM, "static scratch too small");
-  int64_t chunk = (int64_t)((kStaticScratchBytes - o) / (B * 4)) / 128 * 128;
-  const int64_t npad = (lo.N + 127) / 128 * 128;
-  if (chunk > npad) chunk = npad;
+  // the scratch array: the hidden activations of the largest case (SLIDE_STATIC_MAX_BATCH samples, hidden_dim
+  // 2048), then what launch_dense_topk works in
+  float* hbuf = (float*)ctx->static_scratch;
+  char* scratch = ctx->static_scratch + (size_t)SLIDE_STATIC_MAX_BATCH * 2048 * 4;
+  const DenseLayout dense = dense_layout(b->batch, lo.N, lo.H);
+  if ((size_t)(scratch - ctx->static_scratch) + dense.total > kStaticScratchBytes)
+    return set_err(ctx, SLIDE_ENOMEM, "static scratch too small");
   const float* h = b->hidden;
+  SpmmArgs sp{};
   if (lo.D > 0) {
-    SpmmArgs sp = make_spmm(ctx, b);
+    sp = make_spmm(ctx, b);
     sp.h = hbuf;
     sp.xse = nullptr;                                   // (no training step follows on these activations)
-    HIPCHK(ctx, launch_spmm_relu(b->batch, sp, ctx->ctrl(), s));
     h = hbuf;
   }
+  HIPCHK(ctx, launch_dense_prepare(b->batch, lo.H, h, sp, scratch, dense, ctx->ctrl(), s));
   ctx->last_h = h;
   ctx->last_B = b->batch;
   ctx->last_labels = 0;
   ctx->last_dh = nullptr;
-  HIPCHK(ctx, launch_dense_topk(b->batch, lo.N, lo.H, h, ctx->buf.W2, ctx->buf.b2, topk, zc, chunk, best, cand, ccnt,
+  HIPCHK(ctx, launch_dense_topk(b->batch, lo.N, lo.H, h, ctx->buf.W2, ctx->buf.b2, topk, scratch, dense, ctx->num_cus,
                                 d_out_ids, d_out_scores, s));
   return SLIDE_OK;
 }

@@ -2,303 +2,590 @@
 // the k best per sample.  This is the dense evaluation the paper compares the hashed retrieval
 // against (Section 2.1: the tables are meant to return the neurons with the highest activations;
 // Section 4: accuracy is measured on full predictions).  Unlike the training path it is a dense
-// contraction: an fp32 matrix-core kernel (fp32 so that the scores agree with a double-precision
-// evaluation to 1e-4; half-precision matrix instructions would not), run over the neurons in
-// chunks, with a running list of the k best per sample.  From the second chunk on the scoring
-// kernel itself compares every score with the sample's current k-th best and hands only the ones
-// that beat it to the merge (a few per sample and chunk once the list has settled); the scores
-// also go to a scratch buffer, which the merge reads only for the first chunk or when a sample's
-// candidate buffer overflowed.
+// contraction, run on the matrix cores.
+//
+// Launches: (1) the samples' hidden activations, split for the matrix cores; (2) the scores of an evenly
+// spaced sample of about 8,192 neurons; (3) per sample the topk-th best of these, which is a bar that at
+// least topk neurons of the layer reach; (4) the scores of all neurons, of which only those that reach
+// their sample's bar are kept (about topk * N / 8,192 of them: the scores themselves are never written);
+// (5) per sample the topk best of these.  Layers of fewer than 16,384 neurons end after (3) with every
+// neuron sampled.  The bar comes from the whole id range, so an order of the ids (by frequency, say) does not
+// matter.
 #include "slide_internal.h"
+#include "spmm.h"
 #include "topk.h"
+
+#include <algorithm>
 
 namespace slide {
 
-constexpr int kBN = 128;   // neurons per workgroup tile of the scoring kernel (chunks are multiples of it)
-constexpr int kTopkBuf = 2048;     // keys held in LDS by the top-k merge
-constexpr int kCand = kTopkBuf - 64; // candidate keys per sample and chunk handed over by the scoring kernel
-
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kNB = 128;       // neurons per workgroup tile: 32 per wave
-constexpr int kKB = 32;        // contraction block: 16 matrix instructions of depth 2
-constexpr int kHP = kKB + 4;   // LDS pitch of a staged row of h (16-byte reads without bank conflicts)
-constexpr int kLocalCand = 2048; // candidates a workgroup gathers in LDS before handing them over
-constexpr int kCntPitch = 16;  // words between the candidate counters of two samples (one line each)
+constexpr int kScoreThreads = 512;         // eight waves, 32 neurons each
+constexpr int kTileNeurons = kScoreThreads / 2;
+constexpr int kSampled = 8192;             // neurons the bars are taken from (up to twice as many)
+constexpr int kCandMax = 16384;            // candidate keys per sample and launch
+constexpr int kCntPitch = 16;              // words between the candidate counters of two samples (one line each)
+constexpr int kFrag = 512;                 // values of an operand fragment: 32 rows x 16 coordinates
+constexpr int kResFrags = 16;              // (row block, coordinate block) pairs of h that may stay in LDS for good
+constexpr int kBlockPad = 8;               // coordinate blocks are padded (with zeros) to a multiple of this
+constexpr int kListed = 128;               // scores a wave lists before it hands them over
+constexpr int kCornerWords = 512 + 3 * kListed;    // LDS words of a wave: half a block of scores and that list
+constexpr size_t kCorners = (size_t)kScoreThreads / 64 * kCornerWords * 4;
+constexpr size_t kTriple = 3 * kFrag * 2;  // bytes of a fragment's three parts
+// Coordinate blocks of h staged at a time when it does not all fit.
+__host__ __device__ constexpr int stage_blocks(int NIB) { return NIB == 8 ? 2 : NIB == 1 ? 8 : 4; }
 
-// zc[i][j - j0] = b2[j] + sum_k h[i][k] * W2[j][k] for j0 <= j < j0 + nc, on the fp32 matrix cores
-// (32x32x2: one value of each operand per lane and step, 16 accumulators per lane and 32x32 block).
-// Rows of the product are samples, columns neurons.  A wave owns 32 neurons and all (up to 256) samples
-// of the tile: its W2 values come straight from memory (lane l: row l%32, the 16 consecutive k of
-// half l/32, so the two lanes of a row read one 128-byte line per block), the h values from an LDS
-// tile staged per block of 32 k (double-buffered, one barrier per block).  Step c of a block
-// contracts k = c and k = 16 + c: any pairing works as long as both operands use it.
-// Epilogue: bias, the score to zc, and -- from the second chunk on -- every score that beats the
-// sample's current topk-th key goes to the sample's candidate buffer.
-// NIB: row blocks of 32 samples per tile (1, 2, 4 or 8; rows past the batch are zeros).
-template <int NIB>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))) void dense_scores_kernel(int B, int64_t N, int H, const float* __restrict__ h,
-                                                           const float* __restrict__ W2,
-                                                           const float* __restrict__ b2, int64_t j0, int nc,
-                                                           float* __restrict__ zc, int topk,
-                                                           const uint64_t* __restrict__ best,
-                                                           uint64_t* __restrict__ cand, uint32_t* ccnt) {
-  constexpr int MB = NIB * 32;                                   // samples per tile
-  __shared__ __attribute__((aligned(16))) float hs[2][(MB * kHP * 4 < kLocalCand * 12 ? kLocalCand * 3 : MB * kHP)];
-  __shared__ uint64_t bars[MB];
-  __shared__ __attribute__((aligned(16))) float thr[MB];                                      // score of the bar: a cheap first test
-  __shared__ uint32_t lcnt;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  const int i0 = blockIdx.y * MB;
-  const int rows = min(B - i0, MB);
-  const int64_t n0 = j0 + (int64_t)blockIdx.x * kNB + wave * 32;
-  const int64_t nend = j0 + nc;
-  const int64_t jrow = min(n0 + col, N - 1);                     // clamped: columns past the end are not stored
-  const float* wrow = W2 + (size_t)jrow * H + 16 * half;
-  if (tid < MB) {
-    const uint64_t bar = (best && tid < rows) ? best[(size_t)(i0 + tid) * 64 + topk - 1] : 0ull;
-    bars[tid] = bar;
-    thr[tid] = bar == ~0ull ? -INFINITY : topk_score(bar);       // (list not full yet: everything is a candidate)
+// Eight floats as three bf16 vectors whose sum they are exactly (8 + 8 + 8 significand bits, each part
+// rounded to nearest, so that what a product of parts leaves out has either sign).  Values so large that
+// the first part rounds to infinity, infinities and NaN give a non-finite score, which the caller evaluates
+// again in plain arithmetic.
+__device__ __forceinline__ void split8(const float4& a, const float4& b, bf16x8 (&out)[3]) {
+  const f32x2 x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bf16x2 hi = __builtin_convertvector(x[q], bf16x2);
+    const f32x2 r1 = x[q] - __builtin_convertvector(hi, f32x2);
+    const bf16x2 mid = __builtin_convertvector(r1, bf16x2);
+    const f32x2 r2 = r1 - __builtin_convertvector(mid, f32x2);
+    const bf16x2 lo = __builtin_convertvector(r2, bf16x2);
+    out[0][2 * q] = hi[0]; out[0][2 * q + 1] = hi[1];
+    out[1][2 * q] = mid[0]; out[1][2 * q + 1] = mid[1];
+    out[2][2 * q] = lo[0]; out[2][2 * q + 1] = lo[1];
   }
+}
 
-  f32x16 acc[NIB];
-#pragma unroll
-  for (int ib = 0; ib < NIB; ++ib)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[ib][r] = 0.f;
-
-  // staging of h: 256 threads x NIB float4 cover MB rows x 32 k
-  const int srow = tid >> 3, sk = (tid & 7) * 4;
-  float4 hreg[NIB], wreg[4];
-  auto load_block = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < NIB; ++q) {
-      const int r = srow + 32 * q;
-      hreg[q] = (r < rows && k0 + sk < H) ? *(const float4*)(h + (size_t)(i0 + r) * H + k0 + sk)
-                                           : make_float4(0.f, 0.f, 0.f, 0.f);
+// (1) One workgroup per sample (rows past the batch: zeros): the hidden activations -- computed here in
+// sparse-input mode -- and their three parts in fragment order: fragment (row block, coordinate block, part)
+// is the 1 KB a wave reads as one operand, lane l holding row l % 32, coordinates 8 * (l / 32) .. + 7.
+__global__ __launch_bounds__(1024) void dense_prepare_kernel(int B, int H, int nkb, const float* __restrict__ h,
+                                                             SpmmArgs sp, bf16x8* __restrict__ frags, Ctrl* ctrl,
+                                                             int stage_words) {
+  extern __shared__ float lds[];                         // [stage_words] rows of W1, [H] the sample's activations
+  float* hvec = lds + stage_words;
+  const int i = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
+  if (i < B) {
+    if (sp.W1 && H <= nthr && spmm_stage_rows(stage_words, H, nthr) >= 32) {
+      spmm_sample_staged(sp, i, B, lds, stage_words, hvec, ctrl);
+    } else if (sp.W1) {
+      const int wave = tid >> 6;
+      if (wave * 128 < H) spmm_sample(sp, i, B, wave, tid & 63, hvec, ctrl);
+    } else {
+      for (int c = tid; c < H; c += nthr) hvec[c] = h[(size_t)i * H + c];
     }
-#pragma unroll
-    for (int wq = 0; wq < 4; ++wq)
-      wreg[wq] = (k0 + 16 * half + 4 * wq < H) ? *(const float4*)(wrow + k0 + 4 * wq) : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
-  auto store_block = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < NIB; ++q) *(float4*)&hs[buf][(srow + 32 * q) * kHP + sk] = hreg[q];
-  };
-
-  load_block(0);
-  store_block(0);
+  }
   __syncthreads();
-  const int nkb = (H + kKB - 1) / kKB;
-  for (int kb = 0; kb < nkb; ++kb) {
-    const int cur = kb & 1;
-    float4 w[4] = {wreg[0], wreg[1], wreg[2], wreg[3]};
-    if (kb + 1 < nkb) load_block((kb + 1) * kKB);                // in flight while this block is contracted
-    const float* hb = &hs[cur][col * kHP + 16 * half];
+  for (int c8 = tid; c8 < 2 * nkb; c8 += nthr) {          // (nkb: padded)
+    float x[8];
 #pragma unroll
-    for (int wq = 0; wq < 4; ++wq) {
-      float4 a[NIB];
+    for (int e = 0; e < 8; ++e) x[e] = (i < B && 8 * c8 + e < H) ? hvec[8 * c8 + e] : 0.f;
+    bf16x8 part[3];
+    split8(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]), part);
+    const int kb = c8 >> 1, lane = (c8 & 1) * 32 + (i & 31);
 #pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) a[ib] = *(const float4*)(hb + ib * 32 * kHP + 4 * wq);
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) acc[ib] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].x, w[wq].x, acc[ib], 0, 0, 0);
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) acc[ib] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].y, w[wq].y, acc[ib], 0, 0, 0);
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) acc[ib] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].z, w[wq].z, acc[ib], 0, 0, 0);
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) acc[ib] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ib].w, w[wq].w, acc[ib], 0, 0, 0);
+    for (int p = 0; p < 3; ++p) frags[((size_t)((i >> 5) * nkb + kb) * 3 + p) * 64 + lane] = part[p];
+  }
+}
+
+// A score in plain arithmetic, for the few that come out non-finite on the matrix cores.
+__device__ __forceinline__ float plain_score(const float* __restrict__ h, const float* __restrict__ w, float bias, int H) {
+  float s = 0.f;
+  for (int k = 0; k < H; ++k) s = fmaf(h[k], w[k], s);
+  return s + bias;
+}
+// Key of such a score while it waits for that (before every other key, so it passes every bar).
+__device__ __forceinline__ uint64_t open_key(uint32_t id) { return id; }
+__device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0; }
+
+// (2), (4) Scores of the neurons j0 + c * stride, c < nc (clamped to the layer), for all samples.
+// The 32-bit product is formed from bf16 products: with x = x0 + x1 + x2 the six products of parts whose
+// indices add up to at most two are accumulated in 32 bits; the three left out are below 2^-25 of |h||w| each,
+// the size of one rounding of the 32-bit chain this replaced, and its error against 64 bits was the same
+// 4e-8 (the bias is added last: sums that start from it lose four times that).  Six bf16 passes at 1/16 of the
+// cost each against one pass at the 32-bit matrix rate: the 44 GFLOP of 256 samples x 670K neurons x 128 took
+// 564 us there, 110 of them for writing the scores, and 250 here (matrix cores busy 43 % of the time: the rest
+// is the barrier per stage with eight waves per compute unit); 8 samples, bound by reading W2: 118 and 75 us
+// (4.6 TB/s).
+// Product rows are samples, columns neurons.  A wave owns 32 neurons and all NIB * 32 samples of the
+// workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
+// workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in
+// fragment order -- RES: it all fits (48 KB), is staged once, and the waves never meet again; otherwise the next stage is fetched under the products of this one.
+// STORE: every score goes to zs (the sampled neurons); otherwise the scores that reach their sample's bar go
+// to its candidate buffer.
+template <int NIB, bool STORE, bool RES>
+__global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4) void dense_scores_kernel(
+    int B, int64_t N, int H, int nkbp, const float4* frags, const float* __restrict__ W2, const float* __restrict__ b2, int64_t j0, int nc, int stride, float* __restrict__ zs,
+    const uint64_t* __restrict__ bars, uint64_t* __restrict__ cand, uint32_t* ccnt, int cand_cap) {
+  constexpr int MB = NIB * 32;                           // samples per workgroup
+  constexpr int KS = stage_blocks(NIB);                  // coordinate blocks per stage
+  constexpr int PIECES = NIB * KS * 192;                 // 16-byte pieces of a stage
+  constexpr int PPT = (RES ? kResFrags * 192 : PIECES) / kScoreThreads;   // ... per thread
+  extern __shared__ f32x4 hs[];                          // [row block][coordinate block][part][lane], twice unless RES; the waves' corners
+  __shared__ uint64_t bar_s[MB];
+  __shared__ float thr[MB];                              // score of the bar
+  __shared__ __attribute__((aligned(16))) float thr4[MB / 4];   // lowest of four samples' (row block, half, group)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int i0 = blockIdx.y * MB, rows = min(B - i0, MB);
+  const int ntiles = (nc + kTileNeurons - 1) / kTileNeurons;
+  if ((int)blockIdx.x >= ntiles) return;
+  // coordinate blocks to go through (at least four where they are staged: the loads run two blocks ahead, and no
+  // further than the next tile)
+  const int nkb = RES ? (H + 15) / 16 : max(4, (H + 16 * KS - 1) / (16 * KS) * KS);
+  const f32x4* mine = (const f32x4*)frags + (size_t)blockIdx.y * NIB * nkbp * 192;
+
+  // The stage that starts at block kb0 (RES: everything), a fragment part (1 KB) per wave and step: part q % per
+  // of row block q / per.
+  constexpr int WAVES = kScoreThreads / 64;
+  const int per = RES ? nkb * 3 : KS * 3;
+  auto fetch = [&](int kb0, int u) -> f32x4 {
+    const int q = min(u * WAVES + wave, NIB * per - 1), ib = q / per, r = q - ib * per;
+    return mine[((size_t)(ib * nkbp + kb0) * 3 + r) * 64 + lane];
+  };
+  auto put = [&](int buf, int u, const f32x4& x) {
+    const int q = u * WAVES + wave;
+    if (!RES || q < NIB * per) hs[(RES ? 0 : buf * PIECES) + q * 64 + lane] = x;
+  };
+  auto neuron_of = [&](int tile) -> int64_t {
+    const int64_t j = j0 + (int64_t)(tile * kTileNeurons + wave * 32 + col) * stride;
+    return j < N ? j : N - 1;                            // (columns past the end are not looked at)
+  };
+  // The W2 values to come: block lk of tile lt.  (Loads are unconditional, so that the waits for them can be
+  // counted: past the end of the row the last four values are read again, against zeros of h.)
+  int lt = blockIdx.x, lk = 0;
+  const float* wrow = W2 + (size_t)neuron_of(lt) * H;
+  const float* wnext = wrow;                             // the row of the workgroup's next tile (!RES)
+  const int kmax = H - 4;
+  float4 wb0[2], wb1[2];
+  auto issue = [&](float4 (&w)[2]) {
+    const int k = lk * 16 + 8 * half;
+    w[0] = *(const float4*)(wrow + min(k, kmax));
+    w[1] = *(const float4*)(wrow + min(k + 4, kmax));
+    if (RES) {
+      if (++lk == nkb) {
+        lk = 0;
+        lt = lt + (int)gridDim.x < ntiles ? lt + (int)gridDim.x : lt;
+        wrow = W2 + (size_t)neuron_of(lt) * H;
+      }
+    } else {                                             // (a branch would let the compiler move the stage's loads behind it)
+      const bool wrap = lk + 1 == nkb;
+      lk = wrap ? 0 : lk + 1;
+      wrow = wrap ? wnext : wrow;
     }
-    if (kb + 1 < nkb) store_block(cur ^ 1);                      // the other buffer was last read before the previous barrier
+  };
+  issue(wb0);
+  issue(wb1);
+  if (!STORE)
+    for (int q = tid; q < MB; q += kScoreThreads) {
+      const uint64_t bar = q < rows ? bars[i0 + q] : 0ull;
+      bar_s[q] = bar;
+      thr[q] = q >= rows ? INFINITY : bar == ~0ull ? -INFINITY : topk_score(bar);
+    }
+  for (int u = 0; u < PPT; ++u) put(0, u, fetch(0, u));
+  __syncthreads();
+  if constexpr (!STORE) {
+    if (tid < MB / 4) {
+      const float* t = thr + (tid >> 3) * 32 + 8 * (tid & 3) + 4 * ((tid >> 2) & 1);
+      thr4[tid] = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
+      if (t[0] != t[0] || t[1] != t[1] || t[2] != t[2] || t[3] != t[3]) thr4[tid] = -INFINITY;   // (a bar of NaN)
+    }
     __syncthreads();
   }
 
-  // lane holds column `col`, rows 8*(r/4) + 4*half + r%4 of each 32x32 block.  Two passes, so that the
-  // 128 score stores of a lane are issued back to back with no memory operation of another kind between
-  // them: first the scores that beat their sample's bar are gathered in LDS (over the h tiles, which are
-  // no longer read), then everything is stored.  The gathered candidates are handed to the samples'
-  // global buffers afterwards, one entry per thread, so that the round trips of the counter updates overlap.
-  uint64_t* lkey = (uint64_t*)&hs[0][0];
-  uint32_t* lsmp = (uint32_t*)(lkey + kLocalCand);
-  if (tid == 0) lcnt = 0;
-  __syncthreads();
-  const int64_t n = n0 + col;
-  const bool live = n < nend;
-  const float bias = live ? b2[n] : 0.f;
-  if (best != nullptr) {
-    {
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int il0 = ib * 32 + 8 * g + 4 * half;            // four consecutive samples
-          const float4 t4 = *(const float4*)&thr[il0];
-          const float t[4] = {t4.x, t4.y, t4.z, t4.w};
-          float z[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = acc[ib][4 * g + e] + bias;
-          if (live && (!(z[0] < t[0]) | !(z[1] < t[1]) | !(z[2] < t[2]) | !(z[3] < t[3]))) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (!(z[e] < t[e]) && il0 + e < rows) {              // rare: now the exact test, ties by id
-                const uint64_t key = topk_key(z[e], (uint32_t)n);
-                if (key < bars[il0 + e]) {
-                  const uint32_t pos = atomicAdd(&lcnt, 1u);
-                  if (pos < (uint32_t)kLocalCand) { lkey[pos] = key; lsmp[pos] = (uint32_t)(il0 + e); }
-                }
-              }
-          }
-        }
+  // the wave's corner: half a 32x32 block of scores, and the scores that passed the first test (score, column,
+  // sample), handed to the samples' buffers together when the list fills and at the end: the exact test (ties by
+  // id) and a lane's counter update and store each
+  float* bounce = (float*)(hs + (RES ? NIB * nkb * 192 : 2 * PIECES)) + wave * kCornerWords;
+  float* list_z = bounce + 512;
+  int* list_c = (int*)list_z + kListed;
+  int* list_i = list_c + kListed;
+  int listed = 0;
+  auto flush = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    for (int q = lane; q < listed; q += 64) {
+      const float z = list_z[q];
+      const int il = list_i[q];
+      const uint32_t id = (uint32_t)(j0 + (int64_t)list_c[q] * stride);
+      const uint64_t key = fabsf(z) < INFINITY ? topk_key(z, id) : open_key(id);
+      if (key <= bar_s[il]) {
+        const uint32_t pos = atomicAdd(&ccnt[(size_t)(i0 + il) * kCntPitch], 1u);
+        if (pos < (uint32_t)cand_cap) cand[(size_t)(i0 + il) * cand_cap + pos] = key;
       }
     }
-  }
-  if (live) {
-    const bool whole = rows == MB;
-    float* zcol = zc + (size_t)(i0 + 4 * half) * nc + (size_t)(n - j0);
-    if (whole) {
+    __builtin_amdgcn_wave_barrier();
+    listed = 0;
+  };
+
+  f32x16 acc[NIB];
+  // the products of one coordinate block: block kl of what hb points at
+  auto contract = [&](float4 (&wr)[2], const bf16x8* hb, int ib_pitch) {
+    bf16x8 w[3];
+    split8(wr[0], wr[1], w);
+    issue(wr);
+    if (!RES) asm volatile("" ::: "memory");             // (not later: see below)
+    constexpr int G = NIB < 2 ? NIB : 2;                 // row blocks interleaved (independent accumulators)
 #pragma unroll
-      for (int ib = 0; ib < NIB; ++ib)
+    for (int ib = 0; ib < NIB; ib += G) {
+      bf16x8 a[G][3];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) zcol[(size_t)(ib * 32 + 8 * (r >> 2) + (r & 3)) * nc] = acc[ib][r] + bias;
-    } else {
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a[g][p] = hb[(ib + g) * ib_pitch + p * 64];
+#pragma unroll
+      for (int pr = 0; pr < 6; ++pr) {
+        constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};   // small products first
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          acc[ib + g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][pa[pr]], w[pb[pr]], acc[ib + g], 0, 0, 0);
+      }
+    }
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[ib][r] = 0.f;
+  };
+  auto finish = [&](int tile, float bias) {
+    // lane holds column `col`, rows 8*(r/4) + 4*half + r%4 of each 32x32 block
+    const int c = tile * kTileNeurons + wave * 32 + col;
+    const bool live = c < nc;
+    if constexpr (STORE) {
 #pragma unroll
       for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int rl = ib * 32 + 8 * (r >> 2) + (r & 3);
-          if (rl + 4 * half < rows) zcol[(size_t)rl * nc] = acc[ib][r] + bias;
+          const int il = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+          if (live && il < rows) zs[(size_t)(i0 + il) * nc + c] = acc[ib][r] + bias;
         }
-    }
-  }
-  __syncthreads();
-  const uint32_t nl = lcnt;
-  if (nl > (uint32_t)kLocalCand) {
-    // more candidates than the LDS holds: every sample of the tile is told to stream this chunk's scores
-    if (tid < rows) atomicAdd(&ccnt[(size_t)(i0 + tid) * kCntPitch], (uint32_t)kCand + 1u);
-    return;
-  }
-  for (uint32_t e = tid; e < nl; e += 256) {
-    const int i = i0 + (int)lsmp[e];
-    const uint32_t pos = atomicAdd(&ccnt[(size_t)i * kCntPitch], 1u);
-    if (pos < (uint32_t)kCand) cand[(size_t)i * kCand + pos] = lkey[e];
-  }
-}
-
-__device__ void bitonic_sort_keys(uint64_t* keys, int n) {
-  for (int k = 2; k <= n; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n / 2; i += 256) {
-        const int a = 2 * j * (i / j) + (i % j), b = a + j;
-        const bool up = (a & k) == 0;
-        const uint64_t x = keys[a], y = keys[b];
-        if ((x > y) == up) { keys[a] = y; keys[b] = x; }
+    } else {
+      // First test, whole blocks: the largest of four consecutive samples' scores (NaN counts as largest) against
+      // the lowest of their bars.  The blocks in which something passes (about half of them) go through the wave's
+      // corner of the LDS, half a block at a time, and every lane hands on what reaches its own bar.
+      uint32_t todo = 0;
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) {
+        const float4 low = *(const float4*)&thr4[(ib * 2 + half) * 4];
+        const float t[4] = {low.x, low.y, low.z, low.w};
+        bool pass = false;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float top = __builtin_elementwise_maximum(__builtin_elementwise_maximum(acc[ib][4 * g], acc[ib][4 * g + 1]),
+                                                          __builtin_elementwise_maximum(acc[ib][4 * g + 2], acc[ib][4 * g + 3]));
+          pass |= !(top + bias < t[g]);                  // (the rounded sum grows with its first operand)
+        }
+        if (__any(live && pass)) todo |= 1u << ib;
       }
-      __syncthreads();
+#pragma unroll 1
+      while (todo) {
+        const int ib = __ffs(todo) - 1;
+        todo &= todo - 1;
+#pragma unroll 1
+        for (int hf = 0; hf < 2; ++hf) {
+          uint32_t mask = 0;                             // rows of this half block that the lane hands on
+#pragma unroll
+          for (int I = 0; I < 2 * NIB; ++I)
+            if (2 * ib + hf == I) {
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const int r = 8 * (I & 1) + q, il = (I >> 1) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+                const float z = acc[I >> 1][r] + bias;
+                bounce[q * 64 + lane] = z;
+                mask |= !(z < thr[il]) ? 1u << q : 0u;
+              }
+            }
+          if (!live) mask = 0;
+#pragma unroll 1
+          while (true) {
+            const unsigned long long m = __ballot(mask != 0u);
+            if (!m) break;
+            if (listed + 64 > kListed) flush();
+            if (mask) {
+              const int q = __ffs(mask) - 1, r = 8 * hf + q;
+              mask &= mask - 1;
+              const int at = listed + __popcll(m & ((1ull << lane) - 1ull));
+              list_z[at] = bounce[q * 64 + lane];
+              list_c[at] = c;
+              list_i[at] = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+            }
+            listed += __popcll(m);
+          }
+        }
+      }
     }
-}
-
-// One workgroup per sample: folds one chunk of neurons into the sample's running list of the topk
-// best keys (best[i][0..64), ascending; ~0 = empty).  Normally the chunk arrives as the candidate keys
-// the scoring kernel collected; for the first chunk, or when more than kCand scores beat the bar, it
-// streams the chunk's scores instead: only scores that beat the current topk-th key are collected,
-// and when the LDS buffer fills it is sorted and cut back to topk, which raises the bar.  The last
-// chunk also decodes the list into the caller's arrays.
-__global__ __launch_bounds__(256) void topk_merge_kernel(int nc, int64_t j0, const float* __restrict__ zc, int topk,
-                                                         uint64_t* __restrict__ best, int first, int last,
-                                                         const uint64_t* __restrict__ cand, uint32_t* ccnt,
-                                                         int32_t* __restrict__ out_ids,
-                                                         float* __restrict__ out_scores) {
-  __shared__ uint64_t keys[kTopkBuf];
-  __shared__ uint32_t cnt;
-  const int i = blockIdx.x, tid = threadIdx.x;
-  uint64_t* mine = best + (size_t)i * 64;
-  const uint32_t ncand = first ? 0u : ccnt[(size_t)i * kCntPitch];
-  const bool stream = first || ncand > (uint32_t)kCand;
-  __syncthreads();
-  if (tid == 0) ccnt[(size_t)i * kCntPitch] = 0;
-  if (!stream && ncand == 0 && !last) return;          // nothing beat the bar: the list stands
-  int nsort = kTopkBuf;
-  if (!stream) {
-    nsort = 128;                                        // power of two holding the list and the candidates
-    while (nsort < 64 + (int)ncand) nsort <<= 1;
-    const uint64_t* cv = cand + (size_t)i * kCand;
-    for (int q = tid; q < nsort; q += 256)
-      keys[q] = q < topk ? mine[q] : (q >= 64 && q < 64 + (int)ncand ? cv[q - 64] : ~0ull);
-    __syncthreads();
+  };
+  const bf16x8* hb = (const bf16x8*)hs + lane;
+  if constexpr (RES) {
+    const int units = ((ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x) * nkb;
+    int tile = blockIdx.x, kb = 0;
+    float bias, bias_next = b2[neuron_of(tile)];
+    auto unit = [&](float4 (&wr)[2]) {
+      if (kb == 0) {
+        clear();
+        bias = bias_next;
+        bias_next = b2[neuron_of(tile + (int)gridDim.x < ntiles ? tile + (int)gridDim.x : tile)];
+      }
+      contract(wr, hb + kb * 192, nkb * 192);
+      if (++kb < nkb) return;
+      finish(tile, bias);
+      kb = 0;
+      tile += gridDim.x;
+    };
+    for (int u = 0; u < units; u += 2) {
+      unit(wb0);
+      if (u + 1 < units) unit(wb1);
+    }
   } else {
-    for (int q = tid; q < kTopkBuf; q += 256) keys[q] = (q < topk && !first) ? mine[q] : ~0ull;
-    if (tid == 0) cnt = (uint32_t)topk;
-    __syncthreads();
-    uint64_t bar = keys[topk - 1];
-    const float* row = zc + (size_t)i * nc;
-    for (int base = 0; base < nc; base += 256) {
-      const int q = base + tid;
-      if (q < nc) {
-        const uint64_t key = topk_key(row[q], (uint32_t)(j0 + q));
-        if (key < bar) keys[atomicAdd(&cnt, 1u)] = key;   // at most 256 more per round: the buffer has room
-      }
-      __syncthreads();
-      if (cnt > (uint32_t)(kTopkBuf - 256)) {              // (uniform: cnt is read after the barrier)
+    int buf = 0;
+    float bias_next = b2[neuron_of(blockIdx.x)];
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {   // (the same for every wave of the workgroup)
+      const int64_t next = neuron_of(tile + (int)gridDim.x < ntiles ? tile + (int)gridDim.x : tile);
+      wnext = W2 + (size_t)next * H;
+      const float bias = bias_next;
+      bias_next = b2[next];
+      clear();
+      for (int kb = 0; kb < nkb; kb += KS) {
+        // the next stage (after the last: the next tile's first)
+        const int nkb0 = kb + KS < nkb ? kb + KS : 0;
+        static_assert(PPT == 3 || PPT == 6, "fragment parts per wave and stage");
+        f32x4 n3, n4, n5;
+        const f32x4 n0 = fetch(nkb0, 0), n1 = fetch(nkb0, 1), n2 = fetch(nkb0, 2);
+        if constexpr (PPT == 6) { n3 = fetch(nkb0, 3); n4 = fetch(nkb0, 4); n5 = fetch(nkb0, 5); }
+        asm volatile("" ::: "memory");                   // These loads stay ahead of the products (the compiler would move
+        __builtin_amdgcn_sched_barrier(0);               // them to their use, and does so with pointers it knows to be
+                                                         // read-only: frags and W2 are not __restrict__).
+#pragma unroll
+        for (int kl = 0; kl < KS; kl += 2) {
+          contract(wb0, hb + buf * PIECES + kl * 192, KS * 192);
+          contract(wb1, hb + buf * PIECES + (kl + 1) * 192, KS * 192);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        put(buf ^ 1, 0, n0); put(buf ^ 1, 1, n1); put(buf ^ 1, 2, n2);
+        if constexpr (PPT == 6) { put(buf ^ 1, 3, n3); put(buf ^ 1, 4, n4); put(buf ^ 1, 5, n5); }
         __syncthreads();
-        bitonic_sort_keys(keys, kTopkBuf);
-        for (int p = topk + tid; p < kTopkBuf; p += 256) keys[p] = ~0ull;
-        if (tid == 0) cnt = (uint32_t)topk;
-        __syncthreads();
-        bar = keys[topk - 1];
+        buf ^= 1;
       }
+      finish(tile, bias);
     }
-    __syncthreads();
-    nsort = 128;                                        // the collected keys sit at the front, ~0 behind them
-    while (nsort < (int)cnt) nsort <<= 1;
   }
-  bitonic_sort_keys(keys, nsort);
-  for (int q = tid; q < topk; q += 256) {
-    const uint64_t key = keys[q];
-    mine[q] = key;
-    if (last) {
-      const bool empty = key == ~0ull;
-      out_ids[(size_t)i * topk + q] = empty ? -1 : (int32_t)(uint32_t)key;
-      out_scores[(size_t)i * topk + q] = empty ? -INFINITY : topk_score(key);
+  if constexpr (!STORE) flush();
+}
+
+// (3) Per sample: the topk-th best of the sampled scores (neuron of column c: c * stride) as the bar, or, when
+// every neuron was sampled (out_ids given), the result.
+__global__ __launch_bounds__(kSelectThreads) void dense_bar_kernel(int H, const float* __restrict__ h,
+                                                                   const float* __restrict__ W2,
+                                                                   const float* __restrict__ b2, int nc, int stride,
+                                                                   const float* __restrict__ zs, int topk, uint64_t* __restrict__ bars,
+                                                                   uint32_t* __restrict__ ccnt,
+                                                                   int32_t* __restrict__ out_ids,
+                                                                   float* __restrict__ out_scores) {
+  __shared__ SelectLds lds;
+  const int i = blockIdx.x, tid = threadIdx.x;
+  const float* row = zs + (size_t)i * nc;
+  constexpr int UN = 16;                                 // scores per thread in flight
+  const int found = select_topk(lds, topk, [&](auto&& f) {
+    for (int c0 = tid; c0 < nc; c0 += UN * kSelectThreads) {
+      float z[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) z[u] = row[min(c0 + u * kSelectThreads, nc - 1)];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int c = c0 + u * kSelectThreads;
+        if (c >= nc) continue;
+        const uint32_t j = (uint32_t)c * (uint32_t)stride;
+        if (!(fabsf(z[u]) < INFINITY)) z[u] = plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H);
+        f(topk_key(z[u], j));
+      }
     }
+  }, [&](int place, uint64_t key) {
+    if (out_ids) {
+      out_ids[(size_t)i * topk + place] = (int32_t)(uint32_t)key;
+      out_scores[(size_t)i * topk + place] = topk_score(key);
+    } else if (place == topk - 1) {
+      bars[i] = key;
+    }
+  });
+  if (out_ids) {
+    for (int k = found + tid; k < topk; k += kSelectThreads) {
+      out_ids[(size_t)i * topk + k] = -1;
+      out_scores[(size_t)i * topk + k] = -INFINITY;
+    }
+  } else if (tid == 0) {
+    ccnt[(size_t)i * kCntPitch] = 0;
+    if (found < topk) bars[i] = ~0ull;
   }
 }
 
-size_t dense_cand_keys() { return (size_t)kCand; }
-size_t dense_counter_words() { return (size_t)kCntPitch; }
+// (5) Per sample: folds the candidates of one launch of scores into the running list of the topk best
+// (best[i][0..64), read when `first` is 0); the last launch writes the result.  A sample with more candidates
+// than its buffer holds (the neurons that reach the bar sit between the sampled ones by an unlikely accident)
+// evaluates the launch's neurons itself.
+__global__ __launch_bounds__(kSelectThreads) void dense_merge_kernel(int H, const float* __restrict__ h,
+                                                                     const float* __restrict__ W2,
+                                                                     const float* __restrict__ b2, int64_t j0, int nc, int topk,
+                                                                     uint64_t* __restrict__ best, uint64_t* __restrict__ bars,
+                                                                     int first, int last, const uint64_t* __restrict__ cand,
+                                                                     uint32_t* ccnt, int cand_cap,
+                                                                     int32_t* __restrict__ out_ids,
+                                                                     float* __restrict__ out_scores) {
+  __shared__ SelectLds lds;
+  __shared__ uint64_t list[64];
+  const int i = blockIdx.x, tid = threadIdx.x;
+  const uint32_t ncand = ccnt[(size_t)i * kCntPitch];
+  if (tid < 64) list[tid] = !first && tid < topk ? best[(size_t)i * 64 + tid] : ~0ull;
+  __syncthreads();
+  const uint64_t* mine = cand + (size_t)i * cand_cap;
+  constexpr int UN = 4;
+  const int found = select_topk(lds, topk, [&](auto&& f) {
+    if (tid < 64) f(list[tid]);
+    if (ncand <= (uint32_t)cand_cap) {
+      for (uint32_t q0 = tid; q0 < ncand; q0 += UN * kSelectThreads) {
+        uint64_t k[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) k[u] = mine[min(q0 + (uint32_t)(u * kSelectThreads), ncand - 1u)];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+          if (q0 + (uint32_t)(u * kSelectThreads) >= ncand) continue;
+          const uint32_t j = (uint32_t)k[u];
+          if (is_open(k[u])) k[u] = topk_key(plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H), j);
+          f(k[u]);
+        }
+      }
+    } else {
+      for (int c = tid; c < nc; c += kSelectThreads) {
+        const int64_t j = j0 + c;
+        f(topk_key(plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H), (uint32_t)j));
+      }
+    }
+  }, [&](int place, uint64_t key) {
+    if (last) {
+      out_ids[(size_t)i * topk + place] = (int32_t)(uint32_t)key;
+      out_scores[(size_t)i * topk + place] = topk_score(key);
+    } else {
+      best[(size_t)i * 64 + place] = key;
+      if (place == topk - 1 && key < bars[i]) bars[i] = key;
+    }
+  });
+  for (int k = found + tid; k < topk; k += kSelectThreads) {
+    if (last) {
+      out_ids[(size_t)i * topk + k] = -1;
+      out_scores[(size_t)i * topk + k] = -INFINITY;
+    } else {
+      best[(size_t)i * 64 + k] = ~0ull;
+    }
+  }
+  if (tid == 0) ccnt[(size_t)i * kCntPitch] = 0;
+}
 
-int64_t dense_chunk_neurons(int64_t N, int Bmax) {
-  int64_t nc = ((int64_t)256 << 20) / ((int64_t)Bmax * 4);    // about 256 MiB of scores
-  nc = nc / kBN * kBN;
-  if (nc < kBN) nc = kBN;
-  const int64_t npad = (N + kBN - 1) / kBN * kBN;
-  return nc < npad ? nc : npad;
+// ---- host side --------------------------------------------------------------------------------------
+static int dense_stride(int64_t N) { return (int)std::max<int64_t>(1, N / kSampled); }
+static int64_t dense_sampled(int64_t N) { return (N + dense_stride(N) - 1) / dense_stride(N); }
+static int dense_cand_cap(int64_t N) { return (int)std::min<int64_t>(N, kCandMax); }
+static int padded_blocks(int H) { return ceil_div(ceil_div(H, 16), kBlockPad) * kBlockPad; }
+static int dense_row_blocks(int B) { return B <= 32 ? 1 : B <= 64 ? 2 : B <= 128 ? 4 : 8; }
+
+DenseLayout dense_layout(int Bmax, int64_t N, int H) {
+  DenseLayout d;
+  size_t o = 0;
+  auto take = [&](size_t bytes) { const size_t at = o; o = (o + bytes + 255) / 256 * 256; return at; };
+  const size_t B = (size_t)Bmax, MB = (size_t)dense_row_blocks(Bmax) * 32, rows = (B + MB - 1) / MB * MB;
+  d.frags = take(rows * (size_t)padded_blocks(H) * 16 * 6);
+  d.zs = take(B * (size_t)dense_sampled(N) * 4);
+  d.bars = take(B * 8);
+  d.best = take(B * 64 * 8);
+  d.cand = take(B * (size_t)dense_cand_cap(N) * 8);
+  d.ccnt = take(B * kCntPitch * 4);
+  d.total = o;
+  return d;
+}
+
+template <int NIB, bool STORE>
+static hipError_t launch_scores(int B, int64_t N, int H, const float4* frags, const float* W2, const float* b2,
+                                int64_t j0, int nc, int stride, float* zs, const uint64_t* bars, uint64_t* cand,
+                                uint32_t* ccnt, int cand_cap, int num_cus, hipStream_t s) {
+  const int nkb = ceil_div(H, 16), nkbp = padded_blocks(H), gy = ceil_div(B, NIB * 32), ntiles = ceil_div(nc, kTileNeurons);
+  const bool res = NIB <= 2 && NIB * nkb <= kResFrags;
+  // as many workgroups as fit: three of the resident kind per compute unit (two with the registers of two row
+  // blocks), one of the staging kind
+  const int per_cu = !res ? 1 : NIB == 1 ? 3 : 2;
+  const size_t lds = (res ? NIB * nkb : 2 * NIB * stage_blocks(NIB)) * kTriple + (STORE ? 0 : kCorners);
+  const int gx = std::max(1, std::min(ntiles, num_cus * per_cu / std::min(gy, num_cus)));
+  const dim3 grid(gx, gy), block(kScoreThreads);
+  if (res)
+    hipLaunchKernelGGL((dense_scores_kernel<NIB <= 2 ? NIB : 2, STORE, true>), grid, block, lds, s, B, N, H, nkbp, frags, W2, b2,
+                       j0, nc, stride, zs, bars, cand, ccnt, cand_cap);
+  else
+    hipLaunchKernelGGL((dense_scores_kernel<NIB, STORE, false>), grid, block, lds, s, B, N, H, nkbp, frags, W2,
+                       b2, j0, nc, stride, zs, bars, cand, ccnt, cand_cap);
+  return hipGetLastError();
+}
+
+template <int NIB, bool STORE>
+static hipError_t scores_attr() {
+  hipError_t e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB <= 2 ? NIB : 2, STORE, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kResFrags * kTriple + kCorners));
+  if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, STORE, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * NIB * stage_blocks(NIB) * kTriple + (STORE ? 0 : kCorners)));
+  return e;
+}
+
+// words of LDS for the rows of W1 of one sample: 64 KB, more for rows so long that 32 of them need it
+static int prepare_stage_words(int H) { return (H <= 448 ? 64 : 144) * 256; }
+
+hipError_t predict_setup_attributes() {
+  hipError_t e = hipFuncSetAttribute((const void*)dense_prepare_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+  if (e == hipSuccess) e = scores_attr<1, true>();
+  if (e == hipSuccess) e = scores_attr<2, true>();
+  if (e == hipSuccess) e = scores_attr<1, false>();
+  if (e == hipSuccess) e = scores_attr<2, false>();
+  if (e == hipSuccess) e = scores_attr<4, false>();
+  if (e == hipSuccess) e = scores_attr<8, false>();
+  return e;
+}
+
+hipError_t launch_dense_prepare(int B, int H, const float* h, const SpmmArgs& sp, char* scratch, const DenseLayout& d,
+                                Ctrl* ctrl, hipStream_t s) {
+  const int MB = dense_row_blocks(B) * 32, words = sp.W1 ? prepare_stage_words(H) : 0;
+  hipLaunchKernelGGL(dense_prepare_kernel, dim3(ceil_div(B, MB) * MB), dim3(sp.W1 ? 1024 : 256), (size_t)(words + H) * 4, s, B, H,
+                     padded_blocks(H), h, sp, (bf16x8*)(scratch + d.frags), ctrl, words);
+  return hipGetLastError();
 }
 
 hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const float* W2, const float* b2, int topk,
-                             float* zc, int64_t chunk, uint64_t* best, uint64_t* cand, uint32_t* ccnt,
-                             int32_t* out_ids, float* out_scores, hipStream_t s) {
-  hipError_t e = launch_fill_u32(ccnt, (size_t)B * kCntPitch, 0u, s);
+                             char* scratch, const DenseLayout& d, int num_cus, int32_t* out_ids, float* out_scores,
+                             hipStream_t s) {
+  const float4* frags = (const float4*)(scratch + d.frags);
+  float* zs = (float*)(scratch + d.zs);
+  uint64_t *bars = (uint64_t*)(scratch + d.bars), *best = (uint64_t*)(scratch + d.best), *cand = (uint64_t*)(scratch + d.cand);
+  uint32_t* ccnt = (uint32_t*)(scratch + d.ccnt);
+  const int stride = dense_stride(N), ns = (int)dense_sampled(N), cap = dense_cand_cap(N);
+  const bool all = stride == 1;
+  // the sampled neurons are few: small row blocks, so that the samples spread over the machine
+  hipError_t e = B <= 32 ? launch_scores<1, true>(B, N, H, frags, W2, b2, 0, ns, stride, zs, nullptr, nullptr, nullptr, 0, num_cus, s)
+                         : launch_scores<2, true>(B, N, H, frags, W2, b2, 0, ns, stride, zs, nullptr, nullptr, nullptr, 0, num_cus, s);
   if (e != hipSuccess) return e;
-  // The first chunk is what the merge can stream without an intermediate sort.  Later chunks grow with
-  // the number of neurons already seen -- in random order about topk * chunk / seen scores of a chunk
-  // beat a list settled on the neurons before it, kept near 512 of the kCand a sample can hand over --
-  // up to the scratch buffer's size.
-  const int64_t grow = topk <= 32 ? 16 : 512 / topk;
-  const int64_t first_nc = (kTopkBuf - 256 - 64) / kBN * kBN;
-  int64_t nc = chunk < first_nc ? chunk : first_nc;
-  for (int64_t j0 = 0; j0 < N; j0 += nc, nc = (j0 * grow < chunk ? j0 * grow / kBN * kBN : chunk)) {
-    if (nc > N - j0) nc = N - j0;
-    const int first = j0 == 0 ? 1 : 0, last = j0 + nc >= N ? 1 : 0;
-    const uint64_t* bars = first ? (const uint64_t*)nullptr : best;
-    const unsigned gx = (unsigned)ceil_div(nc, kNB);
-#define SLIDE_SCORES(NIB) \
-    hipLaunchKernelGGL((dense_scores_kernel<NIB>), dim3(gx, (unsigned)ceil_div(B, NIB * 32)), dim3(256), 0, s, B, N, H, h, \
-                       W2, b2, j0, (int)nc, zc, topk, bars, cand, ccnt)
-    if (B <= 32) SLIDE_SCORES(1); else if (B <= 64) SLIDE_SCORES(2); else if (B <= 128) SLIDE_SCORES(4); else SLIDE_SCORES(8);
+  hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(kSelectThreads), 0, s, H, h, W2, b2, ns, stride, zs, topk, bars, ccnt,
+                     all ? out_ids : nullptr, all ? out_scores : nullptr);
+  if (all) return hipGetLastError();
+  // About topk * nc / ns of nc neurons reach the bar; a launch takes as many neurons as bring the candidate
+  // buffers to half their size (all of them up to topk * stride = 8,192).
+  const int64_t most = std::max<int64_t>(kTileNeurons, (int64_t)ns * (cap / 2) / topk / kTileNeurons * kTileNeurons);
+  for (int64_t j0 = 0; j0 < N; j0 += most) {
+    const int nc = (int)std::min<int64_t>(std::min<int64_t>(most, (int64_t)1 << 30), N - j0);
+#define SLIDE_SCORES(NIB) launch_scores<NIB, false>(B, N, H, frags, W2, b2, j0, nc, 1, nullptr, bars, cand, ccnt, cap, num_cus, s)
+    switch (dense_row_blocks(B)) {
+      case 1: e = SLIDE_SCORES(1); break;
+      case 2: e = SLIDE_SCORES(2); break;
+      case 4: e = SLIDE_SCORES(4); break;
+      default: e = SLIDE_SCORES(8); break;
+    }
 #undef SLIDE_SCORES
-    hipLaunchKernelGGL(topk_merge_kernel, dim3(B), dim3(256), 0, s, (int)nc, j0, zc, topk, best, first, last, cand, ccnt,
-                       out_ids, out_scores);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(dense_merge_kernel, dim3(B), dim3(kSelectThreads), 0, s, H, h, W2, b2, j0, nc, topk, best, bars,
+                       j0 == 0 ? 1 : 0, j0 + nc >= N ? 1 : 0, cand, ccnt, cap, out_ids, out_scores);
   }
   return hipGetLastError();
 }

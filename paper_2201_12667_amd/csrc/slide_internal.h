@@ -181,14 +181,17 @@ hipError_t launch_topk(const ActiveDev& ad, const float* z, int topk, int32_t* o
                        float* out_scores, hipStream_t s);
 
 // ---- predict.hip ----------------------------------------------------------------------
-// Scores over all N neurons in chunks of `chunk` neurons (zc: [B][chunk] scratch) and the topk best
-// per sample (best: [B][64] scratch keys).
-int64_t dense_chunk_neurons(int64_t N, int Bmax);
+// Scores over all N neurons and the topk best per sample.  Offsets into the call's scratch, for at most the
+// batch it was made for.
+struct DenseLayout { size_t frags, zs, bars, best, cand, ccnt, total; };
+DenseLayout dense_layout(int Bmax, int64_t N, int H);
+hipError_t predict_setup_attributes();
+// Hidden activations (sp.W1 != nullptr: computed here, into sp.h; else read from h) split for the matrix cores.
+hipError_t launch_dense_prepare(int B, int H, const float* h, const SpmmArgs& sp, char* scratch, const DenseLayout& d,
+                                Ctrl* ctrl, hipStream_t s);
 hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const float* W2, const float* b2, int topk,
-                             float* zc, int64_t chunk, uint64_t* best, uint64_t* cand, uint32_t* ccnt,
-                             int32_t* out_ids, float* out_scores, hipStream_t s);
-size_t dense_cand_keys();     // candidate keys per sample (cand is [B][dense_cand_keys()])
-size_t dense_counter_words(); // words per sample in ccnt
+                             char* scratch, const DenseLayout& d, int num_cus, int32_t* out_ids, float* out_scores,
+                             hipStream_t s);
 
 // ---- update.hip -----------------------------------------------------------------------
 // Rows of one weight matrix to update: for every listed row r, g = sum over its pairs of

@@ -101,6 +101,42 @@ def test_predict_when_every_or_no_later_neuron_beats_the_list(slope):
     model.destroy()
 
 
+@pytest.mark.parametrize("N,H,batch", [(16384, 16, 33), (16640, 32, 32), (40009, 36, 65), (40009, 128, 129),
+                                       (33001, 272, 40), (30011, 264, 200)])
+def test_predict_all_when_the_sampled_neurons_mislead(N, H, batch):
+    """The bar of the dense pass comes from every (N // 8192)-th neuron: here those are the worst of the layer,
+    so that nearly every other neuron reaches the bar (more than a sample's candidate buffer holds for the
+    larger N: that sample evaluates the layer itself), and a few neurons carry weights that are no ordinary numbers
+    (infinite, or so large that their bf16 part is).  Row blocks, staged and resident h, ragged coordinates."""
+    _say("misleading sample", N, H, batch)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=H, K=3, L=3, num_classes=N, batch=batch, bucket_cap=8)
+    gen, model, orc = make_pair(wl)
+    rng = np.random.default_rng(1)
+    bias = (rng.standard_normal(N) * 0.01).astype(np.float32)
+    bias[np.arange(N) % (N // 8192) != 0] += 10
+    W2 = orc.p["W2"].copy()
+    W2[N - 1, H - 1] = np.inf
+    W2[7, 0] = -np.inf
+    W2[N // 2, :4] = 3.4e38 * np.array([1, -1, 1, 0], np.float32)
+    model.p["W2"].copy_(torch.from_numpy(W2))
+    model.p["b2"].copy_(torch.from_numpy(bias))
+    model.build_tables()
+    b = gen.batch(0)
+    b["hidden"][:, [0, H - 1]] = 0.5
+    b["hidden"][:, 1:3] = 0.25
+    for topk in (2, 64):
+        ids, sc = (x.cpu().numpy() for x in model.predict(model.to_device(b), topk, mode=1))
+        assert np.all(ids[:, 0] == N - 1) and np.all(np.isposinf(sc[:, 0]))
+        assert np.all(ids[:, 1] == N // 2) and np.allclose(sc[:, 1], 1.7e38, rtol=1e-5)
+        keep = np.ones(N, bool)
+        keep[[N - 1, 7, N // 2]] = False
+        z = b["hidden"].astype(np.float64) @ W2[keep].astype(np.float64).T + bias[keep].astype(np.float64)
+        if topk > 2:
+            back = np.cumsum(keep) - 1
+            assert _check_topk(back[ids[:, 2:]], sc[:, 2:], z, topk - 2) > 0.97
+    model.destroy()
+
+
 @pytest.mark.parametrize("topk", [1, 33, 64])
 @pytest.mark.parametrize("layout", ["spread", "few-threads", "ties", "nan"])
 def test_predict_retrieved_selection_edges(layout, topk):
