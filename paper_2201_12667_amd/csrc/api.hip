@@ -63,7 +63,8 @@ struct Layout {
   uint32_t nb, wl_cap;
   size_t hash_words;
   // workspace offsets
-  size_t ctrl, hashw, hashoff, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
+  SimhashSplit srp;      // the hash functions as a matrix (SimHash)
+  size_t ctrl, hashw, hashoff, hashmat, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
       ylist, z, delta, partials, msum, loss_i, umeta2, pairs2, umeta1, pairs1, codes_t, entries, bh, pbase, worklist, touched, touched_rows, ws_total;
   // tables offsets
   size_t t_off, t_ids, tables_total;
@@ -160,6 +161,8 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   lo->ctrl = take(sizeof(Ctrl));
   lo->hashw = take(lo->hash_words * 4);
   lo->hashoff = take(hash_offset_count(c) * 4);
+  lo->srp = c->hash_kind == SLIDE_HASH_SIMHASH ? simhash_split(c->hidden_dim, c->K, c->L) : SimhashSplit{};
+  lo->hashmat = take(simhash_matrix_words(lo->srp) * 2);
   lo->xse = take(lo->D ? B * lo->NT1 * 8 : 0);
   lo->dense = dense_layout(lo->Bmax, lo->N, lo->H);
   lo->dense_at = take(lo->dense.total);
@@ -421,6 +424,13 @@ static std::vector<uint32_t> hash_offsets(const slide_config* cfg, const std::ve
   return offs;
 }
 
+// SimHash functions as the matrix the matrix-core kernel reads (empty: not for it).
+static std::vector<uint16_t> hash_matrix(const slide_config* cfg, const Layout& lo, const slide_hash_params* hp) {
+  std::vector<uint16_t> m(simhash_matrix_words(lo.srp), 0);
+  if (!m.empty()) simhash_matrix(lo.srp, cfg->hidden_dim, cfg->K, cfg->L, cfg->srp_nnz, hp->srp_idx, hp->srp_sign, m.data());
+  return m;
+}
+
 // Hash-function parameters -> packed 16-bit coordinate words (validated).
 static int pack_hash_params(const slide_config* cfg, const Layout& lo, const slide_hash_params* hp,
                             std::vector<uint32_t>& words) {
@@ -500,6 +510,11 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
     what = "hipMemcpy(hash offsets)";
     e = hipMemcpy(ctx->ws() + lo.hashoff, offs.data(), offs.size() * 4, hipMemcpyHostToDevice);
   }
+  if (e == hipSuccess && lo.srp.nkb) {
+    const std::vector<uint16_t> mat = hash_matrix(cfg, lo, hp);
+    what = "hipMemcpy(hash matrix)";
+    e = hipMemcpy(ctx->ws() + lo.hashmat, mat.data(), mat.size() * 2, hipMemcpyHostToDevice);
+  }
   if (e == hipSuccess) { what = "hipFuncSetAttribute(hash kernels)"; e = hash_setup_attributes(H); }
   if (e == hipSuccess) { what = "hipFuncSetAttribute(active-set kernels)"; e = active_setup_attributes(&ctx->lds_limit); }
   if (e == hipSuccess) { what = "hipFuncSetAttribute(table kernels)"; e = tables_setup_attributes(); }
@@ -552,6 +567,8 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
   hd.S = cfg->srp_nnz; hd.Spad = (cfg->srp_nnz + 1) / 2 * 2; hd.So = simhash_offset_stride(cfg->srp_nnz);
   hd.words = ctx->at<uint32_t>(lo.hashw);
   hd.offs = ctx->at<uint32_t>(lo.hashoff);
+  hd.smat = lo.srp.nkb ? ctx->at<uint16_t>(lo.hashmat) : nullptr;
+  hd.num_cus = ctx->num_cus;
   hd.dens_a = hp->dens_a; hd.dens_b = hp->dens_b;
   TablesDev& td = ctx->td;
   td.off = (uint32_t*)((char*)buf->tables + lo.t_off);
@@ -584,6 +601,8 @@ int slide_set_hash_params(slide_ctx* ctx, const slide_hash_params* hp, void* hip
     const std::vector<uint32_t> offs = hash_offsets(&ctx->cfg, words);
     HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashw, words.data(), words.size() * 4, hipMemcpyHostToDevice));
     HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashoff, offs.data(), offs.size() * 4, hipMemcpyHostToDevice));
+    const std::vector<uint16_t> mat = hash_matrix(&ctx->cfg, ctx->lo, hp);
+    if (!mat.empty()) HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashmat, mat.data(), mat.size() * 2, hipMemcpyHostToDevice));
   }
   ctx->hd.dens_a = hp->dens_a; ctx->hd.dens_b = hp->dens_b;
   ctx->codes_current = false;

@@ -11,6 +11,10 @@
 // NaN), so that a comparison is one unsigned compare and two selects.
 #include "slide_internal.h"
 
+#include <algorithm>
+#include <cstring>
+#include <vector>
+
 namespace slide {
 
 // Vectors per tile of the row-tile kernel: 64 (a wave per table) while two tiles fit a compute unit's LDS;
@@ -196,6 +200,201 @@ __device__ __forceinline__ uint32_t simhash_code(const HashDev& hd, const uint32
   return code;
 }
 
+// ---------------------------------------------------------------------------------------------
+// SimHash of many vectors on the matrix cores.  A bit is the sign of the 32-bit running sum of S signed
+// coordinates, in storage order; the order only matters when the sum is within its rounding errors of zero.  So
+// the sums are formed as a matrix product of the vectors, split into two bf16 parts, with a matrix of 0 and
+// +-1, and where the product is further from zero than both evaluations' errors together its sign is the bit.
+// The rest (2 in 10,000 for S = 43) is summed exactly as documented, by the whole wave.
+//
+// Errors, with M = the vector's largest magnitude and u = 2^-24: the running sum is off by at most S * S*M*u; the
+// two parts leave 2^-18 of each coordinate out, S*M*2^-18 in all; the matrix cores add 2S non-zero terms, each
+// addition off by at most 2u of a partial sum below S*M (they may truncate).  Together S*M * (5*S*u + 2^-18);
+// the bound used has 6 in place of 5.
+//
+// A wave holds the fragments of 32 vectors in registers (columns of the product) and goes through the hash
+// matrix, 32 rows at a time, which its workgroup keeps in LDS.  The 16 rows whose results land in a lane are 16
+// consecutive bits of the lane's stream, K per table from the most significant: the lower half wave has its own
+// tables, the upper half its own.  The matrix holds the negated signs, so that a set sign bit is a set bit.
+// 325,056 vectors of 128 coordinates, 450 bits of 43 coordinates: 607 us with the kernel below (a lane per
+// vector, three vector instructions and an LDS read per coordinate), 110 here: 75 GFLOP, 32 us at the MFMA rate;
+// the rest is the bits summed exactly (a fifth of the 32 x 32 blocks holds one).  253,855 vectors of 200: 790 -> 201.
+// Vectors longer than 256 coordinates (128 registers of fragments) stay with the kernel below.
+// ---------------------------------------------------------------------------------------------
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// NKB: blocks of 16 coordinates held (H <= 16 * NKB).  hd.smat: [chunk][nblk][NKB][64 lanes][8]; a chunk holds
+// tph tables per half wave.
+template <int NKB>
+__global__ __launch_bounds__(NKB <= 8 ? 1024 : 512) void simhash_rows_kernel(HashDev hd, const float* __restrict__ V,
+                                                                             int64_t rows, uint32_t* __restrict__ codes,
+                                                                             int64_t row_stride, int64_t tab_stride,
+                                                                             const int32_t* __restrict__ rowlist,
+                                                                             const uint32_t* __restrict__ nrows_dev,
+                                                                             int nblk, int tph) {
+  extern __shared__ float4 smat[];                       // [nblk][NKB][64]
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, H = hd.H, S = hd.S, K = hd.K;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  if (rowlist) {
+    const int64_t listed = (int64_t)*nrows_dev;
+    if (listed == rows) rowlist = nullptr;               // every vector: in place, without the list
+    rows = listed;
+  }
+  const int64_t ngroups = (rows + 31) / 32;
+  if ((int64_t)blockIdx.x >= ngroups) return;
+  const float4* src = (const float4*)hd.smat + (size_t)blockIdx.y * nblk * NKB * 64;
+  for (int q = tid; q < nblk * NKB * 64; q += blockDim.x) smat[q] = src[q];
+  __syncthreads();
+  const int t_half = (blockIdx.y * 2 + half) * tph;      // first table of the lane's half
+  const int t_own = max(0, min(tph, hd.L - t_half));     // tables it has
+  // (a workgroup's waves take groups far apart: when the groups do not divide evenly every workgroup has some of
+  // the waves with one group more)
+  for (int64_t g = (int64_t)wave * gridDim.x + blockIdx.x; g < ngroups; g += (int64_t)nw * gridDim.x) {
+    const int64_t q = g * 32 + (lane & 31);
+    const bool live = q < rows;
+    const int64_t row = rowlist ? (int64_t)rowlist[live ? q : rows - 1] : (live ? q : rows - 1);
+    const float* v = V + (size_t)row * H;
+    bf16x8 hi[NKB], mid[NKB];
+    float top = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      const int k = kb * 16 + 8 * half;                  // (past the end: the last coordinates again, against zeros)
+      const float4 a = *(const float4*)(v + min(k, H - 4)), b = *(const float4*)(v + min(k + 4, H - 4));
+      const f32x2 x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bf16x2 h2 = __builtin_convertvector(x[e], bf16x2);
+        const bf16x2 m2 = __builtin_convertvector(x[e] - __builtin_convertvector(h2, f32x2), bf16x2);
+        hi[kb][2 * e] = h2[0]; hi[kb][2 * e + 1] = h2[1];
+        mid[kb][2 * e] = m2[0]; mid[kb][2 * e + 1] = m2[1];
+        top = __builtin_elementwise_maximum(top, __builtin_elementwise_maximum(fabsf(x[e][0]), fabsf(x[e][1])));   // (NaN stays)
+      }
+    }
+    top = __builtin_elementwise_maximum(top, __shfl_xor(top, 32));
+    // magnitudes whose parts would overflow or lose bits: every bit in storage order
+    const bool zero = top == 0.f, plain = !(top < 1e37f) || (!zero && top < 1e-30f);
+    const float bound = zero ? -1.f : plain ? INFINITY : top * (float)S * (3.8146973e-6f + 6.f * 5.9604645e-8f * (float)S);
+    uint64_t stream = 0;
+    int held = 0, t = 0;                                 // bits in the stream, tables done (uniform)
+#pragma unroll 1
+    for (int blk = 0; blk < nblk; ++blk) {
+      const bf16x8* m = (const bf16x8*)(smat + blk * NKB * 64) + lane;
+      f32x16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        const bf16x8 a = m[kb * 64];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, mid[kb], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hi[kb], acc, 0, 0, 0);
+      }
+      uint32_t bits = 0;
+      float low = INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(acc[r]), 31);   // bits << 1 | sign
+        low = __builtin_elementwise_minimum(low, fabsf(acc[r]));               // (NaN stays)
+      }
+      if (__any(live && !(low > bound))) {
+        uint32_t open = 0;                               // bits too close to call
+#pragma unroll
+        for (int r = 0; r < 16; ++r) open |= !(fabsf(acc[r]) > bound) ? 0x8000u >> r : 0u;
+        const int filled = t_own * K - blk * 16;         // (the rows past the half's tables are zeros)
+        open &= filled >= 16 ? 0xffffu : filled > 0 ? 0xffffu & ~(0xffffu >> filled) : 0u;
+        if (!live) open = 0;
+        while (true) {
+          const unsigned long long any = __ballot(open != 0u);
+          if (!any) break;
+          const int src_lane = __ffsll((long long)any) - 1;
+          const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)open, src_lane);
+          const int r = __clz((int)o) - 16, s = blk * 16 + r;                   // the stream's s-th bit
+          const int ti = s / K, tt = (blockIdx.y * 2 + (src_lane >> 5)) * tph + ti;
+          float sum = 0.f;
+          const int e = tt * K + (K - 1 - (s - ti * K));
+          const uint64_t rr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(row >> 32), src_lane) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane((int)row, src_lane);
+          const float* vr = V + (size_t)rr * H;
+          const uint32_t* words = hd.words + (size_t)e * (hd.Spad / 2);
+          for (int s0 = 0; s0 < S; s0 += 64) {
+            const int mine = min(s0 + lane, S - 1);
+            const uint32_t w = words[mine >> 1] >> (16 * (mine & 1));
+            const float x = vr[w & 0x7fffu];
+            const int signed_x = __float_as_int((w & 0x8000u) ? -x : x);
+            for (int k = 0; k < min(64, S - s0); ++k) sum += __int_as_float(__builtin_amdgcn_readlane(signed_x, k));
+          }
+          if (lane == src_lane) {
+            bits = (bits & ~(0x8000u >> r)) | (sum > 0.f ? 0x8000u >> r : 0u);
+            open &= ~(0x8000u >> r);
+          }
+        }
+      }
+      if (zero) bits = 0;
+      stream = (stream << 16) | bits;
+      held += 16;
+      while (held >= K && t < tph) {
+        held -= K;
+        const uint32_t code = (uint32_t)(stream >> held) & ((1u << K) - 1u);
+        if (live && t < t_own) codes[row * row_stride + (int64_t)(t_half + t) * tab_stride] = code;
+        ++t;
+      }
+    }
+  }
+}
+
+constexpr int kSimhashMaxBlocks = 16;      // coordinate blocks of the longest vectors taken
+constexpr size_t kSimhashLds = 128 * 1024; // LDS for the hash matrix
+
+SimhashSplit simhash_split(int H, int K, int L) {
+  SimhashSplit p{};
+  const int nkb = (H + 15) / 16;
+  if (nkb > kSimhashMaxBlocks) return p;
+  p.nkb = nkb <= 2 ? 2 : nkb <= 4 ? 4 : nkb <= 8 ? 8 : nkb <= 13 ? 13 : 16;
+  const int most = (int)(kSimhashLds / 1024) / p.nkb, per_half = (L + 1) / 2;      // blocks of a chunk; tables of a half
+  const int tables = most * 16 / K > 0 ? most * 16 / K : 1;                        // ... that a chunk can hold
+  p.chunks = (per_half + tables - 1) / tables;
+  p.tph = (per_half + p.chunks - 1) / p.chunks;
+  p.nblk = (p.tph * K + 15) / 16;
+  return p;
+}
+
+// The hash matrix in fragment order: lane l of block (chunk, blk, kb) holds row l % 32, coordinates
+// 16*kb + 8*(l / 32) .. + 7.  Row 8*(r/4) + 4*half + r%4 of a block is bit 16*blk + r of the half's stream.
+void simhash_matrix(const SimhashSplit& p, int H, int K, int L, int S, const int32_t* idx, const int8_t* sign, uint16_t* out) {
+  std::vector<int> sum(H);
+  for (int c = 0; c < p.chunks; ++c)
+    for (int half = 0; half < 2; ++half)
+      for (int s = 0; s < p.tph * K; ++s) {
+        const int t = (c * 2 + half) * p.tph + s / K;
+        if (t >= L) continue;
+        const int e = t * K + (K - 1 - s % K), blk = s / 16, r = s % 16, m = 8 * (r / 4) + 4 * half + r % 4;
+        std::fill(sum.begin(), sum.end(), 0);
+        for (int q = 0; q < S; ++q) sum[idx[(size_t)e * S + q]] -= sign[(size_t)e * S + q];
+        for (int k = 0; k < H; ++k) {                    // (a coordinate listed more than once: small integers, exact in bf16)
+          if (!sum[k]) continue;
+          const float f = (float)sum[k];
+          uint32_t u;
+          memcpy(&u, &f, 4);
+          const int kb = k / 16, lane = ((k % 16) / 8) * 32 + m;
+          out[((((size_t)c * p.nblk + blk) * p.nkb + kb) * 64 + lane) * 8 + k % 8] = (uint16_t)(u >> 16);
+        }
+      }
+}
+
+template <int NKB>
+static hipError_t launch_simhash(const HashDev& hd, const SimhashSplit& p, const float* V, int64_t rows, uint32_t* codes,
+                                 int64_t row_stride, int64_t tab_stride, const int32_t* rowlist, const uint32_t* nrows_dev,
+                                 int num_cus, hipStream_t s) {
+  const int per = num_cus / p.chunks > 0 ? num_cus / p.chunks : 1;
+  const int64_t groups = (rows + 31) / 32;
+  hipLaunchKernelGGL((simhash_rows_kernel<NKB>), dim3((unsigned)(groups < per ? groups : per), p.chunks),
+                     dim3(NKB <= 8 ? 1024 : 512), (size_t)p.nblk * NKB * 1024, s, hd, V, rows, codes, row_stride, tab_stride,
+                     rowlist, nrows_dev, p.nblk, p.tph);
+  return hipGetLastError();
+}
+
 // MODE 0: SimHash; 2,4,8,16: DWTA with that bin size.  UNI: a tile holds 64 vectors, so a wave works
 // on one table at a time and reads its coordinates through scalar loads.
 // rowlist == nullptr: vectors 0 .. rows-1 of V.  Otherwise the vectors rowlist[0 .. *nrows_dev) of V
@@ -287,6 +486,18 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
                        const uint32_t* nrows_dev, int tables_per_block, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int tpb = tables_per_block < 1 ? 1 : tables_per_block;
+  if (hd.kind == SLIDE_HASH_SIMHASH && hd.smat) {
+    const SimhashSplit p = simhash_split(hd.H, hd.K, hd.L);
+#define SLIDE_SRP(NKB) return launch_simhash<NKB>(hd, p, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, hd.num_cus, s)
+    switch (p.nkb) {
+      case 2: SLIDE_SRP(2);
+      case 4: SLIDE_SRP(4);
+      case 8: SLIDE_SRP(8);
+      case 13: SLIDE_SRP(13);
+      case 16: SLIDE_SRP(16);
+    }
+#undef SLIDE_SRP
+  }
   if (hd.kind == SLIDE_HASH_SIMHASH)
     return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
   switch (hd.m) {
@@ -314,6 +525,11 @@ hipError_t hash_setup_attributes(int H) {
   SLIDE_SET((hash_rows_kernel<4, false>))
   SLIDE_SET((hash_rows_kernel<8, false>))
   SLIDE_SET((hash_rows_kernel<16, false>))
+#undef SLIDE_SET
+#define SLIDE_SET(NKB) \
+  e = hipFuncSetAttribute((const void*)&simhash_rows_kernel<NKB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSimhashLds); \
+  if (e != hipSuccess) return e;
+  SLIDE_SET(2) SLIDE_SET(4) SLIDE_SET(8) SLIDE_SET(13) SLIDE_SET(16)
 #undef SLIDE_SET
   return hipSuccess;
 }

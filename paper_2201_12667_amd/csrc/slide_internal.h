@@ -50,8 +50,16 @@ struct HashDev {
                           // two u16 (bit 15 = subtract)
   const uint32_t* offs;   // the same coordinates as byte offsets into the row-tile kernel's LDS tile, one
                           // entry each (SimHash: bit 31 = subtract; padding entries point at a zero cell)
+  const uint16_t* smat;   // SimHash, H <= 256: the hash functions as a matrix of bf16 0 and -+1 (simhash_matrix)
+  int num_cus;            // compute units of the device
   uint32_t dens_a, dens_b;
 };
+// SimHash on the matrix cores: coordinate blocks held per vector (0: not taken), chunks of the hash matrix,
+// 32-row blocks per chunk, tables per half wave and chunk.
+struct SimhashSplit { int nkb, chunks, nblk, tph; };
+SimhashSplit simhash_split(int H, int K, int L);
+inline size_t simhash_matrix_words(const SimhashSplit& p) { return (size_t)p.chunks * p.nblk * p.nkb * 512; }
+void simhash_matrix(const SimhashSplit& p, int H, int K, int L, int S, const int32_t* idx, const int8_t* sign, uint16_t* out);
 
 struct AdamDev {
   float beta1, omb1, beta2, omb2, lr, inv_bc1, inv_bc2, eps;

@@ -41,6 +41,34 @@ def test_hash_codes_bit_exact(kind, H, K, L):
     model.destroy()
 
 
+@pytest.mark.parametrize("H,K,L,rows", [(4, 1, 1, 1), (32, 4, 8, 33), (36, 17, 3, 100), (64, 9, 50, 64), (128, 9, 50, 700),
+                                        (200, 9, 51, 333), (208, 5, 100, 31), (256, 24, 5, 65), (256, 9, 90, 97)])
+def test_simhash_sums_near_zero(H, K, L, rows):
+    """SimHash bits whose sums are zero, or within rounding of it, beside ordinary ones: vectors of small integers
+    (exact zeros, where storage order does not matter), of large values that cancel except for small ones (where it
+    decides), of the extremes of the range; every padding of the coordinates and every split of the tables."""
+    _say("simhash near zero", H, K, L, rows)
+    wl = synth.small(synth.HASH_SIMHASH, hidden_dim=H, K=K, L=L, input_dim=0, num_classes=300, batch=8)
+    gen, model, orc = make_pair(wl)
+    rng = np.random.default_rng(H + K)
+    V = rng.standard_normal((rows, H)).astype(np.float32)
+    third = max(rows // 3, 1)
+    V[:third] = rng.integers(-2, 3, (third, H))
+    V[third:2 * third] *= 10.0 ** rng.integers(-6, 7, (len(V[third:2 * third]), H))
+    for r, scale in ((0, 1e30), (1, 1e37), (2, 1e-37), (3, 1e-44)):
+        if rows > 40:
+            V[30 + r] = V[60 % rows] * scale
+    if rows > 50:
+        V[40] = 0
+        V[41, 0] = np.inf
+        V[42, H - 1] = np.nan
+        V[43] = -0.0
+    want = orc.hash.codes(V)
+    got = model.debug_hash(V)
+    assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+    model.destroy()
+
+
 @pytest.mark.parametrize("kind,policy,C,N", [(synth.HASH_SIMHASH, 1, 16, 2000), (synth.HASH_SIMHASH, 0, 5, 1500),
                                              (synth.HASH_DWTA, 1, 16, 20011), (synth.HASH_DWTA, 0, 3, 5000),
                                              (synth.HASH_SIMHASH, 1, 128, 30000),
