@@ -10,6 +10,7 @@
 // For DWTA the tile holds order-preserving integer keys instead of floats (0 = entry absent: zero or
 // NaN), so that a comparison is one unsigned compare and two selects.
 #include "slide_internal.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 #include <cstring>
@@ -198,6 +199,228 @@ __device__ __forceinline__ uint32_t simhash_code(const HashDev& hd, const uint32
     code |= (acc > 0.0f ? 1u : 0u) << k;
   }
   return code;
+}
+
+// ---------------------------------------------------------------------------------------------
+// DWTA (bins of eight) of many vectors when the functions are many: the winner of a bin depends on the order of
+// the coordinates only, so every vector's coordinates are replaced by their ranks first (equal values get
+// equal ranks), and a bin is then decided on 16-bit keys, two vectors to a lane: key = (rank + 128) << 3 | (7 -
+// position), so that one maximum gives the winner and, among equals, the lowest position.  Per bin and 128
+// vectors: 8 LDS reads, 7 ORs, 4 three-operand packed maxima and 5 more instructions, against twice 8 reads and
+// 25 instructions with 32-bit keys.  (The maximum is the packed 16-bit floating one: the keys of present
+// coordinates are ordinary positive numbers and order like integers.)
+//
+// The ranks: a wave sorts a vector's 128 keys in its registers (a bitonic network, two keys a lane, exchanges by
+// DPP moves and half-wave swaps: 104 instructions), puts them in LDS, and every coordinate finds its place by
+// bisection.  That costs about as much as 600 functions, hence the rule in launch_hash.
+// 670,091 vectors of 128 coordinates, 2,400 functions: 1,311 -> 739 us (about 200 of them for the ranks; the bins issue 50 instructions each, 17 of them
+// vector ones: with eight waves a SIMD the waits for the offsets and keys are the rest).
+// ---------------------------------------------------------------------------------------------
+constexpr int kRankThreads = 512;
+constexpr int kRankRows = 128;             // vectors per workgroup
+constexpr int kRankPitch = 65;             // words between consecutive coordinates (the pitch the byte offsets are for)
+constexpr int kRankMaxH = 128;
+constexpr int kRankMinFunctions = 600;
+static size_t ranked_lds(int H) { return ((size_t)H * kRankPitch + kRankThreads / 64 * 128) * 4; }
+constexpr uint32_t kRankBase = 128;        // (keys of present coordinates start at 1024: normal 16-bit floats)
+
+__device__ __forceinline__ uint32_t med3(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t d;
+  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ uint32_t max3_pk(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t d;
+  asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t min_pk(uint32_t a, uint32_t b) {
+  const u16x2 r = __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b));
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// Ascending sort of 128 keys, lane l holding elements 2l (a) and 2l + 1 (b).  A lane keeps the smaller of a pair
+// where its mask is 0 and the larger where it is ~0: the median of both and the mask.
+struct SortMasks { uint32_t m1, m2, m4, m8, d16, d32; };   // ~0 in lanes with that bit set
+__device__ __forceinline__ SortMasks sort_masks(int lane) {
+  return {(lane & 1) ? ~0u : 0u, (lane & 2) ? ~0u : 0u, (lane & 4) ? ~0u : 0u, (lane & 8) ? ~0u : 0u,
+          (lane & 16) ? ~0u : 0u, (lane & 32) ? ~0u : 0u};
+}
+template <int CTRL> __device__ __forceinline__ uint32_t dpp0(uint32_t v) { return dpp_u32<CTRL>(0u, v); }
+__device__ __forceinline__ uint32_t lane_xor4(uint32_t v) { return dpp0<0x1B>(dpp0<kDppRowHalfMirror>(v)); }   // (7 ^ 3)
+template <int CTRL> __device__ __forceinline__ void exchange(uint32_t& a, uint32_t& b, uint32_t k) {   // same element of lane ^ x
+  const uint32_t pa = dpp0<CTRL>(a), pb = dpp0<CTRL>(b);
+  a = med3(a, pa, k); b = med3(b, pb, k);
+}
+template <int CTRL> __device__ __forceinline__ void exchange_mirror(uint32_t& a, uint32_t& b, uint32_t k) {   // the other element
+  const uint32_t pa = dpp0<CTRL>(b), pb = dpp0<CTRL>(a);
+  a = med3(a, pa, k); b = med3(b, pb, k);
+}
+__device__ __forceinline__ void exchange_xor4(uint32_t& a, uint32_t& b, uint32_t k) {
+  const uint32_t pa = lane_xor4(a), pb = lane_xor4(b);
+  a = med3(a, pa, k); b = med3(b, pb, k);
+}
+__device__ __forceinline__ void exchange_own(uint32_t& a, uint32_t& b, uint32_t dir) {
+  const uint32_t x = med3(a, b, dir), y = med3(a, b, ~dir);
+  a = x; b = y;
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void tail16(uint32_t& a, uint32_t& b, const SortMasks& m, uint32_t dir) {   // distances 16 .. 1
+  exchange<kDppRowRor + 8>(a, b, m.m8 ^ dir);
+  exchange_xor4(a, b, m.m4 ^ dir);
+  exchange<kDppQuadSwap2>(a, b, m.m2 ^ dir);
+  exchange<kDppQuadSwap1>(a, b, m.m1 ^ dir);
+  exchange_own(a, b, dir);
+}
+__device__ __forceinline__ void sort128(uint32_t& a, uint32_t& b, const SortMasks& m) {
+  exchange_own(a, b, 0u);                                // runs of 2
+  exchange_mirror<kDppQuadSwap1>(a, b, m.m1);            // 4
+  exchange_own(a, b, 0u);
+  exchange_mirror<0x1B>(a, b, m.m2);                     // 8: quad_perm [3,2,1,0]
+  exchange<kDppQuadSwap1>(a, b, m.m1);
+  exchange_own(a, b, 0u);
+  exchange_mirror<kDppRowHalfMirror>(a, b, m.m4);        // 16
+  exchange<kDppQuadSwap2>(a, b, m.m2);
+  exchange<kDppQuadSwap1>(a, b, m.m1);
+  exchange_own(a, b, 0u);
+  exchange_mirror<kDppRowMirror>(a, b, m.m8 ^ m.d16);    // 32, every other run descending
+  exchange_xor4(a, b, m.m4 ^ m.d16);
+  exchange<kDppQuadSwap2>(a, b, m.m2 ^ m.d16);
+  exchange<kDppQuadSwap1>(a, b, m.m1 ^ m.d16);
+  exchange_own(a, b, m.d16);
+  swap16(a, b);                                          // 64 (lane ^ 16: both elements face each other after the swap)
+  exchange_own(a, b, m.d32);
+  swap16(a, b);
+  tail16(a, b, m, m.d32);
+  swap32(a, b);                                          // 128
+  exchange_own(a, b, 0u);
+  swap32(a, b);
+  swap16(a, b);
+  exchange_own(a, b, 0u);
+  swap16(a, b);
+  tail16(a, b, m, 0u);
+}
+
+__global__ __launch_bounds__(kRankThreads, 8) void dwta_ranked_kernel(HashDev hd, const uint32_t* __restrict__ offs,
+                                                                      const float* __restrict__ V, int64_t rows,
+                                                                      uint32_t* __restrict__ codes, int64_t row_stride,
+                                                                      int64_t tab_stride, const int32_t* __restrict__ rowlist,
+                                                                      const uint32_t* __restrict__ nrows_dev) {
+  // [H][kRankPitch] keys of two vectors per word (vector l low, 64 + l high); then, while the ranks are found, the
+  // sorted keys of a vector per wave
+  extern __shared__ uint32_t rk[];
+  const int H = hd.H, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int NW = kRankThreads / 64, PER = kRankRows / NW;   // vectors per wave
+  if (rowlist) {
+    const int64_t listed = (int64_t)*nrows_dev;
+    if (listed == rows) rowlist = nullptr;               // every vector: in place, without the list
+    rows = listed;
+  }
+  const int64_t row0 = (int64_t)blockIdx.x * kRankRows;
+  if (row0 >= rows) return;
+  auto row_of = [&](int r) -> int64_t {                  // vector r of the workgroup, -1 = none
+    const int64_t q = row0 + r;
+    return q < rows ? (rowlist ? (int64_t)rowlist[q] : q) : -1;
+  };
+  {
+    const SortMasks m = sort_masks(lane);
+    uint32_t* sorted = rk + H * kRankPitch + wave * 128;
+    const bool own = 2 * lane < H;                       // (H is a multiple of eight)
+    float2 x[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int64_t row = row_of(wave * PER + u);
+      x[u] = own && row >= 0 ? *(const float2*)(V + (size_t)row * H + 2 * lane) : make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; u += 2) {                   // two vectors at a time: their sorts overlap
+      uint32_t key[4], sa[2], sb[2];
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        key[2 * v] = own ? dwta_key(x[u + v].x) : ~0u;
+        key[2 * v + 1] = own ? dwta_key(x[u + v].y) : ~0u;
+        sa[v] = key[2 * v]; sb[v] = key[2 * v + 1];
+      }
+#pragma unroll
+      for (int v = 0; v < 2; ++v) sort128(sa[v], sb[v], m);
+      uint32_t pos[4] = {0u, 0u, 0u, 0u};                // keys of the vector below this one
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {                      // (one set of sorted keys: four workgroups fit a compute unit)
+        *(uint2*)(sorted + 2 * lane) = make_uint2(sa[v], sb[v]);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int d = 64; d > 0; d >>= 1)
+#pragma unroll
+          for (int q = 2 * v; q < 2 * v + 2; ++q) pos[q] += sorted[pos[q] + d - 1] < key[q] ? (uint32_t)d : 0u;
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (own) {
+        const int r = wave * PER + u;                    // (PER is even and divides 64: both vectors in the same half)
+        uint16_t* out = (uint16_t*)(rk + 2 * lane * kRankPitch + (r & 63)) + (r >> 6);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          out[(q & 1) * 2 * kRankPitch + (q >> 1) * 2] = (uint16_t)(key[q] ? (pos[q] + 1u + kRankBase) << 3 : 0u);
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t tile_base = (uint32_t)(uintptr_t)rk;    // (the low half of a generic LDS address is the LDS address)
+  const int64_t lo_row = row_of(lane), hi_row = row_of(64 + lane);
+  const uint32_t codemask = (1u << (3 * hd.K)) - 1u;
+  for (int t = wave; t < hd.L; t += NW) {
+    uint32_t c0 = 0, c1 = 0, least = ~0u;
+    for (int k = hd.K - 1; k >= 0; --k) {
+      uint32_t key[8];
+      read8_lane_rows(key, offs + (size_t)(t * hd.K + k) * 8, tile_base);
+#pragma unroll
+      for (int p = 0; p < 7; ++p) key[p] |= (uint32_t)(7 - p) * 0x10001u;
+      const uint32_t best = max3_pk(max3_pk(key[0], key[1], key[2]), max3_pk(key[3], key[4], key[5]), max3_pk(key[6], key[7], key[7]));
+      c0 = (c0 << 3) | (best & 7u);
+      c1 = (c1 << 3) | ((best >> 16) & 7u);
+      least = min_pk(least, best);
+    }
+    c0 ^= codemask;
+    c1 ^= codemask;
+    // a bin without an entry in some vector (rare): that vector's code again, its empty bins borrowing from the
+    // probe sequence
+    const bool e0 = lo_row >= 0 && (least & 0xffffu) < (kRankBase << 3), e1 = hi_row >= 0 && (least >> 16) < (kRankBase << 3);
+    if (__any(e0 || e1)) {
+      for (int h = 0; h < 2; ++h) {
+        if (!(h ? e1 : e0)) continue;
+        const uint16_t* col = (const uint16_t*)(rk + lane) + h;
+        auto raw = [&](int e) -> int {                   // winner of elementary hash e, -1 = no entry
+          uint32_t best = 0;
+          for (int p = 0; p < 8; ++p) {
+            const uint32_t v = *(const uint16_t*)((const char*)col + offs[(size_t)e * 8 + p]);
+            if (v) best = max(best, v | (uint32_t)(7 - p));
+          }
+          return best ? 7 - (int)(best & 7u) : -1;
+        };
+        bool any = false;
+        for (int c = 0; c < H && !any; ++c) any = col[c * 2 * kRankPitch] != 0;
+        uint32_t code = 0;
+        for (int k = 0; k < hd.K && any; ++k) {
+          const int e = t * hd.K + k;
+          int v = raw(e);
+          for (uint32_t tr = 1; tr <= 100 && v < 0; ++tr)
+            v = raw((int)(((hd.dens_a * (uint32_t)(e + 1) + hd.dens_b * tr) >> 8) % (uint32_t)hd.NH));
+          code |= (uint32_t)(v < 0 ? 0 : v) << (3 * k);
+        }
+        if (h) c1 = code; else c0 = code;
+      }
+    }
+    if (lo_row >= 0) codes[lo_row * row_stride + (int64_t)t * tab_stride] = c0;
+    if (hi_row >= 0) codes[hi_row * row_stride + (int64_t)t * tab_stride] = c1;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -500,6 +723,13 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
   }
   if (hd.kind == SLIDE_HASH_SIMHASH)
     return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
+  // Ranks (a lane pair's worth of vectors at least) pay from about 600 functions on; below, and for vectors of more
+  // coordinates than a wave sorts two to a lane, the row tiles.
+  if (hd.m == 8 && hd.H <= kRankMaxH && hd.NH >= kRankMinFunctions) {
+    hipLaunchKernelGGL(dwta_ranked_kernel, dim3((unsigned)ceil_div(rows, kRankRows)), dim3(kRankThreads), ranked_lds(hd.H), s, hd,
+                       hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev);
+    return hipGetLastError();
+  }
   switch (hd.m) {
     case 2: return launch_mode<2>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
     case 4: return launch_mode<4>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
@@ -528,6 +758,8 @@ hipError_t hash_setup_attributes(int H) {
 #undef SLIDE_SET
 #define SLIDE_SET(NKB) \
   e = hipFuncSetAttribute((const void*)&simhash_rows_kernel<NKB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSimhashLds); \
+  if (e != hipSuccess) return e;
+  e = hipFuncSetAttribute((const void*)&dwta_ranked_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ranked_lds(kRankMaxH));
   if (e != hipSuccess) return e;
   SLIDE_SET(2) SLIDE_SET(4) SLIDE_SET(8) SLIDE_SET(13) SLIDE_SET(16)
 #undef SLIDE_SET

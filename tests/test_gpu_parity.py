@@ -41,6 +41,33 @@ def test_hash_codes_bit_exact(kind, H, K, L):
     model.destroy()
 
 
+@pytest.mark.parametrize("H,K,L,rows", [(8, 3, 200, 1), (32, 6, 100, 127), (72, 5, 121, 129), (120, 8, 75, 300),
+                                        (128, 6, 400, 64), (128, 7, 99, 515)])
+def test_dwta_on_ranks(H, K, L, rows):
+    """Many DWTA functions of short vectors (decided on ranks): ties within a bin, few distinct values, empty bins and
+    all-zero vectors, signed zeros, NaN and infinities, values that differ in the last bit only; ragged row counts."""
+    _say("dwta ranks", H, K, L, rows)
+    wl = synth.small(synth.HASH_DWTA, hidden_dim=H, K=K, L=L, input_dim=0, num_classes=300, batch=8)
+    gen, model, orc = make_pair(wl)
+    rng = np.random.default_rng(H + rows)
+    V = rng.standard_normal((rows, H)).astype(np.float32)
+    V[1::7] = rng.integers(-1, 3, V[1::7].shape)                 # ties and zeros
+    V[2::7] = np.maximum(V[2::7], 0)
+    V[3::7] = np.nextafter(np.float32(1), np.float32(2)) * np.where(rng.random(V[3::7].shape) < 0.5, 1, np.float32(1) - np.float32(2) ** -24).astype(np.float32)
+    V[4::7] *= (rng.random(V[4::7].shape) < 0.05)                # nearly empty
+    V[5::7][:, ::3] = np.nan
+    V[6::7][:, 1::4] = np.inf
+    V[6::7][:, 2::4] = -np.inf
+    if rows > 20:
+        V[14] = 0
+        V[15] = -0.0
+        V[16] = np.nan
+    want = orc.hash.codes(V)
+    got = model.debug_hash(V)
+    assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+    model.destroy()
+
+
 @pytest.mark.parametrize("H,K,L,rows", [(4, 1, 1, 1), (32, 4, 8, 33), (36, 17, 3, 100), (64, 9, 50, 64), (128, 9, 50, 700),
                                         (200, 9, 51, 333), (208, 5, 100, 31), (256, 24, 5, 65), (256, 9, 90, 97)])
 def test_simhash_sums_near_zero(H, K, L, rows):
