@@ -54,18 +54,25 @@ __device__ void sample_hash_codes(const HashDev& hd, const float* hvec, int8_t* 
                                   uint32_t* __restrict__ codes_global) {
   const int tid = threadIdx.x, nthr = blockDim.x;
   if (hd.kind == SLIDE_HASH_SIMHASH) {
+    // eight words (sixteen coordinates) requested before the first is used: the sum itself is a chain
     const int half = hd.Spad / 2;
     for (int e = tid; e < hd.NH; e += nthr) {
       const uint32_t* __restrict__ sw = hd.words + (size_t)e * half;
       float acc = 0.0f;
-      for (int s2 = 0; s2 < half; ++s2) {
-        const uint32_t w = sw[s2];
-        const float x0 = hvec[w & 0x7fffu];
-        acc = (w & 0x8000u) ? acc - x0 : acc + x0;
-        if (2 * s2 + 1 < hd.S) {
-          const float x1 = hvec[(w >> 16) & 0x7fffu];
-          acc = (w & 0x80000000u) ? acc - x1 : acc + x1;
+      for (int s0 = 0; s0 < half; s0 += 8) {
+        uint32_t w[8];
+        float x[16];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = sw[min(s0 + u, half - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const float x0 = hvec[w[u] & 0x7fffu], x1 = hvec[(w[u] >> 16) & 0x7fffu];
+          x[2 * u] = (w[u] & 0x8000u) ? -x0 : x0;        // (a - x is a + (-x) bit for bit)
+          x[2 * u + 1] = (w[u] & 0x80000000u) ? -x1 : x1;
         }
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (2 * s0 + u < hd.S) acc += x[u];
       }
       raw[e] = acc > 0.0f ? 1 : 0;
     }
@@ -78,16 +85,38 @@ __device__ void sample_hash_codes(const HashDev& hd, const float* hvec, int8_t* 
     }
   } else {
     const int half = hd.m / 2;
-    for (int e = tid; e < hd.NH; e += nthr) {
-      int best_p = -1;
-      float best = 0.0f;
-      for (int p2 = 0; p2 < half; ++p2) {
-        const uint32_t w = hd.words[(size_t)e * half + p2];
-        const float x0 = hvec[w & 0xffffu], x1 = hvec[w >> 16];
-        if (x0 != 0.0f && x0 == x0 && (best_p < 0 || x0 > best)) { best_p = 2 * p2; best = x0; }
-        if (x1 != 0.0f && x1 == x1 && (best_p < 0 || x1 > best)) { best_p = 2 * p2 + 1; best = x1; }
+    auto winner = [&](int& best_p, float& best, int p2, uint32_t w) {
+      const float x0 = hvec[w & 0xffffu], x1 = hvec[w >> 16];
+      if (x0 != 0.0f && x0 == x0 && (best_p < 0 || x0 > best)) { best_p = 2 * p2; best = x0; }
+      if (x1 != 0.0f && x1 == x1 && (best_p < 0 || x1 > best)) { best_p = 2 * p2 + 1; best = x1; }
+    };
+    if (hd.m == 8) {
+      // a bin's coordinates in one read, the reads of four bins under way together
+      const uint4* __restrict__ bins = (const uint4*)hd.words;
+      for (int e0 = tid; e0 < hd.NH; e0 += 4 * nthr) {
+        uint4 w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = bins[min(e0 + u * nthr, hd.NH - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int e = e0 + u * nthr;
+          if (e >= hd.NH) continue;
+          int best_p = -1;
+          float best = 0.0f;
+          winner(best_p, best, 0, w[u].x);
+          winner(best_p, best, 1, w[u].y);
+          winner(best_p, best, 2, w[u].z);
+          winner(best_p, best, 3, w[u].w);
+          raw[e] = (int8_t)best_p;
+        }
       }
-      raw[e] = (int8_t)best_p;
+    } else {
+      for (int e = tid; e < hd.NH; e += nthr) {
+        int best_p = -1;
+        float best = 0.0f;
+        for (int p2 = 0; p2 < half; ++p2) winner(best_p, best, p2, hd.words[(size_t)e * half + p2]);
+        raw[e] = (int8_t)best_p;
+      }
     }
     __syncthreads();
     for (int t = tid; t < hd.L; t += nthr) {
