@@ -681,6 +681,7 @@ int slide_train_step(slide_ctx* ctx, const slide_batch* b, float* d_loss, void* 
   }
   const bool rows = rows_mode && update_sliced_applies(b->batch, lo.H, ctx->lds_limit);
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_UPDATE, s, [&] {
+    if (rows_mode && !rows && update_waves_applies(lo.H)) return launch_update_waves(lo.H, out, in, fin, a, ctx->num_cus, s);
     return rows ? launch_update_sliced(lo.H, b->batch, out, in, fin, a, ctx->lds_limit, ctx->num_cus, s)
                 : launch_update(lo.H, out, in, fin, a, ctx->num_cus, s); }));
   ctx->t = t;

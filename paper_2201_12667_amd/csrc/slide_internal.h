@@ -235,6 +235,10 @@ bool update_sliced_applies(int B, int H, size_t lds_limit);
 hipError_t update_setup_attributes(size_t lds_limit);
 hipError_t launch_update_sliced(int H, int B, const RowUpdate& out, const RowUpdate& in, const FinishArgs& fin,
                                 const AdamDev& ad, size_t lds_limit, int num_cus, hipStream_t s);
+// The same when the vectors do not fit the LDS: a wave per row (see update.hip).
+bool update_waves_applies(int H);
+hipError_t launch_update_waves(int H, const RowUpdate& out, const RowUpdate& in, const FinishArgs& fin, const AdamDev& ad,
+                               int num_cus, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 

@@ -687,6 +687,109 @@ hipError_t launch_update_sliced(int H, int B, const RowUpdate& out_, const RowUp
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same for such batches when the sample vectors do not fit the LDS (more than 512 samples): a WAVE per row
+// again, the vectors read from the caches, a lane owning four neighbouring columns (up to 256 of them; from 129 on,
+// so that more than half of the lanes have some).  The row's list entries are wave-uniform values, so a pair costs
+// one 16-byte read per lane from a scalar base and twelve instructions instead of the thirty that lane groups with
+// rows of their own spend on addresses and on columns past the end, and six waves a SIMD fit instead of four.
+// A wave takes kWaveRows neighbouring row slots of a tile at a time: headers together, the next row's list entries
+// and coefficients while the current row's vectors are summed.
+// 1,024 samples, 6.5 M pairs on 254K rows of 200: 767 -> 597 us (four, eight or sixteen vectors in flight alike:
+// the 5.2 GB of vectors come at 9 TB/s from the L2s).  With four pairs to a row (2,048 samples on 670K rows of 256)
+// the plain kernel is ahead, 911 against 930: it is taken for saturated buckets only.
+// ---------------------------------------------------------------------------------------------
+constexpr int kWaveRows = 8;
+
+__device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, const AdamDev& ad, int block, int nblocks) {
+  const PairsDev& pd = ru.pd;
+  const float* __restrict__ coef = ru.coef;
+  const int lane = threadIdx.x & 63;
+  const int wave_global = __builtin_amdgcn_readfirstlane(block * (kUpdateThreads / 64) + (int)(threadIdx.x >> 6));
+  const int nwaves = nblocks * (kUpdateThreads / 64);
+  constexpr int UNR = 8;                                   // vectors in flight (a divisor of 64)
+  const int col = 4 * lane;
+  const bool col_ok = col < H;                             // (H is a multiple of 4)
+  const bool bias_lane = ru.bias != nullptr && lane == 0;
+  const float* V = ru.V + (col_ok ? col : 0);              // (lanes past the end read the first columns and store nothing)
+  const int cpt = ((int)*pd.max_nu + kWaveRows - 1) / kWaveRows, nitems = pd.ntiles * cpt;
+  for (int item = wave_global; item < nitems; item += nwaves) {
+    const int ch = item / pd.ntiles, t = item - ch * pd.ntiles;
+    const int nr = min(kWaveRows, pd.tile_nu[t] - ch * kWaveRows);
+    if (nr <= 0) continue;
+    const int4 head = pd.umeta[(size_t)t * pd.rows_per_tile + ch * kWaveRows + min(lane, nr - 1)];
+    auto entry = [&](int st, int cn, int q0) -> int2 {     // this lane's list entry of the batch at q0 (past the end: the first)
+      return pd.pairs[(uint32_t)st + (q0 + lane < cn ? q0 + lane : 0)];
+    };
+    int j = __builtin_amdgcn_readlane(head.x, 0), st = __builtin_amdgcn_readlane(head.y, 0), cn = __builtin_amdgcn_readlane(head.z, 0);
+    int2 e = entry(st, cn, 0);
+    float d = lane < cn ? coef[e.y] : 0.f;
+    for (int r = 0; r < nr; ++r) {
+      const size_t ro = (size_t)j * H + (col_ok ? col : 0);
+      const float4 w0 = *(const float4*)(ru.W + ro), m0 = load_stream(ru.M + ro), v0 = load_stream(ru.Vv + ro);
+      const int rn = min(r + 1, nr - 1);                   // the next row's entries meanwhile
+      const int jn = __builtin_amdgcn_readlane(head.x, rn), stn = __builtin_amdgcn_readlane(head.y, rn), cnn = __builtin_amdgcn_readlane(head.z, rn);
+      const int2 en = entry(stn, cnn, 0);
+      float dn = 0.f;
+      float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+      float gb = 0.f;
+      for (int q0 = 0; q0 < cn; q0 += 64) {
+        if (q0) { e = entry(st, cn, q0); d = q0 + lane < cn ? coef[e.y] : 0.f; }
+        const int n = min(64, cn - q0);
+        int si = lane < n ? e.x : 0;
+        for (int a0 = 0; a0 < n; a0 += UNR) {              // (lanes past the end hold sample 0, 0.0)
+          float4 x[UNR];
+          float dd[UNR];
+#pragma unroll
+          for (int a = 0; a < UNR; ++a) {
+            dd[a] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), a0 + a));
+            x[a] = *(const float4*)(V + (size_t)__builtin_amdgcn_readlane(si, a0 + a) * H);
+          }
+          // (a batch is summed by itself: lists of a thousand samples lose no more than lists of a hundred)
+          float4 p = make_float4(dd[0] * x[0].x, dd[0] * x[0].y, dd[0] * x[0].z, dd[0] * x[0].w);
+#pragma unroll
+          for (int a = 1; a < UNR; ++a) {
+            p.x += dd[a] * x[a].x; p.y += dd[a] * x[a].y; p.z += dd[a] * x[a].z; p.w += dd[a] * x[a].w;
+          }
+          g.x += p.x; g.y += p.y; g.z += p.z; g.w += p.w;
+        }
+        gb += wave_sum_f32(d);
+      }
+      dn = lane < cnn ? coef[en.y] : 0.f;
+      float4 w = w0, m = m0, v = v0;
+      adam1(w.x, m.x, v.x, g.x, ad); adam1(w.y, m.y, v.y, g.y, ad);
+      adam1(w.z, m.z, v.z, g.z, ad); adam1(w.w, m.w, v.w, g.w, ad);
+      if (col_ok) { *(float4*)(ru.W + ro) = w; store_stream(ru.M + ro, m); store_stream(ru.Vv + ro, v); }
+      if (bias_lane) {
+        float bw = ru.bias[j], bm = ru.mbias[j], bv = ru.vbias[j];
+        adam1(bw, bm, bv, gb, ad);
+        ru.bias[j] = bw; ru.mbias[j] = bm; ru.vbias[j] = bv;
+      }
+      j = jn; st = stn; cn = cnn; e = en; d = dn;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kUpdateThreads, 6) void update_wave_kernel(int H, RowUpdate out, RowUpdate in, FinishArgs fin,
+                                                                        AdamDev ad, int parts) {
+  int blk = blockIdx.x;
+  if (blk < fin.nblocks) { finish_role(H, fin, ad, blk); return; }
+  blk -= fin.nblocks;
+  if (in.W) rowgrad_adam_wave(H, in, ad, blk, parts);
+  rowgrad_adam_wave(H, out, ad, blk, parts);
+}
+
+bool update_waves_applies(int H) { return H > 128 && H <= 256; }
+
+hipError_t launch_update_waves(int H, const RowUpdate& out, const RowUpdate& in, const FinishArgs& fin_, const AdamDev& ad,
+                               int num_cus, hipStream_t s) {
+  FinishArgs fin = fin_;
+  fin.nblocks = fin.b1 ? ceil_div(H, 32) : 1;
+  const int parts = 16 * num_cus;                          // (between two and three times what the device holds)
+  hipLaunchKernelGGL(update_wave_kernel, dim3(fin.nblocks + parts), dim3(kUpdateThreads), 0, s, H, out, in, fin, ad, parts);
+  return hipGetLastError();
+}
+
 hipError_t launch_update(int H, const RowUpdate& out_, const RowUpdate& in_, const FinishArgs& fin_,
                          const AdamDev& ad, int num_cus, hipStream_t s) {
   RowUpdate out = out_, in = in_;

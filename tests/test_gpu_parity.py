@@ -583,7 +583,12 @@ def test_sampling_budget_steps_match_oracle(name, wl):
                               bucket_cap=32, row_major_mode=2)),
     ("h1024-b37", synth.small(synth.HASH_DWTA, hidden_dim=1024, K=2, L=6, num_classes=3001, input_dim=900,
                               bucket_cap=64, row_major_mode=2)),
-    # batches above 512 samples: their vectors do not fit the LDS by useful slices, the plain update runs
+    # batches above 512 samples: their vectors do not fit the LDS by useful slices; a wave per row for 129 .. 256
+    # columns (with lists of several hundred samples in the second shape), the plain update otherwise
+    ("h256-b600", synth.small(synth.HASH_DWTA, hidden_dim=256, K=2, L=5, batch=600, num_classes=2501, input_dim=800,
+                              nnz_mean=5.0, bucket_cap=64, row_major_mode=2)),
+    ("h132-b1025-long-lists", synth.small(synth.HASH_SIMHASH, hidden_dim=132, K=2, L=3, batch=1025, num_classes=301,
+                                          input_dim=40, nnz_mean=3.0, bucket_cap=64, row_major_mode=2)),
     ("h64-b700", synth.small(synth.HASH_SIMHASH, hidden_dim=64, K=3, L=5, batch=700, num_classes=4001,
                                         input_dim=700, nnz_mean=5.0, bucket_cap=32, row_major_mode=2)),
     ("h200-b1024", synth.small(synth.HASH_SIMHASH, hidden_dim=200, K=4, L=6, batch=1024, num_classes=6007,
@@ -608,6 +613,30 @@ def test_row_major_kernels_match_oracle(name, wl):
         res = compare_step(model, orc, gen.batch(s))
         _say(s, {k: round(v, 3) for k, v in res.items() if not k.startswith("_")})
         assert_ok(res)
+    model.destroy()
+
+
+@pytest.mark.parametrize("H,scale", [(32, 300.0), (128, 300.0), (200, 1000.0), (1024, 300.0)])
+def test_step_with_widely_spread_logits(H, scale):
+    """Logits that spread over a hundred and more, so that the soft-max sums of a work item are rescaled several times
+    and most probabilities vanish."""
+    _say("spread logits", H, scale)
+    wl = synth.small(synth.HASH_DWTA, input_dim=0, hidden_dim=H, K=3 if H < 1024 else 2, batch=19)
+    gen, model, orc = make_pair(wl)
+    orc.p["W2"] *= np.float32(scale)
+    load_state(model, orc)
+    model.build_tables()
+    orc.build_tables()
+    b, w_top = gen.batch(0), float(np.abs(orc.p["W2"]).max())
+    res = compare_step(model, orc, b)
+    _say({k: round(v, 3) for k, v in res.items() if not k.startswith("_")})
+    # Probabilities are off by twice the logits' error, relatively; in the hidden gradient, a difference of rows, that is
+    # an absolute error of the rows' size: eps = (H + 2) 2^-24 max sum |w h| for the logits, one 2^-20 for the sums.
+    eps = (H + 2) * 2.0 ** -24 * w_top * float(np.abs(b["hidden"]).sum(1).max())
+    dh = model.debug_hidden()[1]
+    assert np.all(np.abs(dh - res["_ref"]["dh"]) <= (2 * eps + 2.0 ** -20) * w_top / wl.batch)
+    res.pop("dh")
+    assert_ok(res)
     model.destroy()
 
 
