@@ -30,8 +30,8 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // Forward over the active set, one pass over the gathered rows of W2.
 // Work item = up to kChunk consecutive active neurons of one sample, handled by one wave.  A row
 // is read by LPR lanes (float4 each, CH of them per lane), so 64/LPR rows are in flight per wave.
-// For each row: logit z = w.h + b (stored), and a running soft-max state (max M, sum s of
-// exp(z - M), acc = sum of exp(z - M) * w) that is rescaled when the maximum moves.  acc/s is the
+// For each row: logit z = w.h + b (stored), and a running soft-max state (reference M, sum s of
+// exp(z - M), acc = sum of exp(z - M) * w) that is rescaled when the reference moves.  acc/s is the
 // probability-weighted sum of the rows, which is all the hidden-layer gradient needs, so the rows
 // are not read a second time.  Partial states are merged per sample by combine_kernel.
 // The same launch builds the row lists of the two weight matrices (tile workgroups behind the logit
@@ -39,6 +39,7 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // workers are bandwidth-bound.
 // ---------------------------------------------------------------------------------------------
 constexpr int kForwardThreads = 512;
+constexpr float kSoftmaxSlack = 16.f;
 
 template <int LPR, int CH, bool FULL>
 __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const float* __restrict__ h, const float* __restrict__ W2,
@@ -103,17 +104,21 @@ __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const 
       const float zz = dot + bj;
       if (valid) {
         if (sub == 0) z[slot] = zz;
-        const float Mn = fmaxf(M, zz);
-        const float sc = __expf(M - Mn), e = __expf(zz - Mn);
-        s = s * sc + e;
+        // M need not be the maximum, only near enough that no exponential overflows: it moves (and the sums are
+        // rescaled) when a logit is beyond it by more than kSoftmaxSlack, in practice once per item.
+        if (zz > M + kSoftmaxSlack) {
+          const float sc = __expf(M - zz);
+          s *= sc;
+#pragma unroll
+          for (int c = 0; c < CH; ++c) { acc[c].x *= sc; acc[c].y *= sc; acc[c].z *= sc; acc[c].w *= sc; }
+          M = zz;
+        }
+        const float e = __expf(zz - M);
+        s += e;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-          acc[c].x = acc[c].x * sc + e * row[c].x;
-          acc[c].y = acc[c].y * sc + e * row[c].y;
-          acc[c].z = acc[c].z * sc + e * row[c].z;
-          acc[c].w = acc[c].w * sc + e * row[c].w;
+          acc[c].x += e * row[c].x; acc[c].y += e * row[c].y; acc[c].z += e * row[c].z; acc[c].w += e * row[c].w;
         }
-        M = Mn;
       }
     }
 #pragma unroll
