@@ -212,9 +212,10 @@ __device__ __forceinline__ uint32_t simhash_code(const HashDev& hd, const uint32
 //
 // The ranks: a wave sorts a vector's 128 keys in its registers (a bitonic network, two keys a lane, exchanges by
 // DPP moves and half-wave swaps: 104 instructions), puts them in LDS, and every coordinate finds its place by
-// bisection.  That costs about as much as 600 functions, hence the rule in launch_hash.
-// 670,091 vectors of 128 coordinates, 2,400 functions: 1,311 -> 739 us (about 200 of them for the ranks; the bins issue 50 instructions each, 17 of them
-// vector ones: with eight waves a SIMD the waits for the offsets and keys are the rest).
+// bisection.  That costs about as much as it saves on 500 functions, hence the rule in launch_hash.
+// 670,091 vectors of 128 coordinates, 2,400 functions: 1,311 -> 739 us, about 200 of them for the ranks.  The bins
+// issue 50 instructions each, 17 of them vector ones; with eight waves a SIMD (four workgroups' LDS just fits a
+// compute unit: with three it took 853) the waits for offsets and keys are the rest.
 // ---------------------------------------------------------------------------------------------
 constexpr int kRankThreads = 512;
 constexpr int kRankRows = 128;             // vectors per workgroup
@@ -723,8 +724,9 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
   }
   if (hd.kind == SLIDE_HASH_SIMHASH)
     return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
-  // Ranks (a lane pair's worth of vectors at least) pay from about 600 functions on; below, and for vectors of more
-  // coordinates than a wave sorts two to a lane, the row tiles.
+  // On ranks from 600 functions on, where finding the ranks has paid (builds of 300,000 vectors, row tiles and
+  // ranks: 600 functions 458 and 435 us with 128 coordinates, 449 and 443 with 64; 2,400 functions 1,458 and 1,244);
+  // below, and for vectors of more coordinates than a wave sorts two to a lane, the row tiles.
   if (hd.m == 8 && hd.H <= kRankMaxH && hd.NH >= kRankMinFunctions) {
     hipLaunchKernelGGL(dwta_ranked_kernel, dim3((unsigned)ceil_div(rows, kRankRows)), dim3(kRankThreads), ranked_lds(hd.H), s, hd,
                        hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev);

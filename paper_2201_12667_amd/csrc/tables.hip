@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   int32_t* idl = (int32_t*)(sets + 2 * set_words);             // [stage] the partition's ids grouped by bucket
   uint32_t* nslots_p = (uint32_t*)(idl + stage);           // [2] pieces of each partition of the pair
   uint32_t* nmed_p = nslots_p + 2;                             // [2] staged buckets of 9 .. 16 ids / of 17 .. kRankMax
-  uint32_t* medq = nmed_p + 2;                                 // [medcap] the former from the front, the latter from the back
+  uint32_t* nq_p = nmed_p + 2;                                 // [2] buckets for the short / long queue, [2] their first places
+  uint32_t* medq = nq_p + 4;                                   // [medcap] the former from the front, the latter from the back
   const uint32_t* tent = entries + t * N;
   const uint32_t* truns0 = runs + t * nslab * (size_t)(nbins + 1);
   auto ra_of = [&](int set) { return sets + set * set_words; };
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   auto run_partition = [&](const uint32_t d, const int set, const bool cached, const uint32_t (&x0)[kSlotBatch], const int ns0) {
   if (vec) for (int q = tid; q < nlo / 4; q += 256) cur4[q] = make_uint4(0u, 0u, 0u, 0u);
   else for (int b = tid; b < nlo; b += 256) cur[b] = 0;
-  if (tid < 2) nmed_p[tid] = 0;
+  if (tid < 2) { nmed_p[tid] = 0; nq_p[tid] = 0; }
   __syncthreads();
   const uint32_t s0 = pbase[t * (nbins + 1) + d], s1 = pbase[t * (nbins + 1) + d + 1];
   const bool staged = s1 - s0 <= (uint32_t)stage;
@@ -368,17 +369,14 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   __syncthreads();
   visit([&](uint32_t row, uint32_t low) { place[atomicAdd(&cur[low], 1u)] = (int32_t)row; });
   // cur[b] is now the end of bucket b = the start of bucket b + 1
-  uint32_t over = 0;
-  auto enqueue = [&](int b, uint32_t sz) {           // short lists from the back of the worklist, long ones from the front
-    const uint64_t item = ((uint64_t)t << 32) | ((d << lb) + (uint32_t)b);
-    if (sz <= (uint32_t)kWaveSort && sz <= (uint32_t)C) {
-      const uint32_t slot = atomicAdd(&ctrl->wl_short, 1u);
-      if (slot < wl_cap) worklist[wl_cap - 1u - slot] = item;
-    } else {
-      const uint32_t slot = atomicAdd(&ctrl->wl_count, 1u);
-      if (slot < wl_cap) worklist[slot] = item;
-    }
+  // Buckets for the queues (short ones fill the worklist from the back, the others from the front) are counted
+  // here and written together below.
+  auto is_short = [&](uint32_t sz) { return sz <= (uint32_t)kWaveSort && sz <= (uint32_t)C; };
+  auto is_queued = [&](uint32_t sz) {
+    return staged ? sz > (uint32_t)kRankMax || sz > (uint32_t)C : sz >= 2 && !(sz <= (uint32_t)kSmallBucket && sz <= (uint32_t)C);
   };
+  uint32_t nqueued = 0;
+  auto enqueue = [&](uint32_t sz) { atomicAdd(&nq_p[is_short(sz) ? 0 : 1], 1u); };
   if (staged) {
     // The ids sit in idl grouped by bucket, in arrival order, and are sorted where they are; the whole
     // partition then goes to the table in one coalesced copy (a store per bucket costs far more than
@@ -388,10 +386,9 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
     // or over capacity stay as they are and are queued.
     // bucket b = ids a .. a + sz - 1 (every lane of a wave calls it together: the network is wave-wide)
     auto bucket = [&](const int b, const uint32_t a, const uint32_t sz) {
-      if (sz > (uint32_t)C) ++over;
       const bool big = sz > (uint32_t)kRankMax || sz > (uint32_t)C;
       if (big) {
-        enqueue(b, sz);
+        enqueue(sz);
       } else if (sz > 16u) {
         medq[medcap - 1 - atomicAdd(&nmed_p[1], 1u)] = (uint32_t)b;   // (lane groups / waves order these below:
       } else if (sz > 8u) {                                             //  at most stage / 9 of them exist)
@@ -457,6 +454,7 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
     // each, a bitonic sort across the lanes.
     __syncthreads();
     const uint32_t nrow = nmed_p[0], nwav = nmed_p[1];
+    nqueued = nq_p[0] | nq_p[1];
     for (uint32_t m0 = 0; m0 < nrow; m0 += 16) {
       const uint32_t m = m0 + (uint32_t)(tid >> 4);
       const int l16 = tid & 15;
@@ -486,7 +484,6 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   } else {
     for (int b = tid; b < nlo; b += 256) {
       const uint32_t a = b ? cur[b - 1] : 0u, sz = cur[b] - a;
-      if (sz > (uint32_t)C) ++over;
       if (sz < 2) continue;
       if (sz <= (uint32_t)kSmallBucket && sz <= (uint32_t)C) {
         int32_t* p = seg + a;                       // arrival order is arbitrary: restore ascending ids
@@ -497,11 +494,31 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
           p[q + 1] = key;
         }
       } else {
-        enqueue(b, sz);
+        enqueue(sz);
       }
     }
+    __syncthreads();
+    nqueued = nq_p[0] | nq_p[1];
   }
-  if (over) atomicAdd(&ctrl->overflowed, over);
+  // One update of each queue's length per partition: a word that every bucket bumps serves one bucket per 8 ns or so
+  // (the 25,600 over-capacity buckets of the wide shape, each counted twice: the kernel took 310 us, now 172).
+  if (nqueued) {
+    uint32_t mine = 0;
+    if (tid < 2) {
+      mine = nq_p[tid];
+      nq_p[2 + tid] = mine ? atomicAdd(tid == 0 ? &ctrl->wl_short : &ctrl->wl_count, mine) : 0u;
+    }
+    __syncthreads();
+    if (tid < 2) nq_p[tid] = 0;                      // (from here on: places handed out)
+    __syncthreads();
+    for (int b = tid; b < nlo; b += 256) {
+      const uint32_t sz = cur[b] - (b ? cur[b - 1] : 0u);
+      if (!is_queued(sz)) continue;
+      const int q = is_short(sz) ? 0 : 1;
+      const uint32_t slot = nq_p[2 + q] + atomicAdd(&nq_p[q], 1u);
+      if (slot < wl_cap) worklist[q == 0 ? wl_cap - 1u - slot : slot] = ((uint64_t)t << 32) | ((d << lb) + (uint32_t)b);
+    }
+  }
   __syncthreads();                                   // (the next partition of the pair reuses the counters and the staging)
   };
   const uint32_t dA = 2u * blockIdx.x, dB = dA + 1u;
@@ -581,7 +598,7 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
                                                           uint32_t nb, int64_t N, int C, int policy, uint32_t r,
                                                           uint32_t pa, uint32_t pb,
                                                           const uint64_t* __restrict__ worklist,
-                                                          uint32_t wl_cap, const Ctrl* ctrl) {
+                                                          uint32_t wl_cap, Ctrl* ctrl) {
   __shared__ uint64_t keys[kSortCap];
   __shared__ uint32_t sid[kSelStage];
   __shared__ uint32_t hist[256];
@@ -591,6 +608,7 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
   int capp = 1;
   while (capp < C) capp <<= 1;
   const int tid = threadIdx.x, lane = tid & 63;
+  uint32_t over = 0;                           // buckets beyond capacity (all of them are queued here)
   for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
     const uint64_t w = worklist[item];
     const uint64_t t = w >> 32;
@@ -606,6 +624,7 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
       bitonic_sort_u64(keys, n2);
       for (uint32_t i = tid; i < s; i += 256) p[i] = (int32_t)(uint32_t)keys[i];
     } else {
+      ++over;
       const bool in_lds = s <= (uint32_t)kSelStage;
       if (in_lds) for (uint32_t i = tid; i < s; i += 256) sid[i] = (uint32_t)p[i];
       hist[tid] = 0;
@@ -677,6 +696,7 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
     }
     __syncthreads();
   }
+  if (over && tid == 0) atomicAdd(&ctrl->overflowed, over);
 }
 
 // Split of the code into partition digit (high hb bits) and in-partition digit (low lb bits).
@@ -705,7 +725,7 @@ size_t tables_pbase_words(int bits, int64_t N, int L) {
 static int run_block(int nslab) { return nslab < kRunBlock ? nslab : kRunBlock; }
 static size_t part_buckets_lds(int lb, int nsb, int stage) {
   const size_t nlo = (size_t)1 << lb;
-  return (nlo + ((nlo + 63) >> 6) + 2 * (3 * (size_t)nsb + stage / 64) + stage + 4 + med_cap(stage)) * 4;
+  return (nlo + ((nlo + 63) >> 6) + 2 * (3 * (size_t)nsb + stage / 64) + stage + 8 + med_cap(stage)) * 4;
 }
 // The staging area of the bucket kernel: four mean partitions (a fresh layer's partitions stay within a
 // few percent of the mean, a trained one's within a few times), so that tables with many buckets per
