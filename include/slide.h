@@ -204,7 +204,7 @@ int slide_predict(slide_ctx* ctx, const slide_batch* batch, int mode, int topk,
 /* For callers that cannot allocate device memory or hand over a workspace at the call (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): slide_predict with mode 1 (scores
  * of all N neurons, the topk best per sample), with every intermediate -- the hidden activations in
- * sparse-input mode, one chunk of scores, the running best lists, the candidate buffers and their
+ * sparse-input mode and their split parts, the sampled scores, the bars, the candidate buffers and their
  * counters -- in a fixed array of SLIDE_STATIC_SCRATCH_MIB MiB inside the library's device image instead
  * of the context's workspace.  Same arguments, results and ordering rules as slide_predict; calls no
  * hipMalloc / hipFree or other allocating routine.
