@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4
       const int il = list_i[q];
       const uint32_t id = (uint32_t)(j0 + (int64_t)list_c[q] * stride);
       const uint64_t key = fabsf(z) < INFINITY ? topk_key(z, id) : open_key(id);
-      if (key <= bar_s[il]) {
+      // (rows past the batch have no buffer; a non-finite weight times their zeros is NaN and passes the first test)
+      if (il < rows && key <= bar_s[il]) {
         const uint32_t pos = atomicAdd(&ccnt[(size_t)(i0 + il) * kCntPitch], 1u);
         if (pos < (uint32_t)cand_cap) cand[(size_t)(i0 + il) * cand_cap + pos] = key;
       }

@@ -137,6 +137,51 @@ def test_predict_all_when_the_sampled_neurons_mislead(N, H, batch):
     model.destroy()
 
 
+@pytest.mark.parametrize("batch,H,D", [(1, 32, 0), (33, 16, 300), (70, 128, 0), (129, 32, 0), (200, 136, 300)])
+@pytest.mark.parametrize("weights", ["first-row-inf", "first-bias-nan", "first-bias-inf", "all-nan"])
+def test_predict_all_writes_nothing_for_rows_past_the_batch(batch, H, D, weights):
+    """A batch that fills max_batch but not its row block, and a neuron 0 (or a whole layer, as after divergence) whose
+    score is no number for the zeros that fill the block: those rows have no candidate buffer, and the ones of the
+    batch lose nothing.  The first sample's candidates and the activations that lie behind the scratch are whole."""
+    _say("rows past the batch", batch, H, D, weights)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=D, hidden_dim=H, K=3, L=3, num_classes=16411, batch=batch, bucket_cap=8,
+                     nnz_mean=9.0)
+    gen, model, orc = make_pair(wl)
+    W2, bias = orc.p["W2"].copy(), orc.p["b2"].copy()
+    if weights == "first-row-inf":
+        W2[0] = np.inf
+    elif weights == "first-bias-nan":
+        bias[0] = np.nan
+    elif weights == "first-bias-inf":
+        bias[0] = np.inf
+    else:
+        W2[:] = np.nan
+    model.p["W2"].copy_(torch.from_numpy(W2))
+    model.p["b2"].copy_(torch.from_numpy(bias))
+    model.build_tables()
+    b = gen.batch(0)
+    db = model.to_device(b)
+    topk = 5
+    ids, sc = (x.cpu().numpy() for x in model.predict(db, topk, mode=1))
+    h = orc.forward_hidden(b).astype(np.float64)
+    if D:
+        assert np.allclose(model.debug_hidden(want_grad=False)[0], h, rtol=1e-6, atol=1e-7)
+    assert all(len(set(r.tolist())) == topk and r.min() >= 0 and r.max() < wl.num_classes for r in ids)
+    if weights == "all-nan":
+        assert np.all(np.isnan(sc)) and np.array_equal(ids, np.broadcast_to(np.arange(topk), ids.shape))
+    else:
+        # neuron 0 is first or, where its score is a NaN with the sign bit (0 x inf), last; the rest of the layer is in order
+        assert not np.any(np.isfinite(sc[ids == 0]))
+        z = h @ W2[1:].astype(np.float64).T + bias[1:].astype(np.float64)
+        first = ids[:, 0] == 0
+        rest = np.where(first[:, None], ids[:, 1:], ids[:, :-1])
+        got = np.where(first[:, None], sc[:, 1:], sc[:, :-1])
+        assert np.all(rest > 0)
+        assert _check_topk(rest - 1, got, z, topk - 1) > 0.97
+    assert model.status() == 0
+    model.destroy()
+
+
 @pytest.mark.parametrize("topk", [1, 33, 64])
 @pytest.mark.parametrize("layout", ["spread", "few-threads", "ties", "nan"])
 def test_predict_retrieved_selection_edges(layout, topk):
