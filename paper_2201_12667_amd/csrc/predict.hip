@@ -42,8 +42,8 @@ __host__ __device__ constexpr int stage_blocks(int NIB) { return NIB == 8 ? 2 : 
 
 // Eight floats as three bf16 vectors whose sum they are exactly (8 + 8 + 8 significand bits, each part
 // rounded to nearest, so that what a product of parts leaves out has either sign).  Values so large that
-// the first part rounds to infinity, infinities and NaN give a non-finite score, which the caller evaluates
-// again in plain arithmetic.
+// the first part rounds to infinity, infinities and NaN give a score of NaN or infinity, which the caller evaluates
+// again in plain arithmetic (see settled).
 __device__ __forceinline__ void split8(const float4& a, const float4& b, bf16x8 (&out)[3]) {
   const f32x2 x[4] = {{a.x, a.y}, {a.z, a.w}, {b.x, b.y}, {b.z, b.w}};
 #pragma unroll
@@ -91,13 +91,17 @@ __global__ __launch_bounds__(1024) void dense_prepare_kernel(int B, int H, int n
   }
 }
 
-// A score in plain arithmetic, for the few that come out non-finite on the matrix cores.
+// A score in plain arithmetic, for the few that come out as NaN or plus infinity on the matrix cores.
 __device__ __forceinline__ float plain_score(const float* __restrict__ h, const float* __restrict__ w, float bias, int H) {
   float s = 0.f;
   for (int k = 0; k < H; ++k) s = fmaf(h[k], w[k], s);
   return s + bias;
 }
-// Key of such a score while it waits for that (before every other key, so it passes every bar).
+// Whether a matrix-core score stands as it is: a number, or minus infinity (a sum that left the range at that end
+// has left it in any order but for a rounding; the passes have to agree, or a neuron could set a bar that it does not
+// reach itself).  NaN and plus infinity may come of the parts of ordinary values and are evaluated again.
+__device__ __forceinline__ bool settled(float z) { return z < INFINITY; }
+// Key of the others while they wait for that (before every other key, so it passes every bar).
 __device__ __forceinline__ uint64_t open_key(uint32_t id) { return id; }
 __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0; }
 
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4
       const float z = list_z[q];
       const int il = list_i[q];
       const uint32_t id = (uint32_t)(j0 + (int64_t)list_c[q] * stride);
-      const uint64_t key = fabsf(z) < INFINITY ? topk_key(z, id) : open_key(id);
+      const uint64_t key = settled(z) ? topk_key(z, id) : open_key(id);
       // (rows past the batch have no buffer; a non-finite weight times their zeros is NaN and passes the first test)
       if (il < rows && key <= bar_s[il]) {
         const uint32_t pos = atomicAdd(&ccnt[(size_t)(i0 + il) * kCntPitch], 1u);
@@ -399,7 +403,7 @@ __global__ __launch_bounds__(kSelectThreads) void dense_bar_kernel(int H, const 
         const int c = c0 + u * kSelectThreads;
         if (c >= nc) continue;
         const uint32_t j = (uint32_t)c * (uint32_t)stride;
-        if (!(fabsf(z[u]) < INFINITY)) z[u] = plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H);
+        if (!settled(z[u])) z[u] = plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H);
         f(topk_key(z[u], j));
       }
     }

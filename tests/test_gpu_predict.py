@@ -182,6 +182,31 @@ def test_predict_all_writes_nothing_for_rows_past_the_batch(batch, H, D, weights
     model.destroy()
 
 
+@pytest.mark.parametrize("topk", [1, 5])
+def test_predict_all_fills_the_list_when_scores_leave_the_range(topk):
+    """Scores of minus infinity everywhere but at one sampled neuron, whose sum is the lowest finite number when it is
+    rounded after every term and minus infinity when it is not: whichever the kernels find, they have to agree
+    on it, or the neuron sets a bar that nothing reaches and the list comes back short."""
+    _say("scores out of range", topk)
+    N, H, j = 16640, 32, 8000
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=H, K=3, L=3, num_classes=N, batch=3, bucket_cap=8)
+    gen, model, _ = make_pair(wl)
+    W2, bias = np.zeros((N, H), np.float32), np.full(N, -np.inf, np.float32)
+    bias[j] = 0
+    big = np.float32(2.0 ** 128 * (1 - 2.0 ** -8))                        # the largest bf16 number
+    W2[j, 0], W2[j, 1] = -big, np.float32(float(big) - float(np.finfo(np.float32).max))
+    W2[j, 2:] = -0.4 * 2.0 ** 104                                         # 0.4 units in the last place of the sum
+    model.p["W2"].copy_(torch.from_numpy(W2))
+    model.p["b2"].copy_(torch.from_numpy(bias))
+    model.build_tables()
+    b = gen.batch(0)
+    b["hidden"][:] = 1
+    ids, sc = (x.cpu().numpy() for x in model.predict(model.to_device(b), topk, mode=1))
+    assert ids.min() >= 0 and ids.max() < N and all(len(set(r.tolist())) == topk for r in ids)
+    assert np.all(sc <= -np.finfo(np.float32).max) and np.all(np.isneginf(sc[ids != j]))
+    model.destroy()
+
+
 @pytest.mark.parametrize("topk", [1, 33, 64])
 @pytest.mark.parametrize("layout", ["spread", "few-threads", "ties", "nan"])
 def test_predict_retrieved_selection_edges(layout, topk):
