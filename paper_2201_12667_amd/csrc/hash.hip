@@ -498,7 +498,8 @@ __global__ __launch_bounds__(NKB <= 8 ? 1024 : 512) void simhash_rows_kernel(Has
       }
     }
     top = __builtin_elementwise_maximum(top, __shfl_xor(top, 32));
-    // magnitudes whose parts would overflow or lose bits: every bit in storage order
+    // magnitudes whose parts would overflow or lose bits: every bit in storage order (as where top * S leaves the
+    // range, which makes the bound infinite: only then can a partial sum of either order)
     const bool zero = top == 0.f, plain = !(top < 1e37f) || (!zero && top < 1e-30f);
     const float bound = zero ? -1.f : plain ? INFINITY : top * (float)S * (3.8146973e-6f + 6.f * 5.9604645e-8f * (float)S);
     uint64_t stream = 0;

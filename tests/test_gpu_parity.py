@@ -96,6 +96,33 @@ def test_simhash_sums_near_zero(H, K, L, rows):
     model.destroy()
 
 
+@pytest.mark.parametrize("H", [128, 224, 256])
+def test_simhash_sums_that_overflow(H):
+    """Magnitudes below 1e37 whose running sum passes the end of the range and stays infinite, where the sum of the same
+    terms in another order does not; the storage order is not that of the coordinates."""
+    _say("simhash overflow", H)
+    wl = synth.small(synth.HASH_SIMHASH, hidden_dim=H, K=6, L=8, input_dim=0, num_classes=300, batch=8)
+    gen, model, orc = make_pair(wl)
+    hp = gen.hash_params()
+    rng = np.random.default_rng(H)
+    order = np.argsort(rng.random(hp["srp_idx"].shape), axis=1)
+    hp["srp_idx"], hp["srp_sign"] = (np.take_along_axis(hp[n], order, axis=1) for n in ("srp_idx", "srp_sign"))
+    model.set_hash_params(hp)
+    orc.set_hash_params(hp)
+    V = rng.standard_normal((100, H)).astype(np.float32)
+    for r in range(48):                                          # function r: the first terms one way, the rest the other
+        s, idx = hp["srp_sign"][r].astype(np.float32), hp["srp_idx"][r]
+        way = np.where(np.arange(idx.size) < 36, 1, -1) * (1 if r % 2 else -1)
+        V[r] = 9.9e36
+        V[r, idx] = (9.9e36 * way * s).astype(np.float32)
+    V[60:80] *= np.float32(2e36)
+    with np.errstate(all="ignore"):
+        want = orc.hash.codes(V)
+    got = model.debug_hash(V)
+    assert np.array_equal(got, want), np.argwhere(got != want)[:5]
+    model.destroy()
+
+
 @pytest.mark.parametrize("kind,policy,C,N", [(synth.HASH_SIMHASH, 1, 16, 2000), (synth.HASH_SIMHASH, 0, 5, 1500),
                                              (synth.HASH_DWTA, 1, 16, 20011), (synth.HASH_DWTA, 0, 3, 5000),
                                              (synth.HASH_SIMHASH, 1, 128, 30000),
