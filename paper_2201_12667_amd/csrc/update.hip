@@ -693,13 +693,18 @@ hipError_t launch_update_sliced(int H, int B, const RowUpdate& out_, const RowUp
 // so that more than half of the lanes have some).  The row's list entries are wave-uniform values, so a pair costs
 // one 16-byte read per lane from a scalar base and twelve instructions instead of the thirty that lane groups with
 // rows of their own spend on addresses and on columns past the end, and six waves a SIMD fit instead of four.
-// A wave takes kWaveRows neighbouring row slots of a tile at a time: headers together, the next row's list entries
-// and coefficients while the current row's vectors are summed.
-// 1,024 samples, 6.5 M pairs on 254K rows of 200: 767 -> 597 us (four, eight or sixteen vectors in flight alike:
-// the 5.2 GB of vectors come at 9 TB/s from the L2s).  With four pairs to a row (2,048 samples on 670K rows of 256)
-// the plain kernel is ahead, 911 against 930: it is taken for saturated buckets only.
+// A wave takes up to kWaveRows neighbouring row slots of a tile at a time (fewer where that would leave waves without
+// any): headers together, the next row's list entries and coefficients while the current row's vectors are summed.
+// Rows of more than kWaveLong pairs are left out and taken afterwards from the list of long rows, dealt out to the
+// waves one by one: neighbours tend to be long together (ids ordered by frequency), and eight of 2,048 pairs are 2,000
+// dependent reads for one wave.  2,048 samples of 75 features, ids by frequency, 28K rows of W1 and 99K of W2: plain
+// kernel 606 us, without that rule 960, with it 415; 4,850 rows of 470 pairs: 215, 283 and 152.
+// 1,024 samples, 6.5 M pairs on 254K rows of 200: 767 -> 603 us (592 without the look at the long rows; four, eight
+// or sixteen vectors in flight alike: the 5.2 GB of vectors come at 9 TB/s from the L2s).  With four pairs to a row
+// (2,048 samples on 670K rows of 256) the plain kernel is ahead, 911 against 930: it is taken for saturated buckets only.
 // ---------------------------------------------------------------------------------------------
 constexpr int kWaveRows = 8;
+constexpr int kWaveLong = 256;            // (a multiple of kLongRow: the listed long rows include these)
 
 __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, const AdamDev& ad, int block, int nblocks) {
   const PairsDev& pd = ru.pd;
@@ -712,25 +717,47 @@ __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, co
   const bool col_ok = col < H;                             // (H is a multiple of 4)
   const bool bias_lane = ru.bias != nullptr && lane == 0;
   const float* V = ru.V + (col_ok ? col : 0);              // (lanes past the end read the first columns and store nothing)
-  const int cpt = ((int)*pd.max_nu + kWaveRows - 1) / kWaveRows, nitems = pd.ntiles * cpt;
-  for (int item = wave_global; item < nitems; item += nwaves) {
-    const int ch = item / pd.ntiles, t = item - ch * pd.ntiles;
-    const int nr = min(kWaveRows, pd.tile_nu[t] - ch * kWaveRows);
-    if (nr <= 0) continue;
-    const int4 head = pd.umeta[(size_t)t * pd.rows_per_tile + ch * kWaveRows + min(lane, nr - 1)];
-    auto entry = [&](int st, int cn, int q0) -> int2 {     // this lane's list entry of the batch at q0 (past the end: the first)
-      return pd.pairs[(uint32_t)st + (q0 + lane < cn ? q0 + lane : 0)];
-    };
-    int j = __builtin_amdgcn_readlane(head.x, 0), st = __builtin_amdgcn_readlane(head.y, 0), cn = __builtin_amdgcn_readlane(head.z, 0);
+  auto entry = [&](int st, int cn, int q0) -> int2 {       // this lane's list entry of the batch at q0 (past the end: the first)
+    return pd.pairs[(uint32_t)st + (q0 + lane < cn ? q0 + lane : 0)];
+  };
+  const int slots = (int)*pd.max_nu;                       // (of the fullest tile)
+  const int per = min(kWaveRows, max(1, (int)((int64_t)slots * pd.ntiles / nwaves)));
+  const int cpt = (slots + per - 1) / per, nitems = pd.ntiles * cpt;
+  const int nlong = min((int)*pd.nlong, pd.long_cap);
+  int item = wave_global;
+  int64_t l0 = wave_global;
+  while (true) {
+    // The headers of the rows that come next, a lane each: those of an item, or, after the last, those among the
+    // wave's share of the listed long rows that were left out before.
+    int4 head;
+    bool take;
+    if (item < nitems) {
+      const int ch = item / pd.ntiles, t = item - ch * pd.ntiles;
+      const int nr = min(per, pd.tile_nu[t] - ch * per);
+      item += nwaves;
+      if (nr <= 0) continue;
+      head = pd.umeta[(size_t)t * pd.rows_per_tile + ch * per + min(lane, nr - 1)];
+      take = lane < nr && head.z <= kWaveLong;
+    } else {
+      if (l0 >= nlong) break;
+      const int64_t l = l0 + (int64_t)lane * nwaves;
+      l0 += (int64_t)64 * nwaves;
+      head = pd.umeta[pd.longlist[min(l, (int64_t)nlong - 1)]];
+      take = l < nlong && head.z > kWaveLong;
+    }
+    unsigned long long left = __ballot(take);
+    if (!left) continue;
+    int q = __ffsll((long long)left) - 1;
+    int j = __builtin_amdgcn_readlane(head.x, q), st = __builtin_amdgcn_readlane(head.y, q), cn = __builtin_amdgcn_readlane(head.z, q);
     int2 e = entry(st, cn, 0);
     float d = lane < cn ? coef[e.y] : 0.f;
-    for (int r = 0; r < nr; ++r) {
+    while (left) {
       const size_t ro = (size_t)j * H + (col_ok ? col : 0);
       const float4 w0 = *(const float4*)(ru.W + ro), m0 = load_stream(ru.M + ro), v0 = load_stream(ru.Vv + ro);
-      const int rn = min(r + 1, nr - 1);                   // the next row's entries meanwhile
-      const int jn = __builtin_amdgcn_readlane(head.x, rn), stn = __builtin_amdgcn_readlane(head.y, rn), cnn = __builtin_amdgcn_readlane(head.z, rn);
+      left &= left - 1;
+      if (left) q = __ffsll((long long)left) - 1;          // the next row's entries meanwhile
+      const int jn = __builtin_amdgcn_readlane(head.x, q), stn = __builtin_amdgcn_readlane(head.y, q), cnn = __builtin_amdgcn_readlane(head.z, q);
       const int2 en = entry(stn, cnn, 0);
-      float dn = 0.f;
       float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
       float gb = 0.f;
       for (int q0 = 0; q0 < cn; q0 += 64) {
@@ -755,7 +782,7 @@ __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, co
         }
         gb += wave_sum_f32(d);
       }
-      dn = lane < cnn ? coef[en.y] : 0.f;
+      const float dn = lane < cnn ? coef[en.y] : 0.f;
       float4 w = w0, m = m0, v = v0;
       adam1(w.x, m.x, v.x, g.x, ad); adam1(w.y, m.y, v.y, g.y, ad);
       adam1(w.z, m.z, v.z, g.z, ad); adam1(w.w, m.w, v.w, g.w, ad);

@@ -616,6 +616,9 @@ def test_sampling_budget_steps_match_oracle(name, wl):
                               nnz_mean=5.0, bucket_cap=64, row_major_mode=2)),
     ("h132-b1025-long-lists", synth.small(synth.HASH_SIMHASH, hidden_dim=132, K=2, L=3, batch=1025, num_classes=301,
                                           input_dim=40, nnz_mean=3.0, bucket_cap=64, row_major_mode=2)),
+    # rows of W1 on both sides of 256 pairs, few enough rows that a wave takes one at a time
+    ("h136-b1100-lists-around-256", synth.small(synth.HASH_SIMHASH, hidden_dim=136, K=3, L=4, batch=1100, num_classes=501,
+                                                input_dim=64, nnz_mean=14.0, bucket_cap=64, row_major_mode=2)),
     ("h64-b700", synth.small(synth.HASH_SIMHASH, hidden_dim=64, K=3, L=5, batch=700, num_classes=4001,
                                         input_dim=700, nnz_mean=5.0, bucket_cap=32, row_major_mode=2)),
     ("h200-b1024", synth.small(synth.HASH_SIMHASH, hidden_dim=200, K=4, L=6, batch=1024, num_classes=6007,
