@@ -41,12 +41,19 @@ def test_hash_codes_bit_exact(kind, H, K, L):
     model.destroy()
 
 
-@pytest.mark.parametrize("H,K,L,rows", [(8, 3, 200, 1), (32, 6, 100, 127), (72, 5, 121, 129), (120, 8, 75, 300),
+def _ranked_from():
+    """Vectors from which DWTA functions in great number are decided on ranks."""
+    return 320 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("H,K,L,rows", [(8, 3, 334, 1), (32, 6, 167, 127), (72, 5, 201, 129), (120, 8, 75, 300),
                                         (128, 6, 400, 64), (128, 7, 99, 515)])
-def test_dwta_on_ranks(H, K, L, rows):
-    """Many DWTA functions of short vectors (decided on ranks): ties within a bin, few distinct values, empty bins and
-    all-zero vectors, signed zeros, NaN and infinities, values that differ in the last bit only; ragged row counts."""
-    _say("dwta ranks", H, K, L, rows)
+def test_dwta_on_ranks(H, K, L, rows, many):
+    """Many DWTA functions of short vectors, few vectors (row tiles) or many (decided on ranks, the same vectors over and
+    over at ever other places of a workgroup): ties within a bin, few distinct values, empty bins and all-zero vectors,
+    signed zeros, NaN and infinities, values that differ in the last bit only; ragged row counts."""
+    _say("dwta ranks", H, K, L, rows, many)
     wl = synth.small(synth.HASH_DWTA, hidden_dim=H, K=K, L=L, input_dim=0, num_classes=300, batch=8)
     gen, model, orc = make_pair(wl)
     rng = np.random.default_rng(H + rows)
@@ -63,6 +70,9 @@ def test_dwta_on_ranks(H, K, L, rows):
         V[15] = -0.0
         V[16] = np.nan
     want = orc.hash.codes(V)
+    if many:
+        again = np.arange(_ranked_from() + rows) % rows
+        V, want = V[again], want[again]
     got = model.debug_hash(V)
     assert np.array_equal(got, want), np.argwhere(got != want)[:5]
     model.destroy()
@@ -121,6 +131,37 @@ def test_simhash_sums_that_overflow(H):
     got = model.debug_hash(V)
     assert np.array_equal(got, want), np.argwhere(got != want)[:5]
     model.destroy()
+
+
+@pytest.mark.parametrize("batch", [4, 12])
+def test_incremental_rebuild_of_many_functions(batch):
+    """A layer large enough for DWTA on ranks whose steps touch fewer rows than that kernel takes (4 samples) or more
+    (12 samples), but not so many that all are hashed again: the rows hashed through the list give the tables of a full
+    build."""
+    import dataclasses
+    N = _ranked_from() * 3 // 2 + 77
+    wl = synth.small(synth.HASH_DWTA, hidden_dim=32, K=3, L=340, num_classes=N, input_dim=0, batch=batch, bucket_cap=64,
+                     rebuild_every=1, lr=1e-2)
+    _say("incremental, many functions", batch, N)
+    gen, full, orc = make_pair(wl)
+    _, inc, _ = make_pair(dataclasses.replace(wl, incremental_rebuild=True))
+    for m in (full, inc):
+        m.build_tables()
+        m.train_step(m.to_device(gen.batch(0)))
+    hashed = inc.stats()["rehashed_rows"]
+    _say("   rows hashed again", hashed)
+    assert full.stats()["rehashed_rows"] == N
+    assert 0 < hashed < _ranked_from() if batch == 4 else _ranked_from() <= hashed < N
+    assert torch.equal(inc.p["W2"], full.p["W2"])
+    _, ids, _, _, _ = inc.debug_active()
+    some = inc.p["W2"].cpu().numpy()[np.unique(ids)[::997]]
+    codes = orc.hash.codes(some)
+    rng = np.random.default_rng(0)
+    for t in rng.integers(0, wl.L, size=60):
+        for c in list(rng.integers(0, wl.num_buckets, size=20)) + [int(x) for x in codes[:12, t]]:
+            assert np.array_equal(inc.debug_bucket(int(t), int(c)), full.debug_bucket(int(t), int(c))), (t, c)
+    full.destroy()
+    inc.destroy()
 
 
 @pytest.mark.parametrize("kind,policy,C,N", [(synth.HASH_SIMHASH, 1, 16, 2000), (synth.HASH_SIMHASH, 0, 5, 1500),
