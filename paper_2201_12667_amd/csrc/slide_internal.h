@@ -1,6 +1,7 @@
 // Internal declarations shared by the HIP translation units of the SLIDE step library.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "slide.h"
@@ -18,9 +19,12 @@ constexpr int kPairRegions = 32;   // the input layer's pair space is handed out
 struct Ctrl {
   uint32_t status;        // sticky SLIDE_FLAG_* bits
   uint32_t u2, wl_short;  // touched rows of W2 (statistics) / short-bucket worklist length (filled from the back)
-  uint32_t u1, p1;        // touched rows of W1 (statistics) / pair space handed out for the input layer
-  uint32_t wl_count;      // big-bucket worklist length
-  uint32_t overflowed;    // buckets with more than C members at the last build
+  uint32_t u1;            // touched rows of W1 (statistics)
+  // big-bucket worklist length, and how many of its buckets have more than C members at the last build (all such
+  // are on it): one 64-bit update serves both
+  alignas(8) uint32_t wl_count;
+  uint32_t overflowed;
+  uint32_t p1;            // pair space handed out for the input layer
   uint32_t total_pairs;   // A
   uint32_t rehashed;      // rows of W2 hashed by the last build
   uint32_t candidates_lo, candidates_hi;
@@ -40,6 +44,7 @@ struct Ctrl {
   uint32_t max_nch[2];    // most work items of any sample, same parity scheme (a cache line of its own)
   uint32_t pad3[14];
 };
+static_assert(offsetof(Ctrl, wl_count) % 8 == 0 && offsetof(Ctrl, overflowed) == offsetof(Ctrl, wl_count) + 4, "one word of 64 bits");
 
 // Hash functions as the kernels read them.
 struct HashDev {

@@ -194,8 +194,8 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   int32_t* idl = (int32_t*)(sets + 2 * set_words);             // [stage] the partition's ids grouped by bucket
   uint32_t* nslots_p = (uint32_t*)(idl + stage);           // [2] pieces of each partition of the pair
   uint32_t* nmed_p = nslots_p + 2;                             // [2] staged buckets of 9 .. 16 ids / of 17 .. kRankMax
-  uint32_t* nq_p = nmed_p + 2;                                 // [2] buckets for the short / long queue, [2] their first places
-  uint32_t* medq = nq_p + 4;                                   // [medcap] the former from the front, the latter from the back
+  uint32_t* nq_p = nmed_p + 2;                                 // [2] buckets for the short / long queue (the latter's over capacity << 16), [2] handed out, [2] first places
+  uint32_t* medq = nq_p + 6;                                   // [medcap] the former from the front, the latter from the back
   const uint32_t* tent = entries + t * N;
   const uint32_t* truns0 = runs + t * nslab * (size_t)(nbins + 1);
   auto ra_of = [&](int set) { return sets + set * set_words; };
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   auto run_partition = [&](const uint32_t d, const int set, const bool cached, const uint32_t (&x0)[kSlotBatch], const int ns0) {
   if (vec) for (int q = tid; q < nlo / 4; q += 256) cur4[q] = make_uint4(0u, 0u, 0u, 0u);
   else for (int b = tid; b < nlo; b += 256) cur[b] = 0;
-  if (tid < 2) { nmed_p[tid] = 0; nq_p[tid] = 0; }
+  if (tid < 2) { nmed_p[tid] = 0; nq_p[tid] = 0; nq_p[2 + tid] = 0; }
   __syncthreads();
   const uint32_t s0 = pbase[t * (nbins + 1) + d], s1 = pbase[t * (nbins + 1) + d + 1];
   const bool staged = s1 - s0 <= (uint32_t)stage;
@@ -375,8 +375,13 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   auto is_queued = [&](uint32_t sz) {
     return staged ? sz > (uint32_t)kRankMax || sz > (uint32_t)C : sz >= 2 && !(sz <= (uint32_t)kSmallBucket && sz <= (uint32_t)C);
   };
-  uint32_t nqueued = 0;
-  auto enqueue = [&](uint32_t sz) { atomicAdd(&nq_p[is_short(sz) ? 0 : 1], 1u); };
+  uint32_t first_place = 0;
+  auto reserve = [&]() {                             // (the answer is looked at when the buckets are written out)
+    if (tid == 0 && nq_p[0]) first_place = atomicAdd(&ctrl->wl_short, nq_p[0]);
+    if (tid == 1 && nq_p[1])
+      first_place = (uint32_t)atomicAdd((unsigned long long*)&ctrl->wl_count, (nq_p[1] & 0xffffu) | (unsigned long long)(nq_p[1] >> 16) << 32);
+  };
+  auto enqueue_long = [&](uint32_t sz) { atomicAdd(&nq_p[1], sz > (uint32_t)C ? 0x10001u : 1u); };   // (at most 8,192 buckets)
   if (staged) {
     // The ids sit in idl grouped by bucket, in arrival order, and are sorted where they are; the whole
     // partition then goes to the table in one coalesced copy (a store per bucket costs far more than
@@ -387,8 +392,8 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
     // bucket b = ids a .. a + sz - 1 (every lane of a wave calls it together: the network is wave-wide)
     auto bucket = [&](const int b, const uint32_t a, const uint32_t sz) {
       const bool big = sz > (uint32_t)kRankMax || sz > (uint32_t)C;
-      if (big) {
-        enqueue(sz);
+      if (big) {                                         // (never a short one)
+        enqueue_long(sz);
       } else if (sz > 16u) {
         medq[medcap - 1 - atomicAdd(&nmed_p[1], 1u)] = (uint32_t)b;   // (lane groups / waves order these below:
       } else if (sz > 8u) {                                             //  at most stage / 9 of them exist)
@@ -454,7 +459,7 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
     // each, a bitonic sort across the lanes.
     __syncthreads();
     const uint32_t nrow = nmed_p[0], nwav = nmed_p[1];
-    nqueued = nq_p[0] | nq_p[1];
+    reserve();
     for (uint32_t m0 = 0; m0 < nrow; m0 += 16) {
       const uint32_t m = m0 + (uint32_t)(tid >> 4);
       const int l16 = tid & 15;
@@ -493,29 +498,27 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
           while (q >= 0 && p[q] > key) { p[q + 1] = p[q]; --q; }
           p[q + 1] = key;
         }
+      } else if (is_short(sz)) {
+        atomicAdd(&nq_p[0], 1u);
       } else {
-        enqueue(sz);
+        enqueue_long(sz);
       }
     }
     __syncthreads();
-    nqueued = nq_p[0] | nq_p[1];
+    reserve();
   }
-  // One update of each queue's length per partition: a word that every bucket bumps serves one bucket per 8 ns or so
-  // (the 25,600 over-capacity buckets of the wide shape, each counted twice: the kernel took 310 us, now 172).
-  if (nqueued) {
-    uint32_t mine = 0;
-    if (tid < 2) {
-      mine = nq_p[tid];
-      nq_p[2 + tid] = mine ? atomicAdd(tid == 0 ? &ctrl->wl_short : &ctrl->wl_count, mine) : 0u;
-    }
-    __syncthreads();
-    if (tid < 2) nq_p[tid] = 0;                      // (from here on: places handed out)
+  // One update of each queue's length per partition, requested before the sorting above: a word that every bucket bumps
+  // serves one bucket per 8 ns or so (the 25,600 over-capacity buckets of the wide shape, each counted twice: the kernel
+  // took 310 us, now 172).  The count of over-capacity buckets rides in the same update (a word of its own, bumped by
+  // every workgroup of the kernel that cuts them, took 15 us there for 1,650 buckets).
+  if (nq_p[0] | nq_p[1]) {
+    if (tid < 2) nq_p[4 + tid] = first_place;
     __syncthreads();
     for (int b = tid; b < nlo; b += 256) {
       const uint32_t sz = cur[b] - (b ? cur[b - 1] : 0u);
       if (!is_queued(sz)) continue;
       const int q = is_short(sz) ? 0 : 1;
-      const uint32_t slot = nq_p[2 + q] + atomicAdd(&nq_p[q], 1u);
+      const uint32_t slot = nq_p[4 + q] + atomicAdd(&nq_p[2 + q], 1u);
       if (slot < wl_cap) worklist[q == 0 ? wl_cap - 1u - slot : slot] = ((uint64_t)t << 32) | ((d << lb) + (uint32_t)b);
     }
   }
@@ -598,7 +601,7 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
                                                           uint32_t nb, int64_t N, int C, int policy, uint32_t r,
                                                           uint32_t pa, uint32_t pb,
                                                           const uint64_t* __restrict__ worklist,
-                                                          uint32_t wl_cap, Ctrl* ctrl) {
+                                                          uint32_t wl_cap, const Ctrl* ctrl) {
   __shared__ uint64_t keys[kSortCap];
   __shared__ uint32_t sid[kSelStage];
   __shared__ uint32_t hist[256];
@@ -608,7 +611,6 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
   int capp = 1;
   while (capp < C) capp <<= 1;
   const int tid = threadIdx.x, lane = tid & 63;
-  uint32_t over = 0;                           // buckets beyond capacity (all of them are queued here)
   for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
     const uint64_t w = worklist[item];
     const uint64_t t = w >> 32;
@@ -624,7 +626,6 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
       bitonic_sort_u64(keys, n2);
       for (uint32_t i = tid; i < s; i += 256) p[i] = (int32_t)(uint32_t)keys[i];
     } else {
-      ++over;
       const bool in_lds = s <= (uint32_t)kSelStage;
       if (in_lds) for (uint32_t i = tid; i < s; i += 256) sid[i] = (uint32_t)p[i];
       hist[tid] = 0;
@@ -696,7 +697,6 @@ __global__ __launch_bounds__(256) void big_buckets_kernel(const uint32_t* __rest
     }
     __syncthreads();
   }
-  if (over && tid == 0) atomicAdd(&ctrl->overflowed, over);
 }
 
 // Split of the code into partition digit (high hb bits) and in-partition digit (low lb bits).
@@ -725,7 +725,7 @@ size_t tables_pbase_words(int bits, int64_t N, int L) {
 static int run_block(int nslab) { return nslab < kRunBlock ? nslab : kRunBlock; }
 static size_t part_buckets_lds(int lb, int nsb, int stage) {
   const size_t nlo = (size_t)1 << lb;
-  return (nlo + ((nlo + 63) >> 6) + 2 * (3 * (size_t)nsb + stage / 64) + stage + 8 + med_cap(stage)) * 4;
+  return (nlo + ((nlo + 63) >> 6) + 2 * (3 * (size_t)nsb + stage / 64) + stage + 10 + med_cap(stage)) * 4;
 }
 // The staging area of the bucket kernel: four mean partitions (a fresh layer's partitions stay within a
 // few percent of the mean, a trained one's within a few times), so that tables with many buckets per
