@@ -30,8 +30,8 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // Forward over the active set, one pass over the gathered rows of W2.
 // Work item = up to kChunk consecutive active neurons of one sample, handled by one wave.  A row
 // is read by LPR lanes (float4 each, CH of them per lane), so 64/LPR rows are in flight per wave.
-// For each row: logit z = w.h + b (stored), and a running soft-max state (reference M, sum s of
-// exp(z - M), acc = sum of exp(z - M) * w) that is rescaled when the reference moves.  acc/s is the
+// For each row: logit z = w.h + b (stored), and a running soft-max state (max M, sum s of
+// exp(z - M), acc = sum of exp(z - M) * w) that is rescaled when the maximum moves.  acc/s is the
 // probability-weighted sum of the rows, which is all the hidden-layer gradient needs, so the rows
 // are not read a second time.  Partial states are merged per sample by combine_kernel.
 // The same launch builds the row lists of the two weight matrices (tile workgroups behind the logit
@@ -39,7 +39,6 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // workers are bandwidth-bound.
 // ---------------------------------------------------------------------------------------------
 constexpr int kForwardThreads = 512;
-constexpr float kSoftmaxSlack = 16.f;
 
 template <int LPR, int CH, bool FULL>
 __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const float* __restrict__ h, const float* __restrict__ W2,
@@ -104,9 +103,10 @@ __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const 
       const float zz = dot + bj;
       if (valid) {
         if (sub == 0) z[slot] = zz;
-        // M need not be the maximum, only near enough that no exponential overflows: it moves (and the sums are
-        // rescaled) when a logit is beyond it by more than kSoftmaxSlack, in practice once per item.
-        if (zz > M + kSoftmaxSlack) {
+        // The sums are rescaled only when the maximum moves, a few times per item.  (A reference that lags behind the
+        // maximum would do for the gradients, but a confident sample's loss is then the difference of two numbers of
+        // the lag's size: 16 lost the loss four bits and gained 2 of 390 us.)
+        if (zz > M) {
           const float sc = __expf(M - zz);
           s *= sc;
 #pragma unroll

@@ -711,6 +711,36 @@ def test_step_with_widely_spread_logits(H, scale):
     model.destroy()
 
 
+@pytest.mark.parametrize("H", [32, 128, 200])
+def test_loss_of_confident_samples(H):
+    """Logits of 0 but for the label's (W2 = 0, the biases are the logits, so that these are exact): the loss is the log of a
+    sum a little above 1.  That sum takes up to 30 additions at its size (8 or 16 rows of a lane group, the merges of groups,
+    items and lanes) and a logarithm, each off by 2^-24 / sqrt(3) or less in the mean square: 3.2 x 2^-24 in all, twice
+    that allowed on the mean of the absolute errors.  (Above 512 columns a lane group is a wave and adds 64 rows in a
+    row, all rounded alike.)"""
+    _say("confident samples", H)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=H, K=3, L=8, batch=4, num_classes=2003, bucket_cap=64,
+                     rebuild_every=0)
+    gen, model, _ = make_pair(wl)
+    model.build_tables()
+    model.p["W2"].zero_()
+    b = gen.batch(0)
+    label = 977
+    b["y_indptr"], b["y_indices"] = np.arange(5, dtype=np.int32), np.full(4, label, np.int32)
+    db = model.to_device(b)
+    off = []
+    for top in np.linspace(8, 15.9, 24).astype(np.float32):
+        model.p["W2"].zero_()
+        model.p["b2"].zero_()
+        model.p["b2"][label] = float(top)
+        loss = float(model.train_step(db).item())
+        others = np.diff(model.debug_active()[0]) - 1
+        off.append(abs(loss - np.log1p(others * np.exp(-float(top))).mean()))
+    _say("   mean error in units of 2^-24:", round(float(np.mean(off)) * 2 ** 24, 2))
+    assert np.mean(off) <= 6 * 2.0 ** -24
+    model.destroy()
+
+
 def _random_workloads():
     rng = np.random.default_rng(2024)
     out = []
