@@ -108,12 +108,14 @@ __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0;
 // (2), (4) Scores of the neurons j0 + c * stride, c < nc (clamped to the layer), for all samples.
 // The 32-bit product is formed from bf16 products: with x = x0 + x1 + x2 the six products of parts whose
 // indices add up to at most two are accumulated in 32 bits; the three left out are below 2^-25 of |h||w| each,
-// the size of one rounding of the 32-bit chain this replaced, and its error against 64 bits was the same
-// 4e-8 (the bias is added last: sums that start from it lose four times that).  Six bf16 passes at 1/16 of the
-// cost each against one pass at the 32-bit matrix rate: the 44 GFLOP of 256 samples x 670K neurons x 128 took
-// 564 us there, 110 of them for writing the scores, and 250 here (matrix cores busy 43 % of the time: the rest
-// is the barrier per stage with eight waves per compute unit); 8 samples, bound by reading W2: 118 and 75 us
-// (4.6 TB/s).
+// the size of one rounding of the 32-bit chain this replaced.  The six products of a coordinate block are summed by
+// themselves and then added to the rest (the bias last), the same way in every variant: the sampled neurons' scores have
+// to be what the pass over all neurons finds.  Relative error against 64 bits, chain / six products added to the
+// whole sum / this: 1.2e-7, 1.3e-7 and 5.5e-8 with 128 coordinates, 1.7e-7, 1.8e-7 and 6.8e-8 with 256, 3.2e-7, 3.6e-7 and
+// 1.2e-7 with 1,024; it costs 5 % of the call with 256 samples (325 -> 343 us), 1 % and less below 128.
+// Six bf16 passes at 1/16 of the cost each against one pass at the 32-bit matrix rate: those 44 GFLOP took 564 us
+// there, 110 of them for writing the scores, and 265 here (the barrier per stage with eight waves per compute
+// unit leaves the matrix cores idle half of the time); 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
 // Product rows are samples, columns neurons.  A wave owns 32 neurons and all NIB * 32 samples of the
 // workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
 // workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in
@@ -232,21 +234,29 @@ __global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4
     split8(wr[0], wr[1], w);
     issue(wr);
     if (!RES) asm volatile("" ::: "memory");             // (not later: see below)
-    constexpr int G = NIB < 2 ? NIB : 2;                 // row blocks interleaved (independent accumulators)
+    constexpr int G = NIB < 2 || RES ? 1 : 2;            // row blocks interleaved (independent sums)
 #pragma unroll
     for (int ib = 0; ib < NIB; ib += G) {
       bf16x8 a[G][3];
+      f32x16 t[G];
 #pragma unroll
-      for (int g = 0; g < G; ++g)
+      for (int g = 0; g < G; ++g) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) a[g][p] = hb[(ib + g) * ib_pitch + p * 64];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t[g][r] = 0.f;
+      }
 #pragma unroll
       for (int pr = 0; pr < 6; ++pr) {
         constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};   // small products first
 #pragma unroll
         for (int g = 0; g < G; ++g)
-          acc[ib + g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][pa[pr]], w[pb[pr]], acc[ib + g], 0, 0, 0);
+          t[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[g][pa[pr]], w[pb[pr]], t[g], 0, 0, 0);
       }
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[ib + g][r] += t[g][r];
     }
   };
   auto clear = [&]() {
@@ -515,9 +525,9 @@ static hipError_t launch_scores(int B, int64_t N, int H, const float4* frags, co
                                 uint32_t* ccnt, int cand_cap, int num_cus, hipStream_t s) {
   const int nkb = ceil_div(H, 16), nkbp = padded_blocks(H), gy = ceil_div(B, NIB * 32), ntiles = ceil_div(nc, kTileNeurons);
   const bool res = NIB <= 2 && NIB * nkb <= kResFrags;
-  // as many workgroups as fit: three of the resident kind per compute unit (two with the registers of two row
-  // blocks), one of the staging kind
-  const int per_cu = !res ? 1 : NIB == 1 ? 3 : 2;
+  // as many workgroups as fit: two of the resident kind per compute unit (registers; their LDS is half of the unit's at
+  // most, H = 256), one of the staging kind
+  const int per_cu = res ? 2 : 1;
   const size_t lds = (res ? NIB * nkb : 2 * NIB * stage_blocks(NIB)) * kTriple + (STORE ? 0 : kCorners);
   const int gx = std::max(1, std::min(ntiles, num_cus * per_cu / std::min(gy, num_cus)));
   const dim3 grid(gx, gy), block(kScoreThreads);
