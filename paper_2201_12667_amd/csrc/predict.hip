@@ -16,6 +16,7 @@
 #include "topk.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace slide {
 
@@ -585,9 +586,11 @@ hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const floa
   hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(kSelectThreads), 0, s, H, h, W2, b2, ns, stride, zs, topk, bars, ccnt,
                      all ? out_ids : nullptr, all ? out_scores : nullptr);
   if (all) return hipGetLastError();
-  // About topk * nc / ns of nc neurons reach the bar; a launch takes as many neurons as bring the candidate
-  // buffers to half their size (all of them up to topk * stride = 8,192).
-  const int64_t most = std::max<int64_t>(kTileNeurons, (int64_t)ns * (cap / 2) / topk / kTileNeurons * kTileNeurons);
+  // About topk * nc / ns of nc neurons reach the bar, spread like a sum of topk exponentials: with that mean at
+  // cap * topk / (topk + 4 sqrt(topk) + 16) -- a 21st of the candidate buffer for topk = 1, 0.57 of it for 64 -- chance
+  // overflows it for 7 samples in 10^10 and 2.5 in 10^7.  A launch takes as many neurons as that allows (6.4 M and 1.2 M).
+  const int64_t fit = (int64_t)((double)ns * cap / (topk + 4.0 * std::sqrt((double)topk) + 16.0));
+  const int64_t most = std::max<int64_t>(kTileNeurons, fit / kTileNeurons * kTileNeurons);
   for (int64_t j0 = 0; j0 < N; j0 += most) {
     const int nc = (int)std::min<int64_t>(std::min<int64_t>(most, (int64_t)1 << 30), N - j0);
 #define SLIDE_SCORES(NIB) launch_scores<NIB, false>(B, N, H, frags, W2, b2, j0, nc, 1, nullptr, bars, cand, ccnt, cap, num_cus, s)

@@ -54,8 +54,8 @@ def _check_topk(ids, sc, z, topk):
                                input_dim=2500, bucket_cap=64), 10),
     ("fewer-neurons-than-k", synth.small(synth.HASH_SIMHASH, hidden_dim=32, K=3, L=3, batch=9, num_classes=50,
                                          input_dim=100, nnz_mean=5.0, lab_mean=1.0), 64),
-    # 2048 samples: eight sample tiles per neuron tile, two chunks of neurons
-    ("b2048-three-chunks", synth.small(synth.HASH_SIMHASH, hidden_dim=32, K=5, L=4, batch=2048, num_classes=20011,
+    # 2048 samples: eight row blocks of samples
+    ("b2048", synth.small(synth.HASH_SIMHASH, hidden_dim=32, K=5, L=4, batch=2048, num_classes=20011,
                                        input_dim=0, bucket_cap=8), 7),
     ("h4", synth.small(synth.HASH_SIMHASH, hidden_dim=4, K=2, L=3, batch=3, num_classes=700,
                        input_dim=60, nnz_mean=4.0), 3),
@@ -78,9 +78,9 @@ def test_predict_over_all_neurons_matches_oracle(name, wl, topk):
 
 @pytest.mark.parametrize("slope", [0.01, -0.01])
 def test_predict_when_every_or_no_later_neuron_beats_the_list(slope):
-    """The two extremes of the chunked top-k: biases that grow with the neuron id make every score of
-    every later chunk beat the running list (the candidate buffers overflow and the chunk's scores are
-    streamed instead); biases that fall with the id make none beat it (the list of the first chunk stands)."""
+    """Scores that follow the neuron id: biases that grow with it put the whole list at the end of the layer, behind most
+    of the sampled neurons, biases that fall with it at its start.  (One pass over the layer; several:
+    test_predict_all_in_chunks.)"""
     _say("dense predict, bias slope", slope)
     wl = synth.small(synth.HASH_DWTA, num_classes=20011, batch=33)
     gen, model, orc = make_pair(wl)
@@ -134,6 +134,41 @@ def test_predict_all_when_the_sampled_neurons_mislead(N, H, batch):
         if topk > 2:
             back = np.cumsum(keep) - 1
             assert _check_topk(back[ids[:, 2:]], sc[:, 2:], z, topk - 2) > 0.97
+    model.destroy()
+
+
+@pytest.mark.parametrize("layout", ["random", "second", "first", "second-misleads"])
+def test_predict_all_in_chunks(layout):
+    """A layer so large that the 64 best take two passes over it (1.2 M neurons each): the list of the first and its bar go
+    on into the second.  Random scores; the second pass holds all winners; the first does; the second holds a
+    quarter of a million neurons that reach the bar, because the sampled ones are the worst there, more than a
+    sample's candidate buffer."""
+    N, topk, batch = 1_500_007, 64, 5
+    stride = N // 8192
+    ns = -(-N // stride)
+    most = int(ns * 16384 / (topk + 4 * topk ** 0.5 + 16)) // 256 * 256
+    assert N // 2 < most < N
+    _say("chunks", layout, most)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=16, K=3, L=3, num_classes=N, batch=batch, bucket_cap=8)
+    gen, model, orc = make_pair(wl)
+    ids = np.arange(N)
+    bias = (np.random.default_rng(1).standard_normal(N) * 0.01).astype(np.float32)
+    if layout == "second":
+        bias[most:] += 10
+    elif layout == "first":
+        bias[:most] += 10
+    elif layout == "second-misleads":
+        bias[(ids >= most) & (ids % stride != 0)] += 10
+    model.p["b2"].copy_(torch.from_numpy(bias))
+    model.build_tables()
+    b = gen.batch(0)
+    z = b["hidden"].astype(np.float64) @ orc.p["W2"].astype(np.float64).T + bias.astype(np.float64)
+    db = model.to_device(b)
+    for _ in range(2):
+        got, sc = (x.cpu().numpy() for x in model.predict(db, topk, mode=1))
+        assert _check_topk(got, sc, z, topk) > 0.97
+        if layout != "random":
+            assert np.all(got < most) if layout == "first" else np.all(got >= most)
     model.destroy()
 
 
