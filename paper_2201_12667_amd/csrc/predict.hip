@@ -437,10 +437,41 @@ __global__ __launch_bounds__(kSelectThreads) void dense_bar_kernel(int H, const 
   }
 }
 
+// The same for neurons j0 .. j0 + 255 (before j1; H a multiple of four), one for every thread of the workgroup: neuron
+// j0 + 16 * (thread % 16) + thread / 16.  Sixteen lanes read a row together.
+__device__ __forceinline__ float plain_scores(const float* __restrict__ h, const float* __restrict__ W2, const float* __restrict__ b2,
+                                              int64_t j0, int64_t j1, int H) {
+  static_assert(kSelectThreads == 256, "sixteen rows of sixteen lanes");
+  const int l = threadIdx.x & 15, g = threadIdx.x >> 4;
+  float mine = 0.f;
+  for (int s0 = 0; s0 < 16; s0 += 8) {
+    float p[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) p[u] = 0.f;
+    for (int c = 4 * l; c < H; c += 64) {
+      const float4 a = *(const float4*)(h + c);
+      float4 b[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) b[u] = *(const float4*)(W2 + (size_t)min(j0 + (s0 + u) * 16 + g, j1 - 1) * H + c);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) p[u] = fmaf(a.w, b[u].w, fmaf(a.z, b[u].z, fmaf(a.y, b[u].y, fmaf(a.x, b[u].x, p[u]))));
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+#pragma unroll
+      for (int d = 1; d < 16; d <<= 1) p[u] += __shfl_xor(p[u], d);
+      if (l == s0 + u) mine = p[u];
+    }
+  }
+  return mine + b2[min(j0 + l * 16 + g, j1 - 1)];
+}
+
 // (5) Per sample: folds the candidates of one launch of scores into the running list of the topk best
 // (best[i][0..64), read when `first` is 0); the last launch writes the result.  A sample with more candidates
-// than its buffer holds (the neurons that reach the bar sit between the sampled ones by an unlikely accident)
-// evaluates the launch's neurons itself.
+// than its buffer holds (most scores are no numbers, as after divergence, or the neurons that reach the bar sit between
+// the sampled ones: see launch_dense_topk for how unlikely chance makes that) evaluates the launch's neurons itself,
+// twice or more: tens of milliseconds for a layer of 670K x 128, which one workgroup reads at 20 GB/s (8 and 256 such
+// samples: 36 and 48; a row per thread took 98 and 118).
 __global__ __launch_bounds__(kSelectThreads) void dense_merge_kernel(int H, const float* __restrict__ h,
                                                                      const float* __restrict__ W2,
                                                                      const float* __restrict__ b2, int64_t j0, int nc, int topk,
@@ -473,9 +504,10 @@ __global__ __launch_bounds__(kSelectThreads) void dense_merge_kernel(int H, cons
         }
       }
     } else {
-      for (int c = tid; c < nc; c += kSelectThreads) {
-        const int64_t j = j0 + c;
-        f(topk_key(plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H), (uint32_t)j));
+      for (int64_t c = j0; c < j0 + nc; c += kSelectThreads) {   // (every thread of the workgroup)
+        const float z = plain_scores(h + (size_t)i * H, W2, b2, c, j0 + nc, H);
+        const int64_t j = c + (tid & 15) * 16 + (tid >> 4);
+        if (j < j0 + nc) f(topk_key(z, (uint32_t)j));
       }
     }
   }, [&](int place, uint64_t key) {
