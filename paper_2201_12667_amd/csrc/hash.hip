@@ -450,10 +450,15 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// NKB: blocks of 16 coordinates held (H <= 16 * NKB).  hd.smat: [chunk][nblk][NKB][64 lanes][8]; a chunk holds
+// Waves per workgroup (one fills a compute unit's LDS): as many as the registers of their fragments allow without
+// spilling, 16, 12 or 8.
+constexpr int simhash_threads(int nkb) { return nkb <= 6 ? 1024 : nkb <= 10 ? 768 : 512; }
+
+// NKB: blocks of 16 coordinates held (H <= 16 * NKB), rounded up to an even number, so that at most one block of zeros
+// is multiplied (builds of 325,056 vectors, 450 bits: 96 coordinates 434 us, 128 465, 160 519, 192 570, 256 685).  hd.smat: [chunk][nblk][NKB][64 lanes][8]; a chunk holds
 // tph tables per half wave.
 template <int NKB>
-__global__ __launch_bounds__(NKB <= 8 ? 1024 : 512) void simhash_rows_kernel(HashDev hd, const float* __restrict__ V,
+__global__ __launch_bounds__(simhash_threads(NKB)) void simhash_rows_kernel(HashDev hd, const float* __restrict__ V,
                                                                              int64_t rows, uint32_t* __restrict__ codes,
                                                                              int64_t row_stride, int64_t tab_stride,
                                                                              const int32_t* __restrict__ rowlist,
@@ -576,7 +581,7 @@ SimhashSplit simhash_split(int H, int K, int L) {
   SimhashSplit p{};
   const int nkb = (H + 15) / 16;
   if (nkb > kSimhashMaxBlocks) return p;
-  p.nkb = nkb <= 2 ? 2 : nkb <= 4 ? 4 : nkb <= 8 ? 8 : nkb <= 13 ? 13 : 16;
+  p.nkb = (nkb + 1) / 2 * 2;
   const int most = (int)(kSimhashLds / 1024) / p.nkb, per_half = (L + 1) / 2;      // blocks of a chunk; tables of a half
   const int tables = most * 16 / K > 0 ? most * 16 / K : 1;                        // ... that a chunk can hold
   p.chunks = (per_half + tables - 1) / tables;
@@ -615,7 +620,7 @@ static hipError_t launch_simhash(const HashDev& hd, const SimhashSplit& p, const
   const int per = num_cus / p.chunks > 0 ? num_cus / p.chunks : 1;
   const int64_t groups = (rows + 31) / 32;
   hipLaunchKernelGGL((simhash_rows_kernel<NKB>), dim3((unsigned)(groups < per ? groups : per), p.chunks),
-                     dim3(NKB <= 8 ? 1024 : 512), (size_t)p.nblk * NKB * 1024, s, hd, V, rows, codes, row_stride, tab_stride,
+                     dim3(simhash_threads(NKB)), (size_t)p.nblk * NKB * 1024, s, hd, V, rows, codes, row_stride, tab_stride,
                      rowlist, nrows_dev, p.nblk, p.tph);
   return hipGetLastError();
 }
@@ -717,8 +722,11 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
     switch (p.nkb) {
       case 2: SLIDE_SRP(2);
       case 4: SLIDE_SRP(4);
+      case 6: SLIDE_SRP(6);
       case 8: SLIDE_SRP(8);
-      case 13: SLIDE_SRP(13);
+      case 10: SLIDE_SRP(10);
+      case 12: SLIDE_SRP(12);
+      case 14: SLIDE_SRP(14);
       case 16: SLIDE_SRP(16);
     }
 #undef SLIDE_SRP
@@ -771,7 +779,7 @@ hipError_t hash_setup_attributes(int H) {
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)&dwta_ranked_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ranked_lds(kRankMaxH));
   if (e != hipSuccess) return e;
-  SLIDE_SET(2) SLIDE_SET(4) SLIDE_SET(8) SLIDE_SET(13) SLIDE_SET(16)
+  SLIDE_SET(2) SLIDE_SET(4) SLIDE_SET(6) SLIDE_SET(8) SLIDE_SET(10) SLIDE_SET(12) SLIDE_SET(14) SLIDE_SET(16)
 #undef SLIDE_SET
   return hipSuccess;
 }

@@ -79,7 +79,8 @@ def test_dwta_on_ranks(H, K, L, rows, many):
 
 
 @pytest.mark.parametrize("H,K,L,rows", [(4, 1, 1, 1), (32, 4, 8, 33), (36, 17, 3, 100), (64, 9, 50, 64), (128, 9, 50, 700),
-                                        (200, 9, 51, 333), (208, 5, 100, 31), (256, 24, 5, 65), (256, 9, 90, 97)])
+                                        (200, 9, 51, 333), (208, 5, 100, 31), (256, 24, 5, 65), (256, 9, 90, 97),
+                                        (84, 9, 50, 77), (148, 6, 30, 1200), (192, 11, 17, 65)])
 def test_simhash_sums_near_zero(H, K, L, rows):
     """SimHash bits whose sums are zero, or within rounding of it, beside ordinary ones: vectors of small integers
     (exact zeros, where storage order does not matter), of large values that cancel except for small ones (where it
