@@ -9,7 +9,7 @@ constexpr int kSelectThreads = 256;      // threads of a selecting workgroup
 constexpr int kSelectGather = 1024;      // entries at or above the bar that fit its LDS
 
 struct SelectLds {
-  uint64_t keys[kSelectGather];
+  alignas(16) uint64_t keys[kSelectGather];
   uint64_t last;
   int cnt;
 };
@@ -34,11 +34,27 @@ __device__ __forceinline__ float topk_score(uint64_t key) {
 // entries all sit in a few threads' shares) the best entry is handed out and the search repeated.
 // Bound by the latency of the two sweeps and a handful of barriers (one pass over the list per entry, which
 // this replaced, took 22.7 us for the best 10 of 1,300 retrieved neurons and 200 us for 32 of 6,400; now 7.9
-// and 16.5).
+// and 16.5).  A single best entry needs neither bar nor gather: one sweep and a reduction.
 // Every thread of the workgroup (kSelectThreads) calls.
 template <typename Sweep, typename Emit>
 __device__ __forceinline__ int select_topk(SelectLds& s, int topk, Sweep&& sweep, Emit&& emit) {
   const int tid = threadIdx.x;
+  if (topk == 1) {
+    uint64_t best = ~0ull;
+    sweep([&](uint64_t k) { best = k < best ? k : best; });
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+      const uint64_t other = __shfl_xor((unsigned long long)best, d);
+      best = other < best ? other : best;
+    }
+    if ((tid & 63) == 0) s.keys[tid >> 6] = best;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSelectThreads / 64; ++w) best = s.keys[w] < best ? s.keys[w] : best;
+    if (best == ~0ull) return 0;
+    if (tid == 0) emit(0, best);
+    return 1;
+  }
   uint64_t done = 0;                                     // keys up to here have been handed out
   int out = 0;
   while (out < topk) {
@@ -50,8 +66,12 @@ __device__ __forceinline__ int select_topk(SelectLds& s, int topk, Sweep&& sweep
     if (tid == 0) { s.last = ~0ull - 1; s.cnt = 0; }
     __syncthreads();
     int rank = 0;
+    const ulonglong2* pairs = (const ulonglong2*)s.keys;
 #pragma unroll 8
-    for (int q = 0; q < kSelectThreads; ++q) rank += s.keys[q] < best ? 1 : 0;
+    for (int q = 0; q < kSelectThreads / 2; ++q) {
+      const ulonglong2 two = pairs[q];
+      rank += (two.x < best ? 1 : 0) + (two.y < best ? 1 : 0);
+    }
     if (best != ~0ull && rank == want - 1) s.last = best;  // (fewer than `want` threads with an entry: no bar)
     __syncthreads();
     const uint64_t bar = s.last;
