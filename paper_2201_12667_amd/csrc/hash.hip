@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void dwta_ranked_kernel(HashDev hd
                                                                       const float* __restrict__ V, int64_t rows,
                                                                       uint32_t* __restrict__ codes, int64_t row_stride,
                                                                       int64_t tab_stride, const int32_t* __restrict__ rowlist,
-                                                                      const uint32_t* __restrict__ nrows_dev, int64_t at_least) {
+                                                                      const uint32_t* __restrict__ nrows_dev) {
   // [H][kRankPitch] keys of two vectors per word (vector l low, 64 + l high); then, while the ranks are found, the
   // sorted keys of a vector per wave
   extern __shared__ uint32_t rk[];
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void dwta_ranked_kernel(HashDev hd
     rows = listed;
   }
   const int64_t row0 = (int64_t)blockIdx.x * kRankRows;
-  if (row0 >= rows || rows < at_least) return;
+  if (row0 >= rows) return;
   auto row_of = [&](int r) -> int64_t {                  // vector r of the workgroup, -1 = none
     const int64_t q = row0 + r;
     return q < rows ? (rowlist ? (int64_t)rowlist[q] : q) : -1;
@@ -629,14 +629,14 @@ static hipError_t launch_simhash(const HashDev& hd, const SimhashSplit& p, const
 // on one table at a time and reads its coordinates through scalar loads.
 // rowlist == nullptr: vectors 0 .. rows-1 of V.  Otherwise the vectors rowlist[0 .. *nrows_dev) of V
 // (the grid covers rows; tiles past the device-side count leave at once; a count equal to rows means
-// all of them, and the list is not read).  below: with that many vectors or more there is nothing to do here.
+// all of them, and the list is not read).
 template <int MODE, bool UNI>
 __global__ __launch_bounds__(1024) void hash_rows_kernel(HashDev hd, const uint32_t* __restrict__ offs,
                                                         const float* __restrict__ V,
                                                         int64_t rows, int RPT, uint32_t* __restrict__ codes,
                                                         int64_t row_stride, int64_t tab_stride,
                                                         const int32_t* __restrict__ rowlist,
-                                                        const uint32_t* __restrict__ nrows_dev, int tpb, int64_t below) {
+                                                        const uint32_t* __restrict__ nrows_dev, int tpb) {
   extern __shared__ float tile[];                    // [H + 1][RPT + 1]; the last row is zero
   __shared__ int64_t rid[64];                        // vector held by tile column r, -1 = none
   const int stride = RPT + 1, H = hd.H;
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(1024) void hash_rows_kernel(HashDev hd, const uint3
     if (listed == rows) rowlist = nullptr;           // every vector: in place, without the list
     rows = listed;
   }
-  if (row0 >= rows || rows >= below) return;
+  if (row0 >= rows) return;
   if ((int)threadIdx.x < RPT) {
     const int64_t q = row0 + threadIdx.x;
     rid[threadIdx.x] = q < rows ? (rowlist ? (int64_t)rowlist[q] : q) : -1;
@@ -699,16 +699,29 @@ __global__ __launch_bounds__(1024) void hash_rows_kernel(HashDev hd, const uint3
 template <int MODE>
 static hipError_t launch_mode(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
                               int64_t row_stride, int64_t tab_stride, const int32_t* rowlist,
-                              const uint32_t* nrows_dev, int tpb, hipStream_t s, int64_t below = INT64_MAX) {
+                              const uint32_t* nrows_dev, int tpb, hipStream_t s) {
   const int RPT = rows_per_tile(hd.H);
-  dim3 grid((unsigned)ceil_div(std::min(rows, below), RPT), (unsigned)ceil_div(hd.L, tpb));
+  dim3 grid((unsigned)ceil_div(rows, RPT), (unsigned)ceil_div(hd.L, tpb));
   if (RPT == 64)
     hipLaunchKernelGGL((hash_rows_kernel<MODE, true>), grid, dim3(1024), hash_lds_bytes(hd.H), s, hd, hd.offs, V, rows,
-                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, below);
+                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb);
   else
     hipLaunchKernelGGL((hash_rows_kernel<MODE, false>), grid, dim3(1024), hash_lds_bytes(hd.H), s, hd, hd.offs, V, rows,
-                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, below);
+                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb);
   return hipGetLastError();
+}
+
+// On ranks from 600 functions on (1,000 for vectors of up to 96 coordinates: finding the ranks costs the same there,
+// reading a tile less) and where their workgroups of 128 vectors fill the machine, five for every two compute units
+// (82K vectors).  Table builds, row tiles and ranks, us: 2,400 functions of 128 coordinates 355 and 399 for 32K
+// vectors, 522 and 509 for 64K, 611 and 539 for 82K, 1,027 and 911 for 200K; 600 of them 171 and 178 (64K), 204 and
+// 190 (82K), 311 and 319 (200K), 436 and 421 (300K); 1,000 of 64 coordinates 192 and 196 (64K), 222 and 231 (72K), 257
+// and 239 (82K), 528 and 488 (200K); 600 of 72 coordinates 286 and 297 (82K), 385 and 391 (150K).
+// How long a list of rows is only the device knows: both kernels are launched then, and one of them finds a count of 0
+// and leaves (split_listed_kernel).
+int64_t hash_ranked_from(const HashDev& hd) {
+  const bool fits = hd.kind == SLIDE_HASH_DWTA && hd.m == 8 && hd.H <= kRankMaxH && hd.NH >= (hd.H > 96 ? 600 : 1000);
+  return fits ? (int64_t)320 * hd.num_cus : INT64_MAX;
 }
 
 hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
@@ -733,20 +746,12 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
   }
   if (hd.kind == SLIDE_HASH_SIMHASH)
     return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
-  // On ranks from 600 functions on (1,000 for vectors of up to 96 coordinates: finding the ranks costs the same there,
-  // reading a tile less) and where their workgroups of 128 vectors fill the machine, five for every two compute units
-  // (82K vectors).  Table builds, row tiles and ranks, us: 2,400 functions of 128 coordinates 355 and 399 for 32K
-  // vectors, 522 and 509 for 64K, 611 and 539 for 82K, 1,027 and 911 for 200K; 600 of them 171 and 178 (64K), 204 and
-  // 190 (82K), 311 and 319 (200K), 436 and 421 (300K); 1,000 of 64 coordinates 192 and 196 (64K), 222 and 231 (72K), 257
-  // and 239 (82K), 528 and 488 (200K); 600 of 72 coordinates 286 and 297 (82K), 385 and 391 (150K).
-  // How long a list of rows is only the device knows: both kernels are launched, and one of them leaves at once.
-  const int64_t ranked_from = hd.m != 8 || hd.H > kRankMaxH || hd.NH < (hd.H > 96 ? 600 : 1000) ? INT64_MAX : (int64_t)320 * hd.num_cus;
-  if (rows >= ranked_from) {
+  const int64_t ranked_from = hash_ranked_from(hd);
+  if (rows >= ranked_from) {                             // (a list of rows may still be shorter: see hash_ranked_from)
     hipLaunchKernelGGL(dwta_ranked_kernel, dim3((unsigned)ceil_div(rows, kRankRows)), dim3(kRankThreads), ranked_lds(hd.H), s, hd,
-                       hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, ranked_from);
+                       hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, rowlist ? nrows_dev + 1 : nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !rowlist) return e;
-    return launch_mode<8>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s, ranked_from);
   }
   switch (hd.m) {
     case 2: return launch_mode<2>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);

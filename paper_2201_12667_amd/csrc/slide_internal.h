@@ -40,7 +40,9 @@ struct Ctrl {
   uint32_t chunk_alloc[2];
   // running totals since the last slide_reset_stats (updated once per training step)
   unsigned long long sum_pairs, sum_u2, sum_u1, sum_candidates, sum_steps;
-  uint32_t pad2[16];
+  // rows the last build hashed through the list: with the row tiles, with the rank kernel (one of them is 0)
+  uint32_t listed[2];
+  uint32_t pad2[14];
   uint32_t max_nch[2];    // most work items of any sample, same parity scheme (a cache line of its own)
   uint32_t pad3[14];
 };
@@ -73,10 +75,10 @@ struct AdamDev {
 inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // ---- hash.hip -------------------------------------------------------------------------
-// codes[r*row_stride + t*tab_stride] for r < rows, t < L.  With hist != nullptr also
-// pos = atomicAdd(&hist[t*(nb+1) + code], 1) and rank[t*rows + r] = pos.
 // codes[row * row_stride + t * tab_stride] for the vectors 0 .. rows-1 of V, or, with a row list, for the
-// vectors rowlist[0 .. *nrows_dev) (count on the device, at most rows).
+// vectors rowlist[0 .. n) (counts on the device, at most rows: nrows_dev[0] where n < hash_ranked_from, nrows_dev[1]
+// from there on, the other 0).
+int64_t hash_ranked_from(const HashDev& hd);   // vectors from which the rank kernel takes over (INT64_MAX: never)
 hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
                        int64_t row_stride, int64_t tab_stride, const int32_t* rowlist,
                        const uint32_t* nrows_dev, int tables_per_block, hipStream_t s);

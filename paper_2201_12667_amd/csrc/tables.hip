@@ -14,6 +14,8 @@
 #include "slide_internal.h"
 #include "wave_ops.h"
 
+#include <algorithm>
+
 namespace slide {
 
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
@@ -763,9 +765,13 @@ __global__ __launch_bounds__(1024) void collect_touched_kernel(uint8_t* __restri
 
 // When most rows were touched, hashing all of them in place is cheaper than hashing them through
 // the list (whole lines of codes instead of scattered words): the count becomes N, which the hash
-// kernel takes as "no list".
-__global__ void settle_touched_kernel(uint32_t* count, uint32_t N) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && (uint64_t)*count * 4 > (uint64_t)N * 3) *count = N;
+// kernels take as "no list".  Then the count goes to the one of the two that takes as many rows.
+__global__ void split_listed_kernel(uint32_t* count, uint32_t N, uint32_t ranked_from, uint32_t* listed) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  if ((uint64_t)*count * 4 > (uint64_t)N * 3) *count = N;
+  const uint32_t n = *count;
+  listed[0] = n < ranked_from ? n : 0u;
+  listed[1] = n < ranked_from ? 0u : n;
 }
 
 hipError_t tables_setup_attributes() {
@@ -797,8 +803,9 @@ hipError_t launch_build_tables(const HashDev& hd, const TablesDev& td, const flo
     if ((e = launch_fill_u32(&ctrl->rehashed, 1, 0u, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(collect_touched_kernel, dim3((unsigned)ceil_div(td.N, 1024)), dim3(1024), 0, s, touched, td.N,
                        touched_rows, &ctrl->rehashed);
-    hipLaunchKernelGGL(settle_touched_kernel, dim3(1), dim3(64), 0, s, &ctrl->rehashed, (uint32_t)td.N);
-    if ((e = launch_hash(hd, W2, td.N, codes_t, 1, td.N, touched_rows, &ctrl->rehashed, hd.L, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(split_listed_kernel, dim3(1), dim3(64), 0, s, &ctrl->rehashed, (uint32_t)td.N,
+                       (uint32_t)std::min<int64_t>(hash_ranked_from(hd), UINT32_MAX), ctrl->listed);
+    if ((e = launch_hash(hd, W2, td.N, codes_t, 1, td.N, touched_rows, ctrl->listed, hd.L, s)) != hipSuccess) return e;
   } else {
     if ((e = launch_fill_u32(&ctrl->rehashed, 1, (uint32_t)td.N, s)) != hipSuccess) return e;
     if (touched && (e = launch_fill_u32((uint32_t*)touched, (size_t)ceil_div(td.N, 4), 0u, s)) != hipSuccess) return e;
