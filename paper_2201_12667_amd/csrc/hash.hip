@@ -442,7 +442,7 @@ __global__ __launch_bounds__(kRankThreads, 8) void dwta_ranked_kernel(HashDev hd
 // tables, the upper half its own.  The matrix holds the negated signs, so that a set sign bit is a set bit.
 // 325,056 vectors of 128 coordinates, 450 bits of 43 coordinates: 607 us with the kernel below (a lane per
 // vector, three vector instructions and an LDS read per coordinate), 110 here: 75 GFLOP, 32 us at the MFMA rate;
-// the rest is the bits summed exactly (a fifth of the 32 x 32 blocks holds one).  253,855 vectors of 200: 790 -> 201.
+// the rest is the bits summed exactly (a fifth of the 32 x 32 blocks holds one).  253,855 vectors of 200: 790 -> 212.
 // Vectors longer than 256 coordinates (128 registers of fragments) stay with the kernel below.
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));

@@ -113,10 +113,10 @@ __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0;
 // themselves and then added to the rest (the bias last), the same way in every variant: the sampled neurons' scores have
 // to be what the pass over all neurons finds.  Relative error against 64 bits, chain / six products added to the
 // whole sum / this: 1.2e-7, 1.3e-7 and 5.5e-8 with 128 coordinates, 1.7e-7, 1.8e-7 and 6.8e-8 with 256, 3.2e-7, 3.6e-7 and
-// 1.2e-7 with 1,024; it costs 5 % of the call with 256 samples (325 -> 343 us), 1 % and less below 128.
+// 1.2e-7 with 1,024; it costs 5 % of the call with 256 samples (this kernel 298 -> 313 us), 1 % and less below 128.
 // Six bf16 passes at 1/16 of the cost each against one pass at the 32-bit matrix rate: those 44 GFLOP took 564 us
-// there, 110 of them for writing the scores, and 265 here (the barrier per stage with eight waves per compute
-// unit leaves the matrix cores idle half of the time); 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
+// there, 110 of them for writing the scores, and 313 here (matrix cores busy 41 % of the time: the rest is the barrier
+// per stage with eight waves per compute unit); 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
 // Product rows are samples, columns neurons.  A wave owns 32 neurons and all NIB * 32 samples of the
 // workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
 // workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in

@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256) void part_buckets_kernel(const uint32_t* __res
   }
   // One update of each queue's length per partition, requested before the sorting above: a word that every bucket bumps
   // serves one bucket per 8 ns or so (the 25,600 over-capacity buckets of the wide shape, each counted twice: the kernel
-  // took 310 us, now 172).  The count of over-capacity buckets rides in the same update (a word of its own, bumped by
+  // took 310 us, now 181).  The count of over-capacity buckets rides in the same update (a word of its own, bumped by
   // every workgroup of the kernel that cuts them, took 15 us there for 1,650 buckets).
   if (nq_p[0] | nq_p[1]) {
     if (tid < 2) nq_p[4 + tid] = first_place;

@@ -33,8 +33,8 @@ __device__ __forceinline__ float topk_score(uint64_t key) {
 // and each finds its place by counting the better ones.  When one gather cannot hold them (the best
 // entries all sit in a few threads' shares) the best entry is handed out and the search repeated.
 // Bound by the latency of the two sweeps and a handful of barriers (one pass over the list per entry, which
-// this replaced, took 22.7 us for the best 10 of 1,300 retrieved neurons and 200 us for 32 of 6,400; now 7.9
-// and 16.5).  A single best entry needs neither bar nor gather: one sweep and a reduction.
+// this replaced, took 22.7 us for the best 10 of 1,300 retrieved neurons and 200 us for 32 of 6,400; now 7.3
+// and 15.8).  A single best entry needs neither bar nor gather: one sweep and a reduction.
 // Every thread of the workgroup (kSelectThreads) calls.
 template <typename Sweep, typename Emit>
 __device__ __forceinline__ int select_topk(SelectLds& s, int topk, Sweep&& sweep, Emit&& emit) {
