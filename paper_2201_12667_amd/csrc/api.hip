@@ -60,12 +60,12 @@ struct Layout {
   int Bmax, Bpad, H, L, K, C, TW, TWF, NWpad, NT, NT2, NT1, DWpad, bits, PS;
   DenseLayout dense;     // scratch of the prediction over all neurons
   int64_t N, D, Amax, max_chunks, U2max, U1max, P1max, long2, long1;
-  uint32_t nb, wl_cap;
+  uint32_t nb;
   size_t hash_words;
   // workspace offsets
   SimhashSplit srp;      // the hash functions as a matrix (SimHash)
   size_t ctrl, hashw, hashoff, hashmat, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
-      ylist, z, delta, partials, msum, loss_i, umeta2, pairs2, umeta1, pairs1, codes_t, entries, bh, pbase, worklist, touched, touched_rows, ws_total;
+      ylist, z, delta, partials, msum, loss_i, umeta2, pairs2, umeta1, pairs1, codes_t, entries, bh, large, touched, touched_rows, ws_total;
   // tables offsets
   size_t t_off, t_ids, tables_total;
 };
@@ -151,9 +151,6 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   lo->U1max = (int64_t)lo->DWpad * 32;
   lo->long2 = lo->Amax / kLongRow + 1;
   lo->long1 = lo->P1max / kLongRow + 1;
-  const int small = std::min(kSmallBucket, c->bucket_cap);
-  const uint64_t wl = (uint64_t)c->L * (uint64_t)(lo->N / (small + 1) + 1);
-  lo->wl_cap = (uint32_t)std::min<uint64_t>(wl, 0xfffffff0u);
 
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
@@ -183,8 +180,7 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   lo->umeta1 = take((size_t)lo->U1max * 16); lo->pairs1 = take(((size_t)lo->P1max * kPairRegions + (size_t)lo->NT1 * 64) * 8);
   lo->codes_t = take((size_t)lo->L * lo->N * 4); lo->entries = take((size_t)lo->L * lo->N * 4);
   lo->bh = take(tables_bh_words(lo->bits, lo->N, lo->L) * 4);
-  lo->pbase = take(tables_pbase_words(lo->bits, lo->N, lo->L) * 4);
-  lo->worklist = take((size_t)lo->wl_cap * 8);
+  lo->large = take(tables_list_words(lo->bits, lo->N, lo->L) * 4);
   lo->touched = lo->touched_rows = 0;
   if (c->incremental_rebuild) {
     lo->touched = take(((size_t)lo->N + 3) / 4 * 4);
@@ -377,11 +373,11 @@ int do_build(slide_ctx* ctx, hipStream_t s, bool scheduled) {
   const bool only_touched = inc && scheduled && ctx->codes_current;
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_REBUILD, s, [&] {
     return launch_build_tables(ctx->hd, ctx->td, ctx->buf.W2, ctx->at<uint32_t>(lo.codes_t),
-                               ctx->at<uint32_t>(lo.entries), ctx->at<uint32_t>(lo.bh), ctx->at<uint32_t>(lo.pbase),
-                               ctx->at<uint64_t>(lo.worklist), lo.wl_cap, ctx->ctrl(), ctx->cfg.overflow_policy,
+                               ctx->at<uint32_t>(lo.entries), ctx->at<uint32_t>(lo.bh), ctx->at<uint32_t>(lo.large),
+                               ctx->ctrl(), ctx->cfg.overflow_policy,
                                (uint32_t)ctx->r, ctx->prio_a, ctx->prio_b,
                                inc ? ctx->at<uint8_t>(lo.touched) : nullptr,
-                               inc ? ctx->at<int32_t>(lo.touched_rows) : nullptr, only_touched, s); }));
+                               inc ? ctx->at<int32_t>(lo.touched_rows) : nullptr, only_touched, ctx->nxcd, s); }));
   ctx->codes_current = true;
   return SLIDE_OK;
 }
@@ -788,7 +784,8 @@ int slide_get_stats(slide_ctx* ctx, void* hip_stream, slide_stats* out) {
   out->unique_out_rows = c.u2;
   out->unique_in_rows = c.u1;
   out->candidates = ((int64_t)c.candidates_hi << 32) | c.candidates_lo;
-  out->overflowed_buckets = c.overflowed;
+  out->overflowed_buckets = 0;
+  for (uint32_t w = 0; w < kOverWords; ++w) out->overflowed_buckets += c.overflowed[w][0];
   out->rehashed_rows = c.rehashed;
   out->steps = ctx->t;
   out->rebuilds = ctx->r;
@@ -846,7 +843,7 @@ int slide_debug_copy(void* d_dst, const void* d_src, size_t bytes, void* hip_str
 
 int slide_debug_hash(slide_ctx* ctx, const float* d_vectors, int64_t rows, uint32_t* d_codes, void* hip_stream) {
   if (!ctx || !d_vectors || !d_codes || rows < 0) return SLIDE_EINVAL;
-  HIPCHK(ctx, launch_hash(ctx->hd, d_vectors, rows, d_codes, ctx->lo.L, 1, nullptr, nullptr, 4,
+  HIPCHK(ctx, launch_hash(ctx->hd, d_vectors, rows, d_codes, ctx->lo.L, 1, nullptr, nullptr, 4, nullptr,
                           (hipStream_t)hip_stream));
   return SLIDE_OK;
 }

@@ -314,13 +314,14 @@ __global__ __launch_bounds__(kRankThreads, 8) void dwta_ranked_kernel(HashDev hd
                                                                       const float* __restrict__ V, int64_t rows,
                                                                       uint32_t* __restrict__ codes, int64_t row_stride,
                                                                       int64_t tab_stride, const int32_t* __restrict__ rowlist,
-                                                                      const uint32_t* __restrict__ nrows_dev) {
+                                                                      const uint32_t* __restrict__ nrows_dev, Ctrl* build) {
   // [H][kRankPitch] keys of two vectors per word (vector l low, 64 + l high); then, while the ranks are found, the
   // sorted keys of a vector per wave
   extern __shared__ uint32_t rk[];
   const int H = hd.H, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int NW = kRankThreads / 64, PER = kRankRows / NW;   // vectors per wave
+  if (build && blockIdx.x == 0 && tid == 0) start_build(build, rows);
   if (rowlist) {
     const int64_t listed = (int64_t)*nrows_dev;
     if (listed == rows) rowlist = nullptr;               // every vector: in place, without the list
@@ -463,10 +464,11 @@ __global__ __launch_bounds__(simhash_threads(NKB)) void simhash_rows_kernel(Hash
                                                                              int64_t row_stride, int64_t tab_stride,
                                                                              const int32_t* __restrict__ rowlist,
                                                                              const uint32_t* __restrict__ nrows_dev,
-                                                                             int nblk, int tph) {
+                                                                             int nblk, int tph, Ctrl* build) {
   extern __shared__ float4 smat[];                       // [nblk][NKB][64]
   const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, H = hd.H, S = hd.S, K = hd.K;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  if (build && (blockIdx.x | blockIdx.y) == 0 && tid == 0) start_build(build, rows);
   if (rowlist) {
     const int64_t listed = (int64_t)*nrows_dev;
     if (listed == rows) rowlist = nullptr;               // every vector: in place, without the list
@@ -616,12 +618,12 @@ void simhash_matrix(const SimhashSplit& p, int H, int K, int L, int S, const int
 template <int NKB>
 static hipError_t launch_simhash(const HashDev& hd, const SimhashSplit& p, const float* V, int64_t rows, uint32_t* codes,
                                  int64_t row_stride, int64_t tab_stride, const int32_t* rowlist, const uint32_t* nrows_dev,
-                                 int num_cus, hipStream_t s) {
+                                 int num_cus, Ctrl* build, hipStream_t s) {
   const int per = num_cus / p.chunks > 0 ? num_cus / p.chunks : 1;
   const int64_t groups = (rows + 31) / 32;
   hipLaunchKernelGGL((simhash_rows_kernel<NKB>), dim3((unsigned)(groups < per ? groups : per), p.chunks),
                      dim3(simhash_threads(NKB)), (size_t)p.nblk * NKB * 1024, s, hd, V, rows, codes, row_stride, tab_stride,
-                     rowlist, nrows_dev, p.nblk, p.tph);
+                     rowlist, nrows_dev, p.nblk, p.tph, build);
   return hipGetLastError();
 }
 
@@ -636,11 +638,12 @@ __global__ __launch_bounds__(1024) void hash_rows_kernel(HashDev hd, const uint3
                                                         int64_t rows, int RPT, uint32_t* __restrict__ codes,
                                                         int64_t row_stride, int64_t tab_stride,
                                                         const int32_t* __restrict__ rowlist,
-                                                        const uint32_t* __restrict__ nrows_dev, int tpb) {
+                                                        const uint32_t* __restrict__ nrows_dev, int tpb, Ctrl* build) {
   extern __shared__ float tile[];                    // [H + 1][RPT + 1]; the last row is zero
   __shared__ int64_t rid[64];                        // vector held by tile column r, -1 = none
   const int stride = RPT + 1, H = hd.H;
   const int64_t row0 = (int64_t)blockIdx.x * RPT;
+  if (build && (blockIdx.x | blockIdx.y) == 0 && threadIdx.x == 0) start_build(build, rows);
   if (rowlist) {
     const int64_t listed = (int64_t)*nrows_dev;
     if (listed == rows) rowlist = nullptr;           // every vector: in place, without the list
@@ -699,15 +702,15 @@ __global__ __launch_bounds__(1024) void hash_rows_kernel(HashDev hd, const uint3
 template <int MODE>
 static hipError_t launch_mode(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
                               int64_t row_stride, int64_t tab_stride, const int32_t* rowlist,
-                              const uint32_t* nrows_dev, int tpb, hipStream_t s) {
+                              const uint32_t* nrows_dev, int tpb, Ctrl* build, hipStream_t s) {
   const int RPT = rows_per_tile(hd.H);
   dim3 grid((unsigned)ceil_div(rows, RPT), (unsigned)ceil_div(hd.L, tpb));
   if (RPT == 64)
     hipLaunchKernelGGL((hash_rows_kernel<MODE, true>), grid, dim3(1024), hash_lds_bytes(hd.H), s, hd, hd.offs, V, rows,
-                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb);
+                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build);
   else
     hipLaunchKernelGGL((hash_rows_kernel<MODE, false>), grid, dim3(1024), hash_lds_bytes(hd.H), s, hd, hd.offs, V, rows,
-                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb);
+                       RPT, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build);
   return hipGetLastError();
 }
 
@@ -726,12 +729,12 @@ int64_t hash_ranked_from(const HashDev& hd) {
 
 hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
                        int64_t row_stride, int64_t tab_stride, const int32_t* rowlist,
-                       const uint32_t* nrows_dev, int tables_per_block, hipStream_t s) {
+                       const uint32_t* nrows_dev, int tables_per_block, Ctrl* build, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int tpb = tables_per_block < 1 ? 1 : tables_per_block;
   if (hd.kind == SLIDE_HASH_SIMHASH && hd.smat) {
     const SimhashSplit p = simhash_split(hd.H, hd.K, hd.L);
-#define SLIDE_SRP(NKB) return launch_simhash<NKB>(hd, p, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, hd.num_cus, s)
+#define SLIDE_SRP(NKB) return launch_simhash<NKB>(hd, p, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, hd.num_cus, build, s)
     switch (p.nkb) {
       case 2: SLIDE_SRP(2);
       case 4: SLIDE_SRP(4);
@@ -745,19 +748,19 @@ hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t
 #undef SLIDE_SRP
   }
   if (hd.kind == SLIDE_HASH_SIMHASH)
-    return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
+    return launch_mode<0>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build, s);
   const int64_t ranked_from = hash_ranked_from(hd);
   if (rows >= ranked_from) {                             // (a list of rows may still be shorter: see hash_ranked_from)
     hipLaunchKernelGGL(dwta_ranked_kernel, dim3((unsigned)ceil_div(rows, kRankRows)), dim3(kRankThreads), ranked_lds(hd.H), s, hd,
-                       hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, rowlist ? nrows_dev + 1 : nullptr);
+                       hd.offs, V, rows, codes, row_stride, tab_stride, rowlist, rowlist ? nrows_dev + 1 : nullptr, build);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !rowlist) return e;
   }
   switch (hd.m) {
-    case 2: return launch_mode<2>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
-    case 4: return launch_mode<4>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
-    case 8: return launch_mode<8>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
-    case 16: return launch_mode<16>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, s);
+    case 2: return launch_mode<2>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build, s);
+    case 4: return launch_mode<4>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build, s);
+    case 8: return launch_mode<8>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build, s);
+    case 16: return launch_mode<16>(hd, V, rows, codes, row_stride, tab_stride, rowlist, nrows_dev, tpb, build, s);
   }
   return hipErrorInvalidValue;
 }

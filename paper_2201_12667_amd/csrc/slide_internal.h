@@ -10,27 +10,24 @@ namespace slide {
 
 constexpr int kWave = 64;
 constexpr int kChunk = 64;         // active pairs per forward work item
-constexpr int kSmallBucket = 8;    // buckets up to this size are sorted by one thread
 constexpr int kSortCap = 2048;     // keys held in LDS by the big-bucket sorter
 constexpr int kLongRow = 32;       // rows touched by more samples than this are reduced by a whole wave
 constexpr int kPairRegions = 32;   // the input layer's pair space is handed out from this many counters (tile % regions)
 
+constexpr uint32_t kOverWords = 64;
+
 // Device-side counters, one block at the start of the workspace.
 struct Ctrl {
   uint32_t status;        // sticky SLIDE_FLAG_* bits
-  uint32_t u2, wl_short;  // touched rows of W2 (statistics) / short-bucket worklist length (filled from the back)
-  uint32_t u1;            // touched rows of W1 (statistics)
-  // big-bucket worklist length, and how many of its buckets have more than C members at the last build (all such
-  // are on it): one 64-bit update serves both
-  alignas(8) uint32_t wl_count;
-  uint32_t overflowed;
+  uint32_t u2, u1;        // touched rows of W2 and of W1 (statistics)
   uint32_t p1;            // pair space handed out for the input layer
   uint32_t total_pairs;   // A
   uint32_t rehashed;      // rows of W2 hashed by the last build
   uint32_t candidates_lo, candidates_hi;
   uint32_t nlong2, nlong1; // long rows queued by the two transpositions
   uint32_t max_nu2, max_nu1; // most touched rows in any tile
-  uint32_t pad[1];
+  uint32_t nlarge, nunstaged;   // partitions of the table build left to the large form of the bucket kernel, and by that
+  uint32_t pad[2];
   // Pair space of the input layer's row lists: region r (tiles with tile % kPairRegions == r) is handed
   // out from p1r[r].  (Updates of one word from every workgroup of a launch queue up behind each other
   // for tens of nanoseconds apiece, so per-launch counters that many workgroups bump are spread out.)
@@ -45,8 +42,15 @@ struct Ctrl {
   uint32_t pad2[14];
   uint32_t max_nch[2];    // most work items of any sample, same parity scheme (a cache line of its own)
   uint32_t pad3[14];
+  // buckets with more than C members at the last build: their number is the sum (a cache line each)
+  uint32_t overflowed[kOverWords][16];
 };
-static_assert(offsetof(Ctrl, wl_count) % 8 == 0 && offsetof(Ctrl, overflowed) == offsetof(Ctrl, wl_count) + 4, "one word of 64 bits");
+// A table build starts: rows about to be hashed, nothing queued yet (one thread of the build's first kernel).
+__device__ __forceinline__ void start_build(Ctrl* c, int64_t rows) {
+  c->rehashed = (uint32_t)rows;
+  c->nlarge = 0; c->nunstaged = 0;
+  for (uint32_t w = 0; w < kOverWords; ++w) c->overflowed[w][0] = 0;
+}
 
 // Hash functions as the kernels read them.
 struct HashDev {
@@ -77,11 +81,12 @@ inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 // ---- hash.hip -------------------------------------------------------------------------
 // codes[row * row_stride + t * tab_stride] for the vectors 0 .. rows-1 of V, or, with a row list, for the
 // vectors rowlist[0 .. n) (counts on the device, at most rows: nrows_dev[0] where n < hash_ranked_from, nrows_dev[1]
-// from there on, the other 0).
+// from there on, the other 0).  build: the counters of the table build that these codes are for (nullptr: none, or
+// cleared already).
 int64_t hash_ranked_from(const HashDev& hd);   // vectors from which the rank kernel takes over (INT64_MAX: never)
 hipError_t launch_hash(const HashDev& hd, const float* V, int64_t rows, uint32_t* codes,
                        int64_t row_stride, int64_t tab_stride, const int32_t* rowlist,
-                       const uint32_t* nrows_dev, int tables_per_block, hipStream_t s);
+                       const uint32_t* nrows_dev, int tables_per_block, Ctrl* build, hipStream_t s);
 hipError_t hash_setup_attributes(int H);
 size_t hash_lds_bytes(int H);
 int hash_tile_pitch(int H);
@@ -96,12 +101,11 @@ struct TablesDev {
   int L, C;
 };
 hipError_t launch_build_tables(const HashDev& hd, const TablesDev& td, const float* W2, uint32_t* codes_t,
-                               uint32_t* entries, uint32_t* bh, uint32_t* pbase, uint64_t* worklist,
-                               uint32_t wl_cap, Ctrl* ctrl, int policy, uint32_t r, uint32_t prio_a,
+                               uint32_t* entries, uint32_t* bh, uint32_t* large_list, Ctrl* ctrl, int policy, uint32_t r, uint32_t prio_a,
                                uint32_t prio_b, uint8_t* touched, int32_t* touched_rows, bool only_touched,
-                               hipStream_t s);
+                               int nxcd, hipStream_t s);
 size_t tables_bh_words(int bits, int64_t N, int L);      // per-slab run boundaries
-size_t tables_pbase_words(int bits, int64_t N, int L);   // partition starts
+size_t tables_list_words(int bits, int64_t N, int L);    // two lists of partitions
 hipError_t tables_setup_attributes();
 
 // ---- active.hip -----------------------------------------------------------------------

@@ -214,6 +214,45 @@ def test_tables_with_far_more_buckets_than_neurons(kind, K, N, C, policy):
     model.destroy()
 
 
+@pytest.mark.parametrize("kind,H,K,N,C,policy,common", [
+    # one partition per table (no grouping pass), its edges
+    (synth.HASH_SIMHASH, 32, 4, 1, 2, 1, 0), (synth.HASH_SIMHASH, 32, 4, 63, 2, 1, 0), (synth.HASH_SIMHASH, 32, 1, 2048, 16, 1, 0),
+    (synth.HASH_DWTA, 8, 2, 2047, 4, 1, 0), (synth.HASH_SIMHASH, 32, 4, 2049, 16, 1, 0),
+    # edges of a slab; one and two buckets per partition
+    (synth.HASH_SIMHASH, 32, 4, 32768, 64, 1, 0), (synth.HASH_SIMHASH, 32, 5, 32769, 64, 1, 0), (synth.HASH_SIMHASH, 32, 7, 65537, 8, 0, 0),
+    # partitions for the large form (a single bucket; several), for the table itself, of more ids than 16 bits count
+    (synth.HASH_SIMHASH, 32, 2, 60001, 128, 1, 0), (synth.HASH_SIMHASH, 32, 2, 150001, 16, 1, 0), (synth.HASH_SIMHASH, 32, 1, 140001, 100, 1, 0),
+    (synth.HASH_SIMHASH, 32, 2, 150001, 16, 0, 0), (synth.HASH_DWTA, 8, 3, 30001, 9, 1, 2), (synth.HASH_DWTA, 8, 3, 70001, 128, 1, 1),
+    (synth.HASH_DWTA, 8, 3, 70001, 128, 1, 2), (synth.HASH_DWTA, 8, 3, 100003, 1024, 1, 1), (synth.HASH_DWTA, 8, 3, 70001, 1024, 0, 1),
+    # 1,024 and 2,048 partitions per table: smaller slabs
+    (synth.HASH_DWTA, 8, 4, 1050001, 128, 1, 0), (synth.HASH_DWTA, 8, 4, 2100001, 300, 1, 0)])
+def test_tables_of_all_partition_sizes(kind, H, K, N, C, policy, common):
+    """common > 0: nearly all rows are one of that many vectors up to a little noise, so that a few partitions and
+    buckets hold nearly everything."""
+    _say("partition sizes", kind, H, K, N, C, policy, common)
+    from helpers import make_oracle
+    from paper_2201_12667_amd import slide
+    wl = synth.small(kind, hidden_dim=H, K=K, L=2, bucket_cap=C, num_classes=N, overflow_policy=policy, input_dim=0)
+    gen = synth.Generator(wl, 0)
+    w, hp = gen.weights(), gen.hash_params()
+    if common:
+        rng = np.random.default_rng(N)
+        base = rng.standard_normal((common, H)).astype(np.float32)
+        own = rng.random(N) < 0.1
+        rows = base[rng.integers(0, common, N)] + 0.05 * rng.standard_normal((N, H)).astype(np.float32)
+        w["W2"][:] = np.where(own[:, None], w["W2"], rows)
+    model, orc = slide.Slide(slide.config_from_workload(wl), w, hp), make_oracle(wl, w, hp)
+    for rebuild in (False, True):
+        model.build_tables()
+        T = orc.build_tables(first=not rebuild)
+        assert model.stats()["overflowed_buckets"] == T.overflowed
+        for t in range(wl.L):
+            for c in range(wl.num_buckets):
+                got, want = model.debug_bucket(t, c), T.bucket(t, c)
+                assert np.array_equal(got, want), (rebuild, t, c, len(got), len(want))
+    model.destroy()
+
+
 @pytest.mark.parametrize("N,policy", [(5000, 1), (12000, 1), (12000, 0)])
 def test_degenerate_tables_all_rows_identical(N, policy):
     """Two buckets per table hold everything (4,000 identical rows; the all-zero rest, which at
