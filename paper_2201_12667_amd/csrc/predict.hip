@@ -32,7 +32,11 @@ constexpr int kSampled = 8192;             // neurons the bars are taken from (u
 constexpr int kCandMax = 16384;            // candidate keys per sample and launch
 constexpr int kCntPitch = 16;              // words between the candidate counters of two samples (one line each)
 constexpr int kFrag = 512;                 // values of an operand fragment: 32 rows x 16 coordinates
-constexpr int kResFrags = 16;              // (row block, coordinate block) pairs of h that may stay in LDS for good
+// (row block, coordinate block) pairs of h that may stay in LDS for good.  Two workgroups of 48 KB share a compute unit; 128
+// samples of up to 160 coordinates take one with 120 KB, and more samples than that such workgroups side by side
+// (rows of W2 that they share come from the die's L2): against 256 samples staged in turns, a barrier per stage,
+// 256 x 670K x 128 takes 282 us instead of 357, 100 x 400K x 32 74 instead of 98, 2,000 x 100K x 128 420 instead of 453.
+__host__ __device__ constexpr int res_frags(int NIB) { return NIB == 4 ? 40 : 16; }
 constexpr int kBlockPad = 8;               // coordinate blocks are padded (with zeros) to a multiple of this
 constexpr int kListed = 128;               // scores a wave lists before it hands them over
 constexpr int kCornerWords = 512 + 3 * kListed;    // LDS words of a wave: half a block of scores and that list
@@ -115,22 +119,21 @@ __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0;
 // whole sum / this: 1.2e-7, 1.3e-7 and 5.5e-8 with 128 coordinates, 1.7e-7, 1.8e-7 and 6.8e-8 with 256, 3.2e-7, 3.6e-7 and
 // 1.2e-7 with 1,024; it costs 5 % of the call with 256 samples (this kernel 298 -> 313 us), 1 % and less below 128.
 // Six bf16 passes at 1/16 of the cost each against one pass at the 32-bit matrix rate: those 44 GFLOP took 564 us
-// there, 110 of them for writing the scores, and 313 here (matrix cores busy 41 % of the time: the rest is the barrier
-// per stage with eight waves per compute unit); 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
+// there, 110 of them for writing the scores, and 313 here in stages of 256 samples (matrix cores busy 41 % of the time), 245 in resident blocks of 128; 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
 // Product rows are samples, columns neurons.  A wave owns 32 neurons and all NIB * 32 samples of the
 // workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
 // workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in
-// fragment order -- RES: it all fits (48 KB), is staged once, and the waves never meet again; otherwise the next stage is fetched under the products of this one.
+// fragment order -- RES: it all fits (res_frags), is staged once, and the waves never meet again; otherwise the next stage is fetched under the products of this one.
 // STORE: every score goes to zs (the sampled neurons); otherwise the scores that reach their sample's bar go
 // to its candidate buffer.
 template <int NIB, bool STORE, bool RES>
-__global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4) void dense_scores_kernel(
+__global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && STORE ? 3 : 4) void dense_scores_kernel(
     int B, int64_t N, int H, int nkbp, const float4* frags, const float* __restrict__ W2, const float* __restrict__ b2, int64_t j0, int nc, int stride, float* __restrict__ zs,
     const uint64_t* __restrict__ bars, uint64_t* __restrict__ cand, uint32_t* ccnt, int cand_cap) {
   constexpr int MB = NIB * 32;                           // samples per workgroup
   constexpr int KS = stage_blocks(NIB);                  // coordinate blocks per stage
   constexpr int PIECES = NIB * KS * 192;                 // 16-byte pieces of a stage
-  constexpr int PPT = (RES ? kResFrags * 192 : PIECES) / kScoreThreads;   // ... per thread
+  constexpr int PPT = (RES ? res_frags(NIB) * 192 : PIECES) / kScoreThreads;   // ... per thread
   extern __shared__ f32x4 hs[];                          // [row block][coordinate block][part][lane], twice unless RES; the waves' corners
   __shared__ uint64_t bar_s[MB];
   __shared__ float thr[MB];                              // score of the bar
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(kScoreThreads, !RES ? 2 : NIB == 2 && STORE ? 3 : 4
     split8(wr[0], wr[1], w);
     issue(wr);
     if (!RES) asm volatile("" ::: "memory");             // (not later: see below)
-    constexpr int G = NIB < 2 || RES ? 1 : 2;            // row blocks interleaved (independent sums)
+    constexpr int G = NIB < 2 || (RES && NIB < 4) ? 1 : 2;            // row blocks interleaved (independent sums)
 #pragma unroll
     for (int ib = 0; ib < NIB; ib += G) {
       bf16x8 a[G][3];
@@ -557,15 +560,15 @@ static hipError_t launch_scores(int B, int64_t N, int H, const float4* frags, co
                                 int64_t j0, int nc, int stride, float* zs, const uint64_t* bars, uint64_t* cand,
                                 uint32_t* ccnt, int cand_cap, int num_cus, hipStream_t s) {
   const int nkb = ceil_div(H, 16), nkbp = padded_blocks(H), gy = ceil_div(B, NIB * 32), ntiles = ceil_div(nc, kTileNeurons);
-  const bool res = NIB <= 2 && NIB * nkb <= kResFrags;
+  const bool res = NIB <= 4 && NIB * nkb <= res_frags(NIB);
   // as many workgroups as fit: two of the resident kind per compute unit (registers; their LDS is half of the unit's at
   // most, H = 256), one of the staging kind
-  const int per_cu = res ? 2 : 1;
+  const int per_cu = res && NIB < 4 ? 2 : 1;
   const size_t lds = (res ? NIB * nkb : 2 * NIB * stage_blocks(NIB)) * kTriple + (STORE ? 0 : kCorners);
   const int gx = std::max(1, std::min(ntiles, num_cus * per_cu / std::min(gy, num_cus)));
   const dim3 grid(gx, gy), block(kScoreThreads);
   if (res)
-    hipLaunchKernelGGL((dense_scores_kernel<NIB <= 2 ? NIB : 2, STORE, true>), grid, block, lds, s, B, N, H, nkbp, frags, W2, b2,
+    hipLaunchKernelGGL((dense_scores_kernel<NIB <= 4 ? NIB : 4, STORE, true>), grid, block, lds, s, B, N, H, nkbp, frags, W2, b2,
                        j0, nc, stride, zs, bars, cand, ccnt, cand_cap);
   else
     hipLaunchKernelGGL((dense_scores_kernel<NIB, STORE, false>), grid, block, lds, s, B, N, H, nkbp, frags, W2,
@@ -575,7 +578,7 @@ static hipError_t launch_scores(int B, int64_t N, int H, const float4* frags, co
 
 template <int NIB, bool STORE>
 static hipError_t scores_attr() {
-  hipError_t e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB <= 2 ? NIB : 2, STORE, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kResFrags * kTriple + kCorners));
+  hipError_t e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB <= 4 ? NIB : 4, STORE, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(res_frags(NIB) * kTriple + kCorners));
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, STORE, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * NIB * stage_blocks(NIB) * kTriple + (STORE ? 0 : kCorners)));
   return e;
 }
@@ -626,7 +629,7 @@ hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const floa
   for (int64_t j0 = 0; j0 < N; j0 += most) {
     const int nc = (int)std::min<int64_t>(std::min<int64_t>(most, (int64_t)1 << 30), N - j0);
 #define SLIDE_SCORES(NIB) launch_scores<NIB, false>(B, N, H, frags, W2, b2, j0, nc, 1, nullptr, bars, cand, ccnt, cap, num_cus, s)
-    switch (dense_row_blocks(B)) {
+    switch (std::min(dense_row_blocks(B), ceil_div(H, 16) * 4 <= res_frags(4) ? 4 : 8)) {
       case 1: e = SLIDE_SCORES(1); break;
       case 2: e = SLIDE_SCORES(2); break;
       case 4: e = SLIDE_SCORES(4); break;

@@ -137,6 +137,29 @@ def test_predict_all_when_the_sampled_neurons_mislead(N, H, batch):
     model.destroy()
 
 
+@pytest.mark.parametrize("batch", [64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("H", [16, 124, 160, 164])
+def test_predict_all_row_blocks(batch, H):
+    """Edges of the row blocks, resident and staged activations, against 64-bit scores: the lists are the best by those
+    up to near-ties, the scores within the six bf16 products' error (2e-6 of the largest is ten times what 1,024
+    coordinates show)."""
+    _say("dense predict blocks", batch, H)
+    N, topk = 17003, 7
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=H, K=3, L=3, num_classes=N, batch=batch, bucket_cap=8)
+    gen, model, orc = make_pair(wl)
+    model.build_tables()
+    host = gen.batch(0)
+    ids, scores = model.predict(model.to_device(host), topk, 1)
+    z = host["hidden"].astype(np.float64) @ orc.p["W2"].astype(np.float64).T + orc.p["b2"].astype(np.float64)
+    want = -np.sort(-z, axis=1)[:, :topk]
+    ids, scores = ids.cpu().numpy(), scores.cpu().numpy()
+    bar = 2e-6 * np.abs(z).max()
+    assert np.abs(scores - want).max() <= bar
+    assert np.abs(np.take_along_axis(z, ids.astype(np.int64), 1) - scores).max() <= bar
+    assert all(len(set(r)) == topk for r in ids.tolist())
+    model.destroy()
+
+
 @pytest.mark.parametrize("layout", ["random", "second", "first", "second-misleads"])
 def test_predict_all_in_chunks(layout):
     """A layer so large that the 64 best take two passes over it (1.2 M neurons each): the list of the first and its bar go
