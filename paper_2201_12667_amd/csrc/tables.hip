@@ -105,11 +105,21 @@ __global__ __launch_bounds__(1024) void slab_group_kernel(const uint32_t* __rest
   uint32_t* mine = cur + (wave >> 1) * nbins;
   const uint32_t shift = 16u * (uint32_t)(wave & 1);
   uint32_t code[RPT];
+  const uint32_t* own = codes_t + t * N + j0 + r0;
+  // (only a table's last slab is not full: a test per row costs more than what it guards)
+  const bool full = nvalid == kRows;
+  if (full) {
 #pragma unroll
-  for (int k = 0; k < RPT; ++k) code[k] = r0 + k * 64 < nvalid ? codes_t[t * N + j0 + r0 + k * 64] : 0u;
+    for (int k = 0; k < RPT; ++k) code[k] = own[k * 64];
 #pragma unroll
-  for (int k = 0; k < RPT; ++k)
-    if (r0 + k * 64 < nvalid) atomicAdd(&mine[code[k] >> lb], 1u << shift);
+    for (int k = 0; k < RPT; ++k) atomicAdd(&mine[code[k] >> lb], 1u << shift);
+  } else {
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) code[k] = r0 + k * 64 < nvalid ? own[k * 64] : 0u;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k)
+      if (r0 + k * 64 < nvalid) atomicAdd(&mine[code[k] >> lb], 1u << shift);
+  }
   __syncthreads();
   uint32_t* rrow = runs + (t * nslab + slab) * (size_t)(nbins + 1);
   uint32_t carry = 0;
@@ -136,17 +146,27 @@ __global__ __launch_bounds__(1024) void slab_group_kernel(const uint32_t* __rest
   if (tid == 0) rrow[nbins] = (uint32_t)nvalid;
   __syncthreads();
   const uint32_t lowmask = (1u << lb) - 1u;
+  auto put = [&](int k) {
+    const uint32_t at = atomicAdd(&mine[code[k] >> lb], 1u << shift) >> shift & 0xffffu;
+    stage[at] = ((code[k] & lowmask) << kRowBits) | (uint32_t)(r0 + k * 64);
+  };
+  if (full) {
 #pragma unroll
-  for (int k = 0; k < RPT; ++k) {
-    const int r = r0 + k * 64;
-    if (r < nvalid) {
-      const uint32_t at = atomicAdd(&mine[code[k] >> lb], 1u << shift) >> shift & 0xffffu;
-      stage[at] = ((code[k] & lowmask) << kRowBits) | (uint32_t)r;
-    }
+    for (int k = 0; k < RPT; ++k) put(k);
+  } else {
+#pragma unroll
+    for (int k = 0; k < RPT; ++k)
+      if (r0 + k * 64 < nvalid) put(k);
   }
   __syncthreads();
+  struct __attribute__((packed, aligned(4))) Words4 { uint32_t w[4]; };   // (in memory: word-aligned only)
   uint32_t* out = entries + t * N + j0;
-  for (int k = tid; k < nvalid; k += 1024) out[k] = stage[k];
+  for (int k = 4 * tid; k < nvalid; k += 4096) {
+    const uint4 q = *(const uint4*)(stage + k);
+    if (k + 4 <= nvalid) *reinterpret_cast<Words4*>(out + k) = Words4{{q.x, q.y, q.z, q.w}};
+    else
+      for (int i = k; i < nvalid; ++i) out[i] = stage[i];
+  }
 }
 
 __device__ __forceinline__ uint32_t overflow_prio(uint32_t j, uint32_t t, uint32_t r, uint32_t pa, uint32_t pb) {
@@ -613,7 +633,7 @@ __device__ __forceinline__ bool build_partition(const PartArgs& g, uint32_t* lds
   if (d == (uint32_t)g.nbins - 1 && tid == 0) g.off[t * ((size_t)g.nb + 1) + g.nb] = (uint32_t)N;
   if (!fits || n > (uint32_t)(IN_TABLE ? kTableIds : g.stage) || (IN_TABLE && lb == 0)) {   // (lb = 0: see unstaged_partition)
     if (!IN_TABLE && tid == 0) {
-      if (!kLarge) g.large[atomicAdd(&g.ctrl->nlarge, 1u)] = m;
+      if (!kLarge || DIRECT) g.large[atomicAdd(&g.ctrl->nlarge, 1u)] = m;   // (DIRECT: never)
       else g.large[(uint32_t)g.total + atomicAdd(&g.ctrl->nunstaged, 1u)] = m;
     }
     return false;
@@ -882,11 +902,12 @@ __device__ __forceinline__ bool build_partition(const PartArgs& g, uint32_t* lds
 // a contiguous stretch of them.  PW = 4 waves count with two words per bucket, or, from 4,096 buckets per partition
 // on, where the counters decide how many workgroups share a compute unit, PW = 2 with one; V: buckets per lane in
 // the passes over them.
-template <int PW, int V, bool DIRECT>
-__global__ __launch_bounds__(256) void part_buckets_kernel(PartArgs g) {
+// THREADS: 256, or 1,024 where a table of up to 512 codes is a single partition (2,000 ids, eight tables: 18 -> 12 us).
+template <int PW, int V, bool DIRECT, int THREADS = 256>
+__global__ __launch_bounds__(THREADS) void part_buckets_kernel(PartArgs g) {
   extern __shared__ uint4 part_lds[];
   const uint32_t k = blockIdx.x / (uint32_t)g.nxcd, m = (blockIdx.x % (uint32_t)g.nxcd) * (uint32_t)g.per_xcd + k;
-  if (m < (uint32_t)g.total) build_partition<PW, V, 256, DIRECT>(g, (uint32_t*)part_lds, m);
+  if (m < (uint32_t)g.total) build_partition<PW, V, THREADS, DIRECT>(g, (uint32_t*)part_lds, m);
 }
 
 // The partitions too large for that, as the digits of a layer in training are skewed: a workgroup of sixteen waves per
@@ -1011,6 +1032,7 @@ hipError_t tables_setup_attributes() {
   if (e != hipSuccess) return e;
   SLIDE_SET((part_buckets_kernel<4, 2, false>), part_buckets_lds(kWideLb - 1, 4, piece_slots(kStageIds, kMaxSlabs), kStageIds, 256))
   SLIDE_SET((part_buckets_kernel<2, 4, false>), part_buckets_lds(13, 2, piece_slots(kStageIds, kMaxSlabs), kStageIds, 256))
+  SLIDE_SET((part_buckets_kernel<16, 2, true, kLargeThreads>), part_buckets_lds(9, 16, piece_slots(kStageIds, kMaxSlabs), kStageIds, kLargeThreads))
   SLIDE_SET((part_buckets_kernel<4, 2, true>), part_buckets_lds(kWideLb - 1, 4, piece_slots(kStageIds, kMaxSlabs), kStageIds, 256))
   SLIDE_SET((part_buckets_kernel<2, 4, true>), part_buckets_lds(13, 2, piece_slots(kStageIds, kMaxSlabs), kStageIds, 256))
   SLIDE_SET((large_buckets_kernel<16, 2>), part_buckets_lds(9, 16, piece_slots(large_ids(9), kMaxSlabs), large_ids(9), kLargeThreads))
@@ -1072,9 +1094,12 @@ hipError_t launch_build_tables(const HashDev& hd, const TablesDev& td, const flo
   while (g.cut_bits < 6 && nslab << (g.cut_bits + 1) <= 64) ++g.cut_bits;
   g.total = nbins * td.L; g.nxcd = nxcd; g.per_xcd = ceil_div(g.total, nxcd); g.large = large_list;
   const dim3 grid((unsigned)(g.per_xcd * nxcd));
-  const size_t lds = part_buckets_lds(lb, lb < kWideLb ? 4 : 2, g.slot_cap, g.stage, 256);
+  const bool wide = direct && lb <= 9;
+  const size_t lds = wide ? part_buckets_lds(lb, 16, g.slot_cap, g.stage, kLargeThreads) : part_buckets_lds(lb, lb < kWideLb ? 4 : 2, g.slot_cap, g.stage, 256);
 #define SLIDE_PART(PW, V, DIRECT) hipLaunchKernelGGL((part_buckets_kernel<PW, V, DIRECT>), grid, dim3(256), lds, s, g)
-  if (lb < kWideLb) { if (direct) SLIDE_PART(4, 2, true); else SLIDE_PART(4, 2, false); }
+  if (wide)
+    hipLaunchKernelGGL((part_buckets_kernel<16, 2, true, kLargeThreads>), grid, dim3(kLargeThreads), lds, s, g);
+  else if (lb < kWideLb) { if (direct) SLIDE_PART(4, 2, true); else SLIDE_PART(4, 2, false); }
   else { if (direct) SLIDE_PART(2, 4, true); else SLIDE_PART(2, 4, false); }
 #undef SLIDE_PART
   if (td.N <= g.stage) return hipGetLastError();         // (no partition is larger than the layer)
