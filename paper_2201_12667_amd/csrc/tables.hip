@@ -563,7 +563,8 @@ __device__ __forceinline__ void unstaged_partition(const PartArgs& g, uint32_t* 
 // waves take consecutive stretches of the entries and have counters of their own, so the ids of a bucket end up
 // ascending without being sorted.  (What is not ours to decide is the order in which an LDS word serves the lanes of
 // one instruction.  It is lane order on this hardware; a partition in which it were not would be found out while it
-// is copied to the table and sorted like one that did not fit.)  The survivors of an over-capacity bucket are chosen
+// is copied to the table and put right by exchanges of neighbours: with the lanes of a piece reversed on purpose every
+// table still came out right.)  The survivors of an over-capacity bucket are chosen
 // here too, by a wave, or by the workgroup where there are many members.
 // DIRECT: the entries are the codes themselves (one partition per table, one slab: no grouping pass has run).
 // IN_TABLE: a partition of up to kTableIds ids that no staging area holds: the same, with the ids placed in the table
