@@ -11,6 +11,8 @@
 #include "spmm.h"
 #include "wave_ops.h"
 
+#include <algorithm>
+
 namespace slide {
 
 constexpr int kSelWords = 264;     // 256 histogram bins + counters of the sampling-budget selection
@@ -48,28 +50,63 @@ __device__ __forceinline__ size_t act_index(const ActiveDev& ad, int i, int w) {
   return ((size_t)(w >> tws) * ad.B + i) * ad.TW + (w & (ad.TW - 1));
 }
 
-// Hash codes of one vector held in LDS, one thread per elementary hash (same arithmetic, in the
-// same order, as the row-tile kernel in hash.hip).  raw[e]: DWTA winner position or -1, SimHash bit.
-__device__ void sample_hash_codes(const HashDev& hd, const float* hvec, int8_t* raw, uint32_t* codes_out,
-                                  uint32_t* __restrict__ codes_global) {
+// A coordinate as DWTA compares it: ascending like the values, 0 for zeros and NaN, which no bin's winner can be.
+// (The bits of a non-negative number that is no NaN will do as they are, where all of a vector's are.)
+__device__ __forceinline__ uint32_t dwta_key(float x) {
+  const uint32_t u = __float_as_uint(x);
+  return x == 0.0f || x != x ? 0u : (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// The first words of the thread's hash functions, requested before the vector to hash is there: SimHash, sixteen words
+// (32 coordinates) of its first function; DWTA with bins of eight, the coordinates of its first four bins.
+constexpr int kHashAhead = 16;
+template <int KIND>
+__device__ __forceinline__ void sample_hash_request(const HashDev& hd, uint32_t (&ahead)[kHashAhead]) {
   const int tid = threadIdx.x, nthr = blockDim.x;
-  if (hd.kind == SLIDE_HASH_SIMHASH) {
-    // eight words (sixteen coordinates) requested before the first is used: the sum itself is a chain
+  if constexpr (KIND == SLIDE_HASH_SIMHASH) {
+    const uint32_t* __restrict__ sw = hd.wordsT + min(tid, hd.NH - 1);
     const int half = hd.Spad / 2;
+#pragma unroll
+    for (int u = 0; u < kHashAhead; ++u) ahead[u] = sw[(size_t)min(u, half - 1) * hd.NH];
+  } else if (hd.m == 8) {
+    const uint4* __restrict__ bins = (const uint4*)hd.words;
+#pragma unroll
+    for (int u = 0; u < kHashAhead / 4; ++u) {
+      const uint4 w = bins[min(tid + u * nthr, hd.NH - 1)];
+      ahead[4 * u] = w.x; ahead[4 * u + 1] = w.y; ahead[4 * u + 2] = w.z; ahead[4 * u + 3] = w.w;
+    }
+  }
+}
+
+// Hash codes of one vector held in LDS, one thread per elementary hash (same arithmetic, in the
+// same order, as the row-tile kernel in hash.hip); DWTA: its dwta_key bits.  raw[e]: DWTA winner position or -1, SimHash bit.
+template <int KIND>
+__device__ __forceinline__ void sample_hash_codes(const HashDev& hd, const uint32_t (&ahead)[kHashAhead], const float* hvec, int8_t* raw,
+                                  uint32_t* codes_out) {
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  if constexpr (KIND == SLIDE_HASH_SIMHASH) {
+    // eight words (sixteen coordinates) at a time, sixteen words ahead of the sum, which is a chain
+    const int half = hd.Spad / 2;
+    uint32_t w[8], next[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { w[u] = ahead[u]; next[u] = ahead[8 + u]; }
     for (int e = tid; e < hd.NH; e += nthr) {
-      const uint32_t* __restrict__ sw = hd.words + (size_t)e * half;
+      const uint32_t* __restrict__ sw = hd.wordsT + e;
+      if (e != tid) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { w[u] = sw[(size_t)min(u, half - 1) * hd.NH]; next[u] = sw[(size_t)min(8 + u, half - 1) * hd.NH]; }
+      }
       float acc = 0.0f;
       for (int s0 = 0; s0 < half; s0 += 8) {
-        uint32_t w[8];
         float x[16];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) w[u] = sw[min(s0 + u, half - 1)];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const float x0 = hvec[w[u] & 0x7fffu], x1 = hvec[(w[u] >> 16) & 0x7fffu];
           x[2 * u] = (w[u] & 0x8000u) ? -x0 : x0;        // (a - x is a + (-x) bit for bit)
           x[2 * u + 1] = (w[u] & 0x80000000u) ? -x1 : x1;
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { w[u] = next[u]; next[u] = sw[(size_t)min(s0 + 16 + u, half - 1) * hd.NH]; }
 #pragma unroll
         for (int u = 0; u < 16; ++u)
           if (2 * s0 + u < hd.S) acc += x[u];
@@ -81,41 +118,44 @@ __device__ void sample_hash_codes(const HashDev& hd, const float* hvec, int8_t* 
       uint32_t c = 0;
       for (int k = 0; k < hd.K; ++k) c |= (uint32_t)raw[t * hd.K + k] << k;
       codes_out[t] = c;
-      codes_global[t] = c;
     }
   } else {
     const int half = hd.m / 2;
-    auto winner = [&](int& best_p, float& best, int p2, uint32_t w) {
-      const float x0 = hvec[w & 0xffffu], x1 = hvec[w >> 16];
-      if (x0 != 0.0f && x0 == x0 && (best_p < 0 || x0 > best)) { best_p = 2 * p2; best = x0; }
-      if (x1 != 0.0f && x1 == x1 && (best_p < 0 || x1 > best)) { best_p = 2 * p2 + 1; best = x1; }
-    };
+    const uint32_t* key = (const uint32_t*)hvec;         // (order-preserving, 0 for an entry that does not count)
     if (hd.m == 8) {
-      // a bin's coordinates in one read, the reads of four bins under way together
+      // a bin's coordinates in one read; the thread's first four bins have been requested already
       const uint4* __restrict__ bins = (const uint4*)hd.words;
-      for (int e0 = tid; e0 < hd.NH; e0 += 4 * nthr) {
-        uint4 w[4];
+      uint4 w[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = bins[min(e0 + u * nthr, hd.NH - 1)];
+      for (int u = 0; u < 4; ++u) w[u] = make_uint4(ahead[4 * u], ahead[4 * u + 1], ahead[4 * u + 2], ahead[4 * u + 3]);
+      for (int e0 = tid; e0 < hd.NH; e0 += 4 * nthr) {
+        if (e0 != tid) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) w[u] = bins[min(e0 + u * nthr, hd.NH - 1)];
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int e = e0 + u * nthr;
           if (e >= hd.NH) continue;
-          int best_p = -1;
-          float best = 0.0f;
-          winner(best_p, best, 0, w[u].x);
-          winner(best_p, best, 1, w[u].y);
-          winner(best_p, best, 2, w[u].z);
-          winner(best_p, best, 3, w[u].w);
-          raw[e] = (int8_t)best_p;
+          const uint32_t k[8] = {key[w[u].x & 0xffffu], key[w[u].x >> 16], key[w[u].y & 0xffffu], key[w[u].y >> 16],
+                                 key[w[u].z & 0xffffu], key[w[u].z >> 16], key[w[u].w & 0xffffu], key[w[u].w >> 16]};
+          const uint32_t best = max(max(max(k[0], k[1]), max(k[2], k[3])), max(max(k[4], k[5]), max(k[6], k[7])));
+          int pos = 7;                                   // the lowest position that holds it
+#pragma unroll
+          for (int q = 6; q >= 0; --q) pos = k[q] == best ? q : pos;
+          raw[e] = (int8_t)(best ? pos : -1);
         }
       }
     } else {
       for (int e = tid; e < hd.NH; e += nthr) {
-        int best_p = -1;
-        float best = 0.0f;
-        for (int p2 = 0; p2 < half; ++p2) winner(best_p, best, p2, hd.words[(size_t)e * half + p2]);
-        raw[e] = (int8_t)best_p;
+        int pos = -1;
+        uint32_t best = 0;
+        for (int p2 = 0; p2 < half; ++p2) {
+          const uint32_t w = hd.words[(size_t)e * half + p2], k0 = key[w & 0xffffu], k1 = key[w >> 16];
+          if (k0 > best) { best = k0; pos = 2 * p2; }
+          if (k1 > best) { best = k1; pos = 2 * p2 + 1; }
+        }
+        raw[e] = (int8_t)pos;
       }
     }
     __syncthreads();
@@ -135,33 +175,66 @@ __device__ void sample_hash_codes(const HashDev& hd, const float* hvec, int8_t* 
         c |= (uint32_t)val << (k * hd.lgm);
       }
       codes_out[t] = c;
-      codes_global[t] = c;
     }
   }
   __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void lookup_union_kernel(
+// The bitmap of a sample in LDS: quads of four words, permuted within each stretch of eight quads, so that threads
+// which own neighbouring stretches of 4, 8, 16 or 32 words read their k-th quads from different banks.
+__device__ __forceinline__ int bitmap_quad(int q) { return q ^ ((q >> 3) & 7); }
+__device__ __forceinline__ int bitmap_word(int w) { return w ^ (((w >> 5) & 7) << 2); }
+__device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __popc(w.y) + __popc(w.z) + __popc(w.w); }
+
+// One workgroup per sample: hidden activations, hash codes, buckets, and the union of the buckets and labels as an
+// ascending id list, by way of a bitmap in LDS (or of several in turn, for stretches of `segw` words of the ids).
+// All of it is latency: three dependent reads to the hidden activations, two more to the bucket contents, barriers
+// between the phases, and the instructions that each of sixteen waves spends on what is the same for all.  Hash functions and
+// labels are requested before they are needed; a table's bucket is read by 2^lg neighbouring lanes, eight entries each in
+// flight, with no search for who reads what; a thread then counts 2^lcw consecutive words of the bitmap, and one scan over
+// the threads gives the rank of every quad of words, from which every entry finds its own place in the list.
+// Nothing is stored where only the store would be waited for (a store takes a microsecond to be acknowledged, and a wait
+// for an older load waits for it too wherever the compiler cannot count what lies between).
+// Call with this kernel as it was / is, us: 4 samples x 670K neurons x 400 tables 35.5 / 33.4, 32 x 2,000 x 8 44.4 / 41.8,
+// 512 samples x 670K x 200 tables of 2^24 216 / 207.  Threads: 512 cost the wide shape 30 us, 256 the
+// 670K one 12.
+// ROUNDS: the batch is larger than the machine; then two workgroups share a compute unit (64 registers a
+// thread, half of the LDS each), one of them at work while the other waits, and the hidden activations come from a launch of
+// their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
+// pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
+constexpr int kLookupThreads = 1024;
+constexpr int kLookupArgs = 448;       // bytes of the kernel's arguments
+constexpr int kBucketAhead = 8;        // entries of a bucket that a lane requests at once
+
+template <bool ROUNDS, bool BUDGET, int KIND>
+__global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_kernel(
     ActiveDev ad, HashDev hd, const float* __restrict__ h, SpmmArgs sp, const uint32_t* __restrict__ off,
     const int32_t* __restrict__ ids, uint32_t nb, uint32_t* __restrict__ codes,
     const int32_t* __restrict__ y_indptr, const int32_t* __restrict__ y_indices, int include_labels,
-    int32_t* __restrict__ ncand, Ctrl* ctrl, int segw) {
+    int32_t* __restrict__ ncand, Ctrl* ctrl, int segw, int lg, int lcw) {
+  // (BUDGET: a sampling budget applies; the whole bitmap is one segment then)
   extern __shared__ uint32_t lds[];
   uint32_t* bm = lds;                    // [segw] bitmap segment
   uint32_t* o0s = bm + segw;             // [L] bucket start inside its table (first: the table codes)
-  uint32_t* pos = o0s + ad.L;            // [L+1] exclusive prefix of the bucket lengths
-  uint32_t* sm = pos + ad.L + 1;         // [20] scan scratch + counters
+  uint32_t* blen = o0s + ad.L;           // [L] bucket lengths
+  uint32_t* sm = blen + ad.L;            // [20] scan scratch + counters: [17] labels, [18] bucket entries, [19] long buckets
   float* hvec = (float*)(sm + 20);       // [H] the sample's hidden activations
-  uint32_t* tcnt = (uint32_t*)(hvec + hd.H);   // [NT] active neurons per tile, then their exclusive prefix
-  uint32_t* sel = tcnt + ad.NT;          // [kSelWords] sampling budget: digit histogram + counters
-  int8_t* raw = (int8_t*)(sel + kSelWords);    // [NH] elementary hash values
-  const int i = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
+  uint32_t* rk = (uint32_t*)(hvec + hd.H);     // [segw >> lcw] rank of every thread's first word
+  uint16_t* qrk = (uint16_t*)(rk + (segw >> lcw));   // [segw / 4] entries of that thread's before a quad of words
+  uint32_t* sel = (uint32_t*)(qrk + segw / 4);   // [kSelWords] sampling budget (if there is one): digit histogram + counters
+  int8_t* raw = (int8_t*)(sel + (BUDGET ? kSelWords : 0));    // [NH] elementary hash values
+  const int i = blockIdx.x, tid = threadIdx.x;
+  constexpr int nthr = kLookupThreads;
   const int lane = tid & 63;
-  if (tid == 0) { sm[17] = 0; sm[18] = 0; }
+  touch_kernarg<kLookupArgs>();
+  uint32_t ahead[kHashAhead];
+  if (!ROUNDS) sample_hash_request<KIND>(hd, ahead);           // (ROUNDS: no registers for it; the other workgroup covers the wait)
+  if (tid == 0) { sm[17] = 0; sm[18] = 0; sm[19] = 0; }
   if (i == 0 && tid == 0) {                              // consumed after this kernel
     ctrl->nlong2 = 0; ctrl->max_nu2 = 0;
     if (sp.W1) { ctrl->p1 = 0; ctrl->nlong1 = 0; ctrl->max_nu1 = 0; }
     for (int r = 0; r < kPairRegions; ++r) ctrl->p1r[r] = 0;
+    for (uint32_t w = 0; w < kMaxWords; ++w) ctrl->max_nch[ad.par ^ 1][w][0] = 0;   // the previous call's: clear for the next call
   }
 
   // the sample's slice of the sample-major arrays: room for every candidate plus its labels
@@ -170,69 +243,59 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
     y0 = min(max(y_indptr[i], 0), ad.num_labels);
     nlab = min(max(y_indptr[i + 1], y0), ad.num_labels) - y0;
   }
+  const int y_first = tid < nlab ? y_indices[y0 + tid] : -1;   // the thread's first label
   const int base_i = i * ad.PS + y0;
   const int tws = __ffs(ad.TW) - 1;                      // TW is a power of two >= 4
-  const int LT = ad.TW >> 2;                             // lanes per tile in the sweeps (four words per lane)
+  auto label = [&](int q) { return q == tid ? y_first : y_indices[y0 + q]; };   // (q: of the thread's own)
 
-  const bool budgeted = ad.budget > 0 && include_labels;  // (then the whole bitmap is one segment)
   // The labels of bitmap segment [seg0, seg0 + sw) words (their "new bit" test counts the distinct
   // labels, so they go in before any candidate; under a sampling budget they go in after it).
   auto segment_labels = [&](int seg0, int sw) {
-    if (budgeted) return;
+    if (BUDGET) return;
     const int64_t lo = (int64_t)seg0 * 32, hi = lo + (int64_t)sw * 32;
     for (int q = tid; q < nlab; q += nthr) {
-      const int y = y_indices[y0 + q];
+      const int y = label(q);
       if (y < 0 || y >= ad.N) { if (seg0 == 0) atomicOr(&ctrl->status, SLIDE_FLAG_BAD_LABEL); continue; }
       if (y >= lo && y < hi) {
         const uint32_t bit = 1u << (y & 31);
-        const uint32_t old = atomicOr(&bm[(y - lo) >> 5], bit);
+        const uint32_t old = atomicOr(&bm[bitmap_word((int)(y - lo) >> 5)], bit);
         if (!(old & bit)) atomicAdd(&sm[17], 1u);       // distinct labels
       }
     }
   };
-  auto clear_segment = [&](int sw) {
-    for (int q = tid; q < sw / 4; q += nthr) ((uint4*)bm)[q] = make_uint4(0u, 0u, 0u, 0u);
+  auto clear_words = [&](int from, int to) {             // (multiples of four)
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));                       // (made here, not kept through the kernel)
+    for (int q = from / 4 + tid; q < to / 4; q += nthr) ((uint4*)bm)[q] = make_uint4(zero, zero, zero, zero);
   };
 
-  // a1 (sparse-input mode): the sample's hidden activations, by the first waves of the workgroup;
-  // the first bitmap segment is cleared meanwhile.  Dense-hidden mode: the activations are read.
-  if (sp.W1 && hd.H <= nthr && spmm_stage_rows(segw, hd.H, nthr) >= 32) {
-    spmm_sample_staged(sp, i, ad.B, (float*)bm, segw, hvec, ctrl);   // (the bitmap's room is free until it is cleared)
-    clear_segment(min(segw, ad.NWpad));
+  // a1 (sparse-input mode): the sample's hidden activations by the whole workgroup, their rows of W1 staged in a part
+  // of the bitmap's room while the rest is cleared (non-negative and no NaN: their bits are their keys).  Dense-hidden
+  // mode: the activations are read.
+  const int sw0 = min(segw, ad.NWpad);
+  const bool staged = !ROUNDS && sp.W1 && hd.H <= nthr && spmm_stage_rows(segw, hd.H, nthr) >= 32;
+  if (staged) {
+    const int stage = min(segw, 256 * (hd.H + 2) + 4) & ~3;
+    clear_words(stage, sw0);
+    spmm_sample_staged(sp, i, ad.B, (float*)bm, stage, hvec, ctrl, false);
+    clear_words(0, min(stage, sw0));
   } else {
-    clear_segment(min(segw, ad.NWpad));
-    if (sp.W1) {
+    clear_words(0, sw0);
+    if (!ROUNDS && sp.W1) {
       const int wave = tid >> 6;
       if (wave * 128 < hd.H) spmm_sample(sp, i, ad.B, wave, lane, hvec, ctrl);
     } else {
-      for (int c = tid; c < hd.H; c += nthr) hvec[c] = h[(size_t)i * hd.H + c];
+      for (int c = tid; c < hd.H; c += nthr) {
+        const float x = h[(size_t)i * hd.H + c];
+        hvec[c] = KIND == SLIDE_HASH_DWTA ? __uint_as_float(dwta_key(x)) : x;
+      }
     }
   }
   __syncthreads();                                       // (also orders the counters' reset before the labels)
-  segment_labels(0, min(segw, ad.NWpad));
+  segment_labels(0, sw0);
+  if (ROUNDS) sample_hash_request<KIND>(hd, ahead);
   // a2: hash codes of the hidden activations
-  sample_hash_codes(hd, hvec, raw, o0s, codes + (size_t)i * ad.L);
-
-  uint32_t carry = 0;
-  for (int base = 0; base < ad.L; base += nthr) {
-    const int t = base + tid;
-    uint32_t len = 0;
-    if (t < ad.L) {
-      const uint32_t code = o0s[t];
-      const uint32_t a = off[(size_t)t * (nb + 1) + code];
-      const uint32_t b = off[(size_t)t * (nb + 1) + code + 1];
-      len = min(b - a, (uint32_t)ad.C);
-      o0s[t] = a;
-    }
-    uint32_t total;
-    const uint32_t ex = block_excl_scan(len, sm, total);
-    if (t < ad.L) pos[t] = carry + ex;
-    carry += total;
-    __syncthreads();
-  }
-  if (tid == 0) pos[ad.L] = carry;
-  __syncthreads();
-  const uint32_t T = pos[ad.L];
+  sample_hash_codes<KIND>(hd, ahead, hvec, raw, o0s);
 
   // Sampling budget: the bitmap holds the retrieved neurons.  The labels do not count (their bits are
   // taken out first and put back at the end); more than `budget` left: keep the `budget` of smallest
@@ -245,15 +308,12 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
     const int nq = ad.NWpad / 4;
     for (int q = tid; q < nlab; q += nthr) {
       const int y = y_indices[y0 + q];
-      if (y >= 0 && y < ad.N) atomicAnd(&bm[y >> 5], ~(1u << (y & 31)));
+      if (y >= 0 && y < ad.N) atomicAnd(&bm[bitmap_word(y >> 5)], ~(1u << (y & 31)));
     }
     if (tid == 0) { misc[0] = 0; misc[1] = 0; misc[2] = (uint32_t)ad.budget; }
     __syncthreads();
     uint32_t c = 0;
-    for (int q = tid; q < nq; q += nthr) {
-      const uint4 wd = ((const uint4*)bm)[q];
-      c += __popc(wd.x) + __popc(wd.y) + __popc(wd.z) + __popc(wd.w);
-    }
+    for (int q = tid; q < nq; q += nthr) c += popc4(((const uint4*)bm)[q]);
     c = wave_sum(c);
     if (lane == 0 && c) atomicAdd(&misc[0], c);
     __syncthreads();
@@ -265,7 +325,7 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
         __syncthreads();
         const uint32_t prefix = misc[1];
         for (int q = tid; q < nq; q += nthr) {
-          const uint4 wd = ((const uint4*)bm)[q];
+          const uint4 wd = ((const uint4*)bm)[bitmap_quad(q)];
           const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
@@ -300,7 +360,7 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
       }
       const uint32_t last = misc[1];                     // the largest priority that stays
       for (int q = tid; q < nq; q += nthr) {
-        const uint4 wd = ((const uint4*)bm)[q];
+        const uint4 wd = ((const uint4*)bm)[bitmap_quad(q)];
         if (!(wd.x | wd.y | wd.z | wd.w)) continue;
         uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
 #pragma unroll
@@ -312,7 +372,7 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
             if (sample_prio(base, (uint32_t)((4 * q + k) * 32 + b)) > last) ww[k] &= ~(1u << b);
           }
         }
-        ((uint4*)bm)[q] = make_uint4(ww[0], ww[1], ww[2], ww[3]);
+        ((uint4*)bm)[bitmap_quad(q)] = make_uint4(ww[0], ww[1], ww[2], ww[3]);
       }
     } else if (ad.fill && have < (uint32_t)ad.budget) {
       uint32_t need = (uint32_t)ad.budget - have, drawn = 0;
@@ -327,7 +387,7 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
           for (int q = 0; q < nlab; ++q) is_label |= y_indices[y0 + q] == (int)j;
           if (!is_label) {
             const uint32_t bit = 1u << (j & 31);
-            if (!(atomicOr(&bm[j >> 5], bit) & bit)) atomicAdd(&misc[3], 1u);
+            if (!(atomicOr(&bm[bitmap_word((int)(j >> 5))], bit) & bit)) atomicAdd(&misc[3], 1u);
           }
         }
         __syncthreads();
@@ -341,122 +401,208 @@ __global__ __launch_bounds__(1024) void lookup_union_kernel(
       const int y = y_indices[y0 + q];
       if (y < 0 || y >= ad.N) { atomicOr(&ctrl->status, SLIDE_FLAG_BAD_LABEL); continue; }
       const uint32_t bit = 1u << (y & 31);
-      if (!(atomicOr(&bm[y >> 5], bit) & bit)) atomicAdd(&sm[17], 1u);
+      if (!(atomicOr(&bm[bitmap_word(y >> 5)], bit) & bit)) atomicAdd(&sm[17], 1u);
     }
     __syncthreads();
   };
 
-  uint32_t my_cnt = 0;
+  // Buckets: 2^lg lanes to a table, in one go where the tables allow (then a lane keeps its entries for the segments
+  // to come).  What is beyond the lanes' first eight entries each is read by whole waves, four buckets at a time.
+  const int G = 1 << lg, tstep = nthr >> lg;
+  const bool once = ad.L <= tstep;
+  const int direct = kBucketAhead * G;
+  int j[kBucketAhead];
+  uint32_t entries = 0;                                  // (of the buckets this thread leads)
+  uint32_t n = 0;                                        // active neurons in the segments so far
   for (int seg0 = 0; seg0 < ad.NWpad; seg0 += segw) {
+    // (What only depends on these is worked out again for every segment: kept through the loop it would not fit the registers.)
+    int me = tid, lanes = G, quads = 1 << (lcw - 2);
+    asm volatile("" : "+v"(me), "+s"(lanes), "+s"(quads));
+    const int sub = me & (lanes - 1), nq = quads;
     const int sw = min(segw, ad.NWpad - seg0);
-    const int64_t lo = (int64_t)seg0 * 32, hi = lo + (int64_t)sw * 32;
-    if (seg0 > 0) { clear_segment(sw); __syncthreads(); segment_labels(seg0, sw); __syncthreads(); }
-    auto candidate = [&](uint32_t c) -> int {           // the c-th of the sample's T bucket entries
-      int a = 0, b = ad.L;                              // last t with pos[t] <= c
-      while (b - a > 1) { const int mid = (a + b) >> 1; if (pos[mid] <= c) a = mid; else b = mid; }
-      return ids[(size_t)a * ad.N + o0s[a] + (c - pos[a])];
+    const int lo = seg0 * 32;
+    const uint32_t span = (uint32_t)sw * 32u;            // (ids of the segment: id - lo < span)
+    auto set_bit = [&](int id) {
+      const uint32_t r = (uint32_t)id - (uint32_t)lo;    // (-1, no entry, is beyond every span: N is at most 2^30)
+      if (r < span) atomicOr(&bm[bitmap_word((int)(r >> 5))], 1u << (r & 31));
     };
-    for (uint32_t c0 = 0; c0 < T; c0 += 4 * nthr) {     // four entries per thread in flight
-      int j[4];
+    if (seg0 > 0) { clear_words(0, sw); __syncthreads(); segment_labels(seg0, sw); __syncthreads(); }
+    // Every entry of the buckets: f(id), -1 where a lane has none.  (again: the lane's entries, if it keeps them)
+    auto for_direct = [&](bool again, auto&& f) __attribute__((always_inline)) {
+      for (int t = me >> lg; t < ad.L; t += tstep) {
+        if (!(again && once)) {
+          uint32_t a, len;
+          if (seg0 == 0 && !again) {
+            const uint32_t code = o0s[t];
+            if (sub == 0) codes[(size_t)i * ad.L + t] = code;
+            a = off[(size_t)t * (nb + 1) + code];
+            len = min(off[(size_t)t * (nb + 1) + code + 1] - a, (uint32_t)ad.C);
+            if (sub == 0) {                              // (the group's lanes sit in one wave: they have read the code)
+              o0s[t] = a;
+              blen[t] = len;
+              entries += len;
+              if ((int)len > direct) sm[19] = 1;
+            }
+          } else {
+            a = o0s[t];
+            len = blen[t];
+          }
+          const uint32_t first = (uint32_t)t * (uint32_t)ad.N + a + (uint32_t)sub;   // (L * N < 2^32)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { const uint32_t c = c0 + u * nthr + tid; j[u] = c < T ? candidate(c) : -1; }
+          for (int u = 0; u < kBucketAhead; ++u) j[u] = -1;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j[u] >= lo && j[u] < hi) atomicOr(&bm[(j[u] - lo) >> 5], 1u << (j[u] & 31));
-    }
-    __syncthreads();
-    if (budgeted) apply_budget();
-    // sweep, four words per lane: population per tile (the last lane of a tile holds its count)
-    for (int qb = 0; qb < sw / 4; qb += nthr) {
-      const int q = qb + tid;
-      const uint4 wd = q < sw / 4 ? ((const uint4*)bm)[q] : make_uint4(0u, 0u, 0u, 0u);
-      uint32_t c = __popc(wd.x) + __popc(wd.y) + __popc(wd.z) + __popc(wd.w);
-      my_cnt += c;
-      if (q < sw / 4 && (segw < ad.NWpad || ad.write_act)) {   // spill: re-read by the id sweep / by the row lists
-        uint32_t* dst = &ad.act[act_index(ad, i, seg0 + 4 * q)];
-        *(uint4*)dst = wd;
+          for (int u = 0; u < kBucketAhead; ++u)
+            if (sub + u * lanes < (int)len) j[u] = ids[first + (uint32_t)(u * lanes)];
+        }
+#pragma unroll
+        for (int u = 0; u < kBucketAhead; ++u) f(j[u]);
       }
-      c = small_group_incl_scan_add(c, LT);
-      if (q < sw / 4 && (lane & (LT - 1)) == LT - 1) tcnt[(seg0 + 4 * q) >> tws] = c;
+    };
+    auto for_long = [&](auto&& f) __attribute__((always_inline)) {
+      const int wave = __builtin_amdgcn_readfirstlane(me >> 6);
+      for (int t0 = 64 * wave; t0 < ad.L; t0 += nthr) {
+        unsigned long long left = __ballot(t0 + lane < ad.L && (int)blen[min(t0 + lane, ad.L - 1)] > direct);
+        while (left) {
+          uint32_t from[4];
+          int rest[4], most = 0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int t = t0 + (left ? __ffsll((long long)left) - 1 : 0);
+            rest[k] = left ? __builtin_amdgcn_readfirstlane((int)blen[t]) - direct : 0;
+            from[k] = (uint32_t)t * (uint32_t)ad.N + (uint32_t)__builtin_amdgcn_readfirstlane((int)o0s[t]) + (uint32_t)direct;
+            most = max(most, rest[k]);
+            left &= left - 1;
+          }
+          for (int e = lane; e - lane < most; e += 128) {
+            int v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = -1;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (e + 64 * (u & 1) < rest[u >> 1]) v[u] = ids[from[u >> 1] + (uint32_t)(e + 64 * (u & 1))];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) f(v[u]);
+          }
+        }
+      }
+    };
+    // (What the kernel leaves in memory by the way is stored under these reads: a store of its own would be waited for.)
+    if (staged && seg0 == 0 && tid < hd.H) sp.h[(size_t)i * hd.H + tid] = hvec[tid];
+    for_direct(seg0 > 0, set_bit);
+    if (seg0 == 0) {
+      entries = wave_sum(entries);
+      if (lane == 0 && entries) atomicAdd(&sm[18], entries);
     }
     __syncthreads();
-  }
-  for (int d = 32; d > 0; d >>= 1) my_cnt += __shfl_xor(my_cnt, d);
-  if (lane == 0) atomicAdd(&sm[18], my_cnt);
-  __syncthreads();
-  const int n = (int)sm[18];
-  const uint32_t nch = ((uint32_t)n + kChunk - 1) / kChunk;
-  if (tid == 0) {
-    ad.cnt[i] = n; ad.ny[i] = (int32_t)sm[17]; ncand[i] = (int32_t)T; ad.as_base[i] = base_i;
-    // forward work items of this sample: the partial results of its chunk c go to slot
-    // base_i / kChunk + i + c (the samples' slices of the sample-major arrays do not overlap, so neither
-    // do these), and the largest number of items of any sample bounds the forward launch's enumeration
-    // (most samples find the maximum already there: only a larger count updates it)
-    ad.chunk_ptr[i] = base_i / kChunk + i;
-    if (nch > *(volatile uint32_t*)&ctrl->max_nch[ad.par]) atomicMax(&ctrl->max_nch[ad.par], nch);
-    if (i == 0) ctrl->max_nch[ad.par ^ 1] = 0;           // the previous call's: clear for the next call
-  }
+    if (sm[19]) {
+      for_long(set_bit);
+      __syncthreads();
+    }
+    if constexpr (BUDGET) apply_budget();
 
-  // per-tile counts -> exclusive prefix inside the sample (rank of the tile's first active neuron)
-  uint32_t* rk = tcnt;
-  carry = 0;
-  for (int base = 0; base < ad.NT; base += nthr) {
-    const int t = base + tid;
-    const uint32_t v = t < ad.NT ? rk[t] : 0u;
-    uint32_t total;
-    const uint32_t ex = block_excl_scan(v, sm, total);
-    if (t < ad.NT) { rk[t] = carry + ex; ad.rankT[(size_t)t * ad.B + i] = carry + ex; }
-    carry += total;
-    __syncthreads();
-  }
-  if (tid == 0) ad.rankT[(size_t)ad.NT * ad.B + i] = carry;   // closes the last tile's segment
-  // compact ascending id list: sweep the bitmap (still in LDS if it fitted in one segment)
-  const bool in_lds = segw >= ad.NWpad;
-  for (int qb = 0; qb < ad.NWpad / 4; qb += nthr) {
-    const int q = qb + tid;
-    uint4 wd = make_uint4(0u, 0u, 0u, 0u);
-    if (q < ad.NWpad / 4) wd = in_lds ? ((const uint4*)bm)[q] : *(const uint4*)&ad.act[act_index(ad, i, 4 * q)];
-    const uint32_t c = __popc(wd.x) + __popc(wd.y) + __popc(wd.z) + __popc(wd.w);
-    const uint32_t inc = small_group_incl_scan_add(c, LT);
-    if (c) {
-      int slot = base_i + (int)(rk[(4 * q) >> tws] + inc - c);
-      const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
+    // A thread takes 2^lcw consecutive words: their population, its exclusive prefix over the threads, and from these the
+    // rank of every quad of words and of the tiles' ends.
+    const int nchunk = sw >> lcw, tq = ad.TW >> 2;
+    for (int c0 = 0; c0 < nchunk; c0 += nthr) {
+      const int c = c0 + me;
+      uint32_t cnt = 0, before[4] = {0, 0, 0, 0};        // entries before a quad, two to a word
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        uint32_t word = ww[k];
-        while (word) {
-          const int b = __ffs(word) - 1;
-          ad.as_ids[slot] = (4 * q + k) * 32 + b;
-          ++slot;
-          word &= word - 1;
+      for (int hq = 0; hq < 2; ++hq) {
+        if (4 * hq >= nq) break;
+        uint4 wd[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int q = 4 * hq + k;
+          wd[k] = c < nchunk && q < nq ? ((const uint4*)bm)[bitmap_quad(c * nq + q)] : make_uint4(0u, 0u, 0u, 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          before[2 * hq + (k >> 1)] |= cnt << (16 * (k & 1));
+          cnt += (uint32_t)popc4(wd[k]);
+        }
+      }
+      uint32_t total;
+      const uint32_t rank = n + block_excl_scan(cnt, sm, total);
+      n += total;
+      if (c0 + nthr >= nchunk && seg0 + segw >= ad.NWpad && tid == 0) {
+        const uint32_t nch = (n + kChunk - 1) / kChunk;
+        ad.cnt[i] = (int32_t)n; ad.ny[i] = (int32_t)sm[17]; ncand[i] = (int32_t)sm[18]; ad.as_base[i] = base_i;
+        // forward work items of this sample: the partial results of its chunk c go to slot
+        // base_i / kChunk + i + c (the samples' slices of the sample-major arrays do not overlap, so neither
+        // do these), and the largest number of items of any sample bounds the forward launch's enumeration
+        ad.chunk_ptr[i] = base_i / kChunk + i;
+        atomicMax(&ctrl->max_nch[ad.par][i % kMaxWords][0], nch);
+        ad.rankT[(size_t)ad.NT * ad.B + i] = n;          // closes the last tile's segment
+      }
+      if (c < nchunk) {
+        rk[c] = rank;
+#pragma unroll
+        for (int q = 0; q < 8; q += 2) {
+          if (q >= nq) break;
+          if (nq == 1) qrk[c] = 0;
+          else ((uint32_t*)qrk)[(c * nq + q) >> 1] = before[q >> 1];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {                    // rank of each tile's first active neuron
+          if (q >= nq) break;
+          const int quad = seg0 / 4 + c * nq + q;
+          if ((quad & (tq - 1)) == 0)
+            ad.rankT[(size_t)(quad >> (tws - 2)) * ad.B + i] = rank + ((before[q >> 1] >> (16 * (q & 1))) & 0xffffu);
         }
       }
     }
-  }
-  if (!in_lds) __syncthreads();                      // (the labels are then looked up in the list just written)
-  // for every label entry its slot (-1 for invalid or repeated entries): these slots are the label flags
-  for (int q = tid; q < nlab; q += nthr) {
-    const int y = y_indices[y0 + q];
-    int slot = -1;
-    if (y >= 0 && y < ad.N) {
-      int a = 0;
-      bool found;
-      if (in_lds) {                                      // rank of the label in the bitmap = its slot
-        const int w = y >> 5, w0 = w & ~(ad.TW - 1);
-        a = (int)rk[w >> tws] + __popc(bm[w] & ((1u << (y & 31)) - 1u));
-        for (int q = w0; q < w; ++q) a += __popc(bm[q]);
-        found = (bm[w] >> (y & 31)) & 1u;
-      } else {
-        int b = n;
-        while (a < b) { const int mid = (a + b) >> 1; if (ad.as_ids[base_i + mid] < y) a = mid + 1; else b = mid; }
-        found = a < n && ad.as_ids[base_i + a] == y;
+    __syncthreads();
+    // Rank of id lo + r, which the bitmap holds.
+    auto rank_of = [&](uint32_t r) __attribute__((always_inline)) -> uint32_t {
+      const int quad = (int)(r >> 7), b = (int)(r & 127u);
+      const uint4 wd = ((const uint4*)bm)[bitmap_quad(quad)];
+      const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
+      uint32_t at = rk[quad >> (lcw - 2)] + qrk[quad];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int low = b - 32 * k;                      // bits of this word that come before
+        at += __popc(low >= 32 ? ww[k] : low > 0 ? ww[k] & ((1u << low) - 1u) : 0u);
       }
-      if (found) {
-        slot = base_i + a;
-        for (int q2 = 0; q2 < q; ++q2) if (y_indices[y0 + q2] == y) { slot = -1; break; }
+      return at;
+    };
+    if constexpr (!BUDGET) {
+      // every entry puts itself in its place (those that several buckets hold more than once)
+      auto place = [&](int id) __attribute__((always_inline)) {
+        const uint32_t r = (uint32_t)id - (uint32_t)lo;
+        if (r < span) ad.as_ids[base_i + (int)rank_of(r)] = id;
+      };
+      for_direct(true, place);
+      if (sm[19]) for_long(place);
+    } else {
+      for (int q = tid; q < sw / 4; q += nthr) {         // (drawn neurons are nowhere but in the bitmap)
+        const uint4 wd = ((const uint4*)bm)[bitmap_quad(q)];
+        const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
+        int slot = base_i + (int)(rk[q >> (lcw - 2)] + qrk[q]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          for (uint32_t word = ww[k]; word; word &= word - 1) ad.as_ids[slot++] = (seg0 + 4 * q + k) * 32 + __ffs(word) - 1;
       }
     }
-    ad.ylist[y0 + q] = slot;
+    if (ad.write_act)                                    // the row lists are built from the bitmaps
+      for (int q = tid; q < sw / 4; q += nthr)
+        *(uint4*)&ad.act[act_index(ad, i, seg0 + 4 * q)] = ((const uint4*)bm)[bitmap_quad(q)];
+    // for every label entry its slot (-1 for invalid or repeated entries): these slots are the label flags
+    for (int q = tid; q < nlab; q += nthr) {
+      const int y = label(q);
+      if (y < 0 || y >= ad.N) { if (seg0 == 0) ad.ylist[y0 + q] = -1; continue; }
+      const uint32_t r = (uint32_t)y - (uint32_t)lo;
+      if (r >= span) continue;
+      const int slot = base_i + (int)rank_of(r);
+      bool repeated = false;
+      if (nlab <= 64) {                                  // (all labels are in this wave's lanes)
+        for (int k = 0; k < nlab; ++k) repeated |= __builtin_amdgcn_readlane(y_first, k) == y && k < q;
+      } else {
+        for (int q2 = 0; q2 < q && !repeated; ++q2) repeated = y_indices[y0 + q2] == y;
+      }
+      ad.as_ids[slot] = y;
+      ad.ylist[y0 + q] = repeated ? -1 : slot;
+    }
+    __syncthreads();                                     // (before the next segment is cleared)
   }
 }
 
@@ -475,7 +621,12 @@ hipError_t active_setup_attributes(size_t* lds_limit_out) {
   e = hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
   if (lim > 160 * 1024) lim = 160 * 1024;
-  e = hipFuncSetAttribute((const void*)lookup_union_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
+  const void* kernels[] = {
+      (const void*)lookup_union_kernel<false, false, SLIDE_HASH_DWTA>, (const void*)lookup_union_kernel<false, false, SLIDE_HASH_SIMHASH>,
+      (const void*)lookup_union_kernel<false, true, SLIDE_HASH_DWTA>, (const void*)lookup_union_kernel<false, true, SLIDE_HASH_SIMHASH>,
+      (const void*)lookup_union_kernel<true, false, SLIDE_HASH_DWTA>, (const void*)lookup_union_kernel<true, false, SLIDE_HASH_SIMHASH>};
+  for (const void* k : kernels)
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
   if (e != hipSuccess) return e;
   *lds_limit_out = (size_t)lim;
   return hipSuccess;
@@ -484,17 +635,39 @@ hipError_t active_setup_attributes(size_t* lds_limit_out) {
 hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const float* h, const SpmmArgs& sp,
                                const TablesDev& td, uint32_t* codes, const int32_t* y_indptr,
                                const int32_t* y_indices, int include_labels, int32_t* ncand, Ctrl* ctrl,
-                               size_t lds_limit, hipStream_t s) {
-  const size_t fixed = lookup_fixed_lds(ad.L, hd.H, ad.NT, hd.NH);
-  // (slide_init has refused configurations whose fixed part leaves less than kLookupMinSegment words:
+                               size_t lds_limit, int num_cus, hipStream_t s) {
+  // (slide_init has refused configurations that leave less than kLookupMinSegment words:
   // with a tiny segment the kernel would sweep all candidates once per few hundred neurons)
-  if (fixed + (size_t)kLookupMinSegment * 4 > lds_limit) return hipErrorInvalidValue;
-  size_t avail = (lds_limit - fixed) / 4;
-  int segw = (int)(avail / 32 * 32);
-  if (segw > ad.NWpad) segw = ad.NWpad;
-  const size_t bytes = (size_t)segw * 4 + fixed;
-  hipLaunchKernelGGL(lookup_union_kernel, dim3(ad.B), dim3(1024), bytes, s, ad, hd, h, sp, td.off, td.ids, td.nb,
-                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, segw);
+  if (lookup_fixed_lds(ad.L, hd.H, ad.NT, hd.NH) + (size_t)kLookupMinSegment * 4 > lds_limit) return hipErrorInvalidValue;
+  const bool budgeted = ad.budget > 0 && include_labels;
+  // LDS besides the segment; with a segment and the ranks of its threads' and quads' first words
+  const size_t fixed = ((size_t)2 * ad.L + 20 + hd.H + (budgeted ? kSelWords : 0)) * 4 + (((size_t)hd.NH + 3) & ~(size_t)3);
+  auto lds_of = [&](int words, int lcw) { return fixed + (size_t)words * 4 + (size_t)(words >> lcw) * 4 + (size_t)words / 2; };
+  auto words_in = [&](size_t lds) { return (int)std::min<size_t>(lds > fixed ? (lds - fixed) / 148 * 32 : 0, ad.NWpad); };
+  int segw = words_in(lds_limit);
+  const bool rounds = ad.B > num_cus && !sp.W1 && !budgeted;
+  // two workgroups to a compute unit, where that takes at most four segments instead of one
+  if (rounds) {
+    const int half = words_in(lds_limit / 2);
+    if (half > 0) {
+      const int segments = ceil_div(ad.NWpad, half);
+      if (segments <= 4) segw = ceil_div(ceil_div(ad.NWpad, segments), 32) * 32;
+    }
+  }
+  if (segw < 32) return hipErrorInvalidValue;
+  // words to a thread: the fewest that let all threads together take the segment at once (and its ranks fit)
+  int lcw = 2;
+  while (lcw < 5 && ((segw >> lcw) > kLookupThreads || lds_of(segw, lcw) > lds_limit)) ++lcw;
+  // lanes to a table
+  int lg = 0;
+  while (lg < 6 && (ad.L << (lg + 1)) <= kLookupThreads) ++lg;
+  const size_t bytes = lds_of(segw, lcw);
+  const bool dwta = hd.kind == SLIDE_HASH_DWTA;
+  auto kernel = budgeted ? (dwta ? lookup_union_kernel<false, true, SLIDE_HASH_DWTA> : lookup_union_kernel<false, true, SLIDE_HASH_SIMHASH>)
+                : rounds ? (dwta ? lookup_union_kernel<true, false, SLIDE_HASH_DWTA> : lookup_union_kernel<true, false, SLIDE_HASH_SIMHASH>)
+                         : (dwta ? lookup_union_kernel<false, false, SLIDE_HASH_DWTA> : lookup_union_kernel<false, false, SLIDE_HASH_SIMHASH>);
+  hipLaunchKernelGGL(kernel, dim3(ad.B), dim3(kLookupThreads), bytes, s, ad, hd, h, sp, td.off, td.ids, td.nb,
+                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, segw, lg, lcw);
   return hipGetLastError();
 }
 

@@ -64,7 +64,7 @@ struct Layout {
   size_t hash_words;
   // workspace offsets
   SimhashSplit srp;      // the hash functions as a matrix (SimHash)
-  size_t ctrl, hashw, hashoff, hashmat, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
+  size_t ctrl, hashw, hashwT, hashoff, hashmat, xse, dense_at, h, dh, codes, act, rankT, cnt, ny, ncand, as_base, chunk_ptr, tile_nu2, tile_nu1, longlist2, longlist1, as_ids,
       ylist, z, delta, partials, msum, loss_i, umeta2, pairs2, umeta1, pairs1, codes_t, entries, bh, lists, touched, touched_rows, build, ws_total;
   // tables offsets
   size_t t_off, t_ids, tables_total;
@@ -157,6 +157,7 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   const size_t B = lo->Bmax, H = lo->H, A = (size_t)lo->Amax;
   lo->ctrl = take(sizeof(Ctrl));
   lo->hashw = take(lo->hash_words * 4);
+  lo->hashwT = take(c->hash_kind == SLIDE_HASH_SIMHASH ? lo->hash_words * 4 : 0);
   lo->hashoff = take(hash_offset_count(c) * 4);
   lo->srp = c->hash_kind == SLIDE_HASH_SIMHASH ? simhash_split(c->hidden_dim, c->K, c->L) : SimhashSplit{};
   lo->hashmat = take(simhash_matrix_words(lo->srp) * 2);
@@ -357,7 +358,7 @@ int forward_common(slide_ctx* ctx, const slide_batch* b, bool with_labels, hipSt
   int32_t* ncand = ctx->at<int32_t>(lo.ncand);
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_LOOKUP, s, [&] {
     return launch_lookup_union(ad, ctx->hd, h, sp, ctx->td, codes, b->y_indptr, b->y_indices, with_labels ? 1 : 0,
-                               ncand, ctx->ctrl(), ctx->lds_limit, s); }));
+                               ncand, ctx->ctrl(), ctx->lds_limit, ctx->num_cus, s); }));
   t2.ids = ad.as_ids; t2.rankT = ad.rankT; t2.as_base = ad.as_base;
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_FORWARD, s, [&] {
     return launch_forward(ad, lo.H, h, ctx->buf.W2, ctx->buf.b2, ctx->at<float>(lo.z),
@@ -426,6 +427,15 @@ static std::vector<uint16_t> hash_matrix(const slide_config* cfg, const Layout& 
   std::vector<uint16_t> m(simhash_matrix_words(lo.srp), 0);
   if (!m.empty()) simhash_matrix(lo.srp, cfg->hidden_dim, cfg->K, cfg->L, cfg->srp_nnz, hp->srp_idx, hp->srp_sign, m.data());
   return m;
+}
+
+// The SimHash words with word s of all functions beside each other: a lane per function reads them coalesced.
+static std::vector<uint32_t> hash_transposed(const slide_config* cfg, const std::vector<uint32_t>& words) {
+  const size_t nh = (size_t)cfg->K * cfg->L, half = words.size() / nh;
+  std::vector<uint32_t> t(words.size());
+  for (size_t e = 0; e < nh; ++e)
+    for (size_t s = 0; s < half; ++s) t[s * nh + e] = words[e * half + s];
+  return t;
 }
 
 // Hash-function parameters -> packed 16-bit coordinate words (validated).
@@ -508,6 +518,11 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
     what = "hipMemcpy(hash offsets)";
     e = hipMemcpy(ctx->ws() + lo.hashoff, offs.data(), offs.size() * 4, hipMemcpyHostToDevice);
   }
+  if (e == hipSuccess && cfg->hash_kind == SLIDE_HASH_SIMHASH) {
+    const std::vector<uint32_t> t = hash_transposed(cfg, words);
+    what = "hipMemcpy(hash parameters, transposed)";
+    e = hipMemcpy(ctx->ws() + lo.hashwT, t.data(), t.size() * 4, hipMemcpyHostToDevice);
+  }
   if (e == hipSuccess && lo.srp.nkb) {
     const std::vector<uint16_t> mat = hash_matrix(cfg, lo, hp);
     what = "hipMemcpy(hash matrix)";
@@ -564,6 +579,7 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
   hd.m = cfg->dwta_bin; hd.lgm = cfg->hash_kind == SLIDE_HASH_DWTA ? ilog2_exact(cfg->dwta_bin) : 0;
   hd.S = cfg->srp_nnz; hd.Spad = (cfg->srp_nnz + 1) / 2 * 2; hd.So = simhash_offset_stride(cfg->srp_nnz);
   hd.words = ctx->at<uint32_t>(lo.hashw);
+  hd.wordsT = ctx->at<uint32_t>(lo.hashwT);
   hd.offs = ctx->at<uint32_t>(lo.hashoff);
   hd.smat = lo.srp.nkb ? ctx->at<uint16_t>(lo.hashmat) : nullptr;
   hd.num_cus = ctx->num_cus;
@@ -602,6 +618,10 @@ int slide_set_hash_params(slide_ctx* ctx, const slide_hash_params* hp, void* hip
     const std::vector<uint32_t> offs = hash_offsets(&ctx->cfg, words);
     HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashw, words.data(), words.size() * 4, hipMemcpyHostToDevice));
     HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashoff, offs.data(), offs.size() * 4, hipMemcpyHostToDevice));
+    if (ctx->cfg.hash_kind == SLIDE_HASH_SIMHASH) {
+      const std::vector<uint32_t> t = hash_transposed(&ctx->cfg, words);
+      HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashwT, t.data(), t.size() * 4, hipMemcpyHostToDevice));
+    }
     const std::vector<uint16_t> mat = hash_matrix(&ctx->cfg, ctx->lo, hp);
     if (!mat.empty()) HIPCHK(ctx, hipMemcpy(ctx->ws() + ctx->lo.hashmat, mat.data(), mat.size() * 2, hipMemcpyHostToDevice));
   }

@@ -56,7 +56,7 @@ __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const 
   // k % nxcd is how this device family hands out workgroups; slide_init sets nxcd = 1, which turns the
   // split off, when it does not recognise the device.)
   const int B = ad.B;
-  const int maxnch = (int)ctrl->max_nch[ad.par];
+  const int maxnch = max_items(ctrl, ad.par);
   const int nx = ad.nxcd;
   const bool affine = nx > 1 && maxnch >= 8 * nx && nblocks % nx == 0;   // (otherwise the dies would get unequal shares)
   const int xcd = block % nx;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kForwardThreads) void forward_kernel(ActiveDev ad, 
   if (k < nworkers) {
     // With several items per wave the workers would hold every slot of the machine until the end and
     // the tiles would run after them: then the last workers leave at once and make room.
-    const int items = (int)ctrl->max_nch[ad.par] * ad.B;   // (upper bound: samples differ in length)
+    const int items = max_items(ctrl, ad.par) * ad.B;   // (upper bound: samples differ in length)
     // (more of them when the tiles are many for the amount of logit work)
     const int ntiles = t1.ntiles + t2.ntiles;
     const int workers = (ntiles == 0 || items <= 2 * nworkers * (kForwardThreads / 64)) ? nworkers

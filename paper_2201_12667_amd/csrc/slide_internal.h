@@ -14,6 +14,7 @@ constexpr int kLongRow = 32;       // rows touched by more samples than this are
 constexpr int kPairRegions = 32;   // the input layer's pair space is handed out from this many counters (tile % regions)
 
 constexpr uint32_t kOverWords = 64;
+constexpr uint32_t kMaxWords = 8;
 
 // Device-side counters, one block at the start of the workspace.
 struct Ctrl {
@@ -35,9 +36,15 @@ struct Ctrl {
   // running totals since the last slide_reset_stats (updated once per training step)
   unsigned long long sum_pairs, sum_u2, sum_u1, sum_candidates, sum_steps;
   uint32_t pad2[16];
-  uint32_t max_nch[2];    // most work items of any sample, same parity scheme (a cache line of its own)
-  uint32_t pad3[14];
+  // most work items of any sample, same parity scheme: the maximum of these words (a cache line each)
+  uint32_t max_nch[2][kMaxWords][16];
 };
+__device__ __forceinline__ int max_items(const Ctrl* c, int par) {
+  uint32_t m = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kMaxWords; ++w) m = max(m, c->max_nch[par][w][0]);
+  return (int)m;
+}
 
 // Counters of the table build, at the end of the workspace.
 struct BuildCtrl {
@@ -64,6 +71,7 @@ struct HashDev {
   int S, Spad, So;        // SimHash coordinates per bit, padded to even; entries per bit in offs
   const uint32_t* words;  // DWTA: NH*m/2 words of two u16 coordinates; SimHash: NH*Spad/2 words of
                           // two u16 (bit 15 = subtract)
+  const uint32_t* wordsT; // SimHash: the same, word s of every function beside each other ([Spad/2][NH])
   const uint32_t* offs;   // the same coordinates as byte offsets into the row-tile kernel's LDS tile, one
                           // entry each (SimHash: bit 31 = subtract; padding entries point at a zero cell)
   const uint16_t* smat;   // SimHash, H <= 256: the hash functions as a matrix of bf16 0 and -+1 (simhash_matrix)
@@ -186,8 +194,7 @@ bool lookup_bitmap_fits(int NWpad, int NT, int L, int H, int NH, size_t lds_limi
 hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const float* h, const SpmmArgs& sp,
                                const TablesDev& td, uint32_t* codes, const int32_t* y_indptr,
                                const int32_t* y_indices, int include_labels, int32_t* ncand, Ctrl* ctrl,
-                               size_t lds_limit, hipStream_t s);
-
+                               size_t lds_limit, int num_cus, hipStream_t s);
 
 // ---- output.hip -----------------------------------------------------------------------
 hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s);

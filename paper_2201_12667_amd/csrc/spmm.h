@@ -15,7 +15,7 @@ namespace slide {
 // feature index outside [0, D) contributes 0 * 0, which leaves every sum as it is).  The feature
 // segments per tile and the data flags are derived from the staged indices exactly as spmm_sample
 // derives them.  Needs H <= blockDim.x.  Every thread of the workgroup must call; ends with the
-// result in hvec (LDS) and in a.h, after a barrier.
+// result in hvec (LDS) and (keep) in a.h, after a barrier.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ int spmm_stage_rows(int stage_words, int H, int nthr) {
   const int cap = (stage_words - 2) / (H + 2);           // a row, its feature index and its value; two carries
@@ -23,10 +23,12 @@ __device__ __forceinline__ int spmm_stage_rows(int stage_words, int H, int nthr)
 }
 
 __device__ __forceinline__ void spmm_sample_staged(const SpmmArgs& a, int i, int B, float* stage, int stage_words,
-                                                   float* hvec, Ctrl* ctrl) {
+                                                   float* hvec, Ctrl* ctrl, bool keep = true) {
   const int64_t D = a.D;
   const int H = a.H, H4 = H >> 2, rows_per_tile = a.rows_per_tile;
   const int tid = threadIdx.x, nthr = blockDim.x;
+  const int step = nthr / H4, row = tid / H4, piece = tid - row * H4;   // rows at a time; the thread's row among them and its piece of it
+  const int tile_shift = __ffs(rows_per_tile) - 1;       // (a power of two)
   const float* __restrict__ W1 = a.W1;
   int2* __restrict__ xse = a.xse;
   const int cap = spmm_stage_rows(stage_words, H, nthr);
@@ -50,19 +52,18 @@ __device__ __forceinline__ void spmm_sample_staged(const SpmmArgs& a, int i, int
       sv[tid] = bad ? 0.f : v;
     }
     __syncthreads();
-    const int total = cnt * H4;
-    for (int idx0 = 0; idx0 < total; idx0 += 4 * nthr) {  // four row pieces per thread in flight
+    for (int q0 = 0; q0 < cnt; q0 += 4 * step) {          // four row pieces per thread in flight
       float4 w[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int idx = idx0 + u * nthr + tid;
-        const int k = idx < total ? sk[idx / H4] : -1;
-        w[u] = k >= 0 ? *(const float4*)(W1 + (size_t)k * H + 4 * (idx % H4)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int q = q0 + u * step + row;
+        const int k = row < step && q < cnt ? sk[q] : -1;
+        w[u] = k >= 0 ? *(const float4*)(W1 + (size_t)k * H + 4 * piece) : make_float4(0.f, 0.f, 0.f, 0.f);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int idx = idx0 + u * nthr + tid;
-        if (idx < total) ((float4*)stage)[idx] = w[u];
+        const int q = q0 + u * step + row;
+        if (row < step && q < cnt) ((float4*)stage)[q * H4 + piece] = w[u];
       }
     }
     if (kk >= 0) {
@@ -75,7 +76,7 @@ __device__ __forceinline__ void spmm_sample_staged(const SpmmArgs& a, int i, int
       // and ends the predecessor's
       if (xse) {
         const int before = tid > 0 ? sk[tid - 1] : carry[0];
-        const int tile = kk / rows_per_tile, tb = before >= 0 ? before / rows_per_tile : -1;
+        const int tile = kk >> tile_shift, tb = before >= 0 ? before >> tile_shift : -1;
         if (tb != tile) {
           xse[(size_t)tile * B + i].x = pb + tid;
           if (tb >= 0) xse[(size_t)tb * B + i].y = pb + tid;
@@ -98,7 +99,7 @@ __device__ __forceinline__ void spmm_sample_staged(const SpmmArgs& a, int i, int
   }
   if (tid < H) {
     const float r = acc > 0.f ? acc : 0.f;
-    a.h[(size_t)i * H + tid] = r;
+    if (keep) a.h[(size_t)i * H + tid] = r;
     hvec[tid] = r;
   }
   if (flags) atomicOr(&ctrl->status, flags);
