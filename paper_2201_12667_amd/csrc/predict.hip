@@ -5,15 +5,16 @@
 // contraction, run on the matrix cores.
 //
 // Launches: (1) the samples' hidden activations, split for the matrix cores; (2) the scores of an evenly
-// spaced sample of about 8,192 neurons; (3) per sample the topk-th best of these, which is a bar that at
-// least topk neurons of the layer reach; (4) the scores of all neurons, of which only those that reach
-// their sample's bar are kept (about topk * N / 8,192 of them: the scores themselves are never written);
-// (5) per sample the topk best of these.  Layers of fewer than 16,384 neurons end after (3) with every
-// neuron sampled.  The bar comes from the whole id range, so an order of the ids (by frequency, say) does not
+// spaced sample of about 8,192 neurons, of which the best of every 32 are kept; (3) per sample the topk-th best of
+// these, which is a bar that at least topk neurons of the layer reach; (4) the scores of all neurons, of which only
+// those that reach their sample's bar are kept (about topk * N / 8,192 of them: the scores themselves are never
+// written); (5) per sample the topk best of these.  For layers of fewer than 16,384 neurons all scores are written
+// and the topk best of them chosen.  The bar comes from the whole id range, so an order of the ids (by frequency, say) does not
 // matter.
 #include "slide_internal.h"
 #include "spmm.h"
 #include "topk.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 #include <cmath>
@@ -29,6 +30,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kScoreThreads = 512;         // eight waves, 32 neurons each
 constexpr int kTileNeurons = kScoreThreads / 2;
 constexpr int kSampled = 8192;             // neurons the bars are taken from (up to twice as many)
+constexpr int kStreamNeurons = 131072;     // layers from which on up to 32 samples take the form kStream
+constexpr int kMaxGroups = 2 * kSampled / 32;   // groups of 32 of them
 constexpr int kCandMax = 16384;            // candidate keys per sample and launch
 constexpr int kCntPitch = 16;              // words between the candidate counters of two samples (one line each)
 constexpr int kFrag = 512;                 // values of an operand fragment: 32 rows x 16 coordinates
@@ -121,21 +124,35 @@ __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0;
 // whole sum / this: 1.2e-7, 1.3e-7 and 5.5e-8 with 128 coordinates, 1.7e-7, 1.8e-7 and 6.8e-8 with 256, 3.2e-7, 3.6e-7 and
 // 1.2e-7 with 1,024; it costs 5 % of the call with 256 samples (this kernel 298 -> 313 us), 1 % and less below 128.
 // Six bf16 passes at 1/16 of the cost each against one pass at the 32-bit matrix rate: those 44 GFLOP took 564 us
-// there, 110 of them for writing the scores, and 304 here in stages of 256 samples (matrix cores busy 41 % of the time), 266 in resident blocks of 128; 8 samples, bound by reading W2: 118 and 76 us (4.5 TB/s).
+// there, 110 of them for writing the scores, and 304 here in stages of 256 samples (matrix cores busy 41 % of the time), 260 in resident blocks of 128.
 // Product rows are samples, columns neurons.  A wave owns 32 neurons and all NIB * 32 samples of the
 // workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
 // workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in
 // fragment order -- RES: it all fits (res_frags), is staged once, and the waves never meet again; otherwise the next stage is fetched under the products of this one.
-// STORE: every score goes to zs (the sampled neurons); otherwise the scores that reach their sample's bar go
-// to its candidate buffer.
-template <int NIB, bool STORE, bool RES>
-__global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && STORE ? 3 : 4) void dense_scores_kernel(
-    int B, int64_t N, int H, int nkbp, const float4* frags, const float* __restrict__ W2, const float* __restrict__ b2, int64_t j0, int nc, int stride, float* __restrict__ zs,
-    const uint64_t* __restrict__ bars, uint64_t* __restrict__ cand, uint32_t* ccnt, int cand_cap) {
+// kStore: every score goes to zs; kGroupBest: the best of every 32 neurons does, as score_bits (the sampled neurons);
+// kCandidates: the scores that reach their sample's bar go to its candidate buffer.
+enum { kCandidates, kStore, kGroupBest };
+// Forms.  kStages: h is staged in LDS in turns; kResident: it all fits (res_frags), is staged once, and the waves never meet
+// again; kStream: the same for up to 32 samples, which are bound by reading W2: the wave reads its rows 128 bytes at a time
+// (eight lanes to a row), streaming, and turns them over through its corner of the LDS.  8 samples x 670K neurons: 64.7 us
+// (5.3 TB/s) against 75 (4.6) for lanes that read their own rows 32 bytes at a time -- a plain read of W2 in either pattern takes 52 and 61 us,
+// and streaming loads of half lines 101, so the rows have to be whole lines (launch_dense_topk).  A wave has a stretch of
+// neighbouring neurons, as long as any other's, instead of tiles dealt out in turn (5.1 rounds of them took as long as 6).
+enum { kStages, kResident, kStream };
+__host__ __device__ constexpr int score_threads(int MODE, int FORM) { return FORM != kStream ? kScoreThreads : MODE == kCandidates ? 1024 : 256; }
+__host__ __device__ constexpr int score_waves_per_simd(int NIB, int MODE, int FORM) {
+  return FORM == kStream ? (MODE == kCandidates ? 4 : 2) : FORM == kStages || NIB == 4 ? 2 : NIB == 2 && MODE != kCandidates ? 3 : 4;
+}
+template <int NIB, int MODE, int FORM>
+__global__ __launch_bounds__(score_threads(MODE, FORM), score_waves_per_simd(NIB, MODE, FORM)) void dense_scores_kernel(
+    int B, int64_t N, int H, int nkbp, const float* __restrict__ h, const float4* frags, const float* __restrict__ W2, const float* __restrict__ b2, int64_t j0, int nc, int stride, float* __restrict__ zs,
+    int per_wave, const uint64_t* __restrict__ bars, uint64_t* __restrict__ cand, uint32_t* ccnt, int cand_cap) {
+  constexpr bool RES = FORM != kStages, STREAM = FORM == kStream;
+  constexpr int THREADS = score_threads(MODE, FORM);
   constexpr int MB = NIB * 32;                           // samples per workgroup
   constexpr int KS = stage_blocks(NIB);                  // coordinate blocks per stage
   constexpr int PIECES = NIB * KS * 192;                 // 16-byte pieces of a stage
-  constexpr int PPT = (RES ? res_frags(NIB) * 192 : PIECES) / kScoreThreads;   // ... per thread
+  constexpr int PPT = (RES ? res_frags(NIB) * 192 : PIECES) / THREADS;   // ... per thread
   extern __shared__ f32x4 hs[];                          // [row block][coordinate block][part][lane], twice unless RES; the waves' corners
   __shared__ uint64_t bar_s[MB];
   __shared__ float thr[MB];                              // score of the bar
@@ -144,7 +161,10 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
   const int col = lane & 31, half = lane >> 5;
   const int i0 = blockIdx.y * MB, rows = min(B - i0, MB);
   const int ntiles = (nc + kTileNeurons - 1) / kTileNeurons;
-  if ((int)blockIdx.x >= ntiles) return;
+  if (!STREAM && (int)blockIdx.x >= ntiles) return;
+  // kStream: the wave's neurons are columns c_lo .. c_hi - 1, in tiles of 32
+  const int c_lo = STREAM ? min((int)(blockIdx.x * (THREADS / 64) + wave) * per_wave, nc) : 0, c_hi = STREAM ? min(c_lo + per_wave, nc) : nc;
+  auto column = [&](int tile) { return STREAM ? c_lo + tile * 32 + col : tile * kTileNeurons + wave * 32 + col; };
   // coordinate blocks to go through (at least four where they are staged: the loads run two blocks ahead, and no
   // further than the next tile)
   const int nkb = RES ? (H + 15) / 16 : max(4, (H + 16 * KS - 1) / (16 * KS) * KS);
@@ -152,7 +172,7 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
 
   // The stage that starts at block kb0 (RES: everything), a fragment part (1 KB) per wave and step: part q % per
   // of row block q / per.
-  constexpr int WAVES = kScoreThreads / 64;
+  constexpr int WAVES = THREADS / 64;
   const int per = RES ? nkb * 3 : KS * 3;
   auto fetch = [&](int kb0, int u) -> f32x4 {
     const int q = min(u * WAVES + wave, NIB * per - 1), ib = q / per, r = q - ib * per;
@@ -163,7 +183,7 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
     if (!RES || q < NIB * per) hs[(RES ? 0 : buf * PIECES) + q * 64 + lane] = x;
   };
   auto neuron_of = [&](int tile) -> int64_t {
-    const int64_t j = j0 + (int64_t)(tile * kTileNeurons + wave * 32 + col) * stride;
+    const int64_t j = j0 + (int64_t)column(tile) * stride;
     return j < N ? j : N - 1;                            // (columns past the end are not looked at)
   };
   // The W2 values to come: block lk of tile lt.  (Loads are unconditional, so that the waits for them can be
@@ -189,17 +209,40 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
       wrow = wrap ? wnext : wrow;
     }
   };
-  issue(wb0);
-  issue(wb1);
-  if (!STORE)
-    for (int q = tid; q < MB; q += kScoreThreads) {
+  // kStream: a stage is two coordinate blocks of the wave's 32 rows, 8 lanes of 16 bytes to a row; DEPTH of them ahead.
+  constexpr int DEPTH = !STREAM ? 1 : MODE == kGroupBest ? 4 : 2;
+  const int nst = (nkb + 1) / 2;
+  f32x4 sb[DEPTH][4];
+  int st = 0, ss = 0;                                    // tile and stage to come
+  const int piece = lane & 7, row8 = lane >> 3;
+  auto issue_stage = [&](f32x4 (&x)[4]) {
+    const int k = min(ss * 32 + 4 * piece, kmax);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const int64_t j = j0 + (int64_t)max(min(c_lo + st * 32 + d * 8 + row8, c_hi - 1), 0) * stride;
+      const f32x4* at = (const f32x4*)(W2 + (size_t)j * H + k);
+      x[d] = MODE == kCandidates ? __builtin_nontemporal_load(at) : *at;
+    }
+    const bool wrap = ss + 1 == nst;
+    ss = wrap ? 0 : ss + 1;
+    st += wrap ? 1 : 0;                                  // (past the last tile: its last row again)
+  };
+  if constexpr (STREAM) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) issue_stage(sb[d]);
+  } else {
+    issue(wb0);
+    issue(wb1);
+  }
+  if (MODE == kCandidates)
+    for (int q = tid; q < MB; q += THREADS) {
       const uint64_t bar = q < rows ? bars[i0 + q] : 0ull;
       bar_s[q] = bar;
       thr[q] = q >= rows ? INFINITY : bar == ~0ull ? -INFINITY : topk_score(bar);
     }
   for (int u = 0; u < PPT; ++u) put(0, u, fetch(0, u));
   __syncthreads();
-  if constexpr (!STORE) {
+  if constexpr (MODE == kCandidates) {
     if (tid < MB / 4) {
       const float* t = thr + (tid >> 3) * 32 + 8 * (tid & 3) + 4 * ((tid >> 2) & 1);
       thr4[tid] = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
@@ -211,8 +254,9 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
   // the wave's corner: half a 32x32 block of scores, and the scores that passed the first test (score, column,
   // sample), handed to the samples' buffers together when the list fills and at the end: the exact test (ties by
   // id) and a lane's counter update and store each
-  float* bounce = (float*)(hs + (RES ? NIB * nkb * 192 : 2 * PIECES)) + wave * kCornerWords;
-  float* list_z = bounce + 512;
+  constexpr int BOUNCE = STREAM ? 1024 : 512;            // (kStream: the wave's rows pass through it, too)
+  float* bounce = (float*)(hs + (RES ? NIB * nkb * 192 : 2 * PIECES)) + wave * (BOUNCE + (MODE == kCandidates ? 3 * kListed : 0));
+  float* list_z = bounce + BOUNCE;
   int* list_c = (int*)list_z + kListed;
   int* list_i = list_c + kListed;
   int listed = 0;
@@ -238,7 +282,7 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
   auto contract = [&](float4 (&wr)[2], const bf16x8* hb, int ib_pitch) {
     bf16x8 w[3];
     split8(wr[0], wr[1], w);
-    issue(wr);
+    if (!STREAM) issue(wr);
     if (!RES) asm volatile("" ::: "memory");             // (not later: see below)
     constexpr int G = NIB < 2 || (RES && NIB < 4) ? 1 : 2;            // row blocks interleaved (independent sums)
 #pragma unroll
@@ -273,9 +317,9 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
   };
   auto finish = [&](int tile, float bias) {
     // lane holds column `col`, rows 8*(r/4) + 4*half + r%4 of each 32x32 block
-    const int c = tile * kTileNeurons + wave * 32 + col;
-    const bool live = c < nc;
-    if constexpr (STORE) {
+    const int c = column(tile);
+    const bool live = c < c_hi;
+    if constexpr (MODE == kStore) {
 #pragma unroll
       for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
@@ -283,6 +327,47 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
           const int il = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
           if (live && il < rows) zs[(size_t)(i0 + il) * nc + c] = acc[ib][r] + bias;
         }
+    } else if constexpr (MODE == kGroupBest) {
+      // the best of the wave's 32 neurons for every sample (as bits that ascend like scores; 0: none)
+      const int ngroups = (nc + 31) / 32, group = STREAM ? c_lo / 32 + tile : tile * (kTileNeurons / 32) + wave;
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) {
+        float z[16];
+        bool open = false;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          z[r] = acc[ib][r] + bias;
+          open |= !settled(z[r]);
+        }
+        if (__any(open)) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int il = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+            if (live && il < rows && !settled(z[r]))
+              z[r] = plain_score(h + (size_t)(i0 + il) * H, W2 + (size_t)neuron_of(tile) * H, bias, H);
+          }
+        }
+        uint32_t v[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = live ? score_bits(z[r]) : 0u;
+        // 32 lanes and 16 rows: every step halves the rows that a lane goes on with and takes the best of two lanes
+        auto halve = [&](int n, bool upper, auto&& other) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            if (q >= n) break;
+            const uint32_t keep = upper ? v[n + q] : v[q], give = upper ? v[q] : v[n + q];
+            v[q] = max(keep, other(give));
+          }
+        };
+        halve(8, lane & 1, [](uint32_t x) { return dpp_u32<kDppQuadSwap1>(x, x); });
+        halve(4, lane & 2, [](uint32_t x) { return dpp_u32<kDppQuadSwap2>(x, x); });
+        halve(2, lane & 8, [](uint32_t x) { return dpp_u32<kDppRowRor + 8>(x, x); });
+        halve(1, lane & 4, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 4 << 10 | 0x1f); });
+        const uint32_t best = max(v[0], (uint32_t)__builtin_amdgcn_ds_swizzle((int)v[0], 16 << 10 | 0x1f));
+        const int r = (lane & 1 ? 8 : 0) + (lane & 2 ? 4 : 0) + (lane & 8 ? 2 : 0) + (lane & 4 ? 1 : 0);
+        const int il = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        if (col < 16 && il < rows && group < ngroups) ((uint32_t*)zs)[(size_t)(i0 + il) * ngroups + group] = best;
+      }
     } else {
       // First test, whole blocks: the largest of four consecutive samples' scores (NaN counts as largest) against
       // the lowest of their bars.  The blocks in which something passes (about half of them) go through the wave's
@@ -340,7 +425,49 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
     }
   };
   const bf16x8* hb = (const bf16x8*)hs + lane;
-  if constexpr (RES) {
+  if constexpr (STREAM) {
+    const int units = (c_hi - c_lo + 31) / 32 * nst;
+    int tile = 0, kb = 0;
+    float bias = 0.f, bias_next = b2[neuron_of(0)];
+    // pieces of a row are permuted among each other by the row's number, so that neither eight lanes with a row
+    // nor eight lanes with a row each meet in a bank
+    f32x4* put_at = (f32x4*)bounce + row8 * 8 + (piece ^ row8);
+    const f32x4* get_at = (const f32x4*)bounce + col * 8;
+    auto unit = [&](f32x4 (&x)[4]) {
+      if (kb == 0) {
+        clear();
+        bias = bias_next;
+        bias_next = b2[neuron_of(tile + 1)];
+      }
+#pragma unroll
+      for (int d = 0; d < 4; ++d) put_at[d * 64] = x[d];
+      issue_stage(x);
+      asm volatile("" ::: "memory");                     // (a wave's accesses to its corner are in order)
+      __builtin_amdgcn_wave_barrier();
+      f32x4 y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = get_at[((q >> 1) * 4 + half * 2 + (q & 1)) ^ (col & 7)];
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        if (b == 0 || kb + 1 < nkb) {
+          float4 w[2] = {make_float4(y[2 * b][0], y[2 * b][1], y[2 * b][2], y[2 * b][3]),
+                         make_float4(y[2 * b + 1][0], y[2 * b + 1][1], y[2 * b + 1][2], y[2 * b + 1][3])};
+          contract(w, hb + (kb + b) * 192, nkb * 192);
+        }
+      kb += 2;
+      if (kb < nkb) return;
+      finish(tile, bias);
+      kb = 0;
+      ++tile;
+    };
+    for (int u = 0; u < units; u += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d)
+        if (u + d < units) unit(sb[d]);
+    }
+  } else if constexpr (RES) {
     const int units = ((ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x) * nkb;
     int tile = blockIdx.x, kb = 0;
     float bias, bias_next = b2[neuron_of(tile)];
@@ -393,18 +520,16 @@ __global__ __launch_bounds__(kScoreThreads, !RES || NIB == 4 ? 2 : NIB == 2 && S
       finish(tile, bias);
     }
   }
-  if constexpr (!STORE) flush();
+  if constexpr (MODE == kCandidates) flush();
 }
 
-// (3) Per sample: the topk-th best of the sampled scores (neuron of column c: c * stride) as the bar, or, when
-// every neuron was sampled (out_ids given), the result.
-__global__ __launch_bounds__(kSelectThreads) void dense_bar_kernel(int H, const float* __restrict__ h,
-                                                                   const float* __restrict__ W2,
-                                                                   const float* __restrict__ b2, int nc, int stride,
-                                                                   const float* __restrict__ zs, int topk, uint64_t* __restrict__ bars,
-                                                                   uint32_t* __restrict__ ccnt,
-                                                                   int32_t* __restrict__ out_ids,
-                                                                   float* __restrict__ out_scores) {
+// (3) Per sample, when every neuron was sampled: the topk best of the scores.
+__global__ __launch_bounds__(kSelectThreads) void dense_select_kernel(int H, const float* __restrict__ h,
+                                                                      const float* __restrict__ W2,
+                                                                      const float* __restrict__ b2, int nc,
+                                                                      const float* __restrict__ zs, int topk,
+                                                                      int32_t* __restrict__ out_ids,
+                                                                      float* __restrict__ out_scores) {
   __shared__ SelectLds lds;
   const int i = blockIdx.x, tid = threadIdx.x;
   const float* row = zs + (size_t)i * nc;
@@ -418,27 +543,47 @@ __global__ __launch_bounds__(kSelectThreads) void dense_bar_kernel(int H, const 
       for (int u = 0; u < UN; ++u) {
         const int c = c0 + u * kSelectThreads;
         if (c >= nc) continue;
-        const uint32_t j = (uint32_t)c * (uint32_t)stride;
-        if (!settled(z[u])) z[u] = plain_score(h + (size_t)i * H, W2 + (size_t)j * H, b2[j], H);
-        f(topk_key(z[u], j));
+        if (!settled(z[u])) z[u] = plain_score(h + (size_t)i * H, W2 + (size_t)c * H, b2[c], H);
+        f(topk_key(z[u], (uint32_t)c));
       }
     }
   }, [&](int place, uint64_t key) {
-    if (out_ids) {
-      out_ids[(size_t)i * topk + place] = (int32_t)(uint32_t)key;
-      out_scores[(size_t)i * topk + place] = topk_score(key);
-    } else if (place == topk - 1) {
-      bars[i] = key;
-    }
+    out_ids[(size_t)i * topk + place] = (int32_t)(uint32_t)key;
+    out_scores[(size_t)i * topk + place] = topk_score(key);
   });
-  if (out_ids) {
-    for (int k = found + tid; k < topk; k += kSelectThreads) {
-      out_ids[(size_t)i * topk + k] = -1;
-      out_scores[(size_t)i * topk + k] = -INFINITY;
-    }
-  } else if (tid == 0) {
+  for (int k = found + tid; k < topk; k += kSelectThreads) {
+    out_ids[(size_t)i * topk + k] = -1;
+    out_scores[(size_t)i * topk + k] = -INFINITY;
+  }
+}
+
+// (3) Per sample: the topk-th best of the groups' bests as the bar, which at least topk neurons reach (one of each of
+// as many groups; the topk-th best of all sampled neurons is hardly higher: groups hold 32 of them, 256 groups and more).
+// A wave per sample; the value is found bit by bit, by counting the groups that reach what is tried.  (The topk-th
+// best of the scores themselves, which this replaced, took two sweeps over 8,192 of them, 14 us.)
+__global__ __launch_bounds__(64) void dense_bar_kernel(int ngroups, const uint32_t* __restrict__ best, int topk,
+                                                       uint64_t* __restrict__ bars, uint32_t* __restrict__ ccnt) {
+  const int i = blockIdx.x, lane = threadIdx.x;
+  uint32_t v[kMaxGroups / 64];
+#pragma unroll
+  for (int u = 0; u < kMaxGroups / 64; ++u) v[u] = u * 64 + lane < ngroups ? best[(size_t)i * ngroups + u * 64 + lane] : 0u;
+  uint32_t bar = 0;                                      // the largest value that topk groups reach
+  if (topk == 1) {                                       // the best of all
+#pragma unroll
+    for (int u = 0; u < kMaxGroups / 64; ++u) bar = max(bar, v[u]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) bar = max(bar, (uint32_t)__shfl_xor((int)bar, d));
+  } else
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t trial = bar | 1u << bit;
+    int reach = 0;
+#pragma unroll
+    for (int u = 0; u < kMaxGroups / 64; ++u) reach += __popcll(__ballot(v[u] >= trial));
+    if (reach >= topk) bar = trial;
+  }
+  if (lane == 0) {
+    bars[i] = (uint64_t)(~bar) << 32 | 0xffffffffu;      // (every id passes: which neuron of the group it is was not kept)
     ccnt[(size_t)i * kCntPitch] = 0;
-    if (found < topk) bars[i] = ~0ull;
   }
 }
 
@@ -572,10 +717,16 @@ static bool blocks_stay(int B, int nkb, int ntiles, int num_cus) {
 
 // LDS of a launch: of a resident block (nkb: its coordinate blocks), of the stages otherwise.
 static constexpr size_t resident_lds(int NIB, int nkb, bool store) { return (size_t)NIB * nkb * kTriple + (store ? 0 : kCorners); }
+// (More than 32 samples: the sampled neurons 14.7 us resident, 19.5 streamed for 256 samples; all of 400K x 64 for 64
+// samples 50.6 and 57.6, 670K x 128 about the same.)
+static constexpr bool streams(int NIB, int MODE) { return MODE != kStore && NIB == 1; }
+static constexpr size_t stream_lds(int NIB, int nkb, int MODE) {
+  return (size_t)NIB * nkb * kTriple + (size_t)score_threads(MODE, kStream) / 64 * (1024 + (MODE == kCandidates ? 3 * kListed : 0)) * 4;
+}
 static constexpr size_t staged_lds(int NIB, bool store) { return (size_t)2 * NIB * stage_blocks(NIB) * kTriple + (store ? 0 : kCorners); }
 
-template <int NIB, bool STORE>
-static hipError_t launch_scores(bool stay, int B, int64_t N, int H, const float4* frags, const float* W2, const float* b2,
+template <int NIB, int MODE>
+static hipError_t launch_scores(bool stay, int B, int64_t N, int H, const float* h, const float4* frags, const float* W2, const float* b2,
                                 int64_t j0, int nc, int stride, float* zs, const uint64_t* bars, uint64_t* cand,
                                 uint32_t* ccnt, int cand_cap, int num_cus, hipStream_t s) {
   const int nkb = ceil_div(H, 16), nkbp = padded_blocks(H), gy = ceil_div(B, NIB * 32), ntiles = ceil_div(nc, kTileNeurons);
@@ -585,23 +736,37 @@ static hipError_t launch_scores(bool stay, int B, int64_t N, int H, const float4
   const int per_cu = res && NIB < 4 ? 2 : 1;
   const int gx = std::max(1, std::min(ntiles, num_cus * per_cu / std::min(gy, num_cus)));
   const dim3 grid(gx, gy), block(kScoreThreads);
-  if constexpr (NIB <= 4) {
-    if (res) {
-      hipLaunchKernelGGL((dense_scores_kernel<NIB, STORE, true>), grid, block, resident_lds(NIB, nkb, STORE), s, B, N, H, nkbp, frags, W2, b2,
-                         j0, nc, stride, zs, bars, cand, ccnt, cand_cap);
+  if constexpr (streams(NIB, MODE)) {
+    // whole lines of W2, neurons enough that a wave's stretch is more than a tile or two
+    if (res && H % 32 == 0 && ((uintptr_t)W2 & 127) == 0 && (MODE == kGroupBest || nc >= kStreamNeurons)) {
+      constexpr int WAVES = score_threads(MODE, kStream) / 64;
+      const int groups = MODE == kGroupBest ? ceil_div(ceil_div(nc, 32), WAVES) : num_cus;
+      const int per_wave = MODE == kGroupBest ? 32 : ceil_div(nc, groups * WAVES);
+      hipLaunchKernelGGL((dense_scores_kernel<NIB, MODE, kStream>), dim3(groups, gy), dim3(WAVES * 64), stream_lds(NIB, nkb, MODE), s, B, N, H,
+                         nkbp, h, frags, W2, b2, j0, nc, stride, zs, per_wave, bars, cand, ccnt, cand_cap);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((dense_scores_kernel<NIB, STORE, false>), grid, block, staged_lds(NIB, STORE), s, B, N, H, nkbp, frags, W2,
-                     b2, j0, nc, stride, zs, bars, cand, ccnt, cand_cap);
+  if constexpr (NIB <= 4) {
+    if (res) {
+      hipLaunchKernelGGL((dense_scores_kernel<NIB, MODE, kResident>), grid, block, resident_lds(NIB, nkb, MODE != kCandidates), s, B, N, H, nkbp, h, frags, W2, b2,
+                         j0, nc, stride, zs, 0, bars, cand, ccnt, cand_cap);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((dense_scores_kernel<NIB, MODE, kStages>), grid, block, staged_lds(NIB, MODE != kCandidates), s, B, N, H, nkbp, h, frags, W2,
+                     b2, j0, nc, stride, zs, 0, bars, cand, ccnt, cand_cap);
   return hipGetLastError();
 }
 
-template <int NIB, bool STORE>
+template <int NIB, int MODE>
 static hipError_t scores_attr() {
-  hipError_t e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, STORE, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)staged_lds(NIB, STORE));
+  constexpr bool STORE = MODE != kCandidates;
+  hipError_t e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, MODE, kStages>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)staged_lds(NIB, STORE));
   if constexpr (NIB <= 4)
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, STORE, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resident_lds(NIB, res_frags(NIB) / NIB, STORE));
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, MODE, kResident>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)resident_lds(NIB, res_frags(NIB) / NIB, STORE));
+  if constexpr (streams(NIB, MODE))
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)dense_scores_kernel<NIB, MODE, kStream>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)stream_lds(NIB, res_frags(NIB) / NIB, MODE));
   return e;
 }
 
@@ -610,12 +775,14 @@ static int prepare_stage_words(int H) { return (H <= 448 ? 64 : 144) * 256; }
 
 hipError_t predict_setup_attributes() {
   hipError_t e = hipFuncSetAttribute((const void*)dense_prepare_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
-  if (e == hipSuccess) e = scores_attr<1, true>();
-  if (e == hipSuccess) e = scores_attr<2, true>();
-  if (e == hipSuccess) e = scores_attr<1, false>();
-  if (e == hipSuccess) e = scores_attr<2, false>();
-  if (e == hipSuccess) e = scores_attr<4, false>();
-  if (e == hipSuccess) e = scores_attr<8, false>();
+  if (e == hipSuccess) e = scores_attr<1, kStore>();
+  if (e == hipSuccess) e = scores_attr<2, kStore>();
+  if (e == hipSuccess) e = scores_attr<1, kGroupBest>();
+  if (e == hipSuccess) e = scores_attr<2, kGroupBest>();
+  if (e == hipSuccess) e = scores_attr<1, kCandidates>();
+  if (e == hipSuccess) e = scores_attr<2, kCandidates>();
+  if (e == hipSuccess) e = scores_attr<4, kCandidates>();
+  if (e == hipSuccess) e = scores_attr<8, kCandidates>();
   return e;
 }
 
@@ -637,20 +804,27 @@ hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const floa
   const int stride = dense_stride(N), ns = (int)dense_sampled(N), cap = dense_cand_cap(N);
   const bool all = stride == 1;
   // the sampled neurons are few: small row blocks, so that the samples spread over the machine
-  hipError_t e = B <= 32 ? launch_scores<1, true>(true, B, N, H, frags, W2, b2, 0, ns, stride, zs, nullptr, nullptr, nullptr, 0, num_cus, s)
-                         : launch_scores<2, true>(true, B, N, H, frags, W2, b2, 0, ns, stride, zs, nullptr, nullptr, nullptr, 0, num_cus, s);
+#define SLIDE_SAMPLED(NIB, MODE) launch_scores<NIB, MODE>(true, B, N, H, h, frags, W2, b2, 0, ns, stride, zs, nullptr, nullptr, nullptr, 0, num_cus, s)
+  if (all) {
+    const hipError_t e = B <= 32 ? SLIDE_SAMPLED(1, kStore) : SLIDE_SAMPLED(2, kStore);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(dense_select_kernel, dim3(B), dim3(kSelectThreads), 0, s, H, h, W2, b2, ns, zs, topk, out_ids, out_scores);
+    return hipGetLastError();
+  }
+  hipError_t e = B <= 32 ? SLIDE_SAMPLED(1, kGroupBest) : SLIDE_SAMPLED(2, kGroupBest);
+#undef SLIDE_SAMPLED
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(kSelectThreads), 0, s, H, h, W2, b2, ns, stride, zs, topk, bars, ccnt,
-                     all ? out_ids : nullptr, all ? out_scores : nullptr);
-  if (all) return hipGetLastError();
-  // About topk * nc / ns of nc neurons reach the bar, spread like a sum of topk exponentials: with that mean at
-  // cap * topk / (topk + 4 sqrt(topk) + 16) -- a 21st of the candidate buffer for topk = 1, 0.57 of it for 64 -- chance
-  // overflows it for 7 samples in 10^10 and 2.5 in 10^7.  A launch takes as many neurons as that allows (6.4 M and 1.2 M).
-  const int64_t fit = (int64_t)((double)ns * cap / (topk + 4.0 * std::sqrt((double)topk) + 16.0));
+  hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(64), 0, s, ceil_div(ns, 32), (const uint32_t*)zs, topk, bars, ccnt);
+  // The bar is about the r-th best of the sampled neurons: r = topk and a few more, those drawn until topk of the g groups
+  // have one (64 of 256: 74).  About r * nc / ns of nc neurons reach it, spread like a sum of r exponentials: with that
+  // mean at cap * r / (r + 4 sqrt(r) + 16) -- a 21st of the candidate buffer for topk = 1, 0.59 of it for 64 -- chance
+  // overflows it for less than one sample in a million.  A launch takes as many neurons as that allows (6.4 M and 1.1 M).
+  const double g = ceil_div(ns, 32), r = std::max<double>(topk, g * std::log(g / (g - topk)));
+  const int64_t fit = (int64_t)((double)ns * cap / (r + 4.0 * std::sqrt(r) + 16.0));
   const int64_t most = std::max<int64_t>(kTileNeurons, fit / kTileNeurons * kTileNeurons);
   for (int64_t j0 = 0; j0 < N; j0 += most) {
     const int nc = (int)std::min<int64_t>(std::min<int64_t>(most, (int64_t)1 << 30), N - j0);
-#define SLIDE_SCORES(NIB) launch_scores<NIB, false>(stay, B, N, H, frags, W2, b2, j0, nc, 1, nullptr, bars, cand, ccnt, cap, num_cus, s)
+#define SLIDE_SCORES(NIB) launch_scores<NIB, kCandidates>(stay, B, N, H, h, frags, W2, b2, j0, nc, 1, nullptr, bars, cand, ccnt, cap, num_cus, s)
     const bool stay = B <= 64 || blocks_stay(B, ceil_div(H, 16), ceil_div(nc, kTileNeurons), num_cus);
     switch (std::min(dense_row_blocks(B), stay ? 4 : 8)) {
       case 1: e = SLIDE_SCORES(1); break;

@@ -15,11 +15,11 @@ struct SelectLds {
 };
 
 // Sort key of (score, id): ascending keys = descending scores, ties to the lower id.  ~0 = no entry.
-__device__ __forceinline__ uint64_t topk_key(float score, uint32_t id) {
+__device__ __forceinline__ uint32_t score_bits(float score) {         // orders like the float
   const uint32_t u = __float_as_uint(score);
-  const uint32_t asc = (u & 0x80000000u) ? ~u : (u | 0x80000000u);   // orders like the float
-  return ((uint64_t)(~asc) << 32) | id;
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+__device__ __forceinline__ uint64_t topk_key(float score, uint32_t id) { return ((uint64_t)(~score_bits(score)) << 32) | id; }
 __device__ __forceinline__ float topk_score(uint64_t key) {
   const uint32_t asc = ~(uint32_t)(key >> 32);
   return __uint_as_float((asc & 0x80000000u) ? (asc & 0x7fffffffu) : ~asc);

@@ -153,6 +153,14 @@ def test_predict_all_row_blocks_of_few_tiles(N, batch, H):
     _row_blocks(N, batch, H)
 
 
+# up to 32 samples and whole lines of W2: a stretch of neurons for every wave (at the size from which that is taken and one
+# short of it, a last stretch that is short or missing, an odd number of coordinate blocks), and rows that are no whole lines
+@pytest.mark.parametrize("N,batch,H", [(131071, 5, 32), (131072, 32, 32), (131072, 1, 96), (139001, 31, 160), (155649, 7, 256),
+                                       (131072 + 4097, 32, 64), (140003, 9, 40)])
+def test_predict_all_row_blocks_of_streamed_layers(N, batch, H):
+    _row_blocks(N, batch, H)
+
+
 def _row_blocks(N, batch, H):
     _say("dense predict blocks", N, batch, H)
     topk = 7
