@@ -312,6 +312,12 @@ int check_batch(slide_ctx* ctx, const slide_batch* b, bool need_labels) {
   return SLIDE_OK;
 }
 
+// Neurons that the tables return for a sample, about (codes spread evenly, but a fuller bucket is the likelier one).
+int64_t pairs_per_sample(const slide_ctx* ctx) {
+  const double per_bucket = 1.25 * (double)ctx->lo.N / (double)ctx->lo.nb;
+  return (int64_t)(ctx->cfg.L * std::min<double>(ctx->cfg.bucket_cap, per_bucket));
+}
+
 // Whether this call's float kernels walk the incidences row-major (see slide_config::row_major_mode).
 // Automatic rule: the tables return about L * min(C, N / 2^bits) neurons per sample; when the batch's
 // total is several times the layer, a touched row belongs to several samples.
@@ -362,7 +368,7 @@ int forward_common(slide_ctx* ctx, const slide_batch* b, bool with_labels, hipSt
   t2.ids = ad.as_ids; t2.rankT = ad.rankT; t2.as_base = ad.as_base;
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_FORWARD, s, [&] {
     return launch_forward(ad, lo.H, h, ctx->buf.W2, ctx->buf.b2, ctx->at<float>(lo.z),
-                          ctx->at<float>(lo.partials), ctx->ctrl(), t1, t2, true, ctx->num_cus, s); }));
+                          ctx->at<float>(lo.partials), ctx->ctrl(), t1, t2, true, pairs_per_sample(ctx), ctx->num_cus, s); }));
   *ad_out = ad;
   return SLIDE_OK;
 }

@@ -40,7 +40,13 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // ---------------------------------------------------------------------------------------------
 constexpr int kForwardThreads = 512;
 
-template <int LPR, int CH, bool FULL>
+// CH: float4 per lane, the first F of which lie within the vector for every lane.
+// With saturated buckets (1,024 samples, 6.5 M pairs of 200 coordinates) this is bound by the latency of the rows: nearly
+// every step of four rows waits for one of its 25 lines to come from beyond the die's L2 (a sixth of them do).  The
+// arithmetic alone takes 220 us of 382, and no longer adds to the rest: no test for the end of the item and no store in a
+// whole step, no test for the vector's end where a float4 lies within it for all lanes.  Two steps' rows under way are
+// slower (494 us with as many waves, 394 with fewer), and so are items of half the size (436 for 416).
+template <int LPR, int CH, int F>
 __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const float* __restrict__ h, const float* __restrict__ W2,
                               const float* __restrict__ b2, float* __restrict__ z, float* __restrict__ partials,
                               const Ctrl* __restrict__ ctrl, int block, int nblocks) {
@@ -72,55 +78,61 @@ __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const 
     const int item = ad.chunk_ptr[i] + ch;             // slot of the partial result
     const int first = ad.as_base[i] + done;
     const int n = min(kChunk, cnt - done);
-    float4 hv[CH], acc[CH];
+    float4 hv[CH], acc[CH], row[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int col = (c * LPR + sub) * 4;
-      hv[c] = (FULL || col < H) ? *(const float4*)(h + (size_t)i * H + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+      hv[c] = (c < F || col < H) ? *(const float4*)(h + (size_t)i * H + col) : make_float4(0.f, 0.f, 0.f, 0.f);
       acc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      row[c] = make_float4(0.f, 0.f, 0.f, 0.f);          // (stays where a lane has no columns)
     }
     // the item's ids and their biases in one coalesced read each (lane l: neuron l of the item), handed to
     // the row groups step by step: a step then waits for its rows only, not for an id first
     const int my_j = ad.as_ids[first + (lane < n ? lane : 0)];
     const float my_b = b2[my_j];
-    float M = -INFINITY, s = 0.f;
-    for (int q0 = 0; q0 < n; q0 += RPW) {
-      const int q = q0 + grp;
-      const bool valid = q < n;
-      const int slot = first + (valid ? q : 0);
-      const int j = __shfl(my_j, valid ? q : 0);
-      const float bj = __shfl(my_b, valid ? q : 0);
-      const float* wr = W2 + (size_t)j * H;
-      float4 row[CH];
+    float M = -INFINITY, s = 0.f, my_z = 0.f;
+    int from = 4 * grp;                                  // (byte address of the lane that holds the group's next neuron)
+    auto step = [&](int k, int j, float bj) __attribute__((always_inline)) {
+      const float* wr = W2 + (uint64_t)(uint32_t)j * (uint32_t)H + 4 * sub;
+#pragma unroll
+      for (int c = 0; c < CH; ++c)
+        if (c < F || (c * LPR + sub) * 4 < H) row[c] = *(const float4*)(wr + c * LPR * 4);
       float dot = 0.f;
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int col = (c * LPR + sub) * 4;
-        row[c] = (FULL || col < H) ? *(const float4*)(wr + col) : make_float4(0.f, 0.f, 0.f, 0.f);
-        dot += row[c].x * hv[c].x + row[c].y * hv[c].y + row[c].z * hv[c].z + row[c].w * hv[c].w;
-      }
+      for (int c = 0; c < CH; ++c) dot += row[c].x * hv[c].x + row[c].y * hv[c].y + row[c].z * hv[c].z + row[c].w * hv[c].w;
       dot = group_sum<LPR>(dot);
       const float zz = dot + bj;
-      if (valid) {
-        if (sub == 0) z[slot] = zz;
-        // The sums are rescaled only when the maximum moves, a few times per item.  (A reference that lags behind the
-        // maximum would do for the gradients, but a confident sample's loss is then the difference of two numbers of
-        // the lag's size: 16 lost the loss four bits and gained 2 of 390 us.)
-        if (zz > M) {
-          const float sc = __expf(M - zz);
-          s *= sc;
+      my_z = sub == k ? zz : my_z;
+      // The sums are rescaled only when the maximum moves, a few times per item.  (A reference that lags behind the
+      // maximum would do for the gradients, but a confident sample's loss is then the difference of two numbers of
+      // the lag's size: 16 lost the loss four bits and gained 2 of 390 us.)
+      if (zz > M) {
+        const float sc = __expf(M - zz);
+        s *= sc;
 #pragma unroll
-          for (int c = 0; c < CH; ++c) { acc[c].x *= sc; acc[c].y *= sc; acc[c].z *= sc; acc[c].w *= sc; }
-          M = zz;
-        }
-        const float e = __expf(zz - M);
-        s += e;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-          acc[c].x += e * row[c].x; acc[c].y += e * row[c].y; acc[c].z += e * row[c].z; acc[c].w += e * row[c].w;
-        }
+        for (int c = 0; c < CH; ++c) { acc[c].x *= sc; acc[c].y *= sc; acc[c].z *= sc; acc[c].w *= sc; }
+        M = zz;
       }
+      const float e = __expf(zz - M);
+      s += e;
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        acc[c].x += e * row[c].x; acc[c].y += e * row[c].y; acc[c].z += e * row[c].z; acc[c].w += e * row[c].w;
+      }
+    };
+    const int whole = n / RPW;                           // steps in which every group has a row
+    for (int k = 0; k < whole; ++k) {
+      const int j = __builtin_amdgcn_ds_bpermute(from, my_j);
+      const float bj = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(my_b)));
+      from += 4 * RPW;
+      step(k, j, bj);
     }
+    if (whole * RPW < n) {
+      const int j = __builtin_amdgcn_ds_bpermute(from, my_j);
+      const float bj = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(my_b)));
+      if (whole * RPW + grp < n) step(whole, j, bj);
+    }
+    if (sub * RPW + grp < n) z[first + sub * RPW + grp] = my_z;   // (step k's lane k of each group has kept it)
 #pragma unroll
     for (int d = LPR; d < 64; d <<= 1) {               // merge the row groups of the wave
       const float Mo = __shfl_xor(M, d), so = __shfl_xor(s, d);
@@ -143,7 +155,7 @@ __device__ __forceinline__ void forward_items(const ActiveDev& ad, int H, const 
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int col = (c * LPR + sub) * 4;
-        if (FULL || col < H) *(float4*)(pp + 4 + col) = acc[c];
+        if (c < F || col < H) *(float4*)(pp + 4 + col) = acc[c];
       }
     }
   }
@@ -171,8 +183,15 @@ __global__ __launch_bounds__(kForwardThreads) void forward_kernel(ActiveDev ad, 
     const int workers = (ntiles == 0 || items <= 2 * nworkers * (kForwardThreads / 64)) ? nworkers
                         : (items < 20 * ntiles ? nworkers * 2 / 3 : nworkers * 5 / 6);
     if (k >= workers) return;
-    if (H == LPR * CH * 4) forward_items<LPR, CH, true>(ad, H, h, W2, b2, z, partials, ctrl, k, workers);
-    else forward_items<LPR, CH, false>(ad, H, h, W2, b2, z, partials, ctrl, k, workers);
+#define SLIDE_ITEMS(C_, F_) forward_items<LPR, C_, F_>(ad, H, h, W2, b2, z, partials, ctrl, k, workers)
+    if (H == LPR * CH * 4) SLIDE_ITEMS(CH, CH);
+    else if constexpr (CH == 4) {
+      // (two float4 a lane at least, or the vector would have fewer lanes)
+      if (H > 3 * LPR * 4) SLIDE_ITEMS(4, 3);
+      else if (H == 3 * LPR * 4) SLIDE_ITEMS(3, 3);
+      else SLIDE_ITEMS(3, 2);
+    } else SLIDE_ITEMS(CH, CH / 2);
+#undef SLIDE_ITEMS
   }
   else {
     if (k >= nworkers + t1.ntiles) transpose_tile<false, false>(t2, k - nworkers - t1.ntiles, dyn_lds);
@@ -216,9 +235,20 @@ hipError_t forward_setup_attributes(size_t lds_limit) {
 
 hipError_t launch_forward(const ActiveDev& ad, int H, const float* h, const float* W2, const float* b2, float* z,
                           float* partials, const Ctrl* ctrl, const TransposeArgs& t1, const TransposeArgs& t2,
-                          bool logits, int num_cus, hipStream_t s) {
-  // three logit workgroups of 16 waves per compute unit (768 on the 256 of an MI355X)
-  const int nworkers = logits ? 3 * num_cus : 0;
+                          bool logits, int64_t pairs_per_sample, int num_cus, hipStream_t s) {
+  // Three logit workgroups of eight waves per compute unit (768 on the 256 of an MI355X).
+  // Long rows of a layer that is more than the dies' L2s hold are the faster the fewer are under way, as long as
+  // their latency is covered: two workgroups a compute unit, one and a half where the layer is more than the memory-side
+  // cache holds and no die has a stretch of the neurons of its own.  Launch, us, three / two / one and a half:
+  // 254K x 200, 1,024 samples, saturated 417 / 382 / 457, 325K x 128 x 256 92 / 84 / 98, 40K x 256 x 600 160 / 117 / 143;
+  // beyond that cache: 670K x 256 x 2,048 samples 424 / 416 / 378, 670K x 128 x 2,000 279 / 255 / 241, 600K x 512 x 600
+  // 242 / 232 / 213.  Shorter rows (200K x 32 77 / 93 / 121) and small layers (20K x 128 80 / 84 / 102) want all, and so do
+  // calls with few items per wave.  (pairs_per_sample: what the tables return where codes are spread evenly.  Leaving it to the
+  // launch's surplus workgroups to see that they are not needed costs half of the gain: what is left is spread unevenly.)
+  const int64_t chunks = pairs_per_sample / kChunk, floats = ad.N * H;
+  const bool far = H >= 128 && floats >= (int64_t)8 << 20 && ad.B * chunks > 32 * (int64_t)num_cus;
+  const bool stretches = ad.nxcd > 1 && chunks >= 8 * ad.nxcd;
+  const int nworkers = !logits ? 0 : !far ? 3 * num_cus : stretches || floats < (int64_t)64 << 20 ? 2 * num_cus : 3 * num_cus / 2;
 #define SLIDE_FWD(L_, C_) return launch_fwd<L_, C_>(ad, H, h, W2, b2, z, partials, ctrl, t1, t2, nworkers, s)
   if (H <= 32) SLIDE_FWD(8, 1);
   if (H <= 64) SLIDE_FWD(8, 2);

@@ -198,11 +198,11 @@ hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const flo
 
 // ---- output.hip -----------------------------------------------------------------------
 hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s);
-// Logits over the active sets (logits = true: three worker workgroups per compute unit); the same
+// Logits over the active sets (logits = true; pairs_per_sample: about how many a sample has); the same
 // launch builds the two sets of row lists (t1: features, t2: active sets; ntiles = 0 leaves one out).
 hipError_t launch_forward(const ActiveDev& ad, int H, const float* h, const float* W2, const float* b2, float* z,
                           float* partials, const Ctrl* ctrl, const TransposeArgs& t1, const TransposeArgs& t2,
-                          bool logits, int num_cus, hipStream_t s);
+                          bool logits, int64_t pairs_per_sample, int num_cus, hipStream_t s);
 hipError_t forward_setup_attributes(size_t lds_limit);
 hipError_t launch_combine(const ActiveDev& ad, int H, const float* h, const float* z, const float* partials,
                           const float* W2, const int32_t* y_indptr, const int32_t* ylist, float* delta,
