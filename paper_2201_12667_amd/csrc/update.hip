@@ -700,10 +700,14 @@ hipError_t launch_update_sliced(int H, int B, const RowUpdate& out_, const RowUp
 // dependent reads for one wave.  2,048 samples of 75 features, ids by frequency, 28K rows of W1 and 99K of W2: plain
 // kernel 606 us, without that rule 960, with it 415; 4,850 rows of 470 pairs: 215, 283 and 152.
 // 1,024 samples, 6.5 M pairs on 254K rows of 200: 767 -> 603 us (592 without the look at the long rows; four, eight
-// or sixteen vectors in flight alike: the 5.2 GB of vectors come at 9 TB/s from the L2s).  With four pairs to a row
+// or sixteen vectors in flight alike) and 603 -> 549 since a wave reads the weights and moments of four rows
+// together, behind their gradients (two or three rows, which leave room for more waves: 570, 564; eight: 564).  What bounds
+// it is the sum of both halves, 318 us for the vectors alone (5.2 GB from the L2s, at the rate at which a compute unit
+// takes such loads) and 305 for the rows alone: loads come back in order, so the one's hits queue behind the other's misses.  With four pairs to a row
 // (2,048 samples on 670K rows of 256) the plain kernel is ahead, 911 against 930: it is taken for saturated buckets only.
 // ---------------------------------------------------------------------------------------------
 constexpr int kWaveRows = 8;
+constexpr int kWaveAdam = 4;              // rows whose weights and moments a wave reads together
 constexpr int kWaveLong = 256;            // (a multiple of kLongRow: the listed long rows include these)
 
 __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, const AdamDev& ad, int block, int nblocks) {
@@ -715,7 +719,8 @@ __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, co
   constexpr int UNR = 8;                                   // vectors in flight (a divisor of 64)
   const int col = 4 * lane;
   const bool col_ok = col < H;                             // (H is a multiple of 4)
-  const bool bias_lane = ru.bias != nullptr && lane == 0;
+  __shared__ float4 grad_lds[kUpdateThreads / 64][kWaveAdam * 64];
+  float4* grads = grad_lds[threadIdx.x >> 6] + lane;
   const float* V = ru.V + (col_ok ? col : 0);              // (lanes past the end read the first columns and store nothing)
   auto entry = [&](int st, int cn, int q0) -> int2 {       // this lane's list entry of the batch at q0 (past the end: the first)
     return pd.pairs[(uint32_t)st + (q0 + lane < cn ? q0 + lane : 0)];
@@ -752,52 +757,78 @@ __device__ __forceinline__ void rowgrad_adam_wave(int H, const RowUpdate& ru, co
     int2 e = entry(st, cn, 0);
     float d = lane < cn ? coef[e.y] : 0.f;
     while (left) {
-      const size_t ro = (size_t)j * H + (col_ok ? col : 0);
-      const float4 w0 = *(const float4*)(ru.W + ro), m0 = load_stream(ru.M + ro), v0 = load_stream(ru.Vv + ro);
-      left &= left - 1;
-      if (left) q = __ffsll((long long)left) - 1;          // the next row's entries meanwhile
-      const int jn = __builtin_amdgcn_readlane(head.x, q), stn = __builtin_amdgcn_readlane(head.y, q), cnn = __builtin_amdgcn_readlane(head.z, q);
-      const int2 en = entry(stn, cnn, 0);
-      float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-      float gb = 0.f;
-      for (int q0 = 0; q0 < cn; q0 += 64) {
-        if (q0) { e = entry(st, cn, q0); d = q0 + lane < cn ? coef[e.y] : 0.f; }
-        const int n = min(64, cn - q0);
-        int si = lane < n ? e.x : 0;
-        for (int a0 = 0; a0 < n; a0 += UNR) {              // (lanes past the end hold sample 0, 0.0)
-          float4 x[UNR];
-          float dd[UNR];
+      // the gradients of up to kWaveAdam rows (kept in the wave's LDS), ...
+      unsigned long long batch = 0;
+      int nr = 0, bias_j = 0;                               // lane r: row r of these ...
+      float bias_g = 0.f;                                   // ... and the gradient of its bias
+      do {
+        batch |= 1ull << q;
+        left &= left - 1;
+        if (left) q = __ffsll((long long)left) - 1;          // the next row's entries meanwhile
+        const int jn = __builtin_amdgcn_readlane(head.x, q), stn = __builtin_amdgcn_readlane(head.y, q), cnn = __builtin_amdgcn_readlane(head.z, q);
+        const int2 en = entry(stn, cnn, 0);
+        float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+        float gb = 0.f;
+        for (int q0 = 0; q0 < cn; q0 += 64) {
+          if (q0) { e = entry(st, cn, q0); d = q0 + lane < cn ? coef[e.y] : 0.f; }
+          const int n = min(64, cn - q0);
+          int si = lane < n ? e.x : 0;
+          for (int a0 = 0; a0 < n; a0 += UNR) {              // (lanes past the end hold sample 0, 0.0)
+            float4 x[UNR];
+            float dd[UNR];
 #pragma unroll
-          for (int a = 0; a < UNR; ++a) {
-            dd[a] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), a0 + a));
-            x[a] = *(const float4*)(V + (size_t)__builtin_amdgcn_readlane(si, a0 + a) * H);
-          }
-          // (a batch is summed by itself: lists of a thousand samples lose no more than lists of a hundred)
-          float4 p = make_float4(dd[0] * x[0].x, dd[0] * x[0].y, dd[0] * x[0].z, dd[0] * x[0].w);
+            for (int a = 0; a < UNR; ++a) {
+              dd[a] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), a0 + a));
+              x[a] = *(const float4*)(V + (size_t)__builtin_amdgcn_readlane(si, a0 + a) * H);
+            }
+            // (a batch is summed by itself: lists of a thousand samples lose no more than lists of a hundred)
+            float4 p = make_float4(dd[0] * x[0].x, dd[0] * x[0].y, dd[0] * x[0].z, dd[0] * x[0].w);
 #pragma unroll
-          for (int a = 1; a < UNR; ++a) {
-            p.x += dd[a] * x[a].x; p.y += dd[a] * x[a].y; p.z += dd[a] * x[a].z; p.w += dd[a] * x[a].w;
+            for (int a = 1; a < UNR; ++a) {
+              p.x += dd[a] * x[a].x; p.y += dd[a] * x[a].y; p.z += dd[a] * x[a].z; p.w += dd[a] * x[a].w;
+            }
+            g.x += p.x; g.y += p.y; g.z += p.z; g.w += p.w;
           }
-          g.x += p.x; g.y += p.y; g.z += p.z; g.w += p.w;
+          gb += wave_sum_f32(d);
         }
-        gb += wave_sum_f32(d);
+        const float dn = lane < cnn ? coef[en.y] : 0.f;
+        grads[nr * 64] = g;
+        bias_j = lane == nr ? j : bias_j;
+        bias_g = lane == nr ? gb : bias_g;
+        ++nr;
+        j = jn; st = stn; cn = cnn; e = en; d = dn;
+      } while (left && nr < kWaveAdam);
+      // ... then the rows themselves, all under way together.  (Loads come back in order: a row's own under way while
+      // its vectors are gathered make every wait for a vector one for the memory.)
+      float4 w[kWaveAdam], m[kWaveAdam], v[kWaveAdam];
+      size_t ro[kWaveAdam];
+#pragma unroll
+      for (int r = 0; r < kWaveAdam; ++r) {
+        const int qr = batch ? __ffsll((long long)batch) - 1 : 0;
+        batch &= batch - 1;
+        ro[r] = (size_t)__builtin_amdgcn_readlane(head.x, qr) * H + (col_ok ? col : 0);
+        if (r < nr) { w[r] = *(const float4*)(ru.W + ro[r]); m[r] = load_stream(ru.M + ro[r]); v[r] = load_stream(ru.Vv + ro[r]); }
       }
-      const float dn = lane < cnn ? coef[en.y] : 0.f;
-      float4 w = w0, m = m0, v = v0;
-      adam1(w.x, m.x, v.x, g.x, ad); adam1(w.y, m.y, v.y, g.y, ad);
-      adam1(w.z, m.z, v.z, g.z, ad); adam1(w.w, m.w, v.w, g.w, ad);
-      if (col_ok) { *(float4*)(ru.W + ro) = w; store_stream(ru.M + ro, m); store_stream(ru.Vv + ro, v); }
+      const bool bias_lane = ru.bias != nullptr && lane < nr;
+      float bw = 0.f, bm = 0.f, bv = 0.f;
+      if (bias_lane) { bw = ru.bias[bias_j]; bm = ru.mbias[bias_j]; bv = ru.vbias[bias_j]; }
+#pragma unroll
+      for (int r = 0; r < kWaveAdam; ++r)
+        if (r < nr) {
+          const float4 g = grads[r * 64];
+          adam1(w[r].x, m[r].x, v[r].x, g.x, ad); adam1(w[r].y, m[r].y, v[r].y, g.y, ad);
+          adam1(w[r].z, m[r].z, v[r].z, g.z, ad); adam1(w[r].w, m[r].w, v[r].w, g.w, ad);
+          if (col_ok) { *(float4*)(ru.W + ro[r]) = w[r]; store_stream(ru.M + ro[r], m[r]); store_stream(ru.Vv + ro[r], v[r]); }
+        }
       if (bias_lane) {
-        float bw = ru.bias[j], bm = ru.mbias[j], bv = ru.vbias[j];
-        adam1(bw, bm, bv, gb, ad);
-        ru.bias[j] = bw; ru.mbias[j] = bm; ru.vbias[j] = bv;
+        adam1(bw, bm, bv, bias_g, ad);
+        ru.bias[bias_j] = bw; ru.mbias[bias_j] = bm; ru.vbias[bias_j] = bv;
       }
-      j = jn; st = stn; cn = cnn; e = en; d = dn;
     }
   }
 }
 
-__global__ __launch_bounds__(kUpdateThreads, 6) void update_wave_kernel(int H, RowUpdate out, RowUpdate in, FinishArgs fin,
+__global__ __launch_bounds__(kUpdateThreads, 4) void update_wave_kernel(int H, RowUpdate out, RowUpdate in, FinishArgs fin,
                                                                         AdamDev ad, int parts) {
   int blk = blockIdx.x;
   if (blk < fin.nblocks) { finish_role(H, fin, ad, blk); return; }
