@@ -249,9 +249,9 @@ struct FinishArgs {
   int nblocks;
 };
 // One launch, three roles by workgroup index: loss mean + hidden bias + statistics, the rows of W1,
-// the rows of W2 (+ b2).
+// the rows of W2 (+ b2).  rows: about how many of both there are.
 hipError_t launch_update(int H, const RowUpdate& out, const RowUpdate& in, const FinishArgs& fin, const AdamDev& ad,
-                         int num_cus, hipStream_t s);
+                         double rows, int num_cus, hipStream_t s);
 // The same launch for batches whose samples share most rows: sample vectors staged in LDS by column
 // slices (see update.hip).  update_sliced_applies: whether a batch of B vectors of length H fits.
 bool update_sliced_applies(int B, int H, size_t lds_limit);

@@ -83,7 +83,8 @@ __device__ __forceinline__ void row_gradient(int H, int sub, const PairsDev& pd,
 // RPW lane groups accumulate interleaved shares of the list, added in a fixed butterfly order), by
 // a whole workgroup each when a row fills a wave (the waves accumulate interleaved shares, added in
 // wave order through LDS).
-template <int LPR, int CH, int UNR, bool FULL>
+// SW: the weights are streamed past the caches like the moments.
+template <int LPR, int CH, int UNR, bool FULL, bool SW>
 __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int block, int nblocks) {
   const PairsDev& pd = ru.pd;
   const float* __restrict__ coef = ru.coef;
@@ -128,7 +129,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
     for (int c = 0; c < CH; ++c) {
       const int col = (c * LPR + sub) * 4;
       if (FULL || col < H) {
-        w[c] = *(const float4*)(W + ro + col);
+        w[c] = SW ? load_stream(W + ro + col) : *(const float4*)(W + ro + col);
         m[c] = load_stream(M + ro + col);
         v[c] = load_stream(Vv + ro + col);
       }
@@ -139,7 +140,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
       if (FULL || col < H) {
         adam1(w[c].x, m[c].x, v[c].x, g[c].x, ad); adam1(w[c].y, m[c].y, v[c].y, g[c].y, ad);
         adam1(w[c].z, m[c].z, v[c].z, g[c].z, ad); adam1(w[c].w, m[c].w, v[c].w, g[c].w, ad);
-        *(float4*)(W + ro + col) = w[c];
+        if (SW) store_stream(W + ro + col, w[c]); else *(float4*)(W + ro + col) = w[c];
         store_stream(M + ro + col, m[c]);
         store_stream(Vv + ro + col, v[c]);
       }
@@ -179,7 +180,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
         for (int c = 0; c < CH; ++c) {
           const int col = (c * LPR + sub) * 4;
           if (FULL || col < H) {
-            w[c] = *(const float4*)(W + ro + col);
+            w[c] = SW ? load_stream(W + ro + col) : *(const float4*)(W + ro + col);
             m[c] = load_stream(M + ro + col);
             v[c] = load_stream(Vv + ro + col);
           }
@@ -198,7 +199,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
           if (FULL || col < H) {
             adam1(w[c].x, m[c].x, v[c].x, g[c].x, ad); adam1(w[c].y, m[c].y, v[c].y, g[c].y, ad);
             adam1(w[c].z, m[c].z, v[c].z, g[c].z, ad); adam1(w[c].w, m[c].w, v[c].w, g[c].w, ad);
-            *(float4*)(W + ro + col) = w[c];
+            if (SW) store_stream(W + ro + col, w[c]); else *(float4*)(W + ro + col) = w[c];
             store_stream(M + ro + col, m[c]);
             store_stream(Vv + ro + col, v[c]);
           }
@@ -239,7 +240,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
     for (int c = 0; c < CH; ++c) {
       const int col = (c * LPR + sub) * 4;
       if (FULL || col < H) {
-        w[c] = *(const float4*)(W + ro + col);
+        w[c] = SW ? load_stream(W + ro + col) : *(const float4*)(W + ro + col);
         m[c] = load_stream(M + ro + col);
         v[c] = load_stream(Vv + ro + col);
       }
@@ -250,7 +251,7 @@ __device__ void rowgrad_adam(int H, const RowUpdate& ru, const AdamDev& ad, int 
       if (FULL || col < H) {
         adam1(w[c].x, m[c].x, v[c].x, g[c].x, ad); adam1(w[c].y, m[c].y, v[c].y, g[c].y, ad);
         adam1(w[c].z, m[c].z, v[c].z, g[c].z, ad); adam1(w[c].w, m[c].w, v[c].w, g[c].w, ad);
-        *(float4*)(W + ro + col) = w[c];
+        if (SW) store_stream(W + ro + col, w[c]); else *(float4*)(W + ro + col) = w[c];
         store_stream(M + ro + col, m[c]);
         store_stream(Vv + ro + col, v[c]);
       }
@@ -332,26 +333,36 @@ __device__ void finish_role(int H, const FinishArgs& f, const AdamDev& ad, int b
 }
 
 
-template <int LPR, int CH, int UNR>
+template <int LPR, int CH, int UNR, bool SW>
 __global__ __launch_bounds__(kUpdateThreads) void update_kernel(int H, RowUpdate out, RowUpdate in, FinishArgs fin, AdamDev ad) {
   int blk = blockIdx.x;
   if (blk < fin.nblocks) { finish_role(H, fin, ad, blk); return; }
   blk -= fin.nblocks;
   // every other workgroup takes its share of both row lists (their sizes are known on the device only)
   if (H == LPR * CH * 4) {                               // the lane groups cover the vector exactly
-    if (in.nblocks) rowgrad_adam<LPR, CH, UNR, true>(H, in, ad, blk, out.nblocks);
-    rowgrad_adam<LPR, CH, UNR, true>(H, out, ad, blk, out.nblocks);
+    if (in.nblocks) rowgrad_adam<LPR, CH, UNR, true, false>(H, in, ad, blk, out.nblocks);
+    rowgrad_adam<LPR, CH, UNR, true, SW>(H, out, ad, blk, out.nblocks);
   } else {
-    if (in.nblocks) rowgrad_adam<LPR, CH, UNR, false>(H, in, ad, blk, out.nblocks);
-    rowgrad_adam<LPR, CH, UNR, false>(H, out, ad, blk, out.nblocks);
+    if (in.nblocks) rowgrad_adam<LPR, CH, UNR, false, false>(H, in, ad, blk, out.nblocks);
+    rowgrad_adam<LPR, CH, UNR, false, SW>(H, out, ad, blk, out.nblocks);
   }
 }
 
 template <int LPR, int CH, int UNR>
-static hipError_t launch_up(int H, const RowUpdate& out, const RowUpdate& in, const FinishArgs& fin,
-                            const AdamDev& ad, hipStream_t s) {
-  hipLaunchKernelGGL((update_kernel<LPR, CH, UNR>), dim3(fin.nblocks + out.nblocks), dim3(kUpdateThreads), 0, s, H,
-                     out, in, fin, ad);
+static hipError_t launch_up(int H, RowUpdate out, const RowUpdate& in, const FinishArgs& fin, const AdamDev& ad, double rows,
+                            int num_cus, hipStream_t s) {
+  // Workgroups for about one and a half work items (64 / LPR rows) a wave, 16 to 128 per compute unit (it holds four of
+  // them): the machine then works its way through the tiles in order and its last round is short.  Launch, us, 8 / 16 / 32 /
+  // 64 / 128 workgroups per compute unit: 670K x 128, 255K rows touched 153 / 142 / 143 / 145 / 159; x 256, 635K rows 921 / 828 /
+  // 895 / 813 / 805; 600K x 512, 410K rows 956 / 911 / 904 / 853 / 776; 167K x 128, 65K rows 43.8 / 42.7 / 42.3 / 45.5 / 52.8.
+  // Weight rows that together exceed the memory-side cache (256 MB) are streamed, too: what the logits have left of them there
+  // is gone by now (635K rows of 256 813 -> 783 us, 190K of 1,024 586 -> 551; rows that do fit: 255K of 128 145 -> 151).
+  const double items = rows * LPR / 64;
+  const int per_cu = items < 4096 ? 8 : (int)std::min(128.0, std::max(16.0, std::ceil(items / (6.0 * num_cus))));
+  out.nblocks = per_cu * num_cus;
+  const dim3 grid(fin.nblocks + out.nblocks), block(kUpdateThreads);
+  if (rows * H * 4 > (double)(256 << 20)) hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, true>), grid, block, 0, s, H, out, in, fin, ad);
+  else hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, false>), grid, block, 0, s, H, out, in, fin, ad);
   return hipGetLastError();
 }
 
@@ -849,13 +860,12 @@ hipError_t launch_update_waves(int H, const RowUpdate& out, const RowUpdate& in,
 }
 
 hipError_t launch_update(int H, const RowUpdate& out_, const RowUpdate& in_, const FinishArgs& fin_,
-                         const AdamDev& ad, int num_cus, hipStream_t s) {
+                         const AdamDev& ad, double rows, int num_cus, hipStream_t s) {
   RowUpdate out = out_, in = in_;
   FinishArgs fin = fin_;
-  out.nblocks = 8 * num_cus;          // twice what the device holds at four waves per SIMD: the tail stays short
   in.nblocks = in.W ? 1 : 0;          // present / absent
   fin.nblocks = fin.b1 ? ceil_div(H, 32) : 1;
-#define SLIDE_UP(L_, C_, U_) return launch_up<L_, C_, U_>(H, out, in, fin, ad, s)
+#define SLIDE_UP(L_, C_, U_) return launch_up<L_, C_, U_>(H, out, in, fin, ad, rows, num_cus, s)
   if (H <= 32) SLIDE_UP(8, 1, 4);
   if (H <= 64) SLIDE_UP(8, 2, 4);
   if (H <= 128) SLIDE_UP(8, 4, 2);
