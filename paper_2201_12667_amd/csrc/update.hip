@@ -351,14 +351,14 @@ __global__ __launch_bounds__(kUpdateThreads) void update_kernel(int H, RowUpdate
 template <int LPR, int CH, int UNR>
 static hipError_t launch_up(int H, RowUpdate out, const RowUpdate& in, const FinishArgs& fin, const AdamDev& ad, double rows,
                             int num_cus, hipStream_t s) {
-  // Workgroups for about one and a half work items (64 / LPR rows) a wave, 16 to 128 per compute unit (it holds four of
+  // Workgroups for about one and a half work items (64 / LPR rows) a wave, 16 to 64 per compute unit (it holds four of
   // them): the machine then works its way through the tiles in order and its last round is short.  Launch, us, 8 / 16 / 32 /
   // 64 / 128 workgroups per compute unit: 670K x 128, 255K rows touched 153 / 142 / 143 / 145 / 159; x 256, 635K rows 921 / 828 /
-  // 895 / 813 / 805; 600K x 512, 410K rows 956 / 911 / 904 / 853 / 776; 167K x 128, 65K rows 43.8 / 42.7 / 42.3 / 45.5 / 52.8.
+  // 895 / 813 / 805; 600K x 512, 410K rows 956 / 911 / 904 / 853 / 776 (64 and 128 are alike over more runs); 167K x 128, 65K rows 43.8 / 42.7 / 42.3 / 45.5 / 52.8.
   // Weight rows that together exceed the memory-side cache (256 MB) are streamed, too: what the logits have left of them there
   // is gone by now (635K rows of 256 813 -> 783 us, 190K of 1,024 586 -> 551; rows that do fit: 255K of 128 145 -> 151).
   const double items = rows * LPR / 64;
-  const int per_cu = items < 4096 ? 8 : (int)std::min(128.0, std::max(16.0, std::ceil(items / (6.0 * num_cus))));
+  const int per_cu = items < 4096 ? 8 : (int)std::min(64.0, std::max(16.0, std::ceil(items / (6.0 * num_cus))));
   out.nblocks = per_cu * num_cus;
   const dim3 grid(fin.nblocks + out.nblocks), block(kUpdateThreads);
   if (rows * H * 4 > (double)(256 << 20)) hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, true>), grid, block, 0, s, H, out, in, fin, ad);
