@@ -406,11 +406,14 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
     __syncthreads();
   };
 
-  // Buckets: 2^lg lanes to a table, in one go where the tables allow (then a lane keeps its entries for the segments
-  // to come).  What is beyond the lanes' first eight entries each is read by whole waves, four buckets at a time.
+  // Buckets: 2^lg lanes to a table, in one go where the tables allow (then a lane keeps its first eight entries for
+  // the passes to come).  What is beyond eight entries a lane is read by whole waves, four buckets at a time, where few
+  // buckets are that long (the chain of reads of one long bucket would hold up all: 4 samples of 670K neurons 33 us a call, 39 by
+  // the table's lanes), and by the table's lanes where many are (214 tables of 36 entries a bucket, 641 samples 55 us, 92 by waves).
   const int G = 1 << lg, tstep = nthr >> lg;
   const bool once = ad.L <= tstep;
   const int direct = kBucketAhead * G;
+  constexpr uint32_t kFewLong = 64;                      // (four buckets for each wave)
   int j[kBucketAhead];
   uint32_t entries = 0;                                  // (of the buckets this thread leads)
   uint32_t n = 0;                                        // active neurons in the segments so far
@@ -430,24 +433,25 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
     // Every entry of the buckets: f(id), -1 where a lane has none.  (again: the lane's entries, if it keeps them)
     auto for_direct = [&](bool again, auto&& f) __attribute__((always_inline)) {
       for (int t = me >> lg; t < ad.L; t += tstep) {
-        if (!(again && once)) {
-          uint32_t a, len;
-          if (seg0 == 0 && !again) {
-            const uint32_t code = o0s[t];
-            if (sub == 0) codes[(size_t)i * ad.L + t] = code;
-            a = off[(size_t)t * (nb + 1) + code];
-            len = min(off[(size_t)t * (nb + 1) + code + 1] - a, (uint32_t)ad.C);
-            if (sub == 0) {                              // (the group's lanes sit in one wave: they have read the code)
-              o0s[t] = a;
-              blen[t] = len;
-              entries += len;
-              if ((int)len > direct) sm[19] = 1;
-            }
-          } else {
-            a = o0s[t];
-            len = blen[t];
+        uint32_t a = 0, len = 0;
+        if (again && once) {
+        } else if (seg0 == 0 && !again) {
+          const uint32_t code = o0s[t];
+          if (sub == 0) codes[(size_t)i * ad.L + t] = code;
+          a = off[(size_t)t * (nb + 1) + code];
+          len = min(off[(size_t)t * (nb + 1) + code + 1] - a, (uint32_t)ad.C);
+          if (sub == 0) {                                // (the group's lanes sit in one wave: they have read the code)
+            o0s[t] = a;
+            blen[t] = len;
+            entries += len;
+            if ((int)len > direct) atomicAdd(&sm[19], 1u);
           }
-          const uint32_t first = (uint32_t)t * (uint32_t)ad.N + a + (uint32_t)sub;   // (L * N < 2^32)
+        } else {
+          a = o0s[t];
+          len = blen[t];
+        }
+        const uint32_t first = (uint32_t)t * (uint32_t)ad.N + a + (uint32_t)sub;   // (L * N < 2^32)
+        if (!(again && once)) {
 #pragma unroll
           for (int u = 0; u < kBucketAhead; ++u) j[u] = -1;
 #pragma unroll
@@ -456,6 +460,23 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         }
 #pragma unroll
         for (int u = 0; u < kBucketAhead; ++u) f(j[u]);
+      }
+    };
+    // ... what of them is beyond the lanes' first: by the lanes of the table, or, where few buckets are that long, by whole waves
+    auto for_rest = [&](auto&& f) __attribute__((always_inline)) {
+      for (int t = me >> lg; t < ad.L; t += tstep) {
+        const int most = (int)blen[t];
+        const uint32_t first = (uint32_t)t * (uint32_t)ad.N + o0s[t];
+        for (int at = direct + sub; at < most; at += 4 * lanes) {
+          int x[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] = -1;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (at + u * lanes < most) x[u] = ids[first + (uint32_t)(at + u * lanes)];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) f(x[u]);
+        }
       }
     };
     auto for_long = [&](auto&& f) __attribute__((always_inline)) {
@@ -494,8 +515,10 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
       if (lane == 0 && entries) atomicAdd(&sm[18], entries);
     }
     __syncthreads();
-    if (sm[19]) {
-      for_long(set_bit);
+    const uint32_t nlong = sm[19];
+    if (nlong) {
+      if (nlong <= kFewLong) for_long(set_bit);
+      else for_rest(set_bit);
       __syncthreads();
     }
     if constexpr (BUDGET) apply_budget();
@@ -572,7 +595,10 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         if (r < span) ad.as_ids[base_i + (int)rank_of(r)] = id;
       };
       for_direct(true, place);
-      if (sm[19]) for_long(place);
+      if (nlong) {
+        if (nlong <= kFewLong) for_long(place);
+        else for_rest(place);
+      }
     } else {
       for (int q = tid; q < sw / 4; q += nthr) {         // (drawn neurons are nowhere but in the bitmap)
         const uint4 wd = ((const uint4*)bm)[bitmap_quad(q)];

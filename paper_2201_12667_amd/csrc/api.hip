@@ -706,8 +706,10 @@ int slide_train_step(slide_ctx* ctx, const slide_batch* b, float* d_loss, void* 
     fin.b1 = ctx->buf.b1; fin.mb1 = ctx->buf.mb1; fin.vb1 = ctx->buf.vb1;
     fin.tile_nu1 = p1.tile_nu; fin.ntiles1 = p1.ntiles;
   }
-  // touched rows, about: of W2 by pairs spread evenly over the layer, of W1 half of the features
-  const double touched = lo.N * (1.0 - std::exp(-(double)b->batch * pairs_per_sample(ctx) / lo.N)) + (lo.D > 0 ? 0.5 * b->nnz : 0.0);
+  // touched rows, about: of W2 by pairs spread evenly over the layer, or all that the buckets hold; of W1 half of the features
+  const double held = (double)c.L * lo.nb * std::min<double>(c.bucket_cap, (double)lo.N / lo.nb);
+  const double pairs = std::min((double)b->batch * pairs_per_sample(ctx), held);
+  const double touched = lo.N * (1.0 - std::exp(-pairs / lo.N)) + (lo.D > 0 ? 0.5 * b->nnz : 0.0);
   const bool rows = rows_mode && update_sliced_applies(b->batch, lo.H, ctx->lds_limit);
   HIPCHK(ctx, stage(ctx, SLIDE_STAGE_UPDATE, s, [&] {
     if (rows_mode && !rows && update_waves_applies(lo.H)) return launch_update_waves(lo.H, out, in, fin, a, ctx->num_cus, s);
