@@ -30,18 +30,9 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published peak
 # entry names the summary under profiles/ it was copied from, and is dropped (None) when a kernel it
 # covers has changed since that profile was taken.
 PROFILED_TRAFFIC = {
-    "cfg2-670k": {"update_kernel": 777.5e6, "forward_kernel": 210.0e6,
-                  "source": "profiles/cfg2-670k_step_kernels.md (FETCH_SIZE x 2048 + WRITE_SIZE x 1024 bytes per "
-                            "dispatch, mean of 45 dispatches, both factors from the copy kernel in the same runs)"},
-    "cfg1-shard167k": {"update_kernel": 212.2e6, "forward_kernel": 51.7e6,
-                       "source": "profiles/cfg1-shard167k_step_kernels.md (mean of 45 dispatches)"},
-    "cfg4-825m": {"update_kernel": 587.1e6, "forward_kernel": 39.0e6,
-                  "source": "profiles/cfg4-825m_step_kernels.md (mean of 45 dispatches)"},
-    "cfg3-wide325k": {"update_kernel": 424.9e6, "forward_kernel": 108.9e6,
+    "cfg3-wide325k": {"update_kernel": 424.9e6, "forward_kernel": None,
                       "source": "profiles/cfg3-wide325k_step_kernels.md (update_sliced_kernel; mean of 45 dispatches "
                                 "of a workload whose touched rows shrink step by step)"},
-    "cfg5-text8-shape": {"update_kernel": 1966.6e6, "forward_kernel": 921.7e6,
-                         "source": "profiles/cfg5-text8-shape_step_kernels.md (update_wave_kernel; mean of 45 dispatches)"},
 }
 
 
