@@ -703,7 +703,7 @@ hipError_t launch_update_sliced(int H, int B, const RowUpdate& out_, const RowUp
 // again, the vectors read from the caches, a lane owning four neighbouring columns (up to 256 of them; from 129 on,
 // so that more than half of the lanes have some).  The row's list entries are wave-uniform values, so a pair costs
 // one 16-byte read per lane from a scalar base and twelve instructions instead of the thirty that lane groups with
-// rows of their own spend on addresses and on columns past the end, and six waves a SIMD fit instead of four.
+// rows of their own spend on addresses and on columns past the end.
 // A wave takes up to kWaveRows neighbouring row slots of a tile at a time (fewer where that would leave waves without
 // any): headers together, the next row's list entries and coefficients while the current row's vectors are summed.
 // Rows of more than kWaveLong pairs are left out and taken afterwards from the list of long rows, dealt out to the
@@ -714,8 +714,9 @@ hipError_t launch_update_sliced(int H, int B, const RowUpdate& out_, const RowUp
 // or sixteen vectors in flight alike) and 603 -> 549 since a wave reads the weights and moments of four rows
 // together, behind their gradients (two or three rows, which leave room for more waves: 570, 564; eight: 564).  What bounds
 // it is the sum of both halves, 318 us for the vectors alone (5.2 GB from the L2s, at the rate at which a compute unit
-// takes such loads) and 305 for the rows alone: loads come back in order, so the one's hits queue behind the other's misses.  With four pairs to a row
-// (2,048 samples on 670K rows of 256) the plain kernel is ahead, 911 against 930: it is taken for saturated buckets only.
+// takes such loads) and 305 for the rows alone: loads come back in order, so the one's hits queue behind
+// the other's misses.  With four pairs to a row (2,048 samples on 670K rows of 256) the plain kernel is ahead, 911 against 930:
+// it is taken for saturated buckets only.
 // ---------------------------------------------------------------------------------------------
 constexpr int kWaveRows = 8;
 constexpr int kWaveAdam = 4;              // rows whose weights and moments a wave reads together
