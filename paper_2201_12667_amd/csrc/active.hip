@@ -203,7 +203,7 @@ __device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __po
 // their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
 // pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
 constexpr int kLookupThreads = 1024;
-constexpr int kLookupArgs = 448;       // bytes of the kernel's arguments
+constexpr int kLookupArgs = 400;       // bytes of the kernel's arguments
 constexpr int kBucketAhead = 8;        // entries of a bucket that a lane requests at once
 
 template <bool ROUNDS, bool BUDGET, int KIND>
