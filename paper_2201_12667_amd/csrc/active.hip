@@ -8,14 +8,11 @@
 //                 It also emits the compact ascending id list per sample + the labels' slots and hands
 //                 the sample its forward work items (chunks of kChunk active neurons).
 #include "slide_internal.h"
+#include "lookup_plan.h"
 #include "spmm.h"
 #include "wave_ops.h"
 
-#include <algorithm>
-
 namespace slide {
-
-constexpr int kSelWords = 264;     // 256 histogram bins + counters of the sampling-budget selection
 
 // Counter-based random numbers of the sampling budget (Section 3.7): the 32-bit finaliser of
 // MurmurHash3, a bijection, keyed by (seed, step, sample) and then by neuron or draw number.
@@ -202,7 +199,6 @@ __device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __po
 // thread, half of the LDS each), one of them at work while the other waits, and the hidden activations come from a launch of
 // their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
 // pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
-constexpr int kLookupThreads = 1024;
 constexpr int kLookupArgs = 400;       // bytes of the kernel's arguments
 constexpr int kBucketAhead = 8;        // entries of a bucket that a lane requests at once
 
@@ -220,9 +216,9 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
   uint32_t* sm = blen + ad.L;            // [20] scan scratch + counters: [17] labels, [18] bucket entries, [19] long buckets
   float* hvec = (float*)(sm + 20);       // [H] the sample's hidden activations
   uint32_t* rk = (uint32_t*)(hvec + hd.H);     // [segw >> lcw] rank of every thread's first word
-  uint16_t* qrk = (uint16_t*)(rk + (segw >> lcw));   // [segw / 4] entries of that thread's before a quad of words
-  uint32_t* sel = (uint32_t*)(qrk + segw / 4);   // [kSelWords] sampling budget (if there is one): digit histogram + counters
-  int8_t* raw = (int8_t*)(sel + (BUDGET ? kSelWords : 0));    // [NH] elementary hash values
+  uint16_t* qrk = (uint16_t*)(rk + (segw >> lcw));   // [segw / 4] entries of that thread's before a quad of words, or, BUDGET,
+  uint32_t* sel = (uint32_t*)qrk;        // [kSelWords] digit histogram + counters of the sampling budget
+  int8_t* raw = BUDGET ? (int8_t*)(sel + kSelWords) : (int8_t*)(qrk + segw / 4);   // [NH] elementary hash values
   const int i = blockIdx.x, tid = threadIdx.x;
   constexpr int nthr = kLookupThreads;
   const int lane = tid & 63;
@@ -561,7 +557,7 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         rk[c] = rank;
 #pragma unroll
         for (int q = 0; q < 8; q += 2) {
-          if (q >= nq) break;
+          if (BUDGET || q >= nq) break;
           if (nq == 1) qrk[c] = 0;
           else ((uint32_t*)qrk)[(c * nq + q) >> 1] = before[q >> 1];
         }
@@ -575,12 +571,15 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
       }
     }
     __syncthreads();
-    // Rank of id lo + r, which the bitmap holds.
+    // Rank of id lo + r, which the bitmap holds.  (BUDGET: only the labels', so their threads' quads before them are counted.)
     auto rank_of = [&](uint32_t r) __attribute__((always_inline)) -> uint32_t {
       const int quad = (int)(r >> 7), b = (int)(r & 127u);
       const uint4 wd = ((const uint4*)bm)[bitmap_quad(quad)];
       const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
-      uint32_t at = rk[quad >> (lcw - 2)] + qrk[quad];
+      uint32_t at = rk[quad >> (lcw - 2)];
+      if constexpr (BUDGET)
+        for (int q = quad & -nq; q < quad; ++q) at += (uint32_t)popc4(((const uint4*)bm)[bitmap_quad(q)]);
+      else at += qrk[quad];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int low = b - 32 * k;                      // bits of this word that come before
@@ -600,13 +599,23 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         else for_rest(place);
       }
     } else {
-      for (int q = tid; q < sw / 4; q += nthr) {         // (drawn neurons are nowhere but in the bitmap)
-        const uint4 wd = ((const uint4*)bm)[bitmap_quad(q)];
-        const uint32_t ww[4] = {wd.x, wd.y, wd.z, wd.w};
-        int slot = base_i + (int)(rk[q >> (lcw - 2)] + qrk[q]);
+      // (drawn neurons are nowhere but in the bitmap: every thread lists what its words hold)
+      for (int c = me; c < nchunk; c += nthr) {
+        int slot = base_i + (int)rk[c];
+        for (int k0 = 0; k0 < nq; k0 += 4) {
+          uint4 wd[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          for (uint32_t word = ww[k]; word; word &= word - 1) ad.as_ids[slot++] = (seg0 + 4 * q + k) * 32 + __ffs(word) - 1;
+          for (int k = 0; k < 4; ++k) wd[k] = k0 + k < nq ? ((const uint4*)bm)[bitmap_quad(c * nq + k0 + k)] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t ww[4] = {wd[k].x, wd[k].y, wd[k].z, wd[k].w};
+            if (!(ww[0] | ww[1] | ww[2] | ww[3])) continue;
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+              for (uint32_t word = ww[w]; word; word &= word - 1)
+                ad.as_ids[slot++] = (seg0 + 4 * (c * nq + k0 + k) + w) * 32 + __ffs(word) - 1;
+          }
+        }
       }
     }
     if (ad.write_act)                                    // the row lists are built from the bitmaps
@@ -632,14 +641,6 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
   }
 }
 
-size_t lookup_fixed_lds(int L, int H, int NT, int NH) {
-  return ((size_t)2 * L + 1 + 20 + H + NT + kSelWords) * 4 + (((size_t)NH + 3) & ~(size_t)3);
-}
-
-bool lookup_bitmap_fits(int NWpad, int NT, int L, int H, int NH, size_t lds_limit) {
-  return lookup_fixed_lds(L, H, NT, NH) + (size_t)NWpad * 4 <= lds_limit;
-}
-
 hipError_t active_setup_attributes(size_t* lds_limit_out) {
   int dev = 0, lim = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -662,38 +663,20 @@ hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const flo
                                const TablesDev& td, uint32_t* codes, const int32_t* y_indptr,
                                const int32_t* y_indices, int include_labels, int32_t* ncand, Ctrl* ctrl,
                                size_t lds_limit, int num_cus, hipStream_t s) {
-  // (slide_init has refused configurations that leave less than kLookupMinSegment words:
-  // with a tiny segment the kernel would sweep all candidates once per few hundred neurons)
-  if (lookup_fixed_lds(ad.L, hd.H, ad.NT, hd.NH) + (size_t)kLookupMinSegment * 4 > lds_limit) return hipErrorInvalidValue;
   const bool budgeted = ad.budget > 0 && include_labels;
-  // LDS besides the segment; with a segment and the ranks of its threads' and quads' first words
-  const size_t fixed = ((size_t)2 * ad.L + 20 + hd.H + (budgeted ? kSelWords : 0)) * 4 + (((size_t)hd.NH + 3) & ~(size_t)3);
-  auto lds_of = [&](int words, int lcw) { return fixed + (size_t)words * 4 + (size_t)(words >> lcw) * 4 + (size_t)words / 2; };
-  auto words_in = [&](size_t lds) { return (int)std::min<size_t>(lds > fixed ? (lds - fixed) / 148 * 32 : 0, ad.NWpad); };
-  int segw = words_in(lds_limit);
   const bool rounds = ad.B > num_cus && !sp.W1 && !budgeted;
-  // two workgroups to a compute unit, where that takes at most four segments instead of one
-  if (rounds) {
-    const int half = words_in(lds_limit / 2);
-    if (half > 0) {
-      const int segments = ceil_div(ad.NWpad, half);
-      if (segments <= 4) segw = ceil_div(ceil_div(ad.NWpad, segments), 32) * 32;
-    }
-  }
-  if (segw < 32) return hipErrorInvalidValue;
-  // words to a thread: the fewest that let all threads together take the segment at once (and its ranks fit)
-  int lcw = 2;
-  while (lcw < 5 && ((segw >> lcw) > kLookupThreads || lds_of(segw, lcw) > lds_limit)) ++lcw;
+  // (slide_init has refused configurations that leave no room for a segment worth sweeping, or, with a budget, for the bitmap)
+  const LookupPlan plan = lookup_plan(ad.L, hd.H, hd.NH, ad.NWpad, budgeted, rounds, lds_limit);
+  if (plan.segw == 0 || (budgeted && plan.segw < ad.NWpad)) return hipErrorInvalidValue;
   // lanes to a table
   int lg = 0;
   while (lg < 6 && (ad.L << (lg + 1)) <= kLookupThreads) ++lg;
-  const size_t bytes = lds_of(segw, lcw);
   const bool dwta = hd.kind == SLIDE_HASH_DWTA;
   auto kernel = budgeted ? (dwta ? lookup_union_kernel<false, true, SLIDE_HASH_DWTA> : lookup_union_kernel<false, true, SLIDE_HASH_SIMHASH>)
                 : rounds ? (dwta ? lookup_union_kernel<true, false, SLIDE_HASH_DWTA> : lookup_union_kernel<true, false, SLIDE_HASH_SIMHASH>)
                          : (dwta ? lookup_union_kernel<false, false, SLIDE_HASH_DWTA> : lookup_union_kernel<false, false, SLIDE_HASH_SIMHASH>);
-  hipLaunchKernelGGL(kernel, dim3(ad.B), dim3(kLookupThreads), bytes, s, ad, hd, h, sp, td.off, td.ids, td.nb,
-                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, segw, lg, lcw);
+  hipLaunchKernelGGL(kernel, dim3(ad.B), dim3(kLookupThreads), plan.bytes, s, ad, hd, h, sp, td.off, td.ids, td.nb,
+                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, plan.segw, lg, plan.lcw);
   return hipGetLastError();
 }
 

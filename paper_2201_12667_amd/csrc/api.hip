@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "slide_internal.h"
+#include "lookup_plan.h"
 
 using namespace slide;
 
@@ -138,12 +139,11 @@ int make_layout(const slide_config* c, Layout* lo, std::string& err) {
   if ((int64_t)c->L * lo->N >= ((int64_t)1 << 32)) FAIL(SLIDE_EINVAL, "L * num_classes does not fit 32 bits");
   lo->max_chunks = lo->Amax / kChunk + c->max_batch + 1;
   {
-    // the lookup kernel keeps, besides a segment of the per-sample bitmap, 2L + H + NT words and K*L bytes
-    // in LDS: that has to leave room for a segment worth sweeping
-    const size_t fixed = lookup_fixed_lds(c->L, c->hidden_dim, lo->NT, c->K * c->L);
-    if (fixed + (size_t)kLookupMinSegment * 4 > kDeviceLdsBytes)
+    // what the lookup kernel keeps in LDS has to leave room for a segment of the per-sample bitmap worth sweeping
+    const size_t need = lookup_accepted_lds(c->L, c->hidden_dim, lo->NT, c->K * c->L, kLookupMinSegment);
+    if (need > kDeviceLdsBytes)
       FAIL(SLIDE_EINVAL, "L, K*L, hidden_dim and num_classes / tile need %zu bytes of LDS in the lookup kernel; "
-                         "%zu are available", fixed + (size_t)kLookupMinSegment * 4, kDeviceLdsBytes);
+                         "%zu are available", need, kDeviceLdsBytes);
   }
   lo->U2max = (int64_t)lo->NWpad * 32;
   lo->P1max = c->max_nnz_per_batch;
@@ -565,12 +565,12 @@ int slide_init(const slide_config* cfg, const slide_buffers* buf, const slide_ha
     slide_destroy(ctx);
     return SLIDE_EHIP;
   }
-  if (cfg->sample_budget > 0 && !lookup_bitmap_fits(lo.NWpad, lo.NT, lo.L, H, NH, ctx->lds_limit)) {
+  if (cfg->sample_budget > 0 && lookup_accepted_lds(lo.L, H, lo.NT, NH, lo.NWpad) > ctx->lds_limit) {
     set_err(nullptr, SLIDE_EINVAL, "sample_budget needs the per-sample bitmap in LDS: num_classes is too large");
     slide_destroy(ctx);
     return SLIDE_EINVAL;
   }
-  if (lookup_fixed_lds(lo.L, H, lo.NT, NH) + (size_t)kLookupMinSegment * 4 > ctx->lds_limit) {
+  if (lookup_accepted_lds(lo.L, H, lo.NT, NH, kLookupMinSegment) > ctx->lds_limit) {
     set_err(nullptr, SLIDE_EINVAL, "the lookup kernel needs more LDS than the device offers (%zu bytes)", ctx->lds_limit);
     slide_destroy(ctx);
     return SLIDE_EINVAL;

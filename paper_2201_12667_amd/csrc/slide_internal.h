@@ -183,12 +183,8 @@ struct SpmmArgs {
   int2* xse;                     // [tiles][B] feature segments per tile (output)
 };
 
-constexpr int kLookupMinSegment = 1024;   // bitmap words the lookup kernel must be able to hold at a time
 constexpr size_t kDeviceLdsBytes = 160 * 1024;   // LDS of a gfx950 compute unit (the only target)
-// LDS the lookup kernel needs besides its bitmap segment.
-size_t lookup_fixed_lds(int L, int H, int NT, int NH);
 hipError_t active_setup_attributes(size_t* lds_limit_out);
-bool lookup_bitmap_fits(int NWpad, int NT, int L, int H, int NH, size_t lds_limit);
 // sp.W1 != nullptr: the workgroup of a sample first computes the sample's hidden activations (h is
 // then sp.h, written here); else h holds them already.
 hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const float* h, const SpmmArgs& sp,

@@ -1,12 +1,14 @@
 """The benchmark configurations at full size, in the launch configuration bench.py times: one
 training step from identical state compared with the oracle in full (active sets bit-exact; logits,
 errors, hidden gradient, Adam state and weights within tolerance), plus sampled buckets."""
+import dataclasses
 import time
 
 import numpy as np
 import pytest
 
 from paper_2201_12667_amd import synth
+from paper_2201_12667_amd.slide import SlideError
 
 pytestmark = pytest.mark.gpu
 
@@ -72,6 +74,28 @@ def test_output_layer_larger_than_one_lds_bitmap():
     assert float((ids.cpu().numpy() == want).mean()) > 0.98
     assert model.status() == 0
     model.destroy()
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("N,batch,budget,fill", [(1_260_544, 9, 20, False), (1_260_544, 9, 3000, True), (1_223_680, 300, 20, True)])
+def test_sampling_budget_up_to_the_largest_layer(N, batch, budget, fill):
+    """The largest layer that a sampling budget is accepted for at these tables (the whole bitmap of a sample in LDS), more
+    retrieved than the budget and fewer, samples of one round and of two; one neuron more is refused."""
+    wl = synth.small(synth.HASH_DWTA, num_classes=N, hidden_dim=16, K=6, L=4, bucket_cap=16, batch=batch, input_dim=500,
+                     nnz_mean=10.0, rebuild_every=0, sample_budget=budget, sample_fill=fill, sample_seed=7)
+    _say("budget on a large layer", N, batch, budget, fill)
+    gen, model, orc = make_pair(wl)
+    model.build_tables()
+    orc.build_tables()
+    for step in range(2):
+        load_state(model, orc)
+        res = compare_step(model, orc, gen.batch(step))
+        _say("  step", step, {k: round(v, 3) for k, v in res.items() if not k.startswith("_")}, res["_loss"])
+        assert_ok(res)
+    assert model.status() == 0
+    model.destroy()
+    with pytest.raises(SlideError, match="num_classes is too large"):
+        make_pair(dataclasses.replace(wl, num_classes=N + 1))
 
 
 @pytest.mark.timeout(600)
