@@ -179,6 +179,50 @@ def _row_blocks(N, batch, H):
     model.destroy()
 
 
+@pytest.mark.parametrize("batch,H", [(8, 32), (8, 40), (40, 32), (100, 32)])
+@pytest.mark.parametrize("layout", ["falls", "falls-roughly", "log"])
+def test_predict_all_costs_the_same_in_any_order_of_the_ids(layout, batch, H):
+    """Scores that follow the neuron id, as where ids go by frequency: as few neurons as in random order reach the bar, so
+    the call takes about as long.  (Where more reach it than a sample's candidate buffer holds, that sample reads the
+    layer by itself, tens of milliseconds for a call of a tenth of one.)  The scores are the biases, the lists exact."""
+    N = 670_091
+    ids, rng = np.arange(N), np.random.default_rng(2)
+    bias = {"falls": -1e-3 * ids, "falls-roughly": -1e-3 * ids + 0.02 * 1e-3 * N * rng.standard_normal(N),
+            "log": -np.log(ids + 10) + 0.3 * rng.standard_normal(N)}[layout].astype(np.float32)
+    _cost_of_scores("order " + layout, N, batch, H, bias)
+
+
+def _cost_of_scores(name, N, batch, H, bias):
+    """Lists and time of a prediction whose scores are the biases (W2 = 0), against the same scores in random order."""
+    _say("dense predict cost", name, N, batch, H)
+    wl = synth.small(synth.HASH_SIMHASH, input_dim=0, hidden_dim=H, K=3, L=3, num_classes=N, batch=batch, bucket_cap=8)
+    gen, model, _ = make_pair(wl)
+    model.p["W2"].zero_()
+    model.build_tables()
+    db = model.to_device(gen.batch(0))
+
+    def timed(scores, topk):
+        model.p["b2"].copy_(torch.from_numpy(scores))
+        ms = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            got, sc = model.predict(db, topk, mode=1)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        want = np.lexsort((np.arange(N), -scores))[:topk]
+        assert np.array_equal(got.cpu().numpy(), np.broadcast_to(want, got.shape))
+        assert np.array_equal(sc.cpu().numpy(), np.broadcast_to(scores[want], sc.shape))
+        return sorted(ms)[3]
+    for topk in (10, 32):
+        spread = timed(np.random.default_rng(3).standard_normal(N).astype(np.float32), topk)
+        here = timed(bias, topk)
+        _say("   topk", topk, "us: %.0f in random order, %.0f so" % (1e3 * spread, 1e3 * here))
+        assert here < 3 * spread + 0.3                     # (an overflowing sample: 5 ms and more)
+    model.destroy()
+
+
 @pytest.mark.parametrize("layout", ["random", "second", "first", "second-misleads"])
 def test_predict_all_in_chunks(layout):
     """A layer so large that the 64 best take two passes over it (1.2 M neurons each): the list of the first and its bar go
