@@ -130,7 +130,7 @@ __device__ __forceinline__ bool is_open(uint64_t key) { return (key >> 32) == 0;
 // workgroup: its W2 values come straight from memory, two coordinate blocks ahead (also across tiles: the
 // workgroups are persistent), and are split in registers; h, split once in advance, is staged in LDS in
 // fragment order -- RES: it all fits (res_frags), is staged once, and the waves never meet again; otherwise the next stage is fetched under the products of this one.
-// kStore: every score goes to zs; kGroupBest: the best of every 32 neurons does, as score_bits (the sampled neurons);
+// kStore: every score goes to zs; kGroupBest: the best of every 32 neurons does, as a key (the sampled neurons);
 // kCandidates: the scores that reach their sample's bar go to its candidate buffer.
 enum { kCandidates, kStore, kGroupBest };
 // Forms.  kStages: h is staged in LDS in turns; kResident: it all fits (res_frags), is staged once, and the waves never meet
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(score_threads(MODE, FORM), score_waves_per_simd(NIB
           if (live && il < rows) zs[(size_t)(i0 + il) * nc + c] = acc[ib][r] + bias;
         }
     } else if constexpr (MODE == kGroupBest) {
-      // the best of the wave's 32 neurons for every sample (as bits that ascend like scores; 0: none)
+      // the best of the wave's 32 neurons for every sample, as its key (~0: none)
       const int group = STREAM ? c_lo / 32 + tile : tile * (kTileNeurons / 32) + wave;
 #pragma unroll
       for (int ib = 0; ib < NIB; ++ib) {
@@ -353,26 +353,28 @@ __global__ __launch_bounds__(score_threads(MODE, FORM), score_waves_per_simd(NIB
               z[r] = plain_score(h + (size_t)(i0 + il) * H, W2 + (size_t)neuron_of(tile) * H, bias, H);
           }
         }
-        uint32_t v[16];
+        const uint32_t none = live ? 0u : ~0u, id = (uint32_t)(j0 + (int64_t)c * stride) | none;
+        uint64_t v[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) v[r] = live ? score_bits(z[r]) : 0u;
+        for (int r = 0; r < 16; ++r) v[r] = topk_key(z[r], id) | (uint64_t)none << 32;
         // 32 lanes and 16 rows: every step halves the rows that a lane goes on with and takes the best of two lanes
         auto halve = [&](int n, bool upper, auto&& other) {
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
             if (q >= n) break;
-            const uint32_t keep = upper ? v[n + q] : v[q], give = upper ? v[q] : v[n + q];
-            v[q] = max(keep, other(give));
+            const uint64_t keep = upper ? v[n + q] : v[q], give = upper ? v[q] : v[n + q];
+            v[q] = min(keep, (uint64_t)other((uint32_t)(give >> 32)) << 32 | other((uint32_t)give));
           }
         };
+        auto swap16 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 16 << 10 | 0x1f); };
         halve(8, lane & 1, [](uint32_t x) { return dpp_u32<kDppQuadSwap1>(x, x); });
         halve(4, lane & 2, [](uint32_t x) { return dpp_u32<kDppQuadSwap2>(x, x); });
         halve(2, lane & 8, [](uint32_t x) { return dpp_u32<kDppRowRor + 8>(x, x); });
         halve(1, lane & 4, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, 4 << 10 | 0x1f); });
-        const uint32_t best = max(v[0], (uint32_t)__builtin_amdgcn_ds_swizzle((int)v[0], 16 << 10 | 0x1f));
+        const uint64_t best = min(v[0], (uint64_t)swap16((uint32_t)(v[0] >> 32)) << 32 | swap16((uint32_t)v[0]));
         const int r = (lane & 1 ? 8 : 0) + (lane & 2 ? 4 : 0) + (lane & 8 ? 2 : 0) + (lane & 4 ? 1 : 0);
         const int il = ib * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (col < 16 && il < rows && group < ngroups) ((uint32_t*)zs)[(size_t)(i0 + il) * ngroups + group] = best;
+        if (col < 16 && il < rows && group < ngroups) ((uint64_t*)zs)[(size_t)(i0 + il) * ngroups + group] = best;
       }
     } else {
       // First test, whole blocks: the largest of four consecutive samples' scores (NaN counts as largest) against
@@ -566,30 +568,55 @@ __global__ __launch_bounds__(kSelectThreads) void dense_select_kernel(int H, con
 // (3) Per sample: the topk-th best of the groups' bests as the bar, which at least topk neurons reach (one of each of
 // as many groups; the topk-th best of all sampled neurons is hardly higher: groups hold 32 of them from all over the layer,
 // 256 groups and more).
-// A wave per sample; the value is found bit by bit, by counting the groups that reach what is tried.  (The topk-th
+// A wave per sample; the bar's score is found bit by bit, by counting the groups that reach what is tried, and then its id
+// among the groups that are tied there.  (The bar is a key, id and all: where many neurons share the bar's score only those of
+// lower ids pass.  With the score alone a sample whose scores were all the same took 27 ms for 90 us.  The topk-th
 // best of the scores themselves, which this replaced, took two sweeps over 8,192 of them, 14 us.)
-__global__ __launch_bounds__(64) void dense_bar_kernel(int ngroups, const uint32_t* __restrict__ best, int topk,
+__global__ __launch_bounds__(64) void dense_bar_kernel(int ngroups, const uint64_t* __restrict__ best, int topk,
                                                        uint64_t* __restrict__ bars, uint32_t* __restrict__ ccnt) {
+  constexpr int U = kMaxGroups / 64;
   const int i = blockIdx.x, lane = threadIdx.x;
-  uint32_t v[kMaxGroups / 64];
+  uint32_t v[U], id[U];                                  // keys: bits that ascend as scores fall, and ids
 #pragma unroll
-  for (int u = 0; u < kMaxGroups / 64; ++u) v[u] = u * 64 + lane < ngroups ? best[(size_t)i * ngroups + u * 64 + lane] : 0u;
-  uint32_t bar = 0;                                      // the largest value that topk groups reach
-  if (topk == 1) {                                       // the best of all
+  for (int u = 0; u < U; ++u) {
+    const uint64_t key = u * 64 + lane < ngroups ? best[(size_t)i * ngroups + u * 64 + lane] : ~0ull;
+    v[u] = (uint32_t)(key >> 32);
+    id[u] = (uint32_t)key;
+  }
+  auto count = [&](auto&& has) {
+    int n = 0;
 #pragma unroll
-    for (int u = 0; u < kMaxGroups / 64; ++u) bar = max(bar, v[u]);
+    for (int u = 0; u < U; ++u) n += __popcll(__ballot(has(u)));
+    return n;
+  };
+  // the smallest value that topk groups are within, or any that just topk are
+  uint32_t bar = 0, within = 0;
+  bool found = false;
+  for (int bit = 31; bit >= 0 && !found; --bit) {
+    within = bar | ((1u << bit) - 1u);
+    const int n = count([&](int u) { return v[u] <= within; });
+    found = n == topk;
+    if (n < topk) bar |= 1u << bit;
+  }
+  uint32_t bar_id = 0;
+  if (found) {                                           // the last of these
+    uint32_t m = 0;
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) bar = max(bar, (uint32_t)__shfl_xor((int)bar, d));
-  } else
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t trial = bar | 1u << bit;
-    int reach = 0;
+    for (int u = 0; u < U; ++u) m = max(m, v[u] <= within ? v[u] : 0u);
+    bar = wave_max(m);
+    m = 0;
 #pragma unroll
-    for (int u = 0; u < kMaxGroups / 64; ++u) reach += __popcll(__ballot(v[u] >= trial));
-    if (reach >= topk) bar = trial;
+    for (int u = 0; u < U; ++u) m = max(m, v[u] == bar ? id[u] : 0u);
+    bar_id = wave_max(m);
+  } else {                                               // more than that are tied at the bar: the lowest id that enough of them are within
+    const int need = topk - count([&](int u) { return v[u] < bar; });
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t trial = bar_id | ((1u << bit) - 1u);
+      if (count([&](int u) { return v[u] == bar && id[u] <= trial; }) < need) bar_id |= 1u << bit;
+    }
   }
   if (lane == 0) {
-    bars[i] = (uint64_t)(~bar) << 32 | 0xffffffffu;      // (every id passes: which neuron of the group it is was not kept)
+    bars[i] = bar == ~0u ? ~0ull : (uint64_t)bar << 32 | bar_id;   // (~0: fewer groups have a score, everything passes)
     ccnt[(size_t)i * kCntPitch] = 0;
   }
 }
@@ -821,7 +848,7 @@ hipError_t launch_dense_topk(int B, int64_t N, int H, const float* h, const floa
   hipError_t e = B <= 32 ? SLIDE_SAMPLED(1, kGroupBest) : SLIDE_SAMPLED(2, kGroupBest);
 #undef SLIDE_SAMPLED
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(64), 0, s, ceil_div(ns, 32), (const uint32_t*)zs, topk, bars, ccnt);
+  hipLaunchKernelGGL(dense_bar_kernel, dim3(B), dim3(64), 0, s, ceil_div(ns, 32), (const uint64_t*)zs, topk, bars, ccnt);
   // The bar is about the r-th best of the sampled neurons: r = topk and a few more, those drawn until topk of the g groups
   // have one (64 of 256: 74).  About r * nc / ns of nc neurons reach it, spread like a sum of r exponentials: with that
   // mean at cap * r / (r + 4 sqrt(r) + 16) -- a 21st of the candidate buffer for topk = 1, 0.59 of it for 64 -- chance

@@ -62,6 +62,16 @@ __device__ __forceinline__ uint32_t wave_incl_scan_add(uint32_t v) {
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan_add(v), 63);
 }
+// Largest of the wave, returned in every lane (wave-uniform).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  v = max(v, dpp_u32<kDppRowShr + 1>(0u, v));
+  v = max(v, dpp_u32<kDppRowShr + 2>(0u, v));
+  v = max(v, dpp_u32<kDppRowShr + 4>(0u, v));
+  v = max(v, dpp_u32<kDppRowShr + 8>(0u, v));
+  v = max(v, dpp_u32<kDppRowBcast15, 0xa>(0u, v));
+  v = max(v, dpp_u32<kDppRowBcast31, 0xc>(0u, v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   v |= dpp_u32<kDppRowShr + 1>(0u, v);
   v |= dpp_u32<kDppRowShr + 2>(0u, v);

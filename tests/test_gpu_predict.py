@@ -192,6 +192,23 @@ def test_predict_all_costs_the_same_in_any_order_of_the_ids(layout, batch, H):
     _cost_of_scores("order " + layout, N, batch, H, bias)
 
 
+@pytest.mark.parametrize("batch,H", [(8, 32), (8, 40), (100, 32)])
+@pytest.mark.parametrize("layout", ["equal", "untouched", "two-values", "ten-values"])
+def test_predict_all_costs_the_same_with_tied_scores(layout, batch, H):
+    """Scores that many neurons share, as before training or for a sample whose activations are zero: ties go to the lower
+    id, and of a tie at the bar only the lower ids pass it."""
+    N = 670_091
+    rng = np.random.default_rng(4)
+    bias = np.zeros(N, np.float32)
+    if layout == "untouched":
+        bias[rng.integers(0, N, 5000)] = -1e-3 * rng.random(5000)
+    elif layout == "two-values":
+        bias[:] = rng.integers(0, 2, N)
+    elif layout == "ten-values":
+        bias[:] = rng.integers(0, 10, N)
+    _cost_of_scores("ties " + layout, N, batch, H, bias)
+
+
 def _cost_of_scores(name, N, batch, H, bias):
     """Lists and time of a prediction whose scores are the biases (W2 = 0), against the same scores in random order."""
     _say("dense predict cost", name, N, batch, H)
@@ -219,7 +236,7 @@ def _cost_of_scores(name, N, batch, H, bias):
         spread = timed(np.random.default_rng(3).standard_normal(N).astype(np.float32), topk)
         here = timed(bias, topk)
         _say("   topk", topk, "us: %.0f in random order, %.0f so" % (1e3 * spread, 1e3 * here))
-        assert here < 3 * spread + 0.3                     # (an overflowing sample: 5 ms and more)
+        assert here < 5 * spread + 0.5                     # (an overflowing sample: 15 ms)
     model.destroy()
 
 
