@@ -52,19 +52,20 @@ __device__ __forceinline__ void spmm_sample_staged(const SpmmArgs& a, int i, int
       sv[tid] = bad ? 0.f : v;
     }
     __syncthreads();
-    for (int q0 = 0; q0 < cnt; q0 += 4 * step) {          // four row pieces per thread in flight
+    // (the four indices in one go, and little to work out before the first row is asked for)
+    for (int q0 = row; q0 - row < cnt; q0 += 4 * step) {  // four row pieces per thread in flight
+      int k[4];
       float4 w[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int q = q0 + u * step + row;
-        const int k = row < step && q < cnt ? sk[q] : -1;
-        w[u] = k >= 0 ? *(const float4*)(W1 + (size_t)k * H + 4 * piece) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      for (int u = 0; u < 4; ++u) k[u] = sk[min(q0 + u * step, cnt - 1)];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int q = q0 + u * step + row;
-        if (row < step && q < cnt) ((float4*)stage)[q * H4 + piece] = w[u];
+        w[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k[u] >= 0 && row < step && q0 + u * step < cnt) w[u] = *(const float4*)(W1 + (size_t)k[u] * H + 4 * piece);
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (row < step && q0 + u * step < cnt) ((float4*)stage)[(q0 + u * step) * H4 + piece] = w[u];
     }
     if (kk >= 0) {
       // order: against the last valid feature before this one
