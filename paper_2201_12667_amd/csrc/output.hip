@@ -3,6 +3,7 @@
 // (paper Section 2.1: activations are computed for the retrieved neurons only; Section 3.6: the
 // first layer is fed by index/value arrays, the second by the first layer's activations).
 #include "slide_internal.h"
+#include "launch_rules.h"
 #include "spmm.h"
 #include "topk.h"
 #include "transpose.h"
@@ -38,7 +39,7 @@ hipError_t launch_spmm_relu(int B, const SpmmArgs& a, Ctrl* ctrl, hipStream_t s)
 // workers): they depend on the lookup only, like the logits, and are latency-bound where the logit
 // workers are bandwidth-bound.
 // ---------------------------------------------------------------------------------------------
-constexpr int kForwardThreads = 512;
+constexpr int kForwardThreads = kForwardWaves * 64;
 
 // CH: float4 per lane, the first F of which lie within the vector for every lane.
 // With saturated buckets (1,024 samples, 6.5 M pairs of 200 coordinates) this is bound by the latency of the rows: nearly
@@ -175,13 +176,8 @@ __global__ __launch_bounds__(kForwardThreads) void forward_kernel(ActiveDev ad, 
   // critical path) before the active-set tiles.
   const int k = blockIdx.x;
   if (k < nworkers) {
-    // With several items per wave the workers would hold every slot of the machine until the end and
-    // the tiles would run after them: then the last workers leave at once and make room.
     const int items = max_items(ctrl, ad.par) * ad.B;   // (upper bound: samples differ in length)
-    // (more of them when the tiles are many for the amount of logit work)
-    const int ntiles = t1.ntiles + t2.ntiles;
-    const int workers = (ntiles == 0 || items <= 2 * nworkers * (kForwardThreads / 64)) ? nworkers
-                        : (items < 20 * ntiles ? nworkers * 2 / 3 : nworkers * 5 / 6);
+    const int workers = logit_workers(nworkers, items, t1.ntiles + t2.ntiles, ad.nxcd);
     if (k >= workers) return;
 #define SLIDE_ITEMS(C_, F_) forward_items<LPR, C_, F_>(ad, H, h, W2, b2, z, partials, ctrl, k, workers)
     if (H == LPR * CH * 4) SLIDE_ITEMS(CH, CH);
