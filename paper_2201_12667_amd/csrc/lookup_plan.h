@@ -40,15 +40,16 @@ inline LookupPlan lookup_plan(int L, int H, int NH, int NWpad, bool budgeted, bo
   };
   LookupPlan p = {budgeted ? NWpad : words_in(limit), 2, 0};
   // two workgroups to a compute unit, where that takes at most four segments instead of one
+  size_t room = limit;                                    // (of a workgroup; half of it then, also for the ranks)
   if (rounds && !budgeted) {
     const int half = words_in(limit / 2);
     if (half > 0) {
       const int segments = (NWpad + half - 1) / half;
-      if (segments <= 4) p.segw = ((NWpad + segments - 1) / segments + 31) / 32 * 32;
+      if (segments <= 4) { p.segw = ((NWpad + segments - 1) / segments + 31) / 32 * 32; room = limit / 2; }
     }
   }
   // words to a thread: the fewest that let all threads together take the segment at once (and its ranks fit)
-  while (p.lcw < 5 && ((p.segw >> p.lcw) > kLookupThreads || lookup_lds(L, H, NH, budgeted, p.segw, p.lcw) > limit)) ++p.lcw;
+  while (p.lcw < 5 && ((p.segw >> p.lcw) > kLookupThreads || lookup_lds(L, H, NH, budgeted, p.segw, p.lcw) > room)) ++p.lcw;
   p.bytes = lookup_lds(L, H, NH, budgeted, p.segw, p.lcw);
   if (p.segw < 32 || p.bytes > limit) p.segw = 0;
   return p;

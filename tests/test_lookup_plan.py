@@ -80,3 +80,16 @@ def test_every_accepted_layer_has_a_segment(lib, TW, rounds):
             segw, lcw, used = _plan(lib, L, H, NH, words, False, rounds)
             assert segw % 32 == 0 and segw >= min(words, 32 if rounds else 1024), (L, H, NH, words, segw)
             assert used <= LDS and 2 <= lcw <= 5
+
+
+@pytest.mark.parametrize("rounds_of", [1, 2, 3, 4])
+def test_two_workgroups_share_a_compute_unit(lib, rounds_of):
+    """Batches of more than one round: up to four segments of half of the LDS, ranks of their words and all."""
+    for L, H, NH in _shapes():
+        half = next((w for w in range(LDS // 8, 0, -32) if _plan(lib, L, H, NH, 4 * w, False, True)[0] <= w), 0) // 32 * 32
+        for per_segment in range(max(32, half - 1024), half + 1, 32):
+            words = per_segment * rounds_of
+            if lib.accepted(L, H, words // 32, NH, 1024) > LDS:
+                continue                                       # (refused)
+            segw, lcw, used = _plan(lib, L, H, NH, words, False, True)
+            assert segw <= half and used <= LDS // 2, (L, H, NH, words, segw, lcw, used)
