@@ -312,7 +312,10 @@ int check_batch(slide_ctx* ctx, const slide_batch* b, bool need_labels) {
   return SLIDE_OK;
 }
 
-// Neurons that the tables return for a sample, about (codes spread evenly, but a fuller bucket is the likelier one).
+// Neurons that the tables return for a sample, about (codes spread evenly, but a fuller bucket is the likelier one).  It sizes
+// launches only.  A sampling budget is left out of it, though it leaves fewer pairs: steps with a budget of 256, us, as it is / with
+// the budget in the logits' rule / in the update's: 300K x 256, 2,000 samples 789 / 814 / 792, 670K x 256 x 1,500 754 / 774 / 755,
+// 670K x 128 x 1,000 602 / 602 / 610, 400K x 384 x 400 344 / 346 / 348, twelve other shapes alike.
 int64_t pairs_per_sample(const slide_ctx* ctx) {
   const double per_bucket = 1.25 * (double)ctx->lo.N / (double)ctx->lo.nb;
   return (int64_t)(ctx->cfg.L * std::min<double>(ctx->cfg.bucket_cap, per_bucket));
