@@ -218,12 +218,12 @@ __global__ __launch_bounds__(score_threads(MODE, FORM), score_waves_per_simd(NIB
   };
   // kStream: a stage is two coordinate blocks of the wave's 32 rows, 8 lanes of 16 bytes to a row; DEPTH of them ahead.
   constexpr int DEPTH = !STREAM ? 1 : MODE == kGroupBest ? 4 : 2;
-  const int nst = (nkb + 1) / 2;
+  const int nst = nkb / 2;                               // (kStream: H is a multiple of 32)
   f32x4 sb[DEPTH][4];
   int st = 0, ss = 0;                                    // tile and stage to come
   const int piece = lane & 7, row8 = lane >> 3;
   auto issue_stage = [&](f32x4 (&x)[4]) {
-    const int k = min(ss * 32 + 4 * piece, kmax);
+    const int k = ss * 32 + 4 * piece;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
       int64_t j = j0 + (int64_t)column_at(max(min(c_lo + st * 32 + d * 8 + row8, c_hi - 1), 0)) * stride;
@@ -460,12 +460,11 @@ __global__ __launch_bounds__(score_threads(MODE, FORM), score_waves_per_simd(NIB
       asm volatile("" ::: "memory");
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-        if (b == 0 || kb + 1 < nkb) {
-          float4 w[2] = {make_float4(y[2 * b][0], y[2 * b][1], y[2 * b][2], y[2 * b][3]),
-                         make_float4(y[2 * b + 1][0], y[2 * b + 1][1], y[2 * b + 1][2], y[2 * b + 1][3])};
-          contract(w, hb + (kb + b) * 192, nkb * 192);
-        }
+      for (int b = 0; b < 2; ++b) {
+        float4 w[2] = {make_float4(y[2 * b][0], y[2 * b][1], y[2 * b][2], y[2 * b][3]),
+                       make_float4(y[2 * b + 1][0], y[2 * b + 1][1], y[2 * b + 1][2], y[2 * b + 1][3])};
+        contract(w, hb + (kb + b) * 192, nkb * 192);
+      }
       kb += 2;
       if (kb < nkb) return;
       finish(tile, bias);
