@@ -38,8 +38,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* sm, ui
   return base + inc - v;
 }
 
-// Position of bitmap word w of sample i in the spill copy of the bitmaps (used only when a bitmap
-// does not fit the LDS in one piece): tile-major, [tile][sample][TW
+// Position of bitmap word w of sample i in the copy of the bitmaps that the row lists are built from (where a
+// call builds them so): tile-major, [tile][sample][TW
 // words], so that the transposition reads one contiguous block per tile; the per-sample writer
 // pays the stride instead (full 4*TW-byte records).
 __device__ __forceinline__ size_t act_index(const ActiveDev& ad, int i, int w) {
@@ -199,7 +199,7 @@ __device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __po
 // thread, half of the LDS each), one of them at work while the other waits, and the hidden activations come from a launch of
 // their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
 // pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
-constexpr int kLookupArgs = 400;       // bytes of the kernel's arguments
+constexpr int kLookupArgs = 396;       // bytes of the kernel's arguments
 constexpr int kBucketAhead = 8;        // entries of a bucket that a lane requests at once
 
 template <bool ROUNDS, bool BUDGET, int KIND>
@@ -640,6 +640,8 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
     __syncthreads();                                     // (before the next segment is cleared)
   }
 }
+
+static_assert(kernarg<decltype(lookup_union_kernel<false, false, SLIDE_HASH_DWTA>)>::bytes == kLookupArgs, "touch_kernarg reads them all");
 
 hipError_t active_setup_attributes(size_t* lds_limit_out) {
   int dev = 0, lim = 0;

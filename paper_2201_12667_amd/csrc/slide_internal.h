@@ -132,8 +132,8 @@ struct ActiveDev {
   int nxcd;                        // accelerator dies whose workgroups alternate in launch order (1: unknown)
   int budget, fill;                // sampling budget of this call (0 = none) and its fill option
   uint32_t sample_seed, step;      // keys of the counter-based generator: seed, number of the step being run
-  uint32_t* act;                   // [NT][B][TW] the samples' bitmaps, tile-major: written when a bitmap exceeds the LDS
-  int write_act;                   // ... or when the row lists are to be built from the bitmaps (!= 0)
+  uint32_t* act;                   // [NT][B][TW] the samples' bitmaps, tile-major: written when the row lists are to be
+  int write_act;                   // built from them (!= 0)
   uint32_t* rankT;                 // [NT+1][B] active neurons of the sample below the tile (last row: |AS_i|)
   int32_t* cnt;                    // [B] |AS_i|
   int32_t* ny;                     // [B] distinct labels

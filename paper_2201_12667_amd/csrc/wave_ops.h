@@ -26,6 +26,17 @@ __device__ __forceinline__ float dpp_f32(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
+// Bytes of the arguments of a kernel (its function type).
+template <class F> struct kernarg;
+template <class... A> struct kernarg<void(A...)> {
+  static constexpr int layout() {
+    int n = 0;
+    ((n = (n + (int)alignof(A) - 1) / (int)alignof(A) * (int)alignof(A) + (int)sizeof(A)), ...);
+    return n;
+  }
+  static constexpr int bytes = layout();
+};
+
 // Reads one word of every 64-byte line of the kernel's arguments (BYTES of them), all at once: they come from memory, at
 // 500 to 700 clocks for the first read of a line by a compute unit, and the compiler reads most of them where they are used.
 template <int BYTES>
@@ -92,17 +103,6 @@ __device__ __forceinline__ uint32_t group_incl_scan_add(uint32_t v, int G) {
     const uint32_t t = __shfl_up(v, d, G);
     if ((lane & (G - 1)) >= d) v += t;
   }
-  return v;
-}
-// The same for G <= 8 (1, 2, 4 or 8), in register moves only.
-__device__ __forceinline__ uint32_t small_group_incl_scan_add(uint32_t v, int G) {
-  const int p = threadIdx.x & (G - 1);
-  uint32_t t = dpp_u32<kDppRowShr + 1>(0u, v);
-  if (p >= 1) v += t;
-  t = dpp_u32<kDppRowShr + 2>(0u, v);
-  if (p >= 2) v += t;
-  t = dpp_u32<kDppRowShr + 4>(0u, v);
-  if (p >= 4) v += t;
   return v;
 }
 // Sum over aligned groups of G lanes, valid in the LAST lane of each group.
