@@ -8,6 +8,7 @@
 //                 It also emits the compact ascending id list per sample + the labels' slots and hands
 //                 the sample its forward work items (chunks of kChunk active neurons).
 #include "slide_internal.h"
+#include "launch_rules.h"
 #include "lookup_plan.h"
 #include "spmm.h"
 #include "wave_ops.h"
@@ -200,7 +201,6 @@ __device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __po
 // their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
 // pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
 constexpr int kLookupArgs = 396;       // bytes of the kernel's arguments
-constexpr int kBucketAhead = 8;        // entries of a bucket that a lane requests at once
 
 template <bool ROUNDS, bool BUDGET, int KIND>
 __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_kernel(
@@ -403,13 +403,11 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
   };
 
   // Buckets: 2^lg lanes to a table, in one go where the tables allow (then a lane keeps its first eight entries for
-  // the passes to come).  What is beyond eight entries a lane is read by whole waves, four buckets at a time, where few
-  // buckets are that long (the chain of reads of one long bucket would hold up all: 4 samples of 670K neurons 33 us a call, 39 by
-  // the table's lanes), and by the table's lanes where many are (214 tables of 36 entries a bucket, 641 samples 55 us, 92 by waves).
+  // the passes to come).  What is beyond eight entries a lane is read by whole waves, four buckets at a time, or, where
+  // that takes longer, by the tables' lanes (tables_of_wave).
   const int G = 1 << lg, tstep = nthr >> lg;
   const bool once = ad.L <= tstep;
   const int direct = kBucketAhead * G;
-  constexpr uint32_t kFewLong = 64;                      // (four buckets for each wave)
   int j[kBucketAhead];
   uint32_t entries = 0;                                  // (of the buckets this thread leads)
   uint32_t n = 0;                                        // active neurons in the segments so far
@@ -458,7 +456,7 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         for (int u = 0; u < kBucketAhead; ++u) f(j[u]);
       }
     };
-    // ... what of them is beyond the lanes' first: by the lanes of the table, or, where few buckets are that long, by whole waves
+    // ... what of them is beyond the lanes' first: by the lanes of the table, or by whole waves, a wave the long ones of `per` tables
     auto for_rest = [&](auto&& f) __attribute__((always_inline)) {
       for (int t = me >> lg; t < ad.L; t += tstep) {
         const int most = (int)blen[t];
@@ -475,10 +473,9 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         }
       }
     };
-    auto for_long = [&](auto&& f) __attribute__((always_inline)) {
-      const int wave = __builtin_amdgcn_readfirstlane(me >> 6);
-      for (int t0 = 64 * wave; t0 < ad.L; t0 += nthr) {
-        unsigned long long left = __ballot(t0 + lane < ad.L && (int)blen[min(t0 + lane, ad.L - 1)] > direct);
+    auto for_long = [&](int per, auto&& f) __attribute__((always_inline)) {
+      for (int t0 = __builtin_amdgcn_readfirstlane(me >> 6) * per; t0 < ad.L; t0 += nthr / 64 * per) {
+        unsigned long long left = __ballot(lane < per && t0 + lane < ad.L && (int)blen[min(t0 + lane, ad.L - 1)] > direct);
         while (left) {
           uint32_t from[4];
           int rest[4], most = 0;
@@ -511,12 +508,11 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
       if (lane == 0 && entries) atomicAdd(&sm[18], entries);
     }
     __syncthreads();
-    const uint32_t nlong = sm[19];
-    if (nlong) {
-      if (nlong <= kFewLong) for_long(set_bit);
-      else for_rest(set_bit);
-      __syncthreads();
-    }
+    const int nlong = __builtin_amdgcn_readfirstlane((int)sm[19]), per = nlong == 0 ? -1 :
+        tables_of_wave(ad.L, ad.C, lg, nlong, __builtin_amdgcn_readfirstlane((int)sm[18]));
+    if (per > 0) for_long(per, set_bit);
+    if (per == 0) for_rest(set_bit);
+    if (per >= 0) __syncthreads();
     if constexpr (BUDGET) apply_budget();
 
     // A thread takes 2^lcw consecutive words: their population, its exclusive prefix over the threads, and from these the
@@ -594,10 +590,8 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
         if (r < span) ad.as_ids[base_i + (int)rank_of(r)] = id;
       };
       for_direct(true, place);
-      if (nlong) {
-        if (nlong <= kFewLong) for_long(place);
-        else for_rest(place);
-      }
+      if (per > 0) for_long(per, place);
+      if (per == 0) for_rest(place);
     } else {
       // (drawn neurons are nowhere but in the bitmap: every thread lists what its words hold)
       for (int c = me; c < nchunk; c += nthr) {

@@ -9,6 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "launch_rules.h"
 extern "C" int workers(int nworkers, int items, int ntiles, int nxcd) { return slide::logit_workers(nworkers, items, ntiles, nxcd); }
+extern "C" int tables_of_wave(int L, int C, int lg, int nlong, int entries) { return slide::tables_of_wave(L, C, lg, nlong, entries); }
 """
 
 
@@ -34,3 +35,42 @@ def test_logit_workers_fill_the_dies_evenly(lib, cus):
                     assert stay == nworkers
                 else:
                     assert stay < nworkers
+
+
+def _lanes(L):
+    lg = 0
+    while lg < 6 and L << (lg + 1) <= 1024:
+        lg += 1
+    return lg
+
+
+@pytest.mark.parametrize("L", [1, 2, 15, 16, 17, 50, 64, 65, 68, 100, 200, 400, 512, 513, 1000, 1024, 1025, 4000])
+def test_long_buckets_are_shared_out(lib, L):
+    """Every table belongs to one wave, and where long buckets go by waves none has many more than its share of them."""
+    lg = _lanes(L)
+    for C in (9 << lg, 16 << lg, 256, 1024):
+        for nlong in sorted({1, min(L, 5), min(L, 64), min(L, 65), max(1, L // 2), L}):
+            for mean in {(8 << lg) + 1, (C + (8 << lg)) // 2, C}:
+                if not (8 << lg) < mean <= C:
+                    continue                                   # (no long buckets)
+                per = lib.tables_of_wave(L, C, lg, nlong, min(nlong * mean, 2 ** 31 - 1))
+                assert 0 <= per <= 64 and (per > 0 or nlong > 64)
+                if per == 0:
+                    continue
+                assert 16 * per >= min(L, 1024)
+                spread = [t * L // nlong for t in range(nlong)]
+                waves = [0] * 16
+                for t in spread:
+                    waves[t // per % 16] += 1
+                assert max(waves) <= max(8, 2 * (nlong // 16 + 1))
+
+
+# tables, capacity, long buckets, entries of a sample; what was measured to be the faster
+@pytest.mark.parametrize("L,C,nlong,entries,waves", [
+    (68, 256, 68, 68 * 146, True), (68, 256, 60, 60 * 200, True), (50, 256, 50, 50 * 195, True), (100, 512, 100, 100 * 390, True),
+    (150, 64, 150, 150 * 48, False), (200, 64, 200, 200 * 48, False), (200, 256, 200, 200 * 195, True), (214, 64, 200, 214 * 36, False),
+    (300, 32, 250, 300 * 19, False), (300, 128, 300, 300 * 97, True), (400, 32, 300, 400 * 19, False), (400, 64, 400, 400 * 48, False),
+    (400, 256, 400, 400 * 195, True), (600, 32, 600, 600 * 19, False), (600, 128, 600, 600 * 97, True), (1000, 16, 800, 1000 * 10, False),
+    (1000, 64, 1000, 1000 * 43, True), (1000, 200, 1000, 1000 * 175, True), (2000, 64, 2000, 2000 * 43, True)])
+def test_long_buckets_go_the_faster_way(lib, L, C, nlong, entries, waves):
+    assert (lib.tables_of_wave(L, C, _lanes(L), nlong, entries) > 0) == waves
