@@ -48,4 +48,18 @@ __attribute__((always_inline)) inline constexpr int tables_of_wave(int L, int C,
   return per;
 }
 
+// Whether the update launch streams about `rows` weight rows of H floats past the caches, like their moments (aligned: to 128
+// bytes).  Rows that together exceed the memory-side cache (256 MB) do not stay there from the logits to the update, nor from one
+// step to the next.  That takes whole lines, parts of which would come and go several times, and from 512 floats on, where a wave
+// takes a row, lanes that are all at work.  Steps, us, cached / streamed: 670K x 128, 642K rows 944 / 930, x 160, 540K 769 / 742,
+// 600K x 256, 358K 596 / 586, x 320, 539K 1,237 / 1,207, x 192, 579K 1,014 / 997, 400K x 480, 331K 1,022 / 1,017; 300K x 384, 178K (261 MB)
+// 431 / 436.  Parts of lines: 353K x 356, 170K 436 / 481, 650K x 300, 220K 541 / 572, 500K x 200, 480K 973 / 1,032, 670K x 120,
+// 668K 1,640 / 1,677.  Longer rows: 250K x 544, 208K 878 / 997, x 672 978 / 1,056, x 928 1,258 / 1,297; x 1,024 1,344 / 1,341 (the launch
+// alone, 190K rows, 586 / 551), 100K rows (391 MB) 639 / 654.
+inline bool streams_weights(double rows, int H, bool aligned) {
+  const double mb = rows * H * 4 / (1 << 20);
+  if (!aligned || H % 32 != 0) return false;
+  return H <= 512 ? mb > 288 : H % 1024 == 0 && mb > 512;
+}
+
 }  // namespace slide

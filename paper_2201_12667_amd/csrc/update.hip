@@ -8,6 +8,7 @@
 // and no atomics.  V is the hidden activations (output layer) or their gradient (input layer),
 // small enough to stay cache resident.  Rows that are not listed are never touched.
 #include "slide_internal.h"
+#include "launch_rules.h"
 #include "wave_ops.h"
 
 #include <algorithm>
@@ -354,14 +355,14 @@ static hipError_t launch_up(int H, RowUpdate out, const RowUpdate& in, const Fin
   // Workgroups for about one and a half work items (64 / LPR rows) a wave, 16 to 64 per compute unit (it holds four of
   // them): the machine then works its way through the tiles in order and its last round is short.  Launch, us, 8 / 16 / 32 /
   // 64 / 128 workgroups per compute unit: 670K x 128, 255K rows touched 153 / 142 / 143 / 145 / 159; x 256, 635K rows 921 / 828 /
-  // 895 / 813 / 805; 600K x 512, 410K rows 956 / 911 / 904 / 853 / 776 (64 and 128 are alike over more runs); 167K x 128, 65K rows 43.8 / 42.7 / 42.3 / 45.5 / 52.8.
-  // Weight rows that together exceed the memory-side cache (256 MB) are streamed, too: what the logits have left of them there
-  // is gone by now (635K rows of 256 813 -> 783 us, 190K of 1,024 586 -> 551; rows that do fit: 255K of 128 145 -> 151).
+  // 895 / 813 / 805; 600K x 512, 410K rows 956 / 911 / 904 / 853 / 776; 167K x 128, 65K rows 43.8 / 42.7 / 42.3 / 45.5 / 52.8.  At most
+  // 64: only layers like the second and third would take more, and the launch that gained most in that run gains little in
+  // others; whole steps with 64 / 128: 600K x 512, 600 samples 3,008 / 2,991, 670K x 256 x 2,048 1,468 / 1,462, 670K x 512 x 300 794 / 789.
   const double items = rows * LPR / 64;
   const int per_cu = items < 4096 ? 8 : (int)std::min(64.0, std::max(16.0, std::ceil(items / (6.0 * num_cus))));
   out.nblocks = per_cu * num_cus;
   const dim3 grid(fin.nblocks + out.nblocks), block(kUpdateThreads);
-  if (rows * H * 4 > (double)(256 << 20)) hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, true>), grid, block, 0, s, H, out, in, fin, ad);
+  if (streams_weights(rows, H, ((uintptr_t)out.W & 127) == 0)) hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, true>), grid, block, 0, s, H, out, in, fin, ad);
   else hipLaunchKernelGGL((update_kernel<LPR, CH, UNR, false>), grid, block, 0, s, H, out, in, fin, ad);
   return hipGetLastError();
 }

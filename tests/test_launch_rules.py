@@ -10,6 +10,7 @@ SHIM = """
 #include "launch_rules.h"
 extern "C" int workers(int nworkers, int items, int ntiles, int nxcd) { return slide::logit_workers(nworkers, items, ntiles, nxcd); }
 extern "C" int tables_of_wave(int L, int C, int lg, int nlong, int entries) { return slide::tables_of_wave(L, C, lg, nlong, entries); }
+extern "C" int streams_weights(double rows, int H, int aligned) { return slide::streams_weights(rows, H, aligned != 0); }
 """
 
 
@@ -19,7 +20,9 @@ def lib(tmp_path_factory):
     (d / "shim.cpp").write_text(SHIM)
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "paper_2201_12667_amd", "csrc"),
                     str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
-    return C.CDLL(str(d / "shim.so"))
+    lib = C.CDLL(str(d / "shim.so"))
+    lib.streams_weights.argtypes = [C.c_double, C.c_int, C.c_int]
+    return lib
 
 
 @pytest.mark.parametrize("cus", [256, 32, 304, 80])
@@ -74,3 +77,15 @@ def test_long_buckets_are_shared_out(lib, L):
     (1000, 64, 1000, 1000 * 43, True), (1000, 200, 1000, 1000 * 175, True), (2000, 64, 2000, 2000 * 43, True)])
 def test_long_buckets_go_the_faster_way(lib, L, C, nlong, entries, waves):
     assert (lib.tables_of_wave(L, C, _lanes(L), nlong, entries) > 0) == waves
+
+
+# rows, their length; whether streaming them was measured to be faster
+@pytest.mark.parametrize("rows,H,faster", [
+    (642_000, 128, True), (540_000, 160, True), (358_000, 256, True), (635_000, 256, True), (539_000, 320, True), (579_000, 192, True),
+    (331_000, 352, True), (331_000, 480, True), (582_000, 512, True), (270_000, 512, True), (208_000, 1024, True),
+    (255_000, 128, False), (178_000, 384, False), (100_000, 1024, False),                         # the cache holds them
+    (170_000, 356, False), (220_000, 300, False), (480_000, 200, False), (668_000, 120, False),   # parts of lines
+    (208_000, 544, False), (208_000, 640, False), (208_000, 672, False), (208_000, 768, False), (208_000, 928, False)])
+def test_weights_are_streamed_where_that_pays(lib, rows, H, faster):
+    assert bool(lib.streams_weights(rows, H, 1)) == faster
+    assert not lib.streams_weights(rows, H, 0)
