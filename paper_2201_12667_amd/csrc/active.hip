@@ -200,14 +200,14 @@ __device__ __forceinline__ int popc4(const uint4& w) { return __popc(w.x) + __po
 // thread, half of the LDS each), one of them at work while the other waits, and the hidden activations come from a launch of
 // their own: 1,024 samples x 254K neurons x 50 tables 89 -> 62 us.  (2,048 samples x 670K x 400 tables 205 -> 194 in two
 // pieces: those wait for 1.6 M buckets scattered over 1.5 GB.)
-constexpr int kLookupArgs = 396;       // bytes of the kernel's arguments
+constexpr int kLookupArgs = 412;       // bytes of the kernel's arguments
 
 template <bool ROUNDS, bool BUDGET, int KIND>
 __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_kernel(
     ActiveDev ad, HashDev hd, const float* __restrict__ h, SpmmArgs sp, const uint32_t* __restrict__ off,
     const int32_t* __restrict__ ids, uint32_t nb, uint32_t* __restrict__ codes,
     const int32_t* __restrict__ y_indptr, const int32_t* __restrict__ y_indices, int include_labels,
-    int32_t* __restrict__ ncand, Ctrl* ctrl, int segw, int lg, int lcw) {
+    int32_t* __restrict__ ncand, Ctrl* ctrl, int segw, int lg, int lcw, LongRule lr) {
   // (BUDGET: a sampling budget applies; the whole bitmap is one segment then)
   extern __shared__ uint32_t lds[];
   uint32_t* bm = lds;                    // [segw] bitmap segment
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
     }
     __syncthreads();
     const int nlong = __builtin_amdgcn_readfirstlane((int)sm[19]), per = nlong == 0 ? -1 :
-        tables_of_wave(ad.L, ad.C, lg, nlong, __builtin_amdgcn_readfirstlane((int)sm[18]));
+        tables_of_wave(lr, lg, nlong, __builtin_amdgcn_readfirstlane((int)sm[18]));
     if (per > 0) for_long(per, set_bit);
     if (per == 0) for_rest(set_bit);
     if (per >= 0) __syncthreads();
@@ -672,7 +672,7 @@ hipError_t launch_lookup_union(const ActiveDev& ad, const HashDev& hd, const flo
                 : rounds ? (dwta ? lookup_union_kernel<true, false, SLIDE_HASH_DWTA> : lookup_union_kernel<true, false, SLIDE_HASH_SIMHASH>)
                          : (dwta ? lookup_union_kernel<false, false, SLIDE_HASH_DWTA> : lookup_union_kernel<false, false, SLIDE_HASH_SIMHASH>);
   hipLaunchKernelGGL(kernel, dim3(ad.B), dim3(kLookupThreads), plan.bytes, s, ad, hd, h, sp, td.off, td.ids, td.nb,
-                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, plan.segw, lg, plan.lcw);
+                     codes, y_indptr, y_indices, include_labels, ncand, ctrl, plan.segw, lg, plan.lcw, long_rule(ad.L, ad.C, lg));
   return hipGetLastError();
 }
 

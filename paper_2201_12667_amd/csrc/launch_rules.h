@@ -1,6 +1,9 @@
 // Rules that size launches, apart from the kernels so that they can be checked without a GPU (constexpr: host and device).
 #pragma once
 
+#include <algorithm>
+#include <cstdint>
+
 namespace slide {
 
 constexpr int kForwardWaves = 8;          // waves of a logit workgroup
@@ -26,26 +29,30 @@ constexpr int kBucketAhead = 8;           // entries of a bucket that a lane of 
 // `nlong` buckets that have more, of L tables, at most C entries each, `entries` in all.
 //   0: by the lanes of their tables, four entries each at a time.  All buckets at once, but a lane's reads are a chain, and from 512
 //      tables on the lanes of an instruction ask for as many lines.
-//   else: by waves, four buckets of 128 entries at a time; a wave takes the long ones of that many tables, about four, as long as
-//      there are waves (fewer full ones are faster than more: 4 samples of 670K neurons, a few long buckets each, 33.1 us a call;
-//      33.7 with the tables spread evenly).
-// Few long buckets (four to a wave) go by waves: by lanes the call above takes 39 us.  More: what takes fewer steps, an idle half
-// step for each four buckets of a wave; the longest bucket is taken for twice the mean.  Retrievals, us, by lanes / by waves:
-// 400 tables of up to 32 (SimHash) 49.7 / 61.3, of 64 70.6 / 74.0, of 256 194 / 152, 400 of 670K x 128 in a few directions, up to 128
-// entries 109 / 93, up to 256 169 / 120, 200 of 64 54.0 / 58.1, of 256 128 / 117, 68 of 256 69 / 63, 1,000 of 16 82 / 114, of 64 203 / 164.
-// (Before, up to 64 long ones were shared out by 64 tables to a wave, one wave for all of them with 68 tables: 94 us a call
-// that takes 47, and by lanes beyond that.)
-__attribute__((always_inline)) inline constexpr int tables_of_wave(int L, int C, int lg, int nlong, int entries) {
-  if (nlong > 64) {
-    const int twice = 2 * (entries / nlong), rest = (twice < C ? twice : C) - (kBucketAhead << lg);
-    const int lanes_go = 2 * ((rest + (4 << lg) - 1) >> (lg + 2)) * ((L + (1024 >> lg) - 1) >> (10 - lg));   // (in half steps)
-    const int waves_go = (nlong + 63) / 64 * (1 + 2 * ((rest + 127) / 128));
-    if (lanes_go * (L < 512 ? 512 : L < 1024 ? L : 1024) <= waves_go * 512) return 0;
-  }
-  const int even = L < 1024 ? (L + 15) / 16 : 64;
-  int per = 64;
-  while (per > even && nlong * per > 4 * L) per = per / 2 > even ? per / 2 : even;
-  return per;
+//   else: by waves, four buckets of 128 entries at a time, a wave the long ones of that many tables: of a sixteenth of them, or, of 256
+//      tables and more of which few have one, an eighth (a few full waves are faster than many with a bucket each).
+// Few long buckets (64) go by waves: by lanes 4 samples of 670K neurons with a few each take 39 us for 33.  More go by lanes where
+// these take fewer steps of their longest bucket, which is taken for twice the mean, than waves take for all: three half steps for
+// each four buckets of a wave.  Retrievals, us, by lanes / by waves: 400 tables of up to 32 entries (SimHash) 49.7 / 61.3, of 64 70.6 / 74.0,
+// of 256 194 / 152, 400 of 670K x 128 in a few directions, up to 128 entries 109 / 93, up to 256 169 / 120, 200 of 64 54.0 / 58.1, of 256
+// 128 / 117, 68 of 256 69 / 63, 1,000 of 16 82 / 114, of 64 203 / 164.  (Before, up to 64 long ones were shared out by 64 tables to a
+// wave, one wave for all of them with 68 tables: 94 us a call that takes 47, and by lanes beyond that.)
+struct LongRule {
+  int even, few;       // tables of a wave
+  int all;             // from that many long buckets on they go by lanes, however long: none is longer than C
+  float steps;         // lanes' steps for an entry, in waves' steps for a bucket
+};
+inline LongRule long_rule(int L, int C, int lg) {
+  const int even = std::min((L + 15) / 16, 64), rounds = (L + (1024 >> lg) - 1) >> (10 - lg);
+  const float steps = 64.0f * (float)rounds * (float)std::max(512, std::min(L, 1024)) / (512.0f * (float)(6 << lg));
+  return {even, L >= 256 ? std::min(2 * even, 64) : even, (int)std::min(1e9f, (float)std::max(0, C - (kBucketAhead << lg)) * steps), steps};
+}
+// (All waves work this out, with one scalar unit for all of them; the whole rule in the kernel cost every call 0.3 to 0.8 us, most
+// of it for the scalar registers that it took.)
+__attribute__((always_inline)) inline constexpr int tables_of_wave(const LongRule r, int lg, int nlong, int entries) {
+  if (nlong <= 64) return r.few;
+  const float beyond = (float)(2 * entries - (kBucketAhead << lg) * nlong);
+  return nlong >= r.all || beyond * r.steps <= (float)nlong * (float)nlong ? 0 : r.even;
 }
 
 // Whether the update launch streams about `rows` weight rows of H floats past the caches, like their moments (aligned: to 128

@@ -9,7 +9,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SHIM = """
 #include "launch_rules.h"
 extern "C" int workers(int nworkers, int items, int ntiles, int nxcd) { return slide::logit_workers(nworkers, items, ntiles, nxcd); }
-extern "C" int tables_of_wave(int L, int C, int lg, int nlong, int entries) { return slide::tables_of_wave(L, C, lg, nlong, entries); }
+extern "C" int tables_of_wave(int L, int C, int lg, int nlong, int entries) { 
+  return slide::tables_of_wave(slide::long_rule(L, C, lg), lg, nlong, entries);
+}
 extern "C" int streams_weights(double rows, int H, int aligned) { return slide::streams_weights(rows, H, aligned != 0); }
 """
 
