@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
       }
       return at;
     };
-    if constexpr (!BUDGET) {
+    if (!BUDGET && (per < 0 || (per > 0 && 4 * __builtin_amdgcn_readfirstlane((int)n) < sw))) {
       // every entry puts itself in its place (those that several buckets hold more than once)
       auto place = [&](int id) __attribute__((always_inline)) {
         const uint32_t r = (uint32_t)id - (uint32_t)lo;
@@ -591,9 +591,11 @@ __global__ __launch_bounds__(kLookupThreads, ROUNDS ? 8 : 4) void lookup_union_k
       };
       for_direct(true, place);
       if (per > 0) for_long(per, place);
-      if (per == 0) for_rest(place);
     } else {
-      // (drawn neurons are nowhere but in the bitmap: every thread lists what its words hold)
+      // Drawn neurons are nowhere but in the bitmap, and what is beyond the lanes' first entries would have to be read again: every
+      // thread lists what its words hold.  (Retrievals, us, long buckets read again / listed: 1,000 tables of 200 entries 356 / 227, 400
+      // of 256 153 / 127, 254 of 20K neurons x 32 47.4 / 39.2.  Where none is long the lanes' entries are at hand, and listing takes longer,
+      // the tiny step 42.0 / 43.0, and so it does where a few are and the bitmap is nearly empty, 4 samples of 670K neurons 32.5 / 33.0.)
       for (int c = me; c < nchunk; c += nthr) {
         int slot = base_i + (int)rk[c];
         for (int k0 = 0; k0 < nq; k0 += 4) {

@@ -33,10 +33,11 @@ constexpr int kBucketAhead = 8;           // entries of a bucket that a lane of 
 //      tables and more of which few have one, an eighth (a few full waves are faster than many with a bucket each).
 // Few long buckets (64) go by waves: by lanes 4 samples of 670K neurons with a few each take 39 us for 33.  More go by lanes where
 // these take fewer steps of their longest bucket, which is taken for twice the mean, than waves take for all: three half steps for
-// each four buckets of a wave.  Retrievals, us, by lanes / by waves: 400 tables of up to 32 entries (SimHash) 49.7 / 61.3, of 64 70.6 / 74.0,
-// of 256 194 / 152, 400 of 670K x 128 in a few directions, up to 128 entries 109 / 93, up to 256 169 / 120, 200 of 64 54.0 / 58.1, of 256
-// 128 / 117, 68 of 256 69 / 63, 1,000 of 16 82 / 114, of 64 203 / 164.  (Before, up to 64 long ones were shared out by 64 tables to a
-// wave, one wave for all of them with 68 tables: 94 us a call that takes 47, and by lanes beyond that.)
+// each four buckets of a wave.  Retrievals, us, by lanes / by waves (when long buckets were read twice, for the bitmap and for the
+// list): 400 tables of up to 32 entries (SimHash) 49.7 / 61.3, of 64 70.6 / 74.0, of 256 194 / 152, 400 of 670K x 128 in a few directions, up
+// to 128 entries 109 / 93, up to 256 169 / 120, 200 of 64 54.0 / 58.1, of 256 128 / 117, 68 of 256 69 / 63, 1,000 of 16 82 / 114, of 64 203 / 164.
+// (Before, up to 64 long ones were shared out by 64 tables to a wave, one wave for all of them with 68 tables: 94 us a call
+// that takes 45, and by lanes beyond that.)
 struct LongRule {
   int even, few;       // tables of a wave
   int all;             // from that many long buckets on they go by lanes, however long: none is longer than C
